@@ -10,41 +10,49 @@
 // 4-element runs of consecutive columns n, which gives 8-byte stores and
 // in-lane row sums for the norm epilogue.
 //
-// Pipeline: k-steps of 32 held in a ring of four LDS slabs that are filled by direct
-// global -> LDS loads (no register staging), three k-steps in flight; one barrier per
-// k-step; MFMA fragments of the next 16-wide slice are read while the current
-// slice is multiplied.  Workgroups are renumbered so that each XCD (own L2)
-// works on a compact patch of output tiles.
+// Pipeline: k-steps of 64 held in a ring of LDS slabs that are filled by direct global -> LDS
+// buffer loads (no register staging); one barrier per k-step; the instruction stream of a step is
+// laid out slot by slot, one MFMA per slot, with the fragment reads and loads of the steps to come
+// behind them.  Workgroups are renumbered so that each XCD (own L2) works on a compact patch of
+// output tiles.
+#include <algorithm>
 #include <atomic>
+#include <type_traits>
+#include <utility>
 #include "vitcop_internal.h"
 #include "device_utils.h"
 
 namespace vitcop {
 
 constexpr int GM_THREADS = 256;
-constexpr int GM_SLABS = 4;          // ring of k-slabs in LDS: three k-steps of loads in flight (k-steps of 32)
 constexpr int GM_PART = 128;         // columns per sum-of-squares partial
-constexpr int GM_XCDS = 8;
+[[maybe_unused]] constexpr int GM_XCDS = 8;
 
 // LDS: the slab ring, reused by the epilogue as one staging region per wavefront of
 // (BM / WAVES_M) rows of (BN / WAVES_N) bf16 + 16 bytes of padding.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NS = GM_SLABS>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NS>
 constexpr size_t gemm_lds_bytes() {
-    constexpr size_t ring = (size_t)NS * (BM + BN) * BK * 2;
+    constexpr size_t ring = (size_t)NS * (BM + BN) * 128;
     constexpr size_t stage = (size_t)4 * (BM / WAVES_M) * ((BN / WAVES_N) * 2 + 16);
     return ring > stage ? ring : stage;
 }
 
-// A slab row holds BK bf16 (64 or 128 bytes, unpadded because direct loads write 1 KiB runs).
-// 16-byte chunk c of row r lives at chunk position c ^ swz(r), which makes the MFMA fragment
-// reads (32 consecutive rows, same chunk) bank-conflict free: LDS serves a 16-byte read 16 lanes at a
-// time, so 16 consecutive rows must fall on the 16 different 16-byte units of a 256-byte bank row.  With
-// 64-byte rows the unit is 4*(r & 3) + position, so the position must differ among r, r+4, r+8, r+12;
-// with 128-byte rows it is 8*(r & 1) + position, so it must differ among the eight rows of equal parity.
-template <int BK>
-__device__ __forceinline__ int gm_swz(int row) {
-    return BK == 32 ? (row >> 2) & 3 : (row >> 1) & 7;
+// calls f with the compile-time indices 0 .. N-1 (a `#pragma unroll` of this many slots is not honoured)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I>{}), ...);
 }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+// A slab row holds 64 bf16 (128 bytes: whole lines, unpadded because direct loads write 1 KiB runs).
+// 16-byte chunk c of row r lives at chunk position c ^ gm_swz(r), which makes the MFMA fragment
+// reads (16 consecutive rows, same chunk) bank-conflict free: LDS serves a 16-byte read 16 lanes at a
+// time, so 16 consecutive rows must fall on the 16 different 16-byte units of a 256-byte bank row.  The
+// unit is 8*(r & 1) + position, so the position must differ among the eight rows of equal parity.
+__device__ __forceinline__ int gm_swz(int row) { return (row >> 1) & 7; }
 
 // y = x W^T (+ residual).  With w2 != nullptr the columns [n_split, N) come from a second weight
 // matrix and go to a second output (two projections of the same input in one launch).
@@ -60,12 +68,16 @@ __device__ __forceinline__ int gm_swz(int row) {
 // columns of a tile belong to the wavefronts with wn = 0, the up columns to wn = 1).
 constexpr int GM_EPI_BF16 = 0, GM_EPI_DIST = 1, GM_EPI_PART = 2, GM_EPI_GATED = 3;
 
-// BK, NS: k-step and slabs in the ring.  With k-steps of 64 a slab row is a whole 128-byte line, so one direct
-// load moves 8 whole lines where k-steps of 32 move 16 half lines (and fetch every line twice, one k-step
-// apart): the CU's load path, which is what bounds the tiles of 128 and 192 columns, carries twice the useful
-// bytes.  Tiles whose three 64-wide slabs do not fit in LDS (256 x 256, 192 x 256) stay at 32 with four slabs;
-// with two slabs of 64 they were slower.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int EPI = GM_EPI_BF16, int NS = GM_SLABS>
+// What bounds the big tiles is power: with the matrix cores 87 % busy the clock falls to 1.7 GHz on random
+// operands.  To get there the loop must keep issuing MFMAs.  16x16x32 instructions (half the accumulator
+// traffic per FLOP of 32x32x16) in an order fixed by sched_barrier, each pinned to accumulation registers by an
+// asm constraint (left to itself the allocator moves 60 % as many registers as there are MFMAs); k-steps of 64
+// (every direct load moves 8 whole lines), for the 256-column tiles in two slabs: one barrier per step, loads
+// one per four MFMAs right behind it so that a CU's load path (64 bytes per clock) is never asked for more than
+// it moves and no wavefront is stuck on issuing one.  Against 32x32x16 with four slabs of 32 and compiler
+// scheduling hints (GPU time, random operands, same box): 11776x4096x4096 354 -> 298 us (1116 -> 1326 TFLOP/s),
+// 8192x8192x8192 921 -> 750 us (1194 -> 1467), 1536x8192x4096 107 -> 93 us, 2536x4096x11008 229 -> 194 us.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS>
 __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     const uint16_t* __restrict__ x, int64_t x_stride, const uint16_t* __restrict__ w,
     uint16_t* __restrict__ y, int64_t y_stride, const uint16_t* __restrict__ res,
@@ -74,17 +86,15 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     int n_split, int64_t w_stride, const float* __restrict__ xsq, const float* __restrict__ wsq,
     float* __restrict__ dist, int64_t dist_stride, int64_t x_batch, int64_t sq_batch,
     int64_t dist_batch) {
+#if defined(__HIP_DEVICE_COMPILE__)
     static_assert(WAVES_M * WAVES_N == 4, "four wavefronts");
-    static_assert(BK == 32 || BK == 64, "slab rows of 64 or 128 bytes");
     constexpr int TM = BM / WAVES_M, TN = BN / WAVES_N;
-    constexpr int MI = TM / 32, NI = TN / 32;
-    constexpr int ROWB = BK * 2;                         // bytes per slab row
-    constexpr int CHUNKS = BK / 8;                       // 16-byte chunks per row
-    constexpr int ROWS_PER_LOAD = 64 / CHUNKS;           // rows covered by one 1 KiB direct load
-    constexpr int KC = BK / 16;                          // 16-wide MFMA slices per k-step
+    constexpr int MI = TM / 16, NI = TN / 16;
+    constexpr int ROWB = 128;                            // bytes per slab row
     constexpr int SLAB = (BM + BN) * ROWB;               // bytes per slab
-    constexpr int NDMA = SLAB / 1024 / 4;                // direct loads per wavefront per slab
-    static_assert(SLAB % 4096 == 0 && (BM * ROWB) % 1024 == 0, "slab splits evenly over loads");
+    constexpr int NL = SLAB / 4096;                      // direct loads per wavefront per slab
+    constexpr int NM = MI * NI, NR = MI + NI;            // MFMAs and fragment reads per 32-wide slice of k
+    static_assert(BM % 32 == 0 && BN % 32 == 0, "a load of the four wavefronts covers 32 rows of one operand");
 
     extern __shared__ __attribute__((aligned(1024))) char gemm_lds[];
     if constexpr (EPI == GM_EPI_PART) dist += blockIdx.y * dist_batch;
@@ -98,7 +108,7 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);      // wavefront index, kept scalar
-    const int l32 = lane & 31, g = lane >> 5;
+    const int l16 = lane & 15, g4 = lane >> 4;
     const int wm = wv % WAVES_M, wn = wv / WAVES_M;
 
     // Workgroup -> tile.  Consecutive workgroup ids go to different XCDs, so id % 8 picks the
@@ -133,263 +143,233 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
         N = n_split;
     }
 
-    f32x16 acc[NI][MI];
+    f32x4 acc[NI][MI];
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < MI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < MI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Direct global -> LDS loads.  Load q of wavefront wv fills slab bytes [(wv*NDMA+q)*1024, +1024):
-    // ROWS_PER_LOAD rows; lane L lands at row L / CHUNKS, chunk position L % CHUNKS, so it must
-    // fetch the chunk that the swizzle assigns to that position.  Rows [0,BM) are x, then W.
-    unsigned goff[NDMA];             // byte offset of this lane's chunk from x (or W) at k = 0
+    // Direct global -> LDS loads.  Load q of wavefront wv fills the 1 KiB of slab rows [32 q + 8 wv, + 8): lane L
+    // lands at row L / 8, chunk position L % 8, so it must fetch the chunk that the swizzle assigns to that
+    // position.  Rows [0,BM) are x, then W (gated: BN/2 gate rows, then the same rows of up).  One descriptor
+    // per operand covers this tile's rows: rows past the end of the matrix, and k-steps past the end of the
+    // range (whose scalar offset is the descriptor's size), are out of range: they move nothing and read as zeros.
+    const int rows_x = min(M - m0, BM), rows_w = min(N - n0, EPI == GM_EPI_GATED ? BN / 2 : BN);
+    const unsigned rec_x = 2u * ((unsigned)(rows_x - 1) * (unsigned)x_stride + (unsigned)K);
+    const unsigned rec_w = 2u * ((unsigned)(rows_w - 1) * (unsigned)w_stride + (unsigned)K);
+    auto descriptor = [](const uint16_t* base, unsigned bytes) __attribute__((always_inline)) {
+        return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);     // raw buffer, 32-bit data format
+    };
+    const auto desc_x = descriptor(x + (int64_t)m0 * x_stride, rec_x);
+    const auto desc_w = descriptor(w + (int64_t)n0 * w_stride, rec_w);
+    const auto desc_u = descriptor((EPI == GM_EPI_GATED ? w2 : w) + (int64_t)n0 * w_stride, rec_w);
+    unsigned goff[NL];               // byte offset of this lane's chunk from its descriptor's base at k = 0
+    const unsigned chunk = (unsigned)((lane % 8) ^ gm_swz(8 * wv + lane / 8)) * 16;     // (the same for every q)
 #pragma unroll
-    for (int q = 0; q < NDMA; ++q) {
-        const int row = (wv * NDMA + q) * ROWS_PER_LOAD + lane / CHUNKS;        // slab row
-        const int chunk = (lane % CHUNKS) ^ gm_swz<BK>(row);
-        if (row < BM)
-            goff[q] = 2u * (unsigned)(min(m0 + row, M - 1) * (int)x_stride + chunk * 8);
-        else if (EPI == GM_EPI_GATED)     // slab rows [BM, BM + BN/2): gate rows n0.., then the same rows of up
-            goff[q] = 2u * (unsigned)(min(n0 + (row - BM) % (BN / 2), N - 1) * (int)w_stride + chunk * 8);
-        else
-            goff[q] = 2u * (unsigned)(min(n0 + row - BM, N - 1) * (int)w_stride + chunk * 8);
+    for (int q = 0; q < NL; ++q) {
+        const int row = 32 * q + 8 * wv + lane / 8;                             // slab row
+        const int wrow = EPI == GM_EPI_GATED && row - BM >= BN / 2 ? row - BM - BN / 2 : row - BM;
+        goff[q] = (row < BM ? 2u * (unsigned)row * (unsigned)x_stride : 2u * (unsigned)wrow * (unsigned)w_stride) + chunk;
     }
-    auto issue_loads = [&](int slab, int k0, int part = 0, int parts = 1) {
-        const char* xb = reinterpret_cast<const char*>(x + k0);
-        const char* wb = reinterpret_cast<const char*>(w + k0);
-        const char* ub = reinterpret_cast<const char*>((EPI == GM_EPI_GATED ? w2 : w) + k0);
-#pragma unroll
-        for (int q = 0; q < NDMA; ++q) {
-            if (q * parts / NDMA != part) continue;
-            const bool is_x = (wv * NDMA + q) * ROWS_PER_LOAD < BM;            // wave-uniform
-            const bool is_up = EPI == GM_EPI_GATED && (wv * NDMA + q) * ROWS_PER_LOAD >= BM + BN / 2;
-            const char* src = (is_x ? xb : is_up ? ub : wb) + goff[q];
-            char* dst = gemm_lds + slab * SLAB + (wv * NDMA + q) * 1024;
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)src,
-                (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-        }
+    auto issue_load = [&](auto q_c, int slab_off, unsigned kx, unsigned kw, unsigned past) __attribute__((always_inline)) {
+        constexpr int q = decltype(q_c)::value;
+        const unsigned off = goff[q] | past;
+        auto dst = (__attribute__((address_space(3))) void*)(gemm_lds + slab_off + (4 * q + wv) * 1024);
+        if constexpr (32 * q < BM) __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_x, dst, 16, off, kx, 0, 0);
+        else if constexpr (EPI == GM_EPI_GATED && 32 * q >= BM + BN / 2)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_u, dst, 16, off, kw, 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_w, dst, 16, off, kw, 0, 0);
     };
 
-    // MFMA fragments: lane (l32, g) reads 8 consecutive k of row l32: chunk 2*kc + g
-    int xrow[MI], wrow[NI];
-#pragma unroll
-    for (int j = 0; j < MI; ++j) xrow[j] = wm * TM + j * 32 + l32;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) wrow[i] = BM + wn * TN + i * 32 + l32;
+    // MFMA fragments: lane (l16, g4) reads 8 consecutive k of row l16: chunk 4*kc + g4 of the k-step's 8
     bf16x8 xf[2][MI], wf[2][NI];
-    auto read_frags = [&](int buf, int slab, int kc) {
-        const char* S = gemm_lds + slab * SLAB;
-#pragma unroll
-        for (int j = 0; j < MI; ++j)
-            xf[buf][j] = *reinterpret_cast<const bf16x8*>(
-                S + xrow[j] * ROWB + (((2 * kc + g) ^ gm_swz<BK>(xrow[j])) << 4));
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-            wf[buf][i] = *reinterpret_cast<const bf16x8*>(
-                S + wrow[i] * ROWB + (((2 * kc + g) ^ gm_swz<BK>(wrow[i])) << 4));
+    const int x_base = (wm * TM + l16) * ROWB + ((g4 ^ gm_swz(l16)) << 4);
+    const int w_base = (BM + wn * TN + l16) * ROWB + ((g4 ^ gm_swz(l16)) << 4);
+    auto read_frag = [&](auto r_c, auto kc_c, int slab_off) __attribute__((always_inline)) {
+        constexpr int r = decltype(r_c)::value, kc = decltype(kc_c)::value;
+        if constexpr (r < MI)
+            xf[kc][r] = *reinterpret_cast<const bf16x8*>(gemm_lds + slab_off + (x_base ^ (kc * 64)) + r * 16 * ROWB);
+        else
+            wf[kc][r - MI] = *reinterpret_cast<const bf16x8*>(gemm_lds + slab_off + (w_base ^ (kc * 64)) + (r - MI) * 16 * ROWB);
     };
-    auto multiply = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-            for (int j = 0; j < MI; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][i], xf[buf][j], acc[i][j], 0, 0, 0);
-    };
-    // scheduling hints: alternate one MFMA with one memory instruction of class `mask`, n times
-    // (0x100 LDS read, 0x020 global read)
-#define VITCOP_INTERLEAVE(mask, n)                                   \
-    _Pragma("unroll") for (int q_ = 0; q_ < (n); ++q_) {             \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);           \
-        __builtin_amdgcn_sched_group_barrier((mask), 1, 0);          \
-    }
-    constexpr int NFRAG = MI + NI, NMFMA = MI * NI;
-    // A step's loads go out in equal shares, one per slice, the last share after the barrier (into the same
-    // slab, free since the barrier of the step before): issued together, one CU's 4 x NDMA loads saturate its
-    // load unit for the whole first slice, and a wavefront stuck on issuing one cannot issue MFMAs meanwhile
-    // (8 % fewer cycles on the 256 x 256 tile, 3-6 % more throughput on the smaller ones).  SPLIT: the form
-    // with two slices and enough MFMAs to pair every fragment read and load with one (scheduling hints).
-    constexpr bool SPLIT = KC == 2 && NDMA % 2 == 0 && NMFMA >= NFRAG + NDMA;
-    constexpr bool SPREAD = !SPLIT && NDMA >= KC;
-    constexpr int LAST_PART = NDMA - ((KC - 1) * NDMA + KC - 1) / KC;      // loads issued after the barrier
 
-    // Pipeline over k-steps of BK.  Slab t % NS holds k-step t; the loads of k-step t+NS-1 are
-    // issued during step t into the slab that step t-1 used (every wavefront left it before
-    // the barrier of step t-1).  Step t, slice by slice (a slice = 16 of k):
-    //   slice 0: multiply; read the fragments of slice 1; issue the loads of step t+NS-1 (or their first half)
-    //   slices 1 .. KC-2: multiply; read the fragments of the next slice
-    //   wait until this wavefront's loads of step t+1 have landed (NS-2 younger steps may
-    //   still be in flight); barrier
-    //   slice KC-1: multiply; read the fragments of slice 0 of step t+1 (and issue the second half)
-    // Past the end the loads repeat the last k-step into slabs nobody reads again.
-    int nk = K / BK, k_lo = 0;
+    // A k-step is 2 NM slots of one MFMA each: slice 0 (k 0..31), then slice 1.  Behind them, in slot order:
+    //   slots 0 ..            the fragments of slice 1 are read, one per slot;
+    //   slot BAR (in slice 1) wait for this wavefront's fragment reads and its loads of step t+1 (those of the NS-2
+    //                         steps after it may still be in flight), then a barrier: slab t % NS has been read by
+    //                         everyone and step t+1 has arrived for everyone;
+    //   slots BAR+1 ..        the fragments of step t+1, slice 0 are read; the loads of step t+NS go out into slab
+    //                         t % NS, one per LSP slots, the last of them during step t+1 (always before its BAR).
+    // The loop runs the same code for every step: past the end the loads are out of range and the fragments are
+    // read from slabs whose contents no MFMA uses.
+    constexpr int BAR = NM + NM / 4;
+    constexpr int RPS = (NR + 2 * NM - BAR - 2) / (2 * NM - BAR - 1);           // reads per slot behind the barrier
+    constexpr int LSP = std::min(4, (2 * NM - 1) / NL);
+    constexpr int FIRST = std::min(NL, (2 * NM - 2 - BAR) / LSP + 1);           // loads of step t+NS issued in step t
+    static_assert(LSP >= 1 && NR <= NM && LSP * (NL - 1) + 1 < 2 * NM, "reads and loads find their slots");
+    static_assert(NS >= 2 && (NS - 2) * NL + FIRST <= 63, "the wait counter holds 63 loads");
+    int nk = (K + 63) / 64, k_lo = 0;
+    // K is a multiple of 32, so the last step may hold one slice only: then the chunks of its second half, which lie
+    // past K but inside the descriptor, are pushed out of range
+    int half_step = K % 64 != 0 ? nk - 1 : -1;
     if constexpr (EPI == GM_EPI_PART) {      // this split's k-steps: [k_lo, k_lo + nk), never empty
         const int all = nk;
         k_lo = (int)((int64_t)all * blockIdx.y / gridDim.y);
         nk = (int)((int64_t)all * (blockIdx.y + 1) / gridDim.y) - k_lo;
+        if (half_step >= 0) half_step -= k_lo;
     }
-    auto k_of = [&](int step) { return (k_lo + min(step, nk - 1)) * BK; };
-    auto step = [&](int t, int slab) {
-#pragma unroll
-        for (int kc = 0; kc < KC - 1; ++kc) {
-            read_frags((kc + 1) & 1, slab, kc + 1);
-            if constexpr (SPREAD) {
-                issue_loads((slab + NS - 1) % NS, k_of(t + NS - 1), kc, KC);
-            } else if (kc == 0) {
-                if constexpr (SPLIT) issue_loads((slab + NS - 1) % NS, k_of(t + NS - 1), 0, 2);
-                else issue_loads((slab + NS - 1) % NS, k_of(t + NS - 1));
-            }
-            multiply(kc & 1);
-            if constexpr (NMFMA >= NFRAG + NDMA) {
-                VITCOP_INTERLEAVE(0x100, NFRAG)
-                if (kc == 0) {
-                    VITCOP_INTERLEAVE(0x020, (SPLIT ? NDMA / 2 : NDMA))
-                    __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NFRAG - (SPLIT ? NDMA / 2 : NDMA), 0);
-                } else {
-                    __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NFRAG, 0);
-                }
-            }
-        }
-        // (a plain s_barrier: __syncthreads would also drain the two younger steps' loads)
-        // (younger loads that may stay in flight: the steps t+2 .. t+NS-2 and what this step has issued so far)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NDMA - (SPLIT ? NDMA / 2 : SPREAD ? LAST_PART : 0)) : "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        read_frags(KC & 1, (slab + 1) % NS, 0);
-        // second half of this step's loads: same slab (free since the barrier of the step before)
-        if constexpr (SPLIT) issue_loads((slab + NS - 1) % NS, k_of(t + NS - 1), 1, 2);
-        if constexpr (SPREAD) issue_loads((slab + NS - 1) % NS, k_of(t + NS - 1), KC - 1, KC);
-        multiply((KC - 1) & 1);
-        if constexpr (NMFMA >= NFRAG) {
-            VITCOP_INTERLEAVE(0x100, NFRAG)
-            if constexpr (SPLIT) {
-                VITCOP_INTERLEAVE(0x020, NDMA / 2)
-                __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NFRAG - NDMA / 2, 0);
-            } else {
-                __builtin_amdgcn_sched_group_barrier(0x008, NMFMA - NFRAG, 0);
-            }
-        }
+    auto k_off = [&](int t, unsigned rec) __attribute__((always_inline)) {
+        return t < nk ? (unsigned)(k_lo + t) * 128u : rec;
     };
-    static_assert(NS >= 3 && (NS - 2) * NDMA <= 63, "the wait counter holds 63 loads");
-#pragma unroll
-    for (int i = 0; i < NS - 1; ++i) issue_loads(i, k_of(i));
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NDMA) : "memory");
+    auto k_past = [&](int t) __attribute__((always_inline)) {
+        return t == half_step && chunk >= 64 ? 0xFFFFFF00u : 0u;
+    };
+    auto step = [&](int t, int slab_off, int next_off, int prev_off) __attribute__((always_inline)) {
+        const unsigned px = k_off(t - 1 + NS, rec_x), pw = k_off(t - 1 + NS, rec_w);
+        const unsigned cx = k_off(t + NS, rec_x), cw = k_off(t + NS, rec_w);
+        const unsigned p_past = k_past(t - 1 + NS), c_past = k_past(t + NS);
+        static_for<2 * NM>([&](auto slot) __attribute__((always_inline)) {
+            constexpr int s = decltype(slot)::value;
+            constexpr int kc = s / NM, i = s % NM / MI, j = s % MI;
+            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                         : "+a"(acc[i][j]) : "v"(wf[kc][i]), "v"(xf[kc][j]));
+            if constexpr (s < NR)
+                read_frag(std::integral_constant<int, s>{}, std::integral_constant<int, 1>{}, slab_off);
+            constexpr int late = s + 2 * NM - BAR - 1;           // slots since the barrier of the step before
+            if constexpr (s < BAR && late % LSP == 0 && late / LSP >= FIRST && late / LSP < NL)
+                issue_load(std::integral_constant<int, late / LSP>{}, prev_off, px, pw, p_past);
+            if constexpr (s == BAR) {
+                // (a plain s_barrier: __syncthreads would also drain the younger steps' loads)
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * NL) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            if constexpr (s > BAR) {
+                static_for<RPS>([&](auto e) __attribute__((always_inline)) {
+                    constexpr int r = (s - BAR - 1) * RPS + decltype(e)::value;
+                    if constexpr (r < NR)
+                        read_frag(std::integral_constant<int, r>{}, std::integral_constant<int, 0>{}, next_off);
+                });
+                if constexpr ((s - BAR - 1) % LSP == 0 && (s - BAR - 1) / LSP < FIRST)
+                    issue_load(std::integral_constant<int, (s - BAR - 1) / LSP>{}, slab_off, cx, cw, c_past);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    static_for<NS>([&](auto i) __attribute__((always_inline)) {
+        static_for<decltype(i)::value == NS - 1 ? FIRST : NL>([&](auto q) __attribute__((always_inline)) {
+            constexpr int st = decltype(i)::value;
+            issue_load(q, st * SLAB, k_off(st, rec_x), k_off(st, rec_w), k_past(st));
+        });
+    });
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL + FIRST) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    read_frags(0, 0, 0);
+    static_for<NR>([&](auto r) __attribute__((always_inline)) { read_frag(r, std::integral_constant<int, 0>{}, 0); });
+    // (the asm MFMAs are opaque to the compiler's hazard rules: the accumulators were written by vector moves)
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    int slab_off = 0, prev_off = (NS - 1) * SLAB;
     int t = 0;
-    for (; t + NS - 1 < nk; t += NS) {
-#pragma unroll
-        for (int i = 0; i < NS; ++i) step(t + i, i);
-    }
-#pragma unroll
-    for (int i = 0; i < NS - 1; ++i)
-        if (t + i < nk) step(t + i, i);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // no load may outlive the workgroup's LDS
-#undef VITCOP_INTERLEAVE
+    do {                             // (K >= 32, and no split is empty: at least one step)
+        const int next_off = slab_off + SLAB == NS * SLAB ? 0 : slab_off + SLAB;
+        step(t, slab_off, next_off, prev_off);
+        prev_off = slab_off;
+        slab_off = next_off;
+    } while (++t < nk);
+    // no load may outlive the workgroup's LDS use; the last MFMAs' results may be read after their passes
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 
+    // In the accumulators a lane owns row m = .. + l16 and the 4-element column runs n = .. + 16 i + 4 g4 + r.
     if constexpr (EPI == GM_EPI_PART) {
-        // lane owns row m = .. + l32 and the 4-element column runs n = .. + 8*(r/4) + 4*g + r%4
 #pragma unroll
         for (int j = 0; j < MI; ++j) {
-            const int m = m0 + wm * TM + j * 32 + l32;
+            const int m = m0 + wm * TM + j * 16 + l16;
             if (m >= M) continue;
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int n = n0 + wn * TN + i * 32 + 8 * r4 + 4 * g;
-                    if (n >= N) continue;            // N % 4 == 0: the run of 4 is all in or all out
-                    float4 o;
-                    o.x = acc[i][j][4 * r4];
-                    o.y = acc[i][j][4 * r4 + 1];
-                    o.z = acc[i][j][4 * r4 + 2];
-                    o.w = acc[i][j][4 * r4 + 3];
-                    *reinterpret_cast<float4*>(dist + (int64_t)m * dist_stride + n) = o;
-                }
+            for (int i = 0; i < NI; ++i) {
+                const int n = n0 + wn * TN + i * 16 + 4 * g4;
+                if (n >= N) continue;            // N % 4 == 0: the run of 4 is all in or all out
+                *reinterpret_cast<f32x4*>(dist + (int64_t)m * dist_stride + n) = acc[i][j];
+            }
         }
         return;
     }
     if constexpr (EPI == GM_EPI_DIST) {
-        // lane owns row m = .. + l32 and the 4-element column runs n = .. + 8*(r/4) + 4*g + r%4
 #pragma unroll
         for (int j = 0; j < MI; ++j) {
-            const int m = m0 + wm * TM + j * 32 + l32;
+            const int m = m0 + wm * TM + j * 16 + l16;
             if (m >= M) continue;
             const float sm = xsq[m];
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int n = n0 + wn * TN + i * 32 + 8 * r4 + 4 * g;
-                    if (n >= N) continue;
-                    // wsq and the rows of dist are padded to a multiple of 4 entries, so the run
-                    // of 4 may be read and written whole even when N cuts it
-                    const float4 sn = *reinterpret_cast<const float4*>(wsq + n);
-                    float4 o;
-                    o.x = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][4 * r4], sm + sn.x)));
-                    o.y = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][4 * r4 + 1], sm + sn.y)));
-                    o.z = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][4 * r4 + 2], sm + sn.z)));
-                    o.w = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][4 * r4 + 3], sm + sn.w)));
-                    *reinterpret_cast<float4*>(dist + (int64_t)m * dist_stride + n) = o;
-                }
+            for (int i = 0; i < NI; ++i) {
+                const int n = n0 + wn * TN + i * 16 + 4 * g4;
+                if (n >= N) continue;
+                // wsq and the rows of dist are padded to a multiple of 4 entries, so the run
+                // of 4 may be read and written whole even when N cuts it
+                const float4 sn = *reinterpret_cast<const float4*>(wsq + n);
+                float4 o;
+                o.x = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][0], sm + sn.x)));
+                o.y = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][1], sm + sn.y)));
+                o.z = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][2], sm + sn.z)));
+                o.w = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][3], sm + sn.w)));
+                *reinterpret_cast<float4*>(dist + (int64_t)m * dist_stride + n) = o;
+            }
         }
         return;
     }
-    // Epilogue.  In the accumulators a lane owns row m = .. + l32 and 4-element runs of columns
-    // n = .. + 8*(r/4) + 4*g + r%4: stored directly, every store instruction would touch 32
-    // rows with 16 bytes each, and the L2 request rate of all CUs finishing a round together
-    // becomes the bottleneck.  So the rounded tile goes through LDS (the slab ring is free now):
-    // each wavefront stages its own TM x TN block, rows padded by 16 bytes, and writes it out
-    // with 16 bytes per lane, consecutive lanes along a row.  The residual is added and the
-    // norm partial is formed on the way in, in the accumulator layout.
+    // Epilogue.  Stored directly, every store instruction would touch 16 rows with 32 bytes each, and the
+    // L2 request rate of all CUs finishing a round together becomes the bottleneck.  So the rounded tile
+    // goes through LDS (the slab ring is free now): each wavefront stages its own TM x TN block, rows padded
+    // by 16 bytes, and writes it out with 16 bytes per lane, consecutive lanes along a row.  The residual is
+    // added and the norm partial is formed on the way in, in the accumulator layout.
     constexpr int STAGE_ROW = TN * 2 + 16;                // bytes; the pad spreads the rows over the banks
     __builtin_amdgcn_s_barrier();                         // every wavefront is done reading the slabs
     char* stage = gemm_lds + wv * (TM * STAGE_ROW);
 #pragma unroll
     for (int j = 0; j < MI; ++j) {
-        const int m = m0 + wm * TM + j * 32 + l32;
+        const int m = m0 + wm * TM + j * 16 + l16;
         float ss = 0.f;
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
+        for (int i = 0; i < NI; ++i) {
+            const int n = n0 + wn * TN + i * 16 + 4 * g4;
+            float c[4];              // (read here and not ahead: the allocator would copy and spill the whole tile)
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int n = n0 + wn * TN + i * 32 + 8 * r4 + 4 * g;
-                float c0 = acc[i][j][4 * r4], c1 = acc[i][j][4 * r4 + 1];
-                float c2 = acc[i][j][4 * r4 + 2], c3 = acc[i][j][4 * r4 + 3];
-                if (res) {
-                    if (m < M && n < N) {            // N % 4 == 0: the run of 4 is all in or all out
-                        const uint2 rr = *reinterpret_cast<const uint2*>(res + (int64_t)m * res_stride + n);
-                        c0 += bf16_lo(rr.x); c1 += bf16_hi(rr.x);
-                        c2 += bf16_lo(rr.y); c3 += bf16_hi(rr.y);
-                    }
-                }
-                uint2 pk;
-                pk.x = pack_bf16(c0, c1);
-                pk.y = pack_bf16(c2, c3);
-                *reinterpret_cast<uint2*>(stage + (j * 32 + l32) * STAGE_ROW + (i * 32 + 8 * r4 + 4 * g) * 2) = pk;
-                if constexpr (TN == GM_PART) {
-                    if (sumsq_parts && n < N) {      // squares of the ROUNDED outputs, two per instruction
-                        const bf16x2 lo = __builtin_bit_cast(bf16x2, pk.x), hi = __builtin_bit_cast(bf16x2, pk.y);
-                        ss = __builtin_amdgcn_fdot2_f32_bf16(lo, lo, ss, false);
-                        ss = __builtin_amdgcn_fdot2_f32_bf16(hi, hi, ss, false);
-                    }
+            for (int r = 0; r < 4; ++r) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(c[r]) : "a"(acc[i][j][r]));
+            if (EPI == GM_EPI_BF16 && res) {
+                if (m < M && n < N) {            // N % 4 == 0: the run of 4 is all in or all out
+                    const uint2 rr = *reinterpret_cast<const uint2*>(res + (int64_t)m * res_stride + n);
+                    c[0] += bf16_lo(rr.x); c[1] += bf16_hi(rr.x);
+                    c[2] += bf16_lo(rr.y); c[3] += bf16_hi(rr.y);
                 }
             }
-        if constexpr (TN == GM_PART) {           // one partial per wavefront; other layouts never get sumsq_parts
-            if (sumsq_parts) {
-                ss += __shfl_xor(ss, 32, 64);
-                const int part = (n0 + wn * TN) / GM_PART;
-                if (g == 0 && m < M && n0 + wn * TN < N) sumsq_parts[(int64_t)part * M + m] = ss;
+            uint2 pk;
+            pk.x = pack_bf16(c[0], c[1]);
+            pk.y = pack_bf16(c[2], c[3]);
+            *reinterpret_cast<uint2*>(stage + (j * 16 + l16) * STAGE_ROW + (i * 16 + 4 * g4) * 2) = pk;
+            if constexpr (TN == GM_PART) {
+                if (sumsq_parts && n < N) {      // squares of the ROUNDED outputs, two per instruction
+                    const bf16x2 lo = __builtin_bit_cast(bf16x2, pk.x), hi = __builtin_bit_cast(bf16x2, pk.y);
+                    ss = __builtin_amdgcn_fdot2_f32_bf16(lo, lo, ss, false);
+                    ss = __builtin_amdgcn_fdot2_f32_bf16(hi, hi, ss, false);
+                }
             }
         }
+        if constexpr (TN == GM_PART) {           // one partial per wavefront; other layouts never get sumsq_parts
+            if (sumsq_parts) {
+                ss += __shfl_xor(ss, 16, 64);
+                ss += __shfl_xor(ss, 32, 64);
+                const int part = (n0 + wn * TN) / GM_PART;
+                if (g4 == 0 && m < M && n0 + wn * TN < N) sumsq_parts[(int64_t)part * M + m] = ss;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);       // one row block's residual at a time: registers
     }
     if constexpr (EPI == GM_EPI_GATED) {
         // gate block of these rows: staged by wavefront (wm, 0); up block: by (wm, 1).  Each of the two takes
         // half of the block's columns: 16-byte chunks of gate and up in, one chunk of silu(gate) * up out.
-        static_assert((BM * ROWB) % (ROWS_PER_LOAD * ROWB) == 0 && (BN / 2) % ROWS_PER_LOAD == 0, "whole loads per half");
+        static_assert((BN / 2) % 32 == 0, "whole loads per half");
         __builtin_amdgcn_s_waitcnt(0xC07F);               // lgkmcnt(0): this wavefront's staging writes are done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -433,11 +413,12 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
             if (m < M) *reinterpret_cast<u32x4*>(y + (int64_t)m * y_stride + n) = val;
         }
     }
+#endif
 }
 
 int gemm_sumsq_parts(int N) { return (N + GM_PART - 1) / GM_PART; }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int EPI = GM_EPI_BF16, int NS = GM_SLABS>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
 static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y,
                            int64_t y_stride, const uint16_t* res, int64_t res_stride, int M, int N,
                            int K, float* sumsq_parts, const uint16_t* w2, uint16_t* y2, int n_split,
@@ -445,8 +426,10 @@ static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const uint16_t* 
                            const float* wsq = nullptr, float* dist = nullptr, int64_t dist_stride = 0,
                            int batch = 1, int64_t x_batch = 0, int64_t sq_batch = 0, int64_t dist_batch = 0) {
     if (w_stride == 0) w_stride = K;
-    auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, BK, EPI, NS>;
-    constexpr size_t lds = gemm_lds_bytes<BM, BN, WAVES_M, WAVES_N, BK, NS>();
+    // as many slabs as fit in LDS, up to four
+    constexpr int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128));
+    auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, NS>;
+    constexpr size_t lds = gemm_lds_bytes<BM, BN, WAVES_M, WAVES_N, NS>();
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     static std::atomic<bool> attr_set{false};   // per kernel instantiation; a second thread repeating the call is harmless
     if (!attr_set.load(std::memory_order_acquire)) {
@@ -465,17 +448,6 @@ static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const uint16_t* 
                        y_stride, res, res_stride, M, N, K, sumsq_parts, tiles_m, tiles_n, group_m, w2,
                        y2, n_split, w_stride, xsq, wsq, dist, dist_stride, x_batch, sq_batch, dist_batch);
     return launch_status("gemm");
-}
-
-// The k-step of a launch: 64 where three (or four) slabs of that width fit in LDS and K allows it, else 32.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, typename... Args>
-static int launch_gemm_k(int K, Args... args) {
-    constexpr size_t slab64 = (size_t)(BM + BN) * 128;
-    if constexpr (3 * slab64 <= 160 * 1024) {
-        constexpr int NS = 4 * slab64 <= 160 * 1024 ? 4 : 3;
-        if (K % 64 == 0) return launch_gemm_cfg<BM, BN, WAVES_M, WAVES_N, 64, EPI, NS>(args...);
-    }
-    return launch_gemm_cfg<BM, BN, WAVES_M, WAVES_N, 32, EPI>(args...);
 }
 
 // Tile shapes.  The wavefront tile sets the LDS bytes read per MFMA, so big tiles are the
@@ -584,7 +556,7 @@ static int launch_tile(TileId id, const uint16_t* x, int64_t x_stride, const uin
                        int64_t y_stride, const uint16_t* res, int64_t res_stride, int M, int N, int K,
                        float* sumsq_parts, const uint16_t* w2, uint16_t* y2, int n_split, hipStream_t s) {
 #define VITCOP_TILE(BM, BN, WM, WN) \
-    return launch_gemm_k<BM, BN, WM, WN, GM_EPI_BF16>(K, x, x_stride, w, y, y_stride, res, res_stride, M, N, K, \
+    return launch_gemm_cfg<BM, BN, WM, WN, GM_EPI_BF16>(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, \
                                                       sumsq_parts, w2, y2, n_split, s)
     switch (id) {
         case T256x256: VITCOP_TILE(256, 256, 2, 2);
@@ -594,7 +566,7 @@ static int launch_tile(TileId id, const uint16_t* x, int64_t x_stride, const uin
         case T128x128: VITCOP_TILE(128, 128, 2, 2);
         case T128x128R: VITCOP_TILE(128, 128, 4, 1);
         default:
-            return launch_gemm_cfg<128, 32, 4, 1, 64>(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, sumsq_parts,
+            return launch_gemm_cfg<128, 32, 4, 1, GM_EPI_BF16>(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, sumsq_parts,
                                                       w2, y2, n_split, s);
     }
 #undef VITCOP_TILE
@@ -700,7 +672,7 @@ static int launch_gemm_splitk(const uint16_t* x, int64_t x_stride, const uint16_
     float* part = static_cast<float*>(ws);
     int rc;
 #define VITCOP_SPLITK(BM, BN)                                                                                    \
-    rc = launch_gemm_k<BM, BN, 2, 2, GM_EPI_PART>(K, x, x_stride, w, nullptr, 0, nullptr, 0, M, N, K, nullptr, w2,   \
+    rc = launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART>(x, x_stride, w, nullptr, 0, nullptr, 0, M, N, K, nullptr, w2,   \
                                                   nullptr, n_split, s, K, nullptr, nullptr, part, N, p.splits, 0, 0, \
                                                   (int64_t)M * N)
     if (p.bm == 256 && p.bn == 256) VITCOP_SPLITK(256, 256);
@@ -778,7 +750,7 @@ int launch_gemm_norm_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w, 
 static int launch_tile_gated(TileId id, const uint16_t* x, int64_t x_stride, const uint16_t* wg, const uint16_t* wu,
                              uint16_t* out, int64_t out_stride, int M, int F, int K, hipStream_t s) {
 #define VITCOP_GATED(BM, BN) \
-    return launch_gemm_k<BM, BN, 2, 2, GM_EPI_GATED>(K, x, x_stride, wg, out, out_stride, nullptr, 0, M, F, K, nullptr, \
+    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_GATED>(x, x_stride, wg, out, out_stride, nullptr, 0, M, F, K, nullptr, \
                                                      wu, nullptr, 0, s)
     switch (id) {
         case T256x256: VITCOP_GATED(256, 256);
@@ -958,7 +930,7 @@ int launch_pairwise_dist(const uint16_t* f, int64_t row_stride, int64_t batch_st
                          int64_t sq_batch, float* dist, int64_t dist_stride, int64_t dist_batch, int n, int K,
                          int batch, hipStream_t s) {
     if (n == 0 || batch == 0) return VITCOP_OK;
-    return launch_gemm_k<128, 128, 2, 2, GM_EPI_DIST>(K, f, row_stride, f, nullptr, 0, nullptr, 0, n, n, K, nullptr,
+    return launch_gemm_cfg<128, 128, 2, 2, GM_EPI_DIST>(f, row_stride, f, nullptr, 0, nullptr, 0, n, n, K, nullptr,
                                                       nullptr, nullptr, 0, s, row_stride, sq, sq, dist, dist_stride, batch,
                                                       batch_stride, sq_batch, dist_batch);
 }

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     };
 
     // A k-step is 2 NM slots of one MFMA each: slice 0 (k 0..31), then slice 1.  Behind them, in slot order:
-    //   slots 0 ..            the fragments of slice 1 are read, one per slot;
+    //   slots 0 ..            the fragments of slice 1 are read (one per slot);
     //   slot BAR (in slice 1) wait for this wavefront's fragment reads and its loads of step t+1 (those of the NS-2
     //                         steps after it may still be in flight), then a barrier: slab t % NS has been read by
     //                         everyone and step t+1 has arrived for everyone;
@@ -203,10 +203,11 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     // The loop runs the same code for every step: past the end the loads are out of range and the fragments are
     // read from slabs whose contents no MFMA uses.
     constexpr int BAR = NM + NM / 4;
+    constexpr int RPS0 = (NR + NM - 1) / NM;                                    // reads per slot ahead of the barrier
     constexpr int RPS = (NR + 2 * NM - BAR - 2) / (2 * NM - BAR - 1);           // reads per slot behind the barrier
     constexpr int LSP = std::min(4, (2 * NM - 1) / NL);
     constexpr int FIRST = std::min(NL, (2 * NM - 2 - BAR) / LSP + 1);           // loads of step t+NS issued in step t
-    static_assert(LSP >= 1 && NR <= NM && LSP * (NL - 1) + 1 < 2 * NM, "reads and loads find their slots");
+    static_assert(LSP >= 1 && LSP * (NL - 1) + 1 < 2 * NM, "reads and loads find their slots");
     static_assert(NS >= 2 && (NS - 2) * NL + FIRST <= 63, "the wait counter holds 63 loads");
     int nk = (K + 63) / 64, k_lo = 0;
     // K is a multiple of 32, so the last step may hold one slice only: then the chunks of its second half, which lie
@@ -233,8 +234,12 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
             constexpr int kc = s / NM, i = s % NM / MI, j = s % MI;
             asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
                          : "+a"(acc[i][j]) : "v"(wf[kc][i]), "v"(xf[kc][j]));
-            if constexpr (s < NR)
-                read_frag(std::integral_constant<int, s>{}, std::integral_constant<int, 1>{}, slab_off);
+            if constexpr (s < NM)
+                static_for<RPS0>([&](auto e) __attribute__((always_inline)) {
+                    constexpr int r = s * RPS0 + decltype(e)::value;
+                    if constexpr (r < NR)
+                        read_frag(std::integral_constant<int, r>{}, std::integral_constant<int, 1>{}, slab_off);
+                });
             constexpr int late = s + 2 * NM - BAR - 1;           // slots since the barrier of the step before
             if constexpr (s < BAR && late % LSP == 0 && late / LSP >= FIRST && late / LSP < NL)
                 issue_load(std::integral_constant<int, late / LSP>{}, prev_off, px, pw, p_past);
@@ -404,10 +409,11 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     constexpr int ROWS_PER_STORE = 64 / LANES_PER_ROW;
     const int srow = lane / LANES_PER_ROW, schunk = lane % LANES_PER_ROW;
     const int n = n0 + wn * TN + schunk * 8;
-    if (n < N) {                                          // N % 8 == 0: the chunk is all in or all out
+    if (n < N && srow < ROWS_PER_STORE) {                 // N % 8 == 0: the chunk is all in or all out
 #pragma unroll
         for (int r0 = 0; r0 < TM; r0 += ROWS_PER_STORE) {
             const int row = r0 + srow;
+            if (TM % ROWS_PER_STORE != 0 && row >= TM) break;
             const int m = m0 + wm * TM + row;
             const u32x4 val = *reinterpret_cast<const u32x4*>(stage + row * STAGE_ROW + schunk * 16);
             if (m < M) *reinterpret_cast<u32x4*>(y + (int64_t)m * y_stride + n) = val;
@@ -418,7 +424,8 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
 
 int gemm_sumsq_parts(int N) { return (N + GM_PART - 1) / GM_PART; }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
+// (as many slabs as fit in LDS, up to four)
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128))>
 static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y,
                            int64_t y_stride, const uint16_t* res, int64_t res_stride, int M, int N,
                            int K, float* sumsq_parts, const uint16_t* w2, uint16_t* y2, int n_split,
@@ -426,8 +433,6 @@ static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const uint16_t* 
                            const float* wsq = nullptr, float* dist = nullptr, int64_t dist_stride = 0,
                            int batch = 1, int64_t x_batch = 0, int64_t sq_batch = 0, int64_t dist_batch = 0) {
     if (w_stride == 0) w_stride = K;
-    // as many slabs as fit in LDS, up to four
-    constexpr int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128));
     auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, NS>;
     constexpr size_t lds = gemm_lds_bytes<BM, BN, WAVES_M, WAVES_N, NS>();
     static_assert(lds <= 160 * 1024, "LDS of a CU");
@@ -451,19 +456,28 @@ static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const uint16_t* 
 }
 
 // Tile shapes.  The wavefront tile sets the LDS bytes read per MFMA, so big tiles are the
-// efficient ones; smaller ones exist to fill all 256 CUs when there are few rows.  `rate` is
-// the measured throughput of a CU on that shape relative to 256x256 (K = 4096, full rounds).
+// efficient ones; smaller ones exist to fill all 256 CUs when there are few rows, and the heights
+// between them so that the rows of a launch end near the end of a round (2536 x 4096: 16 x 16 tiles
+// of 160 x 256 are one round; 192-row tiles fill 224 of the 256 CUs).  `rate` is the measured
+// throughput of a CU on that shape relative to 256x256 (K = 4096, two and three full rounds, random
+// operands: 98, 85.5, 76, 65, 55, 44, 38.7, 32.6, 33.5 us a round in the order below; 160x256 and
+// 224x256 against the next larger shape in use before: 2536x4096x11008 222 -> 174 us, 2536x4096x4096
+// 82 -> 67 us).
 struct TileShape {
     int bm, bn;
     float rate;
     bool sumsq;        // wavefront tile is 128 columns wide: can emit the norm partials
 };
-enum TileId { T256x256, T192x256, T256x128, T192x128, T128x128, T128x128R, T128x32, T192x192G, T_COUNT };
+enum TileId { T256x256, T224x256, T192x256, T160x256, T256x128, T192x128, T160x128, T128x128, T128x128R, T128x32,
+              T192x192G, T160x192G, T_COUNT };
 static const TileShape kTiles[T_COUNT] = {
-    {256, 256, 1.00f, true},  {192, 256, 0.90f, true},  {256, 128, 0.88f, false}, {192, 128, 0.89f, false},
-    {128, 128, 0.76f, false}, {128, 128, 0.74f, true},  {128, 32, 0.0f, false},
-    {192, 192, 0.88f, false},     // gate/up launches only (96 gate + 96 up columns): its epilogue exists in that form alone
+    {256, 256, 1.00f, true},  {224, 256, 1.00f, true},  {192, 256, 0.96f, true},  {160, 256, 0.94f, true},
+    {256, 128, 0.89f, false}, {192, 128, 0.83f, false}, {160, 128, 0.79f, false}, {128, 128, 0.75f, false},
+    {128, 128, 0.73f, true},  {128, 32, 0.0f, false},
+    // gate/up launches only (96 gate + 96 up columns): their epilogue exists in that form alone
+    {192, 192, 0.91f, false}, {160, 192, 0.88f, false},
 };
+constexpr float GM_TILE_US = 98.0f / 4096.0f;      // microseconds per k of a 256x256 tile
 
 // Estimated time of the launch in units of (one 256x256 tile at full rate): rounds over the
 // 256 CUs times the time of one tile.
@@ -560,9 +574,12 @@ static int launch_tile(TileId id, const uint16_t* x, int64_t x_stride, const uin
                                                       sumsq_parts, w2, y2, n_split, s)
     switch (id) {
         case T256x256: VITCOP_TILE(256, 256, 2, 2);
+        case T224x256: VITCOP_TILE(224, 256, 2, 2);
         case T192x256: VITCOP_TILE(192, 256, 2, 2);
+        case T160x256: VITCOP_TILE(160, 256, 2, 2);
         case T256x128: VITCOP_TILE(256, 128, 2, 2);
         case T192x128: VITCOP_TILE(192, 128, 2, 2);
+        case T160x128: VITCOP_TILE(160, 128, 2, 2);
         case T128x128: VITCOP_TILE(128, 128, 2, 2);
         case T128x128R: VITCOP_TILE(128, 128, 4, 1);
         default:
@@ -610,29 +627,33 @@ static SplitKPlan splitk_plan(int M, int N, int K) {
     // 128-column tiles first: for the same number of workgroups they need half the slices of the 256-column
     // tiles, i.e. half the fp32 partials to write and to add up, and at these sizes that traffic, not the
     // matrix cores, sets the time (317 x 4096 x 4096: 28 us with 2 x 32 tiles x 4 slices against 36 us with
-    // 2 x 16 tiles x 8).  Rows per tile: 192 or 256, whichever leaves the shorter slice per workgroup at its
-    // measured rate.
-    const int t256 = (M + 255) / 256, t192 = (M + 191) / 192, cols = (N + 127) / 128;
+    // 2 x 16 tiles x 8).  Rows per tile: 160, 192 or 256, whichever leaves the shorter slice per workgroup at
+    // its measured rate (640 x 4096 x 4096: 24.7 us as 4 x 32 tiles of 160 rows, 27.6 us of 192 rows).
     auto slices = [&](int tiles) { return std::min(std::min(16, 256 / std::max(tiles, 1)), K / 32 / 8); };
-    const int s192 = slices(t192 * cols), s256 = slices(t256 * cols);
-    const float c192 = s192 >= 2 ? 192.0f / (0.89f * (float)s192) : 1e30f;
-    const float c256 = s256 >= 2 ? 256.0f / (0.88f * (float)s256) : 1e30f;
-    const int s128 = c192 <= c256 ? s192 : s256;
+    auto consider = [&](const TileShape& t, int least, float& best) {
+        const int s = slices((M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn));
+        const float c = (float)(t.bm * t.bn) / (t.rate * (float)s);
+        if (s < least || c >= best) return;
+        best = c;
+        p = {t.bm, t.bn, s};
+    };
+    float cost = 1e30f;
+    for (TileId id : {T160x128, T192x128, T256x128}) consider(kTiles[id], 2, cost);
     // (not with slices longer than 4096 of k: inside a layer the 640-row down projection, K = 11008, takes
     // 110 us as 4 x 32 tiles x 2 slices against 91 us as 3 x 16 tiles x 5)
-    if (s128 >= 2 && K / s128 <= 4096) {
-        p.bn = 128;
-        p.bm = c192 <= c256 ? 192 : 256;
-        p.splits = s128;
-        return p;
+    if (p.splits < 2 || K / p.splits > 4096) {
+        p = {};
+        cost = 1e30f;
+        for (TileId id : {T160x256, T192x256, T256x256}) consider(kTiles[id], 3, cost);
     }
-    // 256-column tiles: 256 or 192 rows, whichever pads M less (192 runs at 0.9 of the rate)
-    const int bm = (float)(t192 * 192) / 0.9f < (float)(t256 * 256) ? 192 : 256;
-    const int tiles = (bm == 192 ? t192 : t256) * ((N + 255) / 256);
-    const int splits = slices(tiles);                                       // at least 8 k-steps per slice
-    if (splits < 3) return p;
-    p.bm = bm;
-    p.splits = splits;
+    if (p.splits == 0) return p;
+    // against one launch of whole tiles that needs no second pass: the partials are written and read once at
+    // about 4.5 TB/s, and the reduction costs a launch (920 x 4096 x 4096: 33 us on 8 x 32 tiles of 128 x 128
+    // against 33 + 13 us in two slices)
+    const float split_us = cost / 65536.0f * (float)K * GM_TILE_US + 3.0f + (float)p.splits * (float)M * (float)N * 8.0f / 4.5e6f;
+    float whole = 1e30f;
+    for (int i = 0; i < T128x128R; ++i) whole = std::min(whole, tile_cost(kTiles[i], M, N));
+    if (whole * (float)K * GM_TILE_US < split_us) p = {};
     return p;
 }
 static size_t splitk_workspace_bytes(int M, int N, int K) {
@@ -677,8 +698,10 @@ static int launch_gemm_splitk(const uint16_t* x, int64_t x_stride, const uint16_
                                                   (int64_t)M * N)
     if (p.bm == 256 && p.bn == 256) VITCOP_SPLITK(256, 256);
     else if (p.bm == 192 && p.bn == 256) VITCOP_SPLITK(192, 256);
+    else if (p.bn == 256) VITCOP_SPLITK(160, 256);
     else if (p.bm == 256) VITCOP_SPLITK(256, 128);
-    else VITCOP_SPLITK(192, 128);
+    else if (p.bm == 192) VITCOP_SPLITK(192, 128);
+    else VITCOP_SPLITK(160, 128);
 #undef VITCOP_SPLITK
     if (rc) return rc;
     const SkParts parts{part, 0, p.splits, N, M};
@@ -754,10 +777,14 @@ static int launch_tile_gated(TileId id, const uint16_t* x, int64_t x_stride, con
                                                      wu, nullptr, 0, s)
     switch (id) {
         case T256x256: VITCOP_GATED(256, 256);
+        case T224x256: VITCOP_GATED(224, 256);
         case T192x256: VITCOP_GATED(192, 256);
+        case T160x256: VITCOP_GATED(160, 256);
         case T256x128: VITCOP_GATED(256, 128);
         case T192x128: VITCOP_GATED(192, 128);
+        case T160x128: VITCOP_GATED(160, 128);
         case T192x192G: VITCOP_GATED(192, 192);
+        case T160x192G: VITCOP_GATED(160, 192);
         default: VITCOP_GATED(128, 128);
     }
 #undef VITCOP_GATED
@@ -784,7 +811,7 @@ int launch_gemm_gated_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wg
             TileId id = choose_tile(M, 2 * f_left, K, false, 768);
             if (id == T128x128R) id = T128x128;
             const bool first = f_left == F;              // only the whole launch may still go the separate way
-            if (!(id == T256x256 || id == T192x256 || id == T256x128 || id == T192x128 || id == T128x128)) {
+            if (id > T128x128) {
                 if (first) {
                     fused = false;
                     break;
@@ -795,8 +822,10 @@ int launch_gemm_gated_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wg
             float cut_cost = 0.f;
             int n_main = ws && f_left % 128 == 0 ? main_columns(cut_id, M, 2 * f_left, K, false, 768, &cut_cost)
                                                  : 2 * f_left;
-            // (the 192 x 192 tiles exist in this form only: a cut must beat them too)
-            if (cut_id == T128x128R || cut_cost >= tile_cost(kTiles[T192x192G], M, 2 * f_left)) n_main = 2 * f_left;
+            // (the 192-column tiles exist in this form only: a cut must beat them too)
+            const TileId g192 = tile_cost(kTiles[T160x192G], M, 2 * f_left) < tile_cost(kTiles[T192x192G], M, 2 * f_left)
+                                    ? T160x192G : T192x192G;
+            if (cut_id == T128x128R || cut_cost >= tile_cost(kTiles[g192], M, 2 * f_left)) n_main = 2 * f_left;
             int f_now = f_left;
             if (n_main < 2 * f_left) {
                 const TileShape& t = kTiles[cut_id];
@@ -809,10 +838,10 @@ int launch_gemm_gated_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wg
                     id = cut_id;
                     f_now = n_main / 2;
                 }
-            } else if (tile_cost(kTiles[T192x192G], M, 2 * f_left) < tile_cost(kTiles[id], M, 2 * f_left)) {
+            } else if (tile_cost(kTiles[g192], M, 2 * f_left) < tile_cost(kTiles[id], M, 2 * f_left)) {
                 // a few hundred rows leave the 256-column tiles a third of the CUs short (317 x 22016: 172
-                // tiles); 192 x 192 tiles (230) fill them
-                id = T192x192G;
+                // tiles); 192-column tiles (230 of 160 x 192: 65.5 us, of 192 x 192: 68 us) fill them
+                id = g192;
             }
             int rc = launch_tile_gated(id, x, x_stride, g_w, u_w, o, F, M, f_now, K, s);
             if (rc) return rc;

@@ -42,7 +42,7 @@ def test_tiles_and_k_steps(M, N, K):
     assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(257, 512, 512), (317, 4096, 2080), (640, 4096, 4096), (1024, 1040, 1056), (500, 3072, 1504)])
+@pytest.mark.parametrize("M,N,K", [(257, 512, 4096), (317, 4096, 4064), (640, 4096, 4096), (1024, 1040, 4128), (500, 2064, 3008)])
 def test_split_k(M, N, K):
     assert vc.lib.vitcop_project_workspace_bytes(M, N, K) > 0
     x, w, r = draw(M, N, K, M)

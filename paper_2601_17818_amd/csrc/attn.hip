@@ -1,7 +1,7 @@
 // Causal prefill attention over the surviving tokens: exact
 // softmax(scale Q K^T + causal) V with an online softmax, i.e. what a
 // FlashAttention kernel computes (Sec. 1 and Sec. 2.2 rely on that
-// compatibility; this is the 4 N^2 d term of Eq. 7).  Head dimension 128.
+// compatibility; this is the 4 N^2 d term of Eq. 7).  Head dimensions 128 and 64.
 //
 // Layout of the computation (wave64, v_mfma_f32_32x32x16_bf16):
 //  * a workgroup of 4 wavefronts owns 128 consecutive queries of one
@@ -23,7 +23,7 @@
 
 namespace vitcop {
 
-constexpr int AT_D = 128;
+
 constexpr int AT_BM = 128;
 constexpr int AT_BN = 64;
 constexpr int AT_THREADS = 256;
@@ -212,8 +212,7 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// The kernel for head dimension 128 (the one above remains for 64, and for K/V spans beyond 32-bit byte
-// offsets).  A workgroup of 4 wavefronts owns 128 U queries, each wavefront U blocks of 32: with U = 2 (long
+// The kernel for head dimensions 128 and 64 (the one above remains for K/V spans beyond 32-bit byte offsets).  A workgroup of 4 wavefronts owns 128 U queries, each wavefront U blocks of 32: with U = 2 (long
 // sequences) every K and V^T fragment read from LDS feeds two MFMAs; with U = 1 (the few hundred tokens that
 // survive pruning) a wavefront's chain per key tile is half as long and there are twice the workgroups.
 // K and V tiles (64 keys) arrive by direct
@@ -226,16 +225,17 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(
 // ---------------------------------------------------------------------------
 constexpr int AW_BM = 256;            // queries per workgroup with two query blocks per wavefront (128 with one)
 constexpr int AW_BN = 64;
-// LDS layout of a 64-key tile (rows of 256 B): one direct-to-LDS load writes 1 KiB = the four
-// rows {i, i+16, i+32, i+48}, so row r sits at (r % 16) * (1024 + pad) + (r / 16) * 256.
-// The pad after every KiB shifts consecutive keys across the banks: 16 B for K (16-byte
-// fragment reads of 16 consecutive keys), 64 B for V (8-byte transposing reads: 32 lanes = 4 consecutive
-// keys x 64 B).  Every fragment address is then one per-lane base + a constant.
+// LDS layout of a 64-key tile (rows of 2 D bytes): one direct-to-LDS load writes 1 KiB = the rows
+// {i, i+G, i+2G, ..} with G = D / 8 row groups, so row r sits at (r % G) * (1024 + pad) + (r / G) * 2 D.
+// The pad after every KiB shifts consecutive keys across the banks: 16 B for K (16-byte fragment reads of 16
+// consecutive keys: with D = 64 eight groups and two 128-byte rows apart), 64 B for V (8-byte transposing
+// reads: 32 lanes = 4 consecutive keys x 64 B).  Every fragment address is then one per-lane base + a constant.
 constexpr int AW_KGRP = 1024 + 16;
 constexpr int AW_VGRP = 1024 + 64;
-constexpr int AW_KTILE = 16 * AW_KGRP;           // 16640 B
-constexpr int AW_VTILE = 16 * AW_VGRP;           // 16896 B
-constexpr int AW_STAGE = AW_KTILE + AW_VTILE;    // K then V
+template <int D>
+constexpr int AW_KTILE = D / 8 * AW_KGRP;                    // 16640 or 8320 B
+template <int D>
+constexpr int AW_STAGE = AW_KTILE<D> + D / 8 * AW_VGRP;      // K then V
 constexpr int AW_STAGES = 4;
 constexpr float AW_RESCALE_GAP = 8.0f;
 
@@ -263,7 +263,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // Vector work of the softmax of one 32-key stage (all query blocks of the wavefront), as a list of single
 // instructions in issue order.  The pipeline block below cuts the list into as many runs as it has MFMAs
-// (16 per query block) and puts one run behind each, with scheduling barriers in between, so that the
+// (D / 8 per query block) and puts one run behind each, with scheduling barriers in between, so that the
 // matrix pipe and the vector pipe stay busy together; the order keeps every instruction a
 // few issue slots away from the producer of its operands.
 //   kinds: MASK (diagonal and ragged tiles only) score := -inf where the key is not visible;
@@ -285,13 +285,12 @@ struct SmTable {
     SmOp op[SM_NOPS];
     int start[33];       // run r is op[start[r]] .. op[start[r+1]-1]
     int check;           // the reference check sits between run check-1 and run check
-    int slots;           // runs = MFMAs of a pipeline block: 16 per query block
+    int slots;           // runs = MFMAs of a pipeline block: 16 per query block, 8 with head dimension 64
 };
 // U query blocks per wavefront (1 or 2)
-constexpr SmTable make_sm_table(bool masked, int U) {
+constexpr SmTable make_sm_table(bool masked, int U, int slots) {
     SmTable t{};
     int n = 0;
-    const int slots = 16 * U;
     t.slots = slots;
     if (masked)
         for (int i = 0; i < 16; ++i)
@@ -347,17 +346,22 @@ constexpr SmTable make_sm_table(bool masked, int U) {
     while (r < slots) t.start[++r] = n;
     return t;
 }
-template <int U, bool MASKED>
-constexpr SmTable SM_TABLE_OF = make_sm_table(MASKED, U);
+template <int D, int U, bool MASKED>
+constexpr SmTable SM_TABLE_OF = make_sm_table(MASKED, U, D / 8 * U);
 
-template <bool CAUSAL, int U>
-__global__ __launch_bounds__(256) void attn_wide_kernel(
+template <int D, bool CAUSAL, int U>
+__global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, uint16_t* __restrict__ out, float* __restrict__ lse,
     int N, int Hq, int Hkv, float scale_log2e, int n_qb, int n_heads, int group) {
     extern __shared__ __attribute__((aligned(1024))) char aw_lds[];
     static_assert(U == 1 || U == 2, "query blocks per wavefront");
     constexpr int BM = 128 * U, QW = 32 * U;       // queries per workgroup and per wavefront
+    constexpr int DC = D / 16, DB = D / 32;        // 16-channel steps of the scores, 32-channel blocks of the output
+    constexpr int ROWB = 2 * D;                    // bytes of a K or V row
+    constexpr int GROUPS = D / 8, GPW = GROUPS / 4;        // row groups of a tile, and per wavefront
+    constexpr int LPR = D / 8;                     // lanes that carry one row of a tile load
+    constexpr int LPT = 2 * GPW;                   // loads per wavefront and tile
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -386,16 +390,16 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
     // Query blocks are aligned to the END of the sequence: a ragged block is then the first one,
     // which has the fewest keys to waste wavefronts on (query indices below 0 do not exist).
     const int q0 = N - (n_qb - qb) * BM, wq0 = q0 + QW * wv;
-    const int64_t q_rs = (int64_t)Hq * AT_D, kv_rs = (int64_t)Hkv * AT_D;
+    const int64_t q_rs = (int64_t)Hq * D, kv_rs = (int64_t)Hkv * D;
 
     // Q^T fragments of the query blocks
-    bf16x8 qf[U][8];
+    bf16x8 qf[U][DC];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int query = max(wq0 + 32 * u + l32, 0);
-        const uint16_t* qp = q + ((int64_t)b * N + query) * q_rs + h * AT_D + 8 * g;
+        const uint16_t* qp = q + ((int64_t)b * N + query) * q_rs + h * D + 8 * g;
 #pragma unroll
-        for (int dc = 0; dc < 8; ++dc) qf[u][dc] = *reinterpret_cast<const bf16x8*>(qp + 16 * dc);
+        for (int dc = 0; dc < DC; ++dc) qf[u][dc] = *reinterpret_cast<const bf16x8*>(qp + 16 * dc);
     }
     // The Q fragments are only ever MFMA operands, which may come from the accumulation
     // registers: keep them there, so the 64 of them do not compete with the accumulators and
@@ -404,13 +408,13 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int dc = 0; dc < 8; ++dc) asm volatile("" : "+a"(qf[u][dc]));
+        for (int dc = 0; dc < DC; ++dc) asm volatile("" : "+a"(qf[u][dc]));
 
-    f32x16 o[U][4];
+    f32x16 o[U][DB];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < DB; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[u][i][r] = 0.f;
     // per query: reference of the exponentials (log2 units), the raw score above which it must be
@@ -430,12 +434,12 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
     const int my_tiles = wq0 + QW > 0 ? (wave_kend + AW_BN - 1) / AW_BN : 0;
     // tiles whose 64 keys are visible to all 64 queries and lie inside the sequence: no masking
     const int full_tiles = min(CAUSAL ? max(wq0, 0) / AW_BN : N / AW_BN, min(N / AW_BN, my_tiles));
-    const char* kbase = reinterpret_cast<const char*>(k + (int64_t)b * N * kv_rs + hk * AT_D);
-    const char* vbase = reinterpret_cast<const char*>(v + (int64_t)b * N * kv_rs + hk * AT_D);
+    const char* kbase = reinterpret_cast<const char*>(k + (int64_t)b * N * kv_rs + hk * D);
+    const char* vbase = reinterpret_cast<const char*>(v + (int64_t)b * N * kv_rs + hk * D);
 
-    // Direct-to-LDS loads.  A tile (64 keys) is 16 KiB groups for K and 16 for V: group g holds rows
-    // {g, g+16, g+32, g+48}; a wavefront fetches groups 4*wv .. 4*wv+3 of both, one buffer load of 16 bytes
-    // per lane each: lane L carries row g + 16*(L/16), 16-byte chunk L%16.  The address of a load is split so
+    // Direct-to-LDS loads.  A tile (64 keys) is GROUPS groups of 1 KiB for K and as many for V: group g holds rows
+    // {g, g+GROUPS, ..}; a wavefront fetches GPW groups of both, one buffer load of 16 bytes
+    // per lane each: lane L carries row g + GROUPS*(L/LPR), 16-byte chunk L%LPR.  The address of a load is split so
     // that nothing per-lane ever changes: the descriptor holds the base of this (sample, KV head), the scalar
     // offset the tile and the row group, and ONE vector register the lane's row and chunk.  A load is then
     // three instructions and no vector arithmetic.
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
         (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)aw_lds);
     const unsigned row_bytes = (unsigned)(kv_rs * 2);
     const unsigned tile_stride = AW_BN * row_bytes;
-    const unsigned n_rec = (unsigned)(N - 1) * row_bytes + AT_D * 2;      // through the last row of THIS head
+    const unsigned n_rec = (unsigned)(N - 1) * row_bytes + D * 2;      // through the last row of THIS head
     auto make_desc = [&](const char* base) __attribute__((always_inline)) {
         const uint64_t a = reinterpret_cast<uint64_t>(base);
         u32x4 d;                          // raw buffer: base address, no stride, byte range, 32-bit data format
@@ -456,12 +460,12 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
         return d;
     };
     const u32x4 k_desc = make_desc(kbase), v_desc = make_desc(vbase);
-    const unsigned lane_off = (unsigned)(4 * wv + 16 * (lane >> 4)) * row_bytes + ((unsigned)(lane & 15) << 4);
-    // load j of tile t: row group 4*wv + j/2 of K (j even) or V (j odd)
+    const unsigned lane_off = (unsigned)(GPW * wv + GROUPS * (lane / LPR)) * row_bytes + ((unsigned)(lane % LPR) << 4);
+    // load j of tile t: row group GPW*wv + j/2 of K (j even) or V (j odd)
     auto issue_one = [&](int t, int j) __attribute__((always_inline)) {
         const int i = j >> 1;
-        const unsigned stage = lds_base0 + (t % AW_STAGES) * AW_STAGE;
-        const unsigned dst = (j & 1) ? stage + AW_KTILE + (4 * wv + i) * AW_VGRP : stage + (4 * wv + i) * AW_KGRP;
+        const unsigned stage = lds_base0 + (t % AW_STAGES) * AW_STAGE<D>;
+        const unsigned dst = (j & 1) ? stage + AW_KTILE<D> + (GPW * wv + i) * AW_VGRP : stage + (GPW * wv + i) * AW_KGRP;
         const unsigned off = (unsigned)t * tile_stride + (unsigned)i * row_bytes;
         if (j & 1)
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
@@ -472,11 +476,11 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
     };
     auto issue_tile = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) issue_one(t, j);
+        for (int j = 0; j < LPT; ++j) issue_one(t, j);
     };
 
     // Software pipeline over "stages" of 32 keys (two per tile).  For stage c, with all U query
-    // blocks: S(c) = 8 U MFMAs, softmax(c) = vector work, PV(c) = 8 U MFMAs.  One straight-line
+    // blocks: S(c) = DC U MFMAs, softmax(c) = vector work, PV(c) = 2 DB U MFMAs.  One straight-line
     // block per stage holds softmax(c) next to the MFMAs of PV(c-1) and S(c+1), which do not
     // depend on it; the two MFMA streams are interleaved so that no accumulator is touched
     // twice in a row.  Score accumulators and probability fragments are double buffered by
@@ -493,30 +497,30 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
     // (kept as 32-bit LDS byte addresses so that the constants fold into the instruction offsets)
     typedef __attribute__((address_space(3))) char lds_char;
     const unsigned lds0 = (unsigned)(uintptr_t)(lds_char*)aw_lds;
-    const unsigned k_lane = lds0 + (l32 & 15) * AW_KGRP + (l32 >> 4) * 256 + g * 16;
-    const unsigned v_lane = lds0 + AW_KTILE + (4 * g + tr_e) * AW_VGRP + (16 * (tr_h & 1) + 4 * tr_a) * 2;
+    const unsigned k_lane = lds0 + (l32 % GROUPS) * AW_KGRP + (l32 / GROUPS) * ROWB + g * 16;
+    const unsigned v_lane = lds0 + AW_KTILE<D> + (4 * g + tr_e) * AW_VGRP + (16 * (tr_h & 1) + 4 * tr_a) * 2;
 
     // MFMA fragments are read from LDS one pipeline block ahead of their use, into two register
     // sets that alternate with the stage parity (the spare accumulation registers hold them),
     // so no block waits for LDS.
-    bf16x8 kfr[2][8];                // K rows of the stage whose scores the block forms
-    s16x4 vlo[2][8], vhi[2][8];      // V^T of the stage whose probabilities the block multiplies
+    bf16x8 kfr[2][DC];               // K rows of the stage whose scores the block forms
+    s16x4 vlo[2][2 * DB], vhi[2][2 * DB];      // V^T of the stage whose probabilities the block multiplies
     auto load_k_frags = [&](int set, int t, int kt) __attribute__((always_inline)) {
-        unsigned Ks = k_lane + (t % AW_STAGES) * AW_STAGE + kt * 512;
+        unsigned Ks = k_lane + (t % AW_STAGES) * AW_STAGE<D> + kt * 512;
         asm("" : "+v"(Ks));          // keep base + constant addressing
 #pragma unroll
-        for (int dc = 0; dc < 8; ++dc)
+        for (int dc = 0; dc < DC; ++dc)
             kfr[set][dc] = *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(Ks + dc * 32);
     };
 
     auto scores_only = [&](int par, int t, int kt) __attribute__((always_inline)) {   // prologue: S of the first stage
-        const unsigned Ks = k_lane + (t % AW_STAGES) * AW_STAGE + kt * 512;
+        const unsigned Ks = k_lane + (t % AW_STAGES) * AW_STAGE<D> + kt * 512;
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[par][u][r] = 0.f;
 #pragma unroll
-        for (int dc = 0; dc < 8; ++dc) {
+        for (int dc = 0; dc < DC; ++dc) {
             const bf16x8 a = *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(Ks + dc * 32);
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -524,8 +528,8 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
         }
     };
     auto values_only = [&](int par, int set) __attribute__((always_inline)) {   // drain: PV of the last stage
-        static_for<0, 8>([&](auto n) {
-            constexpr int tt = n.value >> 2, db = n.value & 3;
+        static_for<0, 2 * DB>([&](auto n) {
+            constexpr int tt = n.value / DB, db = n.value % DB;
             typedef __attribute__((ext_vector_type(8))) short s16x8;
             const s16x8 both = __builtin_shufflevector(vlo[set][n.value], vhi[set][n.value], 0, 1, 2, 3, 4, 5, 6, 7);
             const bf16x8 a = __builtin_bit_cast(bf16x8, both);
@@ -541,14 +545,14 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
     // stage c+2 = (tile t+1, half par) and the V rows of stage c = (tile t, half par).
     auto stage_block = [&](int par, int t, auto masked_c, bool has_prev) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_c)::value;
-        constexpr int SLOTS = 16 * U;
+        constexpr int SLOTS = (DC + 2 * DB) * U;
         const int key0 = t * AW_BN + 32 * par;
         // The fragments requested a whole block ago have long arrived; saying so here (a wait on
         // the LDS counter alone) spares the block partial waits: with its own 24 requests queued
         // behind them the 4-bit counter could not express "only the older ones".
         __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0), other counters untouched
-        unsigned Ks = k_lane + ((t + 1) % AW_STAGES) * AW_STAGE + par * 512;
-        unsigned Vs = v_lane + (t % AW_STAGES) * AW_STAGE + par * 512;
+        unsigned Ks = k_lane + ((t + 1) % AW_STAGES) * AW_STAGE<D> + par * 512;
+        unsigned Vs = v_lane + (t % AW_STAGES) * AW_STAGE<D> + par * 512;
         asm("" : "+v"(Ks));          // keep base + constant addressing
         asm("" : "+v"(Vs));
         // diagonal and ragged tiles: key key0 + 4g + 8(r/4) + r%4 of register r is visible to
@@ -629,16 +633,16 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[par ^ 1][u][r] = 0.f;
-        // 16 U slots: one MFMA (those of S(c+1) first, so that they are complete when the next
-        // block reads them, then the 16 of PV(c-1)), one fragment request, one run of vector work
+        // SLOTS slots: one MFMA (those of S(c+1) first, so that they are complete when the next
+        // block reads them, then those of PV(c-1)), one fragment request, one run of vector work
         auto run_slot = [&](auto slot) __attribute__((always_inline)) {
             constexpr int i = slot.value;
-            if constexpr (i < 8 * U) {
+            if constexpr (i < DC * U) {
                 constexpr int dc = i / U, u = i % U;
                 s[par ^ 1][u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[par][dc], qf[u][dc], s[par ^ 1][u], 0, 0, 0);
             } else {
                 if (has_prev) {
-                    constexpr int n = (i - 8 * U) / U, u = i % U, tt = n >> 2, db = n & 3;
+                    constexpr int n = (i - DC * U) / U, u = i % U, tt = n / DB, db = n % DB;
                     typedef __attribute__((ext_vector_type(8))) short s16x8;
                     const s16x8 both = __builtin_shufflevector(vlo[par][n], vhi[par][n], 0, 1, 2, 3, 4, 5, 6, 7);
                     o[u][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both),
@@ -652,21 +656,22 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
                 kfr[par ^ 1][i / (2 * U)] =
                     *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(Ks + (i / (2 * U)) * 32);
             if constexpr (U == 1 || (i & 1) == 1) {
-                constexpr int half = i / U, n = half >> 1, off = (n >> 2) * 256 + (n & 3) * 64;
+                constexpr int half = i / U, n = half >> 1, off = n / DB * 256 + n % DB * 64;
+                constexpr int eight = 8 / GROUPS * ROWB + 8 % GROUPS * AW_VGRP;                        // eight keys further
                 if constexpr ((half & 1) == 0) vlo[par ^ 1][n] = lds_read_tr16(Vs + off);              // keys of slots 0..3
-                else vhi[par ^ 1][n] = lds_read_tr16(Vs + off + 8 * AW_VGRP);                          // keys of slots 4..7
+                else vhi[par ^ 1][n] = lds_read_tr16(Vs + off + eight);                          // keys of slots 4..7
             }
-            static_for<SM_TABLE_OF<U, MASKED>.start[i], SM_TABLE_OF<U, MASKED>.start[i + 1]>([&](auto k) {
-                constexpr SmOp op = SM_TABLE_OF<U, MASKED>.op[k.value];
+            static_for<SM_TABLE_OF<D, U, MASKED>.start[i], SM_TABLE_OF<D, U, MASKED>.start[i + 1]>([&](auto k) {
+                constexpr SmOp op = SM_TABLE_OF<D, U, MASKED>.op[k.value];
                 vector_op(std::integral_constant<int, op.kind>{}, std::integral_constant<int, op.u>{},
                           std::integral_constant<int, op.i>{});
             });
             __builtin_amdgcn_sched_barrier(0);
         };
-        static_for<0, SM_TABLE_OF<U, MASKED>.check>(run_slot);
+        static_for<0, SM_TABLE_OF<D, U, MASKED>.check>(run_slot);
         check_reference();
         __builtin_amdgcn_sched_barrier(0);
-        static_for<SM_TABLE_OF<U, MASKED>.check, SLOTS>(run_slot);
+        static_for<SM_TABLE_OF<D, U, MASKED>.check, SLOTS>(run_slot);
         // the probabilities are consumed in the next block; without this pin the compiler sinks
         // their computation past the end of this block, away from the MFMAs it must hide behind
 #pragma unroll
@@ -687,20 +692,20 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) o[u][db][r] *= alpha[u];
         }
     };
-    // Start of tile t.  After the wait and the barrier, tile t+1 has landed everywhere (the 8
+    // Start of tile t.  After the wait and the barrier, tile t+1 has landed everywhere (the LPT
     // loads of tile t+2 may still be in flight) and tile t-1 is dead everywhere: its last
     // fragments were requested in the previous block and have arrived (lgkmcnt), so the fetch
     // of tile t+3 may overwrite its stage.
-    // (The eight loads of a tile go out together right after the barrier.  Inside the pipeline blocks they were
+    // (The loads of a tile go out together right after the barrier.  Inside the pipeline blocks they were
     // measured 7 to 15 % slower, whether spread one by one over the MFMA slots or as one burst per wavefront,
     // each wavefront in a slot of its own.)
     auto tile_sync = [&](int t) __attribute__((always_inline)) {
-        if (t + 2 < ntiles) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+        if (t + 2 < ntiles) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPT) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -745,9 +750,9 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
         const float l_tot = l_run[u] + __shfl_xor(l_run[u], 32, 64);
         if (query >= 0) {
             const float inv = 1.0f / l_tot;
-            uint16_t* op = out + ((int64_t)b * N + query) * q_rs + h * AT_D;
+            uint16_t* op = out + ((int64_t)b * N + query) * q_rs + h * D;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+            for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     uint2 pk;
@@ -762,16 +767,21 @@ __global__ __launch_bounds__(256) void attn_wide_kernel(
     }
 }
 
+// Head dimension 64: half the MFMAs and the same softmax per stage, so the vector work sets the time and a second
+// query block per wavefront saves nothing; one block leaves registers and LDS for two workgroups per CU, whose
+// vector and matrix work overlap.  20 x 577 x 16 heads, bidirectional: 73 us with the kernel above,
+// 67 with two blocks, 56 with one; 1 x 6400, 16 / 4 heads, causal: 168, 118, 111 us; 4 x 384: 13.7, 12.4, 11.1.
+constexpr int AW_U64 = 1;
 constexpr int AW_U2_MIN_N = 512;   // a wavefront takes two query blocks from this length on,
 constexpr int AW_U2_MIN_WGS = 256;  // if that still leaves more workgroups than this
 
-template <bool CAUSAL, int U>
+template <int D, bool CAUSAL, int U>
 static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                             int B, int N, int Hq, int Hkv, float sl2, hipStream_t s) {
     static std::atomic<bool> attr_set{false};   // set once; a second thread repeating the call is harmless
-    constexpr int lds = AW_STAGES * AW_STAGE;
+    constexpr int lds = AW_STAGES * AW_STAGE<D>;
     if (!attr_set.load(std::memory_order_acquire)) {
-        const int rc = hip_status(hipFuncSetAttribute((const void*)attn_wide_kernel<CAUSAL, U>,
+        const int rc = hip_status(hipFuncSetAttribute((const void*)attn_wide_kernel<D, CAUSAL, U>,
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds),
                                   "hipFuncSetAttribute(attn_wide)");
         if (rc) return rc;
@@ -784,7 +794,7 @@ static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t
     // (sample, head) pairs in flight together: few, so that their query blocks share K/V
     // in L2, but enough to fill the 256 CUs twice over (measured: 32 from N = 2048 up)
     const int group = std::max(32, (512 / n_qb + 7) / 8 * 8);
-    hipLaunchKernelGGL((attn_wide_kernel<CAUSAL, U>), dim3((unsigned)(n_heads * n_qb)), dim3(256), lds, s, q, k, v,
+    hipLaunchKernelGGL((attn_wide_kernel<D, CAUSAL, U>), dim3((unsigned)(n_heads * n_qb)), dim3(256), lds, s, q, k, v,
                        out, lse, N, Hq, Hkv, sl2, n_qb, (int)n_heads, group);
     return launch_status("attn_wide");
 }
@@ -795,30 +805,27 @@ int launch_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_
     if (B == 0 || N == 0) return VITCOP_OK;
     if (N > (1 << 22)) return fail(VITCOP_EUNSUPPORTED, "attention: N=%d above 2^22", N);   // grid.z limit
     const float sl2 = scale * 1.4426950408889634f;
-    if (d == 64) {
-        dim3 grid(Hq, B, (N + AT_BM - 1) / AT_BM);
-        hipLaunchKernelGGL(attn_kernel<64>, grid, dim3(AT_THREADS), 0, s, q, k, v, out, lse, N, Hq, Hkv, sl2,
-                           causal);
-        return launch_status("attn<64>");
-    }
     // the wide kernel addresses K and V of one (sample, KV head) with 32-bit byte offsets
-    const bool wide_ok = ((int64_t)N + AW_BN) * Hkv * AT_D * 2 < ((int64_t)1 << 32);
-    if (wide_ok) {
-        // Two query blocks per wavefront halve the LDS reads per MFMA, which is what long sequences need; one
-        // block halves the chain of MFMAs a wavefront runs per key tile and doubles the workgroups, which is
-        // what the lengths that survive pruning need (a few hundred tokens: one to six key tiles per workgroup,
-        // latency and not throughput): below 512 tokens, or while 256-query workgroups would not fill the CUs.
-        const long wgs2 = (long)Hq * B * ((N + AW_BM - 1) / AW_BM);
-        if (N >= AW_U2_MIN_N && wgs2 > AW_U2_MIN_WGS)
-            return causal ? launch_attn_wide<true, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
-                          : launch_attn_wide<false, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
-        return causal ? launch_attn_wide<true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
-                      : launch_attn_wide<false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
+    const bool wide_ok = ((int64_t)N + AW_BN) * Hkv * d * 2 < ((int64_t)1 << 32);
+    if (!wide_ok) {
+        dim3 grid(Hq, B, (N + AT_BM - 1) / AT_BM);
+        hipLaunchKernelGGL(d == 64 ? attn_kernel<64> : attn_kernel<128>, grid, dim3(AT_THREADS), 0, s, q, k, v, out, lse,
+                           N, Hq, Hkv, sl2, causal);
+        return launch_status("attn");
     }
-    dim3 grid(Hq, B, (N + AT_BM - 1) / AT_BM);
-    hipLaunchKernelGGL(attn_kernel<128>, grid, dim3(AT_THREADS), 0, s, q, k, v, out, lse, N, Hq, Hkv, sl2,
-                       causal);
-    return launch_status("attn");
+    if (d == 64)
+        return causal ? launch_attn_wide<64, true, AW_U64>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
+                      : launch_attn_wide<64, false, AW_U64>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
+    // Two query blocks per wavefront halve the LDS reads per MFMA, which is what long sequences need; one
+    // block halves the chain of MFMAs a wavefront runs per key tile and doubles the workgroups, which is
+    // what the lengths that survive pruning need (a few hundred tokens: one to six key tiles per workgroup,
+    // latency and not throughput): below 512 tokens, or while 256-query workgroups would not fill the CUs.
+    const long wgs2 = (long)Hq * B * ((N + AW_BM - 1) / AW_BM);
+    if (N >= AW_U2_MIN_N && wgs2 > AW_U2_MIN_WGS)
+        return causal ? launch_attn_wide<128, true, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
+                      : launch_attn_wide<128, false, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
+    return causal ? launch_attn_wide<128, true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
+                  : launch_attn_wide<128, false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
 }
 
 }  // namespace vitcop

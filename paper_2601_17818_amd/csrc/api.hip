@@ -1255,16 +1255,12 @@ int vitcop_decoder_decode_step(const vitcop_decoder_decode_t* S, void* ws, size_
             if (rc) return rc;
             a = abuf[0];
         }
-        const uint16_t* const w3[3] = {S->wk[l], S->wq[l], S->wv[l]};
-        uint16_t* const y3[3] = {k_new, qb, v_new};
-        const int n3[3] = {kd, qd, kd};
-        rc = launch_gemm_triple_ws(a, D, w3, y3, n3, B, D, gs, gs_bytes, s);
-        if (rc) return rc;
         // the rotary embedding; the new token's K and V become row N of every sample's cache
         const int32_t* ncs = S->n_cached_samples ? S->n_cached_samples + (size_t)l * B : nullptr;
         const size_t row0 = ncs ? 0 : (size_t)N * kd;
-        rc = launch_rope_append(qb, k_new, v_new, S->positions, B, S->Hq, S->Hkv, S->d, S->theta,
-                                S->k_cache[l] + row0, S->v_cache[l] + row0, (int64_t)S->cache_capacity * kd, s, ncs);
+        rc = launch_gemm_qkv_append_ws(a, D, S->wk[l], S->wq[l], S->wv[l], k_new, qb, v_new, S->Hq, S->Hkv, S->d,
+                                       S->positions, S->theta, B, D, gs, gs_bytes, S->k_cache[l] + row0,
+                                       S->v_cache[l] + row0, (int64_t)S->cache_capacity * kd, ncs, s);
         if (rc) return rc;
         rc = launch_decode_attn(qb, S->k_cache[l], S->v_cache[l], ob, nullptr, B, N + 1, S->Hq, S->Hkv, S->d,
                                 1.0f / std::sqrt((float)S->d), dws, s, (int64_t)S->cache_capacity * kd, nullptr, ncs);

@@ -1,290 +1,31 @@
-// Linear projection y = x W^T for FEW rows (M <= 256): what the projections of a decoder layer
+// Linear projections y = x W^T for FEW rows (M <= 256): what the projections of a decoder layer
 // look like after the pruning of Sec. 3.2.2 has cut the sequence to a few hundred tokens.  The
 // weight matrix is then nearly all of the traffic (one pass over W per launch) and the launch is
-// bound by HBM, not by the matrix cores.  One CU with four wavefronts pulls at most about 50 GB/s
-// from HBM, so the whole chip must take part, whatever N and K are:
+// bound by HBM, not by the matrix cores, so all 256 CUs must stream whatever N and K are:
 //
-//   * the work is cut into units of (128 output columns) x (64 k-values); the units, ordered
-//     column group by column group, are dealt out evenly to at most 256 workgroups, so a
-//     workgroup's share is a k-range of one column group, or the tail of one group and the head
-//     of the next (two segments);
-//   * both operands are fetched with whole 128-byte lines per 8 lanes (the vector memory path
-//     moves lines, so the MFMA operand layout, 32 rows x 32 bytes per instruction, would cost four
-//     times the cycles) into registers, two units ahead of the multiply, and written to one of
-//     two LDS slabs one unit before their use, with the same swizzle as the big-tile GEMM; all
-//     loads are ordinary ones, so the compiler's own counting of outstanding loads places every
-//     wait (mixed with direct-to-LDS loads it falls back to full drains);
-//   * the four wavefronts sit 2 x 2 over the (rows of x) x (128 columns) tile;
+//   * one tile holds all rows of x (32 to 256 in steps of 32) and 64, 96 or 128 columns, and the
+//     k-range is cut into slices until about 256 workgroups exist (gemm_kernel.h; its ring of
+//     direct loads keeps three k-steps of both operands in flight per workgroup);
 //   * up to three weight matrices can sit side by side in one launch (K, Q and V; gate and up);
-//   * every segment writes an fp32 partial tile; a second kernel adds the partials of a column
-//     group in workgroup order (deterministic) and finishes the rows in one of three ways: residual,
-//     bf16 rounding and, for the K projection, the per-128-column sums of squares of the rounded
-//     outputs for the K-norm of Eq. 4; the same plus the RMSNorm of the finished row; or the gated
-//     activation silu(gate) * up of the MLP.  The same reductions serve the split-K launches of the
-//     big-tile kernel (gemm.hip), whose partials are whole slices.
-#include <atomic>
+//   * the slices leave fp32 partial sums; a second kernel adds them in slice order (deterministic)
+//     and finishes the rows in one of three ways: residual, bf16 rounding and, for the K projection,
+//     the per-128-column sums of squares of the rounded outputs for the K-norm of Eq. 4; the same
+//     plus the RMSNorm of the finished row; or the gated activation silu(gate) * up of the MLP.
+//     The same reductions serve the k-slices of launches with more rows (gemm.hip);
+//   * the MLP's gate and up projections need no partial sums where their columns alone keep most
+//     CUs streaming: the activation is then applied in the tile's epilogue.
+#include <algorithm>
 #include <cmath>
-#include "vitcop_internal.h"
-#include "device_utils.h"
+#include "gemm_kernel.h"
 
 namespace vitcop {
 
-constexpr int SK_THREADS = 256;
-constexpr int SK_COLS = 128;          // output columns per unit
-constexpr int SK_UNIT = 64;           // k-values per unit (one 128-byte line per row)
+constexpr int SK_COLS = 128;          // columns per sum-of-squares partial
+constexpr int SK_UNIT = 64;           // k-values per step (one 128-byte line per row)
 constexpr int SK_MAX_ROWS = 256;
 constexpr int SK_MAX_WGS = 256;       // one per CU
 
-// Units held in registers: the one being stored to LDS and one more in flight behind it.  A deeper
-// ring does not put more bytes in flight: a CU's load queue fills, the wavefront blocks on issuing
-// the prologue's loads, and the first multiply only starts later (measured with 4, 6 and 8 slots).
-constexpr int SK_SLOTS = 2;
-
-struct SkPick {
-    int mi, start;
-};
-__device__ __forceinline__ SkPick sk_pick(const SkMats& mats, int n) {
-    const int mi = (n >= mats.n_end[0] ? 1 : 0) + (n >= mats.n_end[1] ? 1 : 0);
-    return {mi, mi == 0 ? 0 : (mi == 1 ? mats.n_end[0] : mats.n_end[1])};
-}
-
-// Workgroup i of P owns the units [first(i), first(i+1)) of the group-major order: total / P units
-// each, one more for the first total % P workgroups (q and r below; no division on the device).
-__host__ __device__ __forceinline__ int sk_first_unit(int i, int q, int r) { return i * q + min(i, r); }
-
-// part[2 * workgroup + segment][m][128] (fp32) = sum over the segment's k-range of x[m,k] W[n,k]
-// for the 128 columns n of the segment's group.  With part == nullptr every workgroup owns exactly
-// one whole column group and writes bf16(sum + residual) to its matrix's output itself.
-template <int MB>
-__global__ __launch_bounds__(SK_THREADS) void gemm_skinny_kernel(
-    const uint16_t* __restrict__ x, int64_t x_stride, SkMats mats, int64_t w_stride, int M, int N, int K,
-    int units_q, int units_r, float* __restrict__ part, const uint16_t* __restrict__ res,
-    int64_t res_stride) {
-    constexpr int NSLOT = SK_SLOTS;
-    constexpr int XROWS = MB * 32;
-    constexpr int ROWS = XROWS + SK_COLS;                // slab rows: x, then the group's rows of W
-    constexpr int SLAB = ROWS * 128;                     // bytes: 64 k-values per row
-    constexpr int NLD = ROWS / 8 / 4;                    // loads per wavefront per unit (8 rows each)
-    constexpr int MI = MB / 2;                           // row blocks per wavefront (2 x 2 wavefronts: rows x columns)
-    constexpr int SROW = 256 + 16;                       // epilogue staging row: 64 fp32, padded
-    constexpr int STAGE = 32 * SROW;                     // per wavefront: one 32 x 64 block
-    static_assert(NSLOT % 2 == 0, "the slab of a unit must be known at compile time");
-    static_assert(MB % 2 == 0, "two wavefronts share the rows");
-    static_assert(2 * SLAB >= 4 * STAGE, "the epilogue reuses the slabs");
-    extern __shared__ __attribute__((aligned(1024))) char sk_lds[];     // 2 * SLAB bytes
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, g = lane >> 5;
-    // A wavefront multiplies MI row blocks of x with 2 column blocks of W: (MI + 2) fragment reads per
-    // 2 MI multiplies; one column block against all rows would read (MB + 1) per MB, and the LDS
-    // reads of the four wavefronts are what bounds the loop at 192 and 256 rows.
-    const int wr = wv & 1, wc = wv >> 1;
-    const int upg = K / SK_UNIT;                         // units per column group
-    const int first = sk_first_unit(blockIdx.x, units_q, units_r);
-    const int last = sk_first_unit(blockIdx.x + 1, units_q, units_r);    // exclusive; last - first <= upg
-    const int m_rows = M;                                // <= MB * 32
-
-    // every wavefront's LDS accesses are done, its writes visible, after this
-    auto lds_barrier = [&]() {
-        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0) only: the global loads stay in flight
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    };
-
-    for (int seg = 0, u_begin = first; u_begin < last; ++seg) {
-        const int grp = (int)((unsigned)u_begin / (unsigned)upg);
-        const int u0 = u_begin - grp * upg;                          // first unit inside the group
-        const int nk = min(last, (grp + 1) * upg) - u_begin;         // units of this segment
-        u_begin += nk;
-        const SkPick pick = sk_pick(mats, grp * SK_COLS);            // which matrix this group belongs to
-        const int n0 = grp * SK_COLS - pick.start;                   // first column inside that matrix
-        const int n_rows = mats.n_end[pick.mi] - pick.start;
-        const uint16_t* wm = mats.w[pick.mi];
-
-        f32x16 acc[MI][2];
-#pragma unroll
-        for (int j = 0; j < MI; ++j)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
-
-        // Load q of wavefront wv covers slab rows (wv*NLD+q)*8 .. +8; lane L fetches chunk L%8 (16
-        // bytes) of row L/8 and stores it at chunk position (L%8) ^ (row%8).
-        // (operand base in scalar registers + a 32-bit lane offset: operands are below 2^31 elements;
-        // whether a load fetches x or W is uniform, so stride, row limit and row shift are picked as
-        // scalars first: a workgroup starts with one wavefront per SIMD, which issues an instruction
-        // every few cycles, so every instruction ahead of the first load delays the whole launch)
-        const char* base[NLD];
-        unsigned src[NLD];
-        int dst[NLD];
-        const int xs32 = (int)x_stride, ws32 = (int)w_stride;
-#pragma unroll
-        for (int q = 0; q < NLD; ++q) {
-            const int row0 = (wv * NLD + q) * 8, row = row0 + (lane >> 3);
-            const bool is_x = row0 < XROWS;                          // uniform: 8 rows never straddle
-            base[q] = reinterpret_cast<const char*>(is_x ? x : wm);
-            const int stride = is_x ? xs32 : ws32, limit = is_x ? m_rows - 1 : n_rows - 1;
-            const int shift = is_x ? 0 : n0 - XROWS;
-            src[q] = 2u * (unsigned)(min(row + shift, limit) * stride) + 16 * (lane & 7);
-            dst[q] = row * 128 + (((lane & 7) ^ (row & 7)) << 4);
-        }
-        u32x4 held[NSLOT][NLD];
-        // Past the segment's end every lane reads the operand's first 16 bytes instead (one line per
-        // instruction, never used): the number of loads in flight stays a compile-time fact, which
-        // the compiler's wait counts need, while the memory pipeline carries next to nothing for
-        // them; with a handful of units per segment, full loads that nobody uses would be a large
-        // part of its work.
-        auto issue_loads = [&](int slot, int step) {
-            const bool live = step < nk;
-            const int64_t off = live ? (int64_t)(u0 + step) * (SK_UNIT * 2) : 0;
-#pragma unroll
-            for (int q = 0; q < NLD; ++q)
-                held[slot][q] = *reinterpret_cast<const u32x4*>(base[q] + off + (live ? src[q] : 0u));
-        };
-        auto store_slab = [&](int slot, int slab) {
-#pragma unroll
-            for (int q = 0; q < NLD; ++q) *reinterpret_cast<u32x4*>(sk_lds + slab * SLAB + dst[q]) = held[slot][q];
-        };
-        // MFMA fragments: lane (l32, g) reads the 8 k-values 16*kc + 8*g .. of a row
-        bf16x8 xf[2][MI], wf[2][2];
-        auto read_frags = [&](int buf, int slab, int kc) {
-            const char* S = sk_lds + slab * SLAB;
-#pragma unroll
-            for (int j = 0; j < MI; ++j) {
-                const int row = (wr * MI + j) * 32 + l32;
-                xf[buf][j] = *reinterpret_cast<const bf16x8*>(S + row * 128 + (((2 * kc + g) ^ (row & 7)) << 4));
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int row = XROWS + (wc * 2 + i) * 32 + l32;
-                wf[buf][i] = *reinterpret_cast<const bf16x8*>(S + row * 128 + (((2 * kc + g) ^ (row & 7)) << 4));
-            }
-        };
-        auto multiply = [&](int buf) {
-#pragma unroll
-            for (int j = 0; j < MI; ++j)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][i], xf[buf][j], acc[j][i], 0, 0, 0);
-        };
-        // Scheduling hints: a phase is MB multiplies; the MI + 2 LDS reads of the next phase's
-        // fragments follow the first multiplies one by one and, if `extra` names a class (0x200 LDS
-        // write, 0x020 global load), every multiply is followed by one instruction of that class;
-        // what is left of the NLD extras closes the phase.
-#define VITCOP_PHASE(extra)                                              \
-    _Pragma("unroll") for (int q_ = 0; q_ < MB; ++q_) {                  \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               \
-        if (q_ < MI + 2) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); \
-        if ((extra) != 0) __builtin_amdgcn_sched_group_barrier((extra), 1, 0); \
-    }                                                                    \
-    if (MB < MI + 2) __builtin_amdgcn_sched_group_barrier(0x100, MI + 2 - MB, 0); \
-    if ((extra) != 0) __builtin_amdgcn_sched_group_barrier((extra), NLD - MB, 0);
-        // Unit t: slab t % 2, registers slot t % NSLOT.  The operands of unit t+1 go to the other
-        // slab (every wavefront left it at the barrier that ended unit t-1); the loads of unit
-        // t+1+NSLOT take the registers just stored.  The fragments of a 16-wide slice are read
-        // while the slice before it is multiplied.
-        auto unit = [&](int t, int slot) {
-            const int slab = slot & 1, next = (slot + 1) % NSLOT;
-            read_frags(1, slab, 1);               // reads before writes: the compiler keeps LDS accesses in order
-            store_slab(next, slab ^ 1);
-            multiply(0);
-            VITCOP_PHASE(0x200)
-            issue_loads(next, t + 1 + NSLOT);
-            read_frags(0, slab, 2);
-            multiply(1);
-            VITCOP_PHASE(0x020)
-            read_frags(1, slab, 3);
-            multiply(0);
-            VITCOP_PHASE(0)
-            lds_barrier();
-            read_frags(0, slab ^ 1, 0);
-            multiply(1);
-            VITCOP_PHASE(0)
-        };
-        // The wavefronts issue their first loads unit by unit in step (a barrier between units):
-        // left alone, the oldest wavefront queues all of its loads first and the unit-0 data of
-        // the youngest, which the first barrier of the pipeline waits for, arrives last.
-        lds_barrier();                            // the slabs are free (previous segment's epilogue)
-#pragma unroll
-        for (int p = 0; p < NSLOT; ++p) {
-            issue_loads(p, p);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
-        store_slab(0, 0);
-        issue_loads(0, NSLOT);
-        lds_barrier();
-        read_frags(0, 0, 0);
-        int t = 0;
-        for (; t + NSLOT <= nk; t += NSLOT) {
-#pragma unroll
-            for (int p = 0; p < NSLOT; ++p) unit(t + p, p);
-        }
-#pragma unroll
-        for (int p = 0; p < NSLOT - 1; ++p)
-            if (t + p < nk) unit(t + p, p);
-#undef VITCOP_PHASE
-
-        // Epilogue.  A lane owns row m = 32 j + l32 and the column runs n = 8 (r/4) + 4 g + r%4 of
-        // its wavefront's 32: stored from there, an instruction would touch 32 rows with 32 bytes
-        // each.  Each wavefront stages one 32 x 64 block at a time in LDS (rows padded by 16 bytes)
-        // and writes it with 16 lanes per 256-byte row piece of the partial tile.
-        lds_barrier();                                       // the last unit's slab reads are done
-        char* stage = sk_lds + wv * STAGE;
-        const int srow = lane >> 4, scol = (lane & 15) * 4;  // store side: row within a group of 4, first column
-        const int n = n0 + wc * 64 + scol;                   // column inside the selected matrix
-        const int m0 = wr * MI * 32;                         // first row of this wavefront
-        // running addresses, 4 rows further per store (kept as additions: what the compiler hoists
-        // to the top of the kernel from here runs ahead of the first load)
-        float* out = part + ((int64_t)(2 * blockIdx.x + seg) * M + m0 + srow) * SK_COLS + wc * 64 + scol;
-        const int64_t y_stride = mats.y_stride[pick.mi];
-        uint16_t* yrow = mats.y[pick.mi] + (int64_t)(m0 + srow) * y_stride + n;
-        const uint16_t* rrow = res + (int64_t)(m0 + srow) * res_stride + n;
-#pragma unroll
-        for (int j = 0; j < MI; ++j) {
-            if (m0 + j * 32 >= m_rows) break;
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    float4 o;
-                    o.x = acc[j][i][4 * r4];
-                    o.y = acc[j][i][4 * r4 + 1];
-                    o.z = acc[j][i][4 * r4 + 2];
-                    o.w = acc[j][i][4 * r4 + 3];
-                    *reinterpret_cast<float4*>(stage + l32 * SROW + (32 * i + 8 * r4 + 4 * g) * 4) = o;
-                }
-            // (a wavefront reads back only what it wrote itself: the LDS counter suffices, no barrier)
-#pragma unroll
-            for (int r0 = 0; r0 < 32; r0 += 4) {
-                const int m = m0 + j * 32 + r0 + srow;
-                float4 o = *reinterpret_cast<const float4*>(stage + (r0 + srow) * SROW + scol * 4);
-                if (m < m_rows) {
-                    if (part != nullptr) {
-                        *reinterpret_cast<float4*>(out) = o;
-                    } else if (n < n_rows) {                         // direct: the segment is the whole k-range
-                        if (res) {
-                            const uint2 rr = *reinterpret_cast<const uint2*>(rrow);
-                            o.x += bf16_lo(rr.x); o.y += bf16_hi(rr.x);
-                            o.z += bf16_lo(rr.y); o.w += bf16_hi(rr.y);
-                        }
-                        uint2 pk;
-                        pk.x = pack_bf16(o.x, o.y);
-                        pk.y = pack_bf16(o.z, o.w);
-                        *reinterpret_cast<uint2*>(yrow) = pk;
-                    }
-                }
-                out += 4 * SK_COLS;
-                yrow += 4 * y_stride;
-                rrow += 4 * res_stride;
-            }
-        }
-    }
-}
-
-// v[0..8) = sum, in workgroup (or slice) order, of the partials of row m, columns n .. n+8 (n a
+// v[0..8) = sum, in slice order, of the partials of row m, columns n .. n+8 (n a
 // multiple of 8).  Four loads are in flight at a time; the additions keep the order.
 __device__ __forceinline__ void sk_sum_tiles(const SkParts& P, int m, int n, float (&v)[8]) {
 #pragma unroll
@@ -311,19 +52,7 @@ __device__ __forceinline__ void sk_sum_tiles(const SkParts& P, int m, int n, flo
             v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
         }
     };
-    if (P.units_q == 0) {
-        sum_range(0, P.units_r - 1, [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.upg + n; });
-        return;
-    }
-    const int grp = n / SK_COLS;
-    auto owner = [&](int u) {               // the workgroup whose unit range holds unit u
-        const int big = P.units_r * (P.units_q + 1);      // units held by the workgroups with one more
-        return u < big ? u / (P.units_q + 1) : P.units_r + (u - big) / P.units_q;
-    };
-    sum_range(owner(grp * P.upg), owner((grp + 1) * P.upg - 1), [&](int i) {
-        const int seg = sk_first_unit(i, P.units_q, P.units_r) / P.upg == grp ? 0 : 1;   // its first or its second group
-        return P.part + ((int64_t)(2 * i + seg) * P.M + m) * SK_COLS + (n & (SK_COLS - 1));
-    });
+    sum_range(0, P.slices - 1, [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.N + n; });
 }
 
 // The same for two column chunks of one 128-column group at once, n .. n+8 and n+delta .. n+delta+8: both
@@ -360,24 +89,12 @@ __device__ __forceinline__ void sk_sum_tiles2(const SkParts& P, int m, int n, in
             w[4] += d.x; w[5] += d.y; w[6] += d.z; w[7] += d.w;
         }
     };
-    if (P.units_q == 0) {
-        sum_range(0, P.units_r - 1, [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.upg + n; });
-        return;
-    }
-    const int grp = n / SK_COLS;
-    auto owner = [&](int u) {
-        const int big = P.units_r * (P.units_q + 1);
-        return u < big ? u / (P.units_q + 1) : P.units_r + (u - big) / P.units_q;
-    };
-    sum_range(owner(grp * P.upg), owner((grp + 1) * P.upg - 1), [&](int i) {
-        const int seg = sk_first_unit(i, P.units_q, P.units_r) / P.upg == grp ? 0 : 1;
-        return P.part + ((int64_t)(2 * i + seg) * P.M + m) * SK_COLS + (n & (SK_COLS - 1));
-    });
+    sum_range(0, P.slices - 1, [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.N + n; });
 }
 
-// y[m, n..n+8) = bf16(sum of the partial tiles of n's column group, in workgroup order, + residual);
+// y[m, n..n+8) = bf16(sum of the slices' partials, in slice order, + residual);
 // one thread per 8 columns, 16 consecutive lanes per 128-column group, which also yields that
-// group's sum of squares of the rounded outputs.  P = workgroups of the first kernel.
+// group's sum of squares of the rounded outputs.
 __global__ __launch_bounds__(256) void gemm_skinny_reduce_kernel(
     SkParts parts, int N, SkMats mats, const uint16_t* __restrict__ res, int64_t res_stride,
     float* __restrict__ sumsq_parts) {
@@ -424,8 +141,6 @@ __global__ __launch_bounds__(256) void gemm_skinny_reduce_kernel(
     }
 }
 
-// Workgroups of the first kernel: one per CU if there is work for that many (two units each at
-// least), never fewer than column groups (so that a workgroup's share stays within two groups).
 // The same reduction followed by an RMSNorm of the finished row (the next operation of a decoder
 // layer after its attention and MLP output projections): y as above, and
 // norm_out[m, :] = y[m, :] / sqrt(mean(y[m, :]^2) + eps) * ln_w, computed from the ROUNDED y exactly as
@@ -494,7 +209,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_reduce_silu_kernel(
     const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int m = (int)(id / chunks), c = (int)(id % chunks);
     if (m >= M) return;
-    // bf16(sum of the partial tiles of the 8 columns from n on, in workgroup order), packed
+    // bf16(sum of the partials of the 8 columns from n on, in slice order), packed
     auto reduced = [&](int n) {
         float v[8];
         sk_sum_tiles(parts, m, n, v);
@@ -518,7 +233,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_reduce_silu_kernel(
 // with (the angles are computed once per pair, as in rope_kernel); of v 16 consecutive columns.
 __global__ __launch_bounds__(256) void qkv_finish_kernel(
     QkvParts P, uint16_t* __restrict__ k, uint16_t* __restrict__ q, uint16_t* __restrict__ v, int Hq, int Hkv,
-    int d, const int32_t* __restrict__ positions, float rope_c) {
+    int d, const int32_t* __restrict__ positions, float rope_c, int64_t kv_stride, const int32_t* __restrict__ kv_rows) {
     const int g16 = d / 16, M = P.parts[0].M;
     const int units = (Hq + 2 * Hkv) * g16;
     const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -557,8 +272,8 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(
         lw[p] = pack_bf16(a[2 * p], a[2 * p + 1]);
         hw[p] = pack_bf16(bvals[2 * p], bvals[2 * p + 1]);
     }
-    const int width = mat == 1 ? Hq * d : Hkv * d;
-    uint16_t* dst = (mat == 0 ? k : (mat == 1 ? q : v)) + (int64_t)m * width;
+    uint16_t* dst = mat == 1 ? q + (int64_t)m * Hq * d
+                             : (mat == 0 ? k : v) + m * kv_stride + (kv_rows ? (int64_t)kv_rows[m] * Hkv * d : 0);
     if (mat != 2) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -579,55 +294,123 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(
 }
 
 int launch_qkv_finish(const QkvParts& P, uint16_t* k, uint16_t* q, uint16_t* v, int Hq, int Hkv, int d,
-                      const int32_t* positions, float theta, hipStream_t s) {
+                      const int32_t* positions, float theta, hipStream_t s, int64_t kv_stride, const int32_t* kv_rows) {
     const int64_t threads = (int64_t)P.parts[0].M * (Hq + 2 * Hkv) * (d / 16);
     if (threads == 0) return VITCOP_OK;
     hipLaunchKernelGGL(qkv_finish_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, P, k, q, v, Hq,
-                       Hkv, d, positions, -2.0f * std::log2(theta) / (float)d);
+                       Hkv, d, positions, -2.0f * std::log2(theta) / (float)d,
+                       kv_stride ? kv_stride : (int64_t)Hkv * d, kv_rows);
     return launch_status("qkv_finish");
 }
 
-// With this many column groups one workgroup per group already keeps most CUs streaming, at a
-// higher rate each, and the partial tiles and their reduction are saved.
+// From this many column groups on the columns alone keep most CUs streaming: whole tiles write their outputs
+// themselves, and the partial sums and their reduction are saved.
 constexpr int SK_DIRECT_GROUPS = 128;
-static bool skinny_direct(int M, int N, bool want_sumsq) {
+static bool skinny_direct(int N, bool want_sumsq) {
     return !want_sumsq && (N + SK_COLS - 1) / SK_COLS >= SK_DIRECT_GROUPS;
-}
-static int skinny_workgroups(int M, int N, int K) {
-    const int groups = (N + SK_COLS - 1) / SK_COLS, total = groups * (K / SK_UNIT);
-    return max(groups, min(SK_MAX_WGS, total / 2));
 }
 
 bool gemm_skinny_applies(int M, int N, int K) {
     return M >= 1 && M <= SK_MAX_ROWS && K % SK_UNIT == 0 && K >= 2 * SK_UNIT && N % 8 == 0;
 }
 
+// Scratch of a launch: twice 128 columns for each of the 256 workgroups (or column groups, if there are more);
+// the plan below stays within it.
+static int skinny_scratch_columns(int N, int K) {
+    const int groups = (N + SK_COLS - 1) / SK_COLS, total = groups * (K / SK_UNIT);
+    return 2 * SK_COLS * std::max(groups, std::min(SK_MAX_WGS, total / 2));
+}
+
 size_t gemm_skinny_workspace_bytes(int M, int N, int K) {
     if (!gemm_skinny_applies(M, N, K)) return 0;
-    return up256((size_t)2 * skinny_workgroups(M, N, K) * M * SK_COLS * 4);
+    return up256((size_t)skinny_scratch_columns(N, K) * M * 4);
 }
 
-template <int MB>
-static int launch_skinny_cfg(const uint16_t* x, int64_t x_stride, const SkMats& mats, int64_t w_stride, int M, int N,
-                             int K, int wgs, int units_q, int units_r, float* part,
-                             const uint16_t* res, int64_t res_stride, hipStream_t s) {
-    auto kern = gemm_skinny_kernel<MB>;
-    constexpr size_t lds = (size_t)2 * (MB * 32 + SK_COLS) * 128;
-    static std::atomic<bool> attr_set{false};   // set once; a second thread repeating the call is harmless
-    if (!attr_set.load(std::memory_order_acquire)) {
-        int rc = hip_status(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                (int)lds),
-                            "hipFuncSetAttribute(gemm_skinny)");
-        if (rc) return rc;
-        attr_set.store(true, std::memory_order_release);
-    }
-    hipLaunchKernelGGL(kern, dim3(wgs), dim3(SK_THREADS), lds, s, x, x_stride, mats, w_stride, M, N, K, units_q,
-                       units_r, part, res, res_stride);
-    return launch_status("gemm_skinny");
+// Time of one launch in microseconds.  A workgroup's step over 64 of k costs what its share of the HBM stream
+// and its rows of x (from L2) take; the stream's rate is shared by the workgroups (with all 256 at work 0.095 ns
+// per k and column, 5.4 TB/s; fewer draw less each than their number would allow, about as its square root),
+// the rows cost 0.03 ns per k each.  Fitted to K = 4096 and 11008 at 32 to 224 rows; within 15 % of each.
+// (Kernel alone, weights from HBM, against the unit-dealing kernel with register staging used before: 115 rows
+// 12288x4096 31.4 -> 27.3 us, 4096x4096 15.2 -> 12.1, 4096x11008 31.0 -> 27.3, gate/up 22016x4096 58.7 + 7 for the
+// reduction -> 48.2; 224 rows 45.7 -> 32.9, 20.3 -> 17.1, 44.1 -> 36.6, 76.1 + 8 -> 57.0; 64 rows 26.6 -> 24.8,
+// 10.9 -> 9.9, 22.7 -> 22.3, 43.9 + 5 -> 42.3.)
+static float skinny_us(int rows, int cols, int wgs, int k) {
+    const float share = std::sqrt(std::min(1.0f, (float)wgs / SK_MAX_WGS));
+    const float rounds = (float)((wgs + SK_MAX_WGS - 1) / SK_MAX_WGS);
+    return 3.0f + rounds * (float)k * (0.095e-3f * (float)cols * share + 0.03e-3f * (float)rows);
 }
+static int skinny_rows(int M) { return (M + 31) / 32 * 32; }
+
+struct SkinnyPlan {
+    int cols, slices;
+    float us;                            // of the launch and the traffic of its partial sums
+};
+static SkinnyPlan skinny_plan(int M, int N, int K) {
+    const int steps = K / SK_UNIT;
+    SkinnyPlan best{0, 0, 1e30f};
+    for (int cols : {64, 96, 128}) {
+        const int tiles = (N + cols - 1) / cols;
+        const int most = std::min(std::min(16, steps), skinny_scratch_columns(N, K) / N);
+        for (int s = 1; s <= most; ++s) {
+            const float us = skinny_us(skinny_rows(M), cols, tiles * s, (steps + s - 1) / s * SK_UNIT) +
+                             (float)s * (float)M * (float)N * 12.0f / 4.5e6f;
+            if (us < best.us) best = {cols, s, us};
+        }
+    }
+    return best;
+}
+
+template <int BM>
+static int launch_skinny_parts(int cols, int slices, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M,
+                               int N, int K, float* part, hipStream_t s) {
+#define VITCOP_SKINNY(BN)                                                                                            \
+    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART>(x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s, K, nullptr, \
+                                                      nullptr, part, N, slices, 0, 0, (int64_t)M * N)
+    if (cols == 64) VITCOP_SKINNY(64);
+    if (cols == 96) VITCOP_SKINNY(96);
+    VITCOP_SKINNY(128);
+#undef VITCOP_SKINNY
+}
+template <int BM>
+static int launch_skinny_gate_up(int cols, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M, int F, int K,
+                                 hipStream_t s) {
+    if (cols == 64)
+        return launch_gemm_cfg<BM, 64, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
+    return launch_gemm_cfg<BM, 128, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
+}
+// f<BM>(args...) for the tile that holds M rows
+#define VITCOP_BY_ROWS(f, M, ...)                  \
+    switch (skinny_rows(M)) {                      \
+        case 32: return f<32>(__VA_ARGS__);        \
+        case 64: return f<64>(__VA_ARGS__);        \
+        case 96: return f<96>(__VA_ARGS__);        \
+        case 128: return f<128>(__VA_ARGS__);      \
+        case 160: return f<160>(__VA_ARGS__);      \
+        case 192: return f<192>(__VA_ARGS__);      \
+        case 224: return f<224>(__VA_ARGS__);      \
+        default: return f<256>(__VA_ARGS__);       \
+    }
+static int launch_skinny_slices(const SkinnyPlan& p, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M,
+                               int N, int K, float* part, hipStream_t s) {
+    VITCOP_BY_ROWS(launch_skinny_parts, M, p.cols, p.slices, x, x_stride, mats, M, N, K, part, s)
+}
+static int launch_skinny_gate_up(int cols, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M, int F, int K,
+                                 hipStream_t s) {
+    VITCOP_BY_ROWS(launch_skinny_gate_up, M, cols, x, x_stride, mats, M, F, K, s)
+}
+template <int BM>
+static int launch_skinny_whole(const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
+                               int64_t res_stride, int M, int N, int K, hipStream_t s) {
+    return launch_gemm_cfg<BM, 128, 2, 2, GM_EPI_BF16>(x, x_stride, mats, res, res_stride, M, N, K, nullptr, s);
+}
+static int launch_skinny_whole(const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
+                               int64_t res_stride, int M, int N, int K, hipStream_t s) {
+    VITCOP_BY_ROWS(launch_skinny_whole, M, x, x_stride, mats, res, res_stride, M, N, K, s)
+}
+#undef VITCOP_BY_ROWS
 
 bool gemm_skinny_fuses_norm(int M, int N, int K) {
-    return gemm_skinny_applies(M, N, K) && !skinny_direct(M, N, false) && partial_reduce_fuses_norm(N);
+    return gemm_skinny_applies(M, N, K) && !skinny_direct(N, false) && partial_reduce_fuses_norm(N);
 }
 
 // Adds up the partial sums of a launch and finishes the rows: plain (+ residual, + norm side output),
@@ -664,36 +447,36 @@ static int launch_skinny_mats(const uint16_t* x, int64_t x_stride, const SkMats&
                               int64_t res_stride, int M, int N, int K, float* sumsq_parts, void* ws, hipStream_t s,
                               const uint16_t* ln_w, float eps, uint16_t* norm_out, int64_t norm_stride,
                               uint16_t* gated_out = nullptr, SkParts* parts_out = nullptr) {
-    const bool direct = gated_out == nullptr && skinny_direct(M, N, sumsq_parts != nullptr);
-    const int wgs = direct ? (N + SK_COLS - 1) / SK_COLS : skinny_workgroups(M, N, K);
-    float* part = direct ? nullptr : static_cast<float*>(ws);
-    const int mb = (M + 31) / 32;
-    const int total = (N + SK_COLS - 1) / SK_COLS * (K / SK_UNIT), units_q = total / wgs, units_r = total % wgs;
-    int rc;
-    if (mb <= 2)
-        rc = launch_skinny_cfg<2>(x, x_stride, mats, K, M, N, K, wgs, units_q, units_r, part, res, res_stride, s);
-    else if (mb <= 4)
-        rc = launch_skinny_cfg<4>(x, x_stride, mats, K, M, N, K, wgs, units_q, units_r, part, res, res_stride, s);
-    else if (mb <= 6)
-        rc = launch_skinny_cfg<6>(x, x_stride, mats, K, M, N, K, wgs, units_q, units_r, part, res, res_stride, s);
-    else
-        rc = launch_skinny_cfg<8>(x, x_stride, mats, K, M, N, K, wgs, units_q, units_r, part, res, res_stride, s);
-    if (parts_out) *parts_out = SkParts{direct ? nullptr : part, units_q, units_r, K / SK_UNIT, M};
-    if (rc || direct) return rc;
-    const SkParts parts{part, units_q, units_r, K / SK_UNIT, M};
-    if (parts_out) return VITCOP_OK;             // the caller finishes the rows itself
+    if (parts_out) parts_out->part = nullptr;
+    if (gated_out == nullptr && skinny_direct(N, sumsq_parts != nullptr))
+        return launch_skinny_whole(x, x_stride, mats, res, res_stride, M, N, K, s);
+    const SkinnyPlan plan = skinny_plan(M, N, K);
+    if (gated_out != nullptr) {
+        const int F = N / 2;
+        const float us64 = skinny_us(skinny_rows(M), 64, F / 32, K), us128 = skinny_us(skinny_rows(M), 128, F / 64, K);
+        if (std::min(us64, us128) <= plan.us + 3.0f) {       // (3 us: the reduction's launch)
+            const SkMats gate_up{{mats.w[0], mats.w[1], mats.w[1]}, {gated_out, gated_out, gated_out}, {F, F, F}, {F, F, F}};
+            return launch_skinny_gate_up(us64 < us128 ? 64 : 128, x, x_stride, gate_up, M, F, K, s);
+        }
+    }
+    const SkParts parts{static_cast<float*>(ws), plan.slices, N, M};
+    const int rc = launch_skinny_slices(plan, x, x_stride, mats, M, N, K, static_cast<float*>(ws), s);
+    if (rc) return rc;
+    if (parts_out) {                             // the caller finishes the rows itself
+        *parts_out = parts;
+        return VITCOP_OK;
+    }
     return launch_partial_reduce(parts, N, mats, res, res_stride, sumsq_parts, ln_w, eps, norm_out, norm_stride,
                                  gated_out, s);
 }
 
-// y = x W^T (+ res) [M,N] for M <= 256.  With w2: columns [n_split, N) use w2 and go to y2 (n_split a
-// multiple of 128); both outputs have row stride y_stride.
+// y = x W^T (+ res) [M,N] for M <= 256.  With w2: columns [n_split, N) use w2 and go to y2, dense (n_split a
+// multiple of 128).
 int launch_gemm_skinny(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y, int64_t y_stride,
                        const uint16_t* res, int64_t res_stride, int M, int N, int K, float* sumsq_parts,
                        const uint16_t* w2, uint16_t* y2, int n_split, void* ws, hipStream_t s,
                        const uint16_t* ln_w, float eps, uint16_t* norm_out, int64_t norm_stride) {
-    SkMats mats{{w, w2 ? w2 : w, w}, {y, w2 ? y2 : y, y}, {y_stride, y_stride, y_stride},
-                {w2 ? n_split : N, N, N}};
+    const SkMats mats = sk_mats(w, y, y_stride, N, w2, y2, n_split, w2 ? N - n_split : 0);
     return launch_skinny_mats(x, x_stride, mats, res, res_stride, M, N, K, sumsq_parts, ws, s, ln_w, eps, norm_out,
                               norm_stride);
 }

@@ -86,13 +86,18 @@ int launch_gemm_pair_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w1,
 // k, q, v = x Wk^T, x Wq^T, x Wv^T (dense [M, Hkv d], [M, Hq d], [M, Hkv d]) with the rotary embedding of q
 // and k at positions[m]: where the projections leave partial sums (few rows, or split-K of K and of the Q/V
 // pair) one launch adds them up and turns q and k; otherwise launch_gemm_triple_ws and rope_kernel.
+// launch_gemm_qkv_append_ws: the same for the M new tokens of a decoding step, whose k and v go to rows of caches
+// (k_dst + m * kv_batch, plus rows[m] cache rows if rows is given); k_new and v_new are scratch [M, Hkv d].
 // gemm_qkv_workspace_bytes: what ws must hold for every path this may take at M rows.
 size_t gemm_qkv_workspace_bytes(int M, int Hq, int Hkv, int d, int K);
 int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wk, const uint16_t* wq,
                             const uint16_t* wv, uint16_t* k, uint16_t* q, uint16_t* v, int Hq, int Hkv, int d,
                             const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
                             hipStream_t s);
-// gemm_skinny.hip
+int launch_gemm_qkv_append_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wk, const uint16_t* wq,
+                              const uint16_t* wv, uint16_t* k_new, uint16_t* q, uint16_t* v_new, int Hq, int Hkv, int d,
+                              const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
+                              uint16_t* k_dst, uint16_t* v_dst, int64_t kv_batch, const int32_t* rows, hipStream_t s);
 // Up to three weight matrices side by side (projections of the same input in one launch): matrix i
 // covers the columns [n_end[i-1], n_end[i]) of the launch (boundaries multiples of 128; unused
 // entries repeat N) and writes its own output with its own row stride.
@@ -102,13 +107,23 @@ struct SkMats {
     int64_t y_stride[3];
     int n_end[3];
 };
-// Where the partial sums of a launch live.  units_q > 0: the tiles of gemm_skinny_kernel
-// (part[2 * workgroup + segment][m][128], workgroups by sk_first_unit over groups of upg units).
-// units_q == 0: the slices of a split-K launch of the big-tile kernel, part[slice][m][n] with
-// units_r slices and row stride upg.
+struct SkPick {
+    int mi, start;                       // matrix of a column and that matrix's first column
+};
+__host__ __device__ inline SkPick sk_pick(const SkMats& mats, int n) {
+    const int mi = (n >= mats.n_end[0] ? 1 : 0) + (n >= mats.n_end[1] ? 1 : 0);
+    return {mi, mi == 0 ? 0 : (mi == 1 ? mats.n_end[0] : mats.n_end[1])};
+}
+// one matrix of N columns, or with w2 a pair: w2 and y2 (row stride y2_stride, 0: y_stride) from column n_split on
+inline SkMats sk_mats(const uint16_t* w, uint16_t* y, int64_t y_stride, int N, const uint16_t* w2 = nullptr,
+                      uint16_t* y2 = nullptr, int n_split = 0, int64_t y2_stride = 0) {
+    return SkMats{{w, w2 ? w2 : w, w}, {y, w2 ? y2 : y, y}, {y_stride, y2_stride ? y2_stride : y_stride, y_stride},
+                  {w2 ? n_split : N, N, N}};
+}
+// The partial sums of a launch cut into k-slices: part[slice][m][n], N columns, M rows.
 struct SkParts {
     const float* part;
-    int units_q, units_r, upg, M;
+    int slices, N, M;
 };
 // k, q and v of a layer (in this order) as partial sums: for each the launch it belongs to and its first
 // column there.
@@ -119,7 +134,8 @@ struct QkvParts {
 // k, q, v [M, Hkv d], [M, Hq d], [M, Hkv d] (dense) = the partial sums added in slice order and rounded to
 // bf16, q and k then turned by the rotary embedding at positions[m] (rope_kernel's arithmetic).
 int launch_qkv_finish(const QkvParts& P, uint16_t* k, uint16_t* q, uint16_t* v, int Hq, int Hkv, int d,
-                      const int32_t* positions, float theta, hipStream_t s);
+                      const int32_t* positions, float theta, hipStream_t s, int64_t kv_stride = 0 /* dense */,
+                      const int32_t* kv_rows = nullptr);
 
 int launch_partial_reduce(const SkParts& parts, int N, const SkMats& mats, const uint16_t* res, int64_t res_stride,
                           float* sumsq_parts, const uint16_t* ln_w, float eps, uint16_t* norm_out,

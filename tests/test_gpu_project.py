@@ -57,3 +57,71 @@ def test_rows_past_the_end_do_not_leak_in():
     big[:300] = x
     y, _ = vc.vitcop_project(big[:300], w, residual=r, scratch=False)
     check(x, w, y, r)
+
+
+@pytest.mark.parametrize("M", [5, 32, 33, 64, 65, 100, 128, 129, 161, 193, 225, 256])
+@pytest.mark.parametrize("N,K", [(528, 128), (4096, 192), (1552, 2048), (16400, 256)])
+def test_few_rows(M, N, K):
+    assert vc.lib.vitcop_project_workspace_bytes(M, N, K) > 0
+    x, w, r = draw(M, N, K, M + N)
+    y, _ = vc.vitcop_project(x, w, residual=r)
+    check(x, w, y, r)
+    y, parts = vc.vitcop_project(x, w, want_sumsq=True)
+    check(x, w, y)
+    sq = torch.nn.functional.pad(y.double() ** 2, (0, -N % 128)).reshape(M, -1, 128).sum(-1).T
+    assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
+
+
+@pytest.mark.parametrize("M", [7, 40, 115, 200])
+@pytest.mark.parametrize("D,Hq,Hkv,d,F", [(512, 4, 2, 64, 1408), (640, 5, 1, 128, 896), (1024, 16, 4, 64, 2816)])
+def test_matrices_side_by_side(M, D, Hq, Hkv, d, F):
+    """K, Q and V as one launch and gate and up as one launch: a decoder layer that keeps every token gives the values
+    of its pieces called one by one (tiles that hold the end of one matrix and the start of the next)."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+
+    def t(*shape, std=1.0):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+    w = {"ln1": t(D), "ln2": t(D), "wq": t(Hq * d, D, std=D ** -0.5), "wk": t(Hkv * d, D, std=D ** -0.5),
+         "wv": t(Hkv * d, D, std=D ** -0.5), "wo": t(D, Hq * d, std=D ** -0.5), "wg": t(F, D, std=D ** -0.5),
+         "wu": t(F, D, std=D ** -0.5), "wd": t(D, F, std=F ** -0.5)}
+    h, pos = t(1, M, D), torch.arange(M, dtype=torch.int32, device="cuda")[None]
+    out = vc.vitcop_decoder_layer_prefill(h, pos, w, Hq, Hkv, d, 0, M, M)
+    x = vc.vitcop_rmsnorm(h[0], w["ln1"])
+    q, k, v = (vc.vitcop_project(x, w[n], scratch=False)[0].reshape(1, M, -1, d) for n in ("wq", "wk", "wv"))
+    for name, ref in (("wq", q), ("wk", k), ("wv", v)):
+        check(x, w[name], ref.reshape(M, -1))
+    vc.vitcop_rope(q, k, pos)
+    a = vc.vitcop_prefill_attn(q, k, v)[0].reshape(M, -1)
+    h1, _ = vc.vitcop_project(a, w["wo"], residual=h[0], scratch=False)
+    x2 = vc.vitcop_rmsnorm(h1, w["ln2"])
+    act = vc.vitcop_silu_mul(vc.vitcop_project(x2, w["wg"], scratch=False)[0], vc.vitcop_project(x2, w["wu"], scratch=False)[0])
+    y, _ = vc.vitcop_project(act, w["wd"], residual=h1, scratch=False)
+    got = out["y"].reshape(M, D).double()
+    # the same sums in another order: now and then a bf16 rounding falls the other way (2^-8 of an intermediate value)
+    # and travels on; the two agree to a small part of that on average, and a wrong column would be off by its size
+    err = (got - y.double()).abs()
+    assert float(err.mean()) <= 2.0 ** -9 * float(y.double().abs().mean())
+    assert float(err.max()) <= 2.0 ** -4 * max(1.0, float(y.double().abs().max()))
+
+
+@pytest.mark.parametrize("B,n_vis,keep", [(1, 1500, 700), (1, 300, 120), (2, 900, 330), (1, 600, 290), (4, 3000, 720)])
+def test_query_and_value_of_unequal_width(B, n_vis, keep):
+    """Q and V of a pruned layer as one launch: grouped-query widths (896 + 128, 1536 + 512, 512 + 256), in every range of rows."""
+    g = torch.Generator(device="cuda").manual_seed(n_vis)
+    for D, Hq, Hkv, d in ((896, 7, 1, 128), (768, 12, 4, 128), (512, 8, 4, 64)):
+        def t(*shape, std=1.0):
+            return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+        T = n_vis + 30
+        x, wq, wk, wv, wo = t(B, T, D), *(t(n, D, std=D ** -0.5) for n in (Hq * d, Hkv * d, Hkv * d)), t(D, Hq * d, std=D ** -0.5)
+        r = vc.vitcop_layer_prefill(x, wq, wk, wv, wo, Hq, Hkv, d, 10, n_vis, keep)
+        idx = r["keep_idx"].long()
+        xs = torch.gather(x, 1, idx[:, :, None].expand(-1, -1, D))
+        Tp = keep + 30
+        q, k, v = (vc.vitcop_project(xs.reshape(B * Tp, D), w, scratch=False)[0].reshape(B, Tp, -1, d) for w in (wq, wk, wv))
+        check(xs.reshape(-1, D), wq, q.reshape(B * Tp, -1))
+        check(xs.reshape(-1, D), wv, v.reshape(B * Tp, -1))
+        a = vc.vitcop_prefill_attn(q, k, v)[0]
+        y, _ = vc.vitcop_project(a.reshape(B * Tp, -1), wo, scratch=False)
+        got, want = r["y"].reshape(B * Tp, D).double(), y.double()
+        # (another order of the fp32 sums: a bf16 rounding of q, k or v falls the other way now and then)
+        assert float((got - want).norm() / want.norm()) <= 2.0 ** -7

@@ -585,9 +585,16 @@ int launch_pairwise_dist(const uint16_t* f, int64_t row_stride, int64_t batch_st
                          int64_t sq_batch, float* dist, int64_t dist_stride, int64_t dist_batch, int n, int K,
                          int batch, hipStream_t s) {
     if (n == 0 || batch == 0) return VITCOP_OK;
-    return launch_gemm_cfg<128, 128, 2, 2, GM_EPI_DIST>(f, row_stride, sk_mats(f, nullptr, 0, n), nullptr, 0, n, n, K,
-                                                        nullptr, s, row_stride, sq, sq, dist, dist_stride, batch,
-                                                        batch_stride, sq_batch, dist_batch);
+    // few tiles (one image's survivors): smaller ones, so that more CUs load (8 x 288 tokens x 4096: 72 tiles of
+    // 128 x 128 take 35 us, 200 of 64 x 64 19 us)
+#define VITCOP_DIST(BT)                                                                                              \
+    return launch_gemm_cfg<BT, BT, 2, 2, GM_EPI_DIST>(f, row_stride, sk_mats(f, nullptr, 0, n), nullptr, 0, n, n, K, \
+                                                      nullptr, s, row_stride, sq, sq, dist, dist_stride, batch,      \
+                                                      batch_stride, sq_batch, dist_batch)
+    const long t128 = (n + 127) / 128;
+    if (t128 * t128 * batch < 256) VITCOP_DIST(64);
+    VITCOP_DIST(128);
+#undef VITCOP_DIST
 }
 
 }  // namespace vitcop

@@ -246,11 +246,23 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
         nk = (int)((int64_t)all * (z + 1) / slices) - k_lo;
         if (half_step >= 0) half_step -= k_lo;
     }
+    // Few rows: every workgroup streams its own rows of W, a power of two apart as often as not, and in step they
+    // all ask for the same few columns of it, i.e. for a part of the memory channels.  So long slices start one
+    // k-step further on from tile to tile and wrap around (64 rows: 12288x4096 25.7 -> 22.6 us, gate/up 22016x4096
+    // 42.5 -> 40.2; 32 rows: 24.1 -> 21.1 and 40.0 -> 36.3).  Not with short slices (4096x4096 in four slices of 16
+    // steps: 10.3 -> 11.7 us) nor with more rows of x, which the workgroups then no longer read together (115 rows,
+    // gate/up: 51.6 -> 53.1 us).
+    constexpr bool ROTATE = (EPI == GM_EPI_PART || EPI == GM_EPI_GATED) && BM <= 64;
+    const int rot = ROTATE && tiles_m == 1 && nk >= 32 ? tile_n % nk : 0;
+    auto k_at = [&](int t) __attribute__((always_inline)) {
+        if constexpr (!ROTATE) return t;
+        return t + rot >= nk ? t + rot - nk : t + rot;
+    };
     auto k_off = [&](int t, unsigned rec) __attribute__((always_inline)) {
-        return t < nk ? (unsigned)(k_lo + t) * 128u : rec;
+        return t < nk ? (unsigned)(k_lo + k_at(t)) * 128u : rec;
     };
     auto k_past = [&](int t) __attribute__((always_inline)) {
-        return t == half_step && chunk >= 64 ? 0xFFFFFF00u : 0u;
+        return k_at(t) == half_step && chunk >= 64 ? 0xFFFFFF00u : 0u;
     };
     auto step = [&](int t, int slab_off, int next_off, int prev_off) __attribute__((always_inline)) {
         const unsigned px = k_off(t - 1 + NS, rec_x), pw = k_off(t - 1 + NS, rec_w);

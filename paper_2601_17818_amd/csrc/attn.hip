@@ -236,7 +236,10 @@ template <int D>
 constexpr int AW_KTILE = D / 8 * AW_KGRP;                    // 16640 or 8320 B
 template <int D>
 constexpr int AW_STAGE = AW_KTILE<D> + D / 8 * AW_VGRP;      // K then V
-constexpr int AW_STAGES = 4;
+// tiles in the ring: four, or three with head dimension 64 and one query block, where three workgroups share a CU and
+// cover the shorter prefetch for each other
+template <int D, int U>
+constexpr int AW_STAGES = D == 64 && U == 1 ? 3 : 4;
 constexpr float AW_RESCALE_GAP = 8.0f;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -362,6 +365,7 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
     constexpr int GROUPS = D / 8, GPW = GROUPS / 4;        // row groups of a tile, and per wavefront
     constexpr int LPR = D / 8;                     // lanes that carry one row of a tile load
     constexpr int LPT = 2 * GPW;                   // loads per wavefront and tile
+    constexpr int ST = AW_STAGES<D, U>;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -408,7 +412,8 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int dc = 0; dc < DC; ++dc) asm volatile("" : "+a"(qf[u][dc]));
+        for (int dc = 0; dc < DC; ++dc)
+            if constexpr (D == 128 || U == 2) asm volatile("" : "+a"(qf[u][dc]));
 
     f32x16 o[U][DB];
 #pragma unroll
@@ -464,7 +469,7 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
     // load j of tile t: row group GPW*wv + j/2 of K (j even) or V (j odd)
     auto issue_one = [&](int t, int j) __attribute__((always_inline)) {
         const int i = j >> 1;
-        const unsigned stage = lds_base0 + (t % AW_STAGES) * AW_STAGE<D>;
+        const unsigned stage = lds_base0 + (t % ST) * AW_STAGE<D>;
         const unsigned dst = (j & 1) ? stage + AW_KTILE<D> + (GPW * wv + i) * AW_VGRP : stage + (GPW * wv + i) * AW_KGRP;
         const unsigned off = (unsigned)t * tile_stride + (unsigned)i * row_bytes;
         if (j & 1)
@@ -506,7 +511,7 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
     bf16x8 kfr[2][DC];               // K rows of the stage whose scores the block forms
     s16x4 vlo[2][2 * DB], vhi[2][2 * DB];      // V^T of the stage whose probabilities the block multiplies
     auto load_k_frags = [&](int set, int t, int kt) __attribute__((always_inline)) {
-        unsigned Ks = k_lane + (t % AW_STAGES) * AW_STAGE<D> + kt * 512;
+        unsigned Ks = k_lane + (t % ST) * AW_STAGE<D> + kt * 512;
         asm("" : "+v"(Ks));          // keep base + constant addressing
 #pragma unroll
         for (int dc = 0; dc < DC; ++dc)
@@ -514,7 +519,7 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
     };
 
     auto scores_only = [&](int par, int t, int kt) __attribute__((always_inline)) {   // prologue: S of the first stage
-        const unsigned Ks = k_lane + (t % AW_STAGES) * AW_STAGE<D> + kt * 512;
+        const unsigned Ks = k_lane + (t % ST) * AW_STAGE<D> + kt * 512;
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -551,8 +556,8 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
         // the LDS counter alone) spares the block partial waits: with its own 24 requests queued
         // behind them the 4-bit counter could not express "only the older ones".
         __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0), other counters untouched
-        unsigned Ks = k_lane + ((t + 1) % AW_STAGES) * AW_STAGE<D> + par * 512;
-        unsigned Vs = v_lane + (t % AW_STAGES) * AW_STAGE<D> + par * 512;
+        unsigned Ks = k_lane + ((t + 1) % ST) * AW_STAGE<D> + par * 512;
+        unsigned Vs = v_lane + (t % ST) * AW_STAGE<D> + par * 512;
         asm("" : "+v"(Ks));          // keep base + constant addressing
         asm("" : "+v"(Vs));
         // diagonal and ragged tiles: key key0 + 4g + 8(r/4) + r%4 of register r is visible to
@@ -700,16 +705,16 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
     // Start of tile t.  After the wait and the barrier, tile t+1 has landed everywhere (the LPT
     // loads of tile t+2 may still be in flight) and tile t-1 is dead everywhere: its last
     // fragments were requested in the previous block and have arrived (lgkmcnt), so the fetch
-    // of tile t+3 may overwrite its stage.
+    // of tile t+3 may overwrite its stage.  (With three stages: of tile t+2, and tile t+1 is the only one in flight.)
     // (The loads of a tile go out together right after the barrier.  Inside the pipeline blocks they were
     // measured 7 to 15 % slower, whether spread one by one over the MFMA slots or as one burst per wavefront,
     // each wavefront in a slot of its own.)
     auto tile_sync = [&](int t) __attribute__((always_inline)) {
-        if (t + 2 < ntiles) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPT) : "memory");
+        if (ST == 4 && t + 2 < ntiles) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPT) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (t + 3 < ntiles) issue_tile(t + 3);
+        if (t + ST - 1 < ntiles) issue_tile(t + ST - 1);
     };
     auto tile_body = [&](int t, auto masked_c, bool first) __attribute__((always_inline)) {
         // even stage c = 2t: PV(c-1) = second half of tile t-1, S(c+1) = second half of tile t
@@ -720,7 +725,7 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
 
     issue_tile(0);
     if (ntiles > 1) issue_tile(1);
-    if (ntiles > 2) issue_tile(2);
+    if (ST == 4 && ntiles > 2) issue_tile(2);
     tile_sync(0);                    // also covers the Q fragments, which were requested first
 
     int t = 1;
@@ -779,7 +784,7 @@ template <int D, bool CAUSAL, int U>
 static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                             int B, int N, int Hq, int Hkv, float sl2, hipStream_t s) {
     static std::atomic<bool> attr_set{false};   // set once; a second thread repeating the call is harmless
-    constexpr int lds = AW_STAGES * AW_STAGE<D>;
+    constexpr int lds = AW_STAGES<D, U> * AW_STAGE<D>;
     if (!attr_set.load(std::memory_order_acquire)) {
         const int rc = hip_status(hipFuncSetAttribute((const void*)attn_wide_kernel<D, CAUSAL, U>,
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds),

@@ -76,11 +76,10 @@ constexpr int GM_EPI_BF16 = 0, GM_EPI_DIST = 1, GM_EPI_PART = 2, GM_EPI_GATED = 
 // operands.  To get there the loop must keep issuing MFMAs.  16x16x32 instructions (half the accumulator
 // traffic per FLOP of 32x32x16) in an order fixed by sched_barrier, each pinned to accumulation registers by an
 // asm constraint (left to itself the allocator moves 60 % as many registers as there are MFMAs); k-steps of 64
-// (every direct load moves 8 whole lines), for the 256-column tiles in two slabs: one barrier per step, loads
-// one per four MFMAs right behind it so that a CU's load path (64 bytes per clock) is never asked for more than
-// it moves and no wavefront is stuck on issuing one.  Against 32x32x16 with four slabs of 32 and compiler
-// scheduling hints (GPU time, random operands, same box): 11776x4096x4096 354 -> 298 us (1116 -> 1326 TFLOP/s),
-// 8192x8192x8192 921 -> 750 us (1194 -> 1467), 1536x8192x4096 107 -> 93 us, 2536x4096x11008 229 -> 194 us.
+// (every direct load moves 8 whole lines), loads one per four or five MFMAs so that a CU's load path
+// (64 bytes per clock) is never asked for more than it moves and no wavefront is stuck on issuing one.
+// Against 32x32x16 with four slabs of 32 and compiler scheduling hints (GPU time, random operands, same box):
+// 11776x4096x4096 354 -> 278 us (1116 -> 1424 TFLOP/s), 1536x8192x4096 107 -> 77 us.
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS>
 __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     const uint16_t* __restrict__ x, int64_t x_stride, SkMats mats, const uint16_t* __restrict__ res,
@@ -226,14 +225,21 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     //                         everyone and step t+1 has arrived for everyone;
     //   slots BAR+1 ..        the fragments of step t+1, slice 0 are read; the loads of step t+NS go out into slab
     //                         t % NS, one per LSP slots, the last of them during step t+1 (always before its BAR).
+    // With two slabs that leaves the last loads half a step to arrive.  EARLY: a second barrier at slot REL, as soon as
+    // the fragments of slice 1 have been read, releases the slab, the loads of step t+2 follow it at once, and BAR
+    // moves to the end of the step, so that every load has a whole step and more (two full rounds of 256x256 201 ->
+    // 195 us, of 224x256 180 -> 170, of 192x256 169 -> 150; 1536x8192x4096 86 -> 77 us; with three slabs no gain).
     // The loop runs the same code for every step: past the end the loads are out of range and the fragments are
     // read from slabs whose contents no MFMA uses.
-    constexpr int BAR = NM + NM / 4;
+    constexpr bool EARLY = NS == 2;
     constexpr int RPS0 = (NR + NM - 1) / NM;                                    // reads per slot ahead of the barrier
+    constexpr int REL = NR / RPS0 + NM / 8;
+    constexpr int BAR = EARLY ? 2 * NM - NR - NM / 8 - 1 : NM + NM / 4;
     constexpr int RPS = (NR + 2 * NM - BAR - 2) / (2 * NM - BAR - 1);           // reads per slot behind the barrier
-    constexpr int LSP = std::min(4, (2 * NM - 1) / NL);
-    constexpr int FIRST = std::min(NL, (2 * NM - 2 - BAR) / LSP + 1);           // loads of step t+NS issued in step t
-    static_assert(LSP >= 1 && LSP * (NL - 1) + 1 < 2 * NM, "reads and loads find their slots");
+    constexpr int LSP = EARLY ? std::min(5, (2 * NM - 2 - REL) / NL) : std::min(4, (2 * NM - 1) / NL);
+    constexpr int FIRST = EARLY ? NL : std::min(NL, (2 * NM - 2 - BAR) / LSP + 1);          // loads of step t+NS issued in step t
+    constexpr int YOUNGER = (NS - 2) * NL + (EARLY ? std::min(NL, (BAR - REL - 1) / LSP + 1) : 0);      // loads behind those of step t+1 at BAR
+    static_assert(LSP >= 1 && LSP * (NL - 1) + 1 < 2 * NM && (!EARLY || REL + 1 + LSP * (NL - 1) < 2 * NM), "reads and loads find their slots");
     static_assert(NS >= 2 && (NS - 2) * NL + FIRST <= 63, "the wait counter holds 63 loads");
     int nk = (K + 63) / 64, k_lo = 0;
     // K is a multiple of 32, so the last step may hold one slice only: then the chunks of its second half, which lie
@@ -279,12 +285,19 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
                     if constexpr (r < NR)
                         read_frag(std::integral_constant<int, r>{}, std::integral_constant<int, 1>{}, slab_off);
                 });
+            if constexpr (EARLY && s == REL) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            if constexpr (EARLY && s > REL && (s - REL - 1) % LSP == 0 && (s - REL - 1) / LSP < NL)
+                issue_load(std::integral_constant<int, (s - REL - 1) / LSP>{}, slab_off, cx, cw, c_past);
             constexpr int late = s + 2 * NM - BAR - 1;           // slots since the barrier of the step before
-            if constexpr (s < BAR && late % LSP == 0 && late / LSP >= FIRST && late / LSP < NL)
+            if constexpr (!EARLY && s < BAR && late % LSP == 0 && late / LSP >= FIRST && late / LSP < NL)
                 issue_load(std::integral_constant<int, late / LSP>{}, prev_off, px, pw, p_past);
             if constexpr (s == BAR) {
                 // (a plain s_barrier: __syncthreads would also drain the younger steps' loads)
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * NL) : "memory");
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(YOUNGER) : "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             }
@@ -294,7 +307,7 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
                     if constexpr (r < NR)
                         read_frag(std::integral_constant<int, r>{}, std::integral_constant<int, 0>{}, next_off);
                 });
-                if constexpr ((s - BAR - 1) % LSP == 0 && (s - BAR - 1) / LSP < FIRST)
+                if constexpr (!EARLY && (s - BAR - 1) % LSP == 0 && (s - BAR - 1) / LSP < FIRST)
                     issue_load(std::integral_constant<int, (s - BAR - 1) / LSP>{}, slab_off, cx, cw, c_past);
             }
             __builtin_amdgcn_sched_barrier(0);

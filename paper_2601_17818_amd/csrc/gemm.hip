@@ -1,4 +1,6 @@
 // Launches of the projection kernel (gemm_kernel.h): which tile shape, how many k-slices, which columns.
+#include <numeric>
+
 #include "gemm_kernel.h"
 
 namespace vitcop {
@@ -116,11 +118,8 @@ static int main_columns(TileId& id, int M, int N, int K, bool need_sumsq, int al
     return best_n;
 }
 
-static int launch_tile(TileId id, const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y,
-                       int64_t y_stride, const uint16_t* res, int64_t res_stride, int M, int N, int K,
-                       float* sumsq_parts, const uint16_t* w2, uint16_t* y2, int n_split, hipStream_t s,
-                       int64_t y2_stride = 0) {
-    const SkMats mats = sk_mats(w, y, y_stride, N, w2, y2, n_split, y2_stride);
+static int launch_tile_mats(TileId id, const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
+                            int64_t res_stride, int M, int N, int K, float* sumsq_parts, hipStream_t s) {
 #define VITCOP_TILE(BM, BN, WM, WN) \
     return launch_gemm_cfg<BM, BN, WM, WN, GM_EPI_BF16>(x, x_stride, mats, res, res_stride, M, N, K, sumsq_parts, s)
     switch (id) {
@@ -137,6 +136,13 @@ static int launch_tile(TileId id, const uint16_t* x, int64_t x_stride, const uin
             return launch_gemm_cfg<128, 32, 4, 1, GM_EPI_BF16>(x, x_stride, mats, res, res_stride, M, N, K, sumsq_parts, s);
     }
 #undef VITCOP_TILE
+}
+static int launch_tile(TileId id, const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y,
+                       int64_t y_stride, const uint16_t* res, int64_t res_stride, int M, int N, int K,
+                       float* sumsq_parts, const uint16_t* w2, uint16_t* y2, int n_split, hipStream_t s,
+                       int64_t y2_stride = 0) {
+    return launch_tile_mats(id, x, x_stride, sk_mats(w, y, y_stride, N, w2, y2, n_split, y2_stride), res, res_stride, M, N,
+                            K, sumsq_parts, s);
 }
 
 int launch_gemm(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y,
@@ -454,6 +460,22 @@ int launch_gemm_triple_ws(const uint16_t* x, int64_t x_stride, const uint16_t* c
     const size_t need = gemm_skinny_workspace_bytes(M, n[0] + n[1] + n[2], K);
     if (ws && need && ws_bytes >= need && n[0] % 128 == 0 && n[1] % 128 == 0)
         return launch_gemm_skinny3(x, x_stride, w, y, n, M, K, ws, s);
+    // many rows: whole tiles of all three in one launch, where that takes no more rounds than the first matrix and the
+    // other two apart: the end of one launch and the start of the next overlap
+    // (layers of 2048 / 5632 at 1200 rows, six of them: 1190 -> 1133 us; of 4096 / 11008 at 2536 rows 5437 -> 5427)
+    const int N = n[0] + n[1] + n[2];
+    if (M > 1024 && n[0] % 128 == 0 && n[1] % 128 == 0 && n[0] > 0 && n[1] > 0) {
+        const int align = std::gcd(n[0], n[1]);
+        TileId id0 = choose_tile(M, n[0], K, false, 768), id12 = choose_tile(M, n[1] + n[2], K, false, n[1]);
+        float c0 = tile_cost(kTiles[id0], M, n[0]), c12 = tile_cost(kTiles[id12], M, n[1] + n[2]);
+        main_columns(id0, M, n[0], K, false, 768, &c0);
+        main_columns(id12, M, n[1] + n[2], K, false, n[1], &c12);
+        const TileId id = choose_tile(M, N, K, false, align);
+        if (id0 != T128x32 && id12 != T128x32 && id != T128x32 && tile_cost(kTiles[id], M, N) <= c0 + c12) {
+            const SkMats mats{{w[0], w[1], w[2]}, {y[0], y[1], y[2]}, {n[0], n[1], n[2]}, {n[0], n[0] + n[1], N}};
+            return launch_tile_mats(id, x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s);
+        }
+    }
     int rc = launch_gemm_ws(x, x_stride, w[0], y[0], n[0], nullptr, 0, M, n[0], K, nullptr, ws, ws_bytes, s);
     if (rc) return rc;
     return launch_gemm_pair_ws(x, x_stride, w[1], y[1], n[1], w[2], y[2], n[2], M, K, ws, ws_bytes, s);
@@ -585,14 +607,15 @@ int launch_pairwise_dist(const uint16_t* f, int64_t row_stride, int64_t batch_st
                          int64_t sq_batch, float* dist, int64_t dist_stride, int64_t dist_batch, int n, int K,
                          int batch, hipStream_t s) {
     if (n == 0 || batch == 0) return VITCOP_OK;
-    // few tiles (one image's survivors): smaller ones, so that more CUs load (8 x 288 tokens x 4096: 72 tiles of
-    // 128 x 128 take 35 us, 200 of 64 x 64 19 us)
+    // few tokens: smaller tiles, so that more CUs load, while all of them run at once, two to a CU (clustering
+    // and merging of 8 x 288 tokens x 4096 134 -> 117 us with 200 tiles of 64 x 64 for 72 of 128 x 128, of 4 x 600 122 -> 115
+    // with 400 for 100; but of 1 x 1856 137 -> 148 with 841 for 225)
 #define VITCOP_DIST(BT)                                                                                              \
     return launch_gemm_cfg<BT, BT, 2, 2, GM_EPI_DIST>(f, row_stride, sk_mats(f, nullptr, 0, n), nullptr, 0, n, n, K, \
                                                       nullptr, s, row_stride, sq, sq, dist, dist_stride, batch,      \
                                                       batch_stride, sq_batch, dist_batch)
-    const long t128 = (n + 127) / 128;
-    if (t128 * t128 * batch < 256) VITCOP_DIST(64);
+    const long t64 = (n + 63) / 64;
+    if (t64 * t64 * batch <= 512) VITCOP_DIST(64);
     VITCOP_DIST(128);
 #undef VITCOP_DIST
 }

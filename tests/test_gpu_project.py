@@ -72,7 +72,7 @@ def test_few_rows(M, N, K):
     assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
 
 
-@pytest.mark.parametrize("M", [7, 40, 115, 200])
+@pytest.mark.parametrize("M", [7, 40, 115, 200, 300, 700, 1100, 2900])
 @pytest.mark.parametrize("D,Hq,Hkv,d,F", [(512, 4, 2, 64, 1408), (640, 5, 1, 128, 896), (1024, 16, 4, 64, 2816)])
 def test_matrices_side_by_side(M, D, Hq, Hkv, d, F):
     """K, Q and V as one launch and gate and up as one launch: a decoder layer that keeps every token gives the values

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
         dist += z * dist_batch;
     }
     const int m0 = tile_m * BM;
-    // n0, N: first column and number of columns, inside this tile's matrix (the partials keep the launch's columns)
+    // n0, N: first column and number of columns, inside this tile's matrix (of a straddling tile: of the launch)
     int n0 = tile_n * (EPI == GM_EPI_GATED ? BN / 2 : BN);
     constexpr bool STRADDLE = EPI == GM_EPI_PART && BN < 256;
     static_assert(EPI != GM_EPI_GATED || WAVES_N == 2, "gate and up halves go to the two wavefront columns");
@@ -157,6 +157,7 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
         } else {
             n0 -= pick.start;
             N = end - pick.start;
+            if constexpr (EPI == GM_EPI_PART) dist += pick.start;        // partials keep the launch's columns
         }
     }
 

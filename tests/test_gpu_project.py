@@ -72,8 +72,13 @@ def test_few_rows(M, N, K):
     assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
 
 
-@pytest.mark.parametrize("M", [7, 40, 115, 200, 300, 700, 1100, 2900])
-@pytest.mark.parametrize("D,Hq,Hkv,d,F", [(512, 4, 2, 64, 1408), (640, 5, 1, 128, 896), (1024, 16, 4, 64, 2816)])
+SIDE_BY_SIDE = ([(M, *layer) for layer in ((512, 4, 2, 64, 1408), (640, 5, 1, 128, 896), (1024, 16, 4, 64, 2816))
+                 for M in (7, 40, 115, 200, 300, 700, 1100, 2900)] +
+                # k-slices of 256 columns, K in a launch of its own and Q and V as a pair
+                [(257, 5888, 36, 36, 128, 512)])
+
+
+@pytest.mark.parametrize("M,D,Hq,Hkv,d,F", SIDE_BY_SIDE)
 def test_matrices_side_by_side(M, D, Hq, Hkv, d, F):
     """K, Q and V as one launch and gate and up as one launch: a decoder layer that keeps every token gives the values
     of its pieces called one by one (tiles that hold the end of one matrix and the start of the next)."""
@@ -125,3 +130,46 @@ def test_query_and_value_of_unequal_width(B, n_vis, keep):
         got, want = r["y"].reshape(B * Tp, D).double(), y.double()
         # (another order of the fp32 sums: a bf16 rounding of q, k or v falls the other way now and then)
         assert float((got - want).norm() / want.norm()) <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,keep", [(8192, 64, 8, 300), (8192, 64, 2, 257), (12288, 48, 8, 350), (12288, 48, 8, 640)])
+def test_query_and_value_pair_in_wide_slices(D, Hq, Hkv, keep):
+    """Q and V of wide pruned layers (k-slices of 256 columns over both matrices): the layer's output and the V cache are
+    those of Q and V projected one by one in whole tiles."""
+    d, T = 128, keep + 100
+    g = torch.Generator(device="cuda").manual_seed(keep)
+
+    def t(*shape, std=1.0):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+    x, wq, wk, wv, wo = t(1, T, D), *(t(n, D, std=D ** -0.5) for n in (Hq * d, Hkv * d, Hkv * d)), t(D, Hq * d, std=D ** -0.5)
+    pos = torch.arange(T, dtype=torch.int32, device="cuda")[None]
+
+    def pieces(xs, at):
+        q, k, v = (vc.vitcop_project(xs, w, scratch=False)[0].reshape(1, keep, -1, d) for w in (wq, wk, wv))
+        for w, y in ((wq, q), (wk, k), (wv, v)):
+            check(xs, w, y.reshape(keep, -1))
+        if at is not None:
+            vc.vitcop_rope(q, k, at)
+        return vc.vitcop_prefill_attn(q, k, v)[0].reshape(keep, -1), k, v
+    r = vc.vitcop_layer_prefill(x, wq, wk, wv, wo, Hq, Hkv, d, 0, T, keep)
+    xs = x[0, r["keep_idx"][0].long()]
+    want = vc.vitcop_project(pieces(xs, None)[0], wo, scratch=False)[0].double()
+    # (another order of the fp32 sums: a bf16 rounding of q, k or v falls the other way now and then)
+    assert float((r["y"][0].double() - want).norm() / want.norm()) <= 2.0 ** -7
+
+    F = 512
+    w = {"ln1": t(D), "ln2": t(D), "wq": wq, "wk": wk, "wv": wv, "wo": wo, "wg": t(F, D, std=D ** -0.5),
+         "wu": t(F, D, std=D ** -0.5), "wd": t(D, F, std=F ** -0.5)}
+    caches = [torch.zeros((1, keep, Hkv, d), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    r = vc.vitcop_decoder_layer_prefill(x, pos, w, Hq, Hkv, d, 0, T, keep, caches=caches)
+    idx = r["keep_idx"][0].long()
+    a, k, v = pieces(vc.vitcop_rmsnorm(x[0], w["ln1"])[idx], pos[:, idx].contiguous())
+    # one rounding to bf16 of sums in another order: at most an ulp apart (2^-7 of the value), and the rotary embedding
+    # keeps the length of the pairs that it turns
+    for got, ref in zip(caches, (k, v)):
+        assert float((got.double() - ref.double()).norm() / ref.double().norm()) <= 2.0 ** -7
+    h1 = vc.vitcop_project(a, wo, residual=x[0, idx].contiguous(), scratch=False)[0]
+    x2 = vc.vitcop_rmsnorm(h1, w["ln2"])
+    act = vc.vitcop_silu_mul(vc.vitcop_project(x2, w["wg"], scratch=False)[0], vc.vitcop_project(x2, w["wu"], scratch=False)[0])
+    want = vc.vitcop_project(act, w["wd"], residual=h1, scratch=False)[0].double()
+    assert float((r["y"][0].double() - want).norm() / want.norm()) <= 2.0 ** -7

@@ -17,13 +17,9 @@
 #include <algorithm>
 #include <cmath>
 #include "gemm_kernel.h"
+#include "gemm_plan.h"
 
 namespace vitcop {
-
-constexpr int SK_COLS = 128;          // columns per sum-of-squares partial
-constexpr int SK_UNIT = 64;           // k-values per step (one 128-byte line per row)
-constexpr int SK_MAX_ROWS = 256;
-constexpr int SK_MAX_WGS = 256;       // one per CU
 
 // v[0..8) = sum, in slice order, of the partials of row m, columns n .. n+8 (n a
 // multiple of 8).  Four loads are in flight at a time; the additions keep the order.
@@ -303,61 +299,9 @@ int launch_qkv_finish(const QkvParts& P, uint16_t* k, uint16_t* q, uint16_t* v, 
     return launch_status("qkv_finish");
 }
 
-// From this many column groups on the columns alone keep most CUs streaming: whole tiles write their outputs
-// themselves, and the partial sums and their reduction are saved.
-constexpr int SK_DIRECT_GROUPS = 128;
-static bool skinny_direct(int N, bool want_sumsq) {
-    return !want_sumsq && (N + SK_COLS - 1) / SK_COLS >= SK_DIRECT_GROUPS;
-}
-
-bool gemm_skinny_applies(int M, int N, int K) {
-    return M >= 1 && M <= SK_MAX_ROWS && K % SK_UNIT == 0 && K >= 2 * SK_UNIT && N % 8 == 0;
-}
-
-// Scratch of a launch: twice 128 columns for each of the 256 workgroups (or column groups, if there are more);
-// the plan below stays within it.
-static int skinny_scratch_columns(int N, int K) {
-    const int groups = (N + SK_COLS - 1) / SK_COLS, total = groups * (K / SK_UNIT);
-    return 2 * SK_COLS * std::max(groups, std::min(SK_MAX_WGS, total / 2));
-}
-
 size_t gemm_skinny_workspace_bytes(int M, int N, int K) {
     if (!gemm_skinny_applies(M, N, K)) return 0;
     return up256((size_t)skinny_scratch_columns(N, K) * M * 4);
-}
-
-// Time of one launch in microseconds.  A workgroup's step over 64 of k costs what its share of the HBM stream
-// and its rows of x (from L2) take; the stream's rate is shared by the workgroups (with all 256 at work 0.095 ns
-// per k and column, 5.4 TB/s; fewer draw less each than their number would allow, about as its square root),
-// the rows cost 0.03 ns per k each.  Fitted to K = 4096 and 11008 at 32 to 224 rows; within 15 % of each.
-// (Kernel alone, weights from HBM, against the unit-dealing kernel with register staging used before: 115 rows
-// 12288x4096 31.4 -> 27.3 us, 4096x4096 15.2 -> 12.1, 4096x11008 31.0 -> 27.3, gate/up 22016x4096 58.7 + 7 for the
-// reduction -> 48.2; 224 rows 45.7 -> 32.9, 20.3 -> 17.1, 44.1 -> 36.6, 76.1 + 8 -> 57.0; 64 rows 26.6 -> 24.8,
-// 10.9 -> 9.9, 22.7 -> 22.3, 43.9 + 5 -> 42.3.)
-static float skinny_us(int rows, int cols, int wgs, int k) {
-    const float share = std::sqrt(std::min(1.0f, (float)wgs / SK_MAX_WGS));
-    const float rounds = (float)((wgs + SK_MAX_WGS - 1) / SK_MAX_WGS);
-    return 3.0f + rounds * (float)k * (0.095e-3f * (float)cols * share + 0.03e-3f * (float)rows);
-}
-static int skinny_rows(int M) { return (M + 31) / 32 * 32; }
-
-struct SkinnyPlan {
-    int cols, slices;
-    float us;                            // of the launch and the traffic of its partial sums
-};
-static SkinnyPlan skinny_plan(int M, int N, int K) {
-    const int steps = K / SK_UNIT;
-    SkinnyPlan best{0, 0, 1e30f};
-    for (int cols : {64, 96, 128}) {
-        const int tiles = (N + cols - 1) / cols;
-        const int most = std::min(std::min(16, steps), skinny_scratch_columns(N, K) / N);
-        for (int s = 1; s <= most; ++s) {
-            const float us = skinny_us(skinny_rows(M), cols, tiles * s, (steps + s - 1) / s * SK_UNIT) +
-                             (float)s * (float)M * (float)N * 12.0f / 4.5e6f;
-            if (us < best.us) best = {cols, s, us};
-        }
-    }
-    return best;
 }
 
 template <int BM>
@@ -452,11 +396,10 @@ static int launch_skinny_mats(const uint16_t* x, int64_t x_stride, const SkMats&
         return launch_skinny_whole(x, x_stride, mats, res, res_stride, M, N, K, s);
     const SkinnyPlan plan = skinny_plan(M, N, K);
     if (gated_out != nullptr) {
-        const int F = N / 2;
-        const float us64 = skinny_us(skinny_rows(M), 64, F / 32, K), us128 = skinny_us(skinny_rows(M), 128, F / 64, K);
-        if (std::min(us64, us128) <= plan.us + 3.0f) {       // (3 us: the reduction's launch)
+        const int F = N / 2, cols = skinny_gated_columns(plan, M, F, K);
+        if (cols != 0) {
             const SkMats gate_up{{mats.w[0], mats.w[1], mats.w[1]}, {gated_out, gated_out, gated_out}, {F, F, F}, {F, F, F}};
-            return launch_skinny_gate_up(us64 < us128 ? 64 : 128, x, x_stride, gate_up, M, F, K, s);
+            return launch_skinny_gate_up(cols, x, x_stride, gate_up, M, F, K, s);
         }
     }
     const SkParts parts{static_cast<float*>(ws), plan.slices, N, M};

@@ -167,7 +167,6 @@ int launch_gemv_qkv_rope(const uint16_t* x, int64_t x_stride, const uint16_t* ln
                          int64_t kv_batch, const int32_t* positions, int B, int Hq, int Hkv, int d, int K, float theta,
                          hipStream_t s, const int32_t* kv_rows = nullptr);
 
-bool gemm_skinny_applies(int M, int N, int K);
 size_t gemm_skinny_workspace_bytes(int M, int N, int K);
 bool gemm_skinny_fuses_norm(int M, int N, int K);
 int launch_gemm_skinny_gated(const uint16_t* x, int64_t x_stride, const uint16_t* wg, const uint16_t* wu, int F,

@@ -61,14 +61,7 @@ int launch_gemm_pair(const uint16_t* x, int64_t x_stride, const uint16_t* w1, ui
 }
 
 static size_t qkv_plan_bytes(const SplitKPlan& p, int M, int N) { return up256((size_t)p.splits * M * N * 4); }
-static size_t splitk_workspace_bytes(int M, int N, int K) {
-    const SplitKPlan p = splitk_candidate(M, N, K);
-    return p.splits ? up256((size_t)p.splits * M * N * 4) : 0;
-}
-// whether a launch with ws_bytes of scratch goes out as k-slices
-static bool splitk_applies(int M, int N, int K, size_t ws_bytes) {
-    return splitk_plan(M, N, K).splits != 0 && ws_bytes >= splitk_workspace_bytes(M, N, K);
-}
+static size_t splitk_workspace_bytes(int M, int N, int K) { return up256((size_t)splitk_most(M, N, K) * M * N * 4); }
 
 // scratch of the trailing columns when main_columns cuts the launch (as one matrix, or as the pair N/2 + N/2)
 static size_t tail_workspace_bytes(int M, int N, int K) {
@@ -110,14 +103,13 @@ static int launch_slices(const SplitKPlan& p, const uint16_t* x, int64_t x_strid
 #undef VITCOP_SPLITK
 }
 
-// y = x W^T (+ res) by split-K (splitk_plan applies, ws holds splitk_workspace_bytes); optionally the
+// y = x W^T (+ res) in the k-slices of p (ws holds splitk_workspace_bytes); optionally the
 // norm side output or the RMSNorm of the finished rows, as in the few-row path.
-static int launch_gemm_splitk(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y, int64_t y_stride,
-                              const uint16_t* res, int64_t res_stride, int M, int N, int K, float* sumsq_parts,
-                              void* ws, hipStream_t s, const uint16_t* ln_w, float eps, uint16_t* norm_out,
-                              int64_t norm_stride, const uint16_t* w2 = nullptr, uint16_t* y2 = nullptr,
-                              int n_split = 0, SkParts* parts_out = nullptr) {
-    const SplitKPlan p = splitk_plan(M, N, K);
+static int launch_gemm_splitk(const SplitKPlan& p, const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y,
+                              int64_t y_stride, const uint16_t* res, int64_t res_stride, int M, int N, int K,
+                              float* sumsq_parts, void* ws, hipStream_t s, const uint16_t* ln_w, float eps,
+                              uint16_t* norm_out, int64_t norm_stride, const uint16_t* w2 = nullptr,
+                              uint16_t* y2 = nullptr, int n_split = 0, SkParts* parts_out = nullptr) {
     float* part = static_cast<float*>(ws);
     const SkMats mats = sk_mats(w, y, y_stride, N, w2, y2, n_split, w2 ? N - n_split : 0);
     const int rc = launch_slices(p, x, x_stride, mats, M, N, K, part, s);
@@ -143,9 +135,12 @@ int launch_gemm_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint1
     if (ws && need && ws_bytes >= need)
         return launch_gemm_skinny(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, sumsq_parts, nullptr,
                                   nullptr, 0, ws, s);
-    if (ws && splitk_applies(M, N, K, ws_bytes))
-        return launch_gemm_splitk(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, sumsq_parts, ws, s, nullptr,
-                                  0.f, nullptr, 0);
+    if (ws && ws_bytes >= splitk_workspace_bytes(M, N, K)) {
+        const SplitKPlan p = splitk_plan(M, N, K, sumsq_parts != nullptr);
+        if (p.splits)
+            return launch_gemm_splitk(p, x, x_stride, w, y, y_stride, res, res_stride, M, N, K, sumsq_parts, ws, s,
+                                      nullptr, 0.f, nullptr, 0);
+    }
     if (ws) {               // a few tiles over whole rounds: leading columns on the big tiles, the rest on their own
         TileId id = choose_tile(M, N, K, sumsq_parts != nullptr, 768);
         const int n_main = main_columns(id, M, N, K, sumsq_parts != nullptr, 768);
@@ -173,9 +168,12 @@ int launch_gemm_norm_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w, 
     if (ws && need && ws_bytes >= need && gemm_skinny_fuses_norm(M, N, K))
         return launch_gemm_skinny(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, nullptr, nullptr, nullptr, 0,
                                   ws, s, ln_w, eps, norm_out, norm_stride);
-    if (ws && splitk_applies(M, N, K, ws_bytes) && partial_reduce_fuses_norm(N))
-        return launch_gemm_splitk(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, nullptr, ws, s, ln_w, eps,
-                                  norm_out, norm_stride);
+    if (ws && ws_bytes >= splitk_workspace_bytes(M, N, K) && partial_reduce_fuses_norm(N)) {
+        const SplitKPlan p = splitk_plan(M, N, K, false, GM_NORM_US);
+        if (p.splits)
+            return launch_gemm_splitk(p, x, x_stride, w, y, y_stride, res, res_stride, M, N, K, nullptr, ws, s, ln_w, eps,
+                                      norm_out, norm_stride);
+    }
     int rc = launch_gemm_ws(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, nullptr, ws, ws_bytes, s);
     if (rc) return rc;
     return launch_rmsnorm(y, y_stride, ln_w, eps, norm_out, norm_stride, M, N, s);
@@ -216,7 +214,7 @@ int launch_gemm_gated_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wg
     // hundred rows): those produce gate and up separately.  A large tail (many rows, whole rounds plus a part
     // of one) stays on this path: first the columns that fill the whole rounds, then the rest on the tiles
     // that suit it.
-    if (F % 8 == 0 && splitk_plan(M, 2 * F, K).splits == 0) {
+    if (F % 8 == 0 && splitk_plan(M, 2 * F, K, false, -silu_us(M, F)).splits == 0) {
         const uint16_t *g_w = wg, *u_w = wu;
         uint16_t* o = out;
         int f_left = F;
@@ -305,9 +303,12 @@ int launch_gemm_pair_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w1,
     const size_t need = gemm_skinny_workspace_bytes(M, N1 + N2, K);
     if (ws && need && ws_bytes >= need && N1 % 128 == 0 && N2 % 128 == 0)
         return launch_gemm_skinny(x, x_stride, w1, y1, N1, nullptr, 0, M, N1 + N2, K, nullptr, w2, y2, N1, ws, s);
-    if (ws && splitk_applies(M, N1 + N2, K, ws_bytes) && N1 % 256 == 0 && N2 % 256 == 0)      // no tile straddles the two outputs
-        return launch_gemm_splitk(x, x_stride, w1, y1, N1, nullptr, 0, M, N1 + N2, K, nullptr, ws, s, nullptr, 0.f,
-                                  nullptr, 0, w2, y2, N1);
+    if (ws && ws_bytes >= splitk_workspace_bytes(M, N1 + N2, K) && N1 % 256 == 0 && N2 % 256 == 0) {
+        const SplitKPlan p = splitk_plan(M, N1 + N2, K);             // (no tile of 256 columns straddles the two outputs)
+        if (p.splits)
+            return launch_gemm_splitk(p, x, x_stride, w1, y1, N1, nullptr, 0, M, N1 + N2, K, nullptr, ws, s, nullptr, 0.f,
+                                      nullptr, 0, w2, y2, N1);
+    }
     if (ws && N1 == N2 && N1 % 128 == 0) {       // the same cut for the pair: the tail lies in the second matrix
         const int N = N1 + N2;
         TileId id = choose_tile(M, N, K, false, N1);
@@ -330,9 +331,9 @@ size_t gemm_qkv_workspace_bytes(int M, int Hq, int Hkv, int d, int K) {
     const int qd = Hq * d, kd = Hkv * d;
     size_t need = std::max(gemm_workspace_bytes(M, kd, K), gemm_workspace_bytes(M, qd + kd, K));
     need = std::max(need, gemm_workspace_bytes(M, kd + qd + kd, K));
-    if (qkv_path(M, qd, kd, d, K) == 2)
-        need = std::max(need, splitk_workspace_bytes(M, kd, K) + splitk_workspace_bytes(M, qd + kd, K));
-    if (qkv_path(M, qd, kd, d, K) == 3) need = std::max(need, qkv_plan_bytes(qkv_plan(M, qd, kd, K), M, qd + 2 * kd));
+    const int path = qkv_path(M, qd, kd, d, K);
+    if (path == 2) need = std::max(need, splitk_workspace_bytes(M, kd, K) + splitk_workspace_bytes(M, qd + kd, K));
+    if (path == 3) need = std::max(need, qkv_plan_bytes(qkv_plan(M, qd, kd, K), M, qd + 2 * kd));
     return need;
 }
 
@@ -369,10 +370,10 @@ int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t*
     const size_t need_k = splitk_workspace_bytes(M, kd, K), need_qv = splitk_workspace_bytes(M, qd + kd, K);
     if (path == 2 && ws_bytes >= need_k + need_qv) {
         SkParts pk{}, pqv{};
-        int rc = launch_gemm_splitk(x, x_stride, wk, k, kd, nullptr, 0, M, kd, K, nullptr, ws, s, nullptr, 0.f, nullptr,
-                                    0, nullptr, nullptr, 0, &pk);
+        int rc = launch_gemm_splitk(splitk_plan(M, kd, K), x, x_stride, wk, k, kd, nullptr, 0, M, kd, K, nullptr, ws, s,
+                                    nullptr, 0.f, nullptr, 0, nullptr, nullptr, 0, &pk);
         if (rc) return rc;
-        rc = launch_gemm_splitk(x, x_stride, wq, q, qd, nullptr, 0, M, qd + kd, K, nullptr,
+        rc = launch_gemm_splitk(splitk_plan(M, qd + kd, K), x, x_stride, wq, q, qd, nullptr, 0, M, qd + kd, K, nullptr,
                                 static_cast<char*>(ws) + need_k, s, nullptr, 0.f, nullptr, 0, wv, v, qd, &pqv);
         if (rc) return rc;
         const QkvParts P{{pk, pqv, pqv}, {0, 0, qd}};

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <initializer_list>
 
 namespace vitcop {
 
@@ -17,21 +18,23 @@ namespace vitcop {
 // operands: 98, 85.5, 76, 65, 55, 44, 38.7, 32.6, 33.5 us a round in the order below; 160x256 and
 // 224x256 against the next larger shape in use before: 2536x4096x11008 222 -> 174 us, 2536x4096x4096
 // 82 -> 67 us).
+// `us` is the time of 4096 of k in a launch of at most a few rounds whose weights come from HBM (launch_us below).
 struct TileShape {
     int bm, bn;
     float rate;
     bool sumsq;        // wavefront tile is 128 columns wide: can emit the norm partials
+    float us;
 };
 enum TileId { T256x256, T224x256, T192x256, T160x256, T256x128, T192x128, T160x128, T128x128, T128x128R, T128x32,
               T192x192G, T160x192G, T_COUNT };
 inline constexpr TileShape kTiles[T_COUNT] = {
-    {256, 256, 1.00f, true},  {224, 256, 1.00f, true},  {192, 256, 0.96f, true},  {160, 256, 0.94f, true},
-    {256, 128, 0.89f, false}, {192, 128, 0.83f, false}, {160, 128, 0.79f, false}, {128, 128, 0.75f, false},
-    {128, 128, 0.73f, true},  {128, 32, 0.0f, false},
-    // gate/up launches only (96 gate + 96 up columns): their epilogue exists in that form alone
-    {192, 192, 0.91f, false}, {160, 192, 0.88f, false},
+    {256, 256, 1.00f, true, 75.5f},  {224, 256, 1.00f, true, 72.7f},  {192, 256, 0.96f, true, 63.5f},
+    {160, 256, 0.94f, true, 59.8f},  {256, 128, 0.89f, false, 47.4f}, {192, 128, 0.83f, false, 41.7f},
+    {160, 128, 0.79f, false, 38.8f}, {128, 128, 0.75f, false, 32.8f}, {128, 128, 0.73f, true, 33.6f},
+    {128, 32, 0.0f, false, 15.3f},
+    // gate/up launches and k-slices only (a gate/up tile holds 96 + 96 columns)
+    {192, 192, 0.91f, false, 55.0f}, {160, 192, 0.88f, false, 48.0f},
 };
-constexpr float GM_TILE_US = 98.0f / 4096.0f;      // microseconds per k of a 256x256 tile
 
 // Estimated time of the launch in units of (one 256x256 tile at full rate): rounds over the
 // 256 CUs times the time of one tile.
@@ -194,72 +197,85 @@ inline int skinny_gated_columns(const SkinnyPlan& plan, int M, int F, int K) {
 // `splits` slices (workgroups of the same launch, gemm_kernel.h) whose fp32 partials the few-row path's reduction
 // kernels add up.
 struct SplitKPlan {
-    int bm = 0, bn = 256, splits = 0;          // splits == 0: does not apply
-    float us = 0.f;                            // estimate, of the launch of whole tiles if splits == 0
+    int bm = 0, bn = 256, splits = 0;          // splits == 0: whole tiles
+    float us = 0.f;                            // estimate of what is taken
 };
-constexpr float GM_LAUNCH_US = 3.0f;
-inline float splitk_us(float slice_cost, int M, int N, int K, int splits) {      // slice_cost: tile area / rate / slices
-    return slice_cost / 65536.0f * (float)K * GM_TILE_US + 2.0f * GM_LAUNCH_US +
-           (float)splits * (float)M * (float)N * 8.0f / 4.5e6f;
+inline int tile_count(const TileShape& t, int M, int N) { return (M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn); }
+// Microseconds of one launch, alone or in `slices` over k: a start and an end that grow with the tile (pipeline fill,
+// epilogue), and rounds over its k, slower by a fifth with all CUs at work than with few.  This, the cost of
+// partial sums and the table's `us` are one fit to 435 sizes of 257 to 1024 rows (256 to 12288 columns, K 768 to
+// 28672, weights from HBM) on each tile shape and up to 16 slices: 6 % rms; what it picks takes 1 % longer on average
+// than the best measured.  The rates of full rounds alone, used before, priced a single round of whole tiles up to
+// a sixth too low and slices at their traffic, and left the 128 x 32 tiles out (800 x 5120 x 13824: whole tiles
+// 144 us, three slices 111; 576 x 512 x 3584: 14 slices 21.0 us, six to eight 17.7; 320 x 2048 x 2048: eight slices
+// 22.1 us, 128 x 32 tiles 12.5).
+inline float launch_us(const TileShape& t, int M, int N, int K, int slices = 1) {
+    const int wgs = tile_count(t, M, N) * slices, rounds = (wgs + 255) / 256;
+    const float fill = std::min(1.0f, (float)wgs / 256.0f);
+    return 5.3f + 8.2f / 65536.0f * (float)(t.bm * t.bn) +
+           (float)rounds * (float)K / (4096.0f * (float)slices) * t.us * (0.81f + 0.19f * fill);
 }
+// What a slice adds: its share of the reduction (partials written and read once, in slice order).
+inline float slice_us(int M, int N) { return 0.25f + 1.05e-6f * (float)M * (float)N; }
+constexpr float GM_REDUCTION_US = 1.3f;        // the reduction's launch
+// Launches that only slices spare or only whole tiles spare: the RMSNorm after a projection and the rotary embedding
+// (in the slices' reduction), the activation after gate and up (in the whole tiles' epilogue).
+constexpr float GM_NORM_US = 4.0f, GM_ROPE_US = 5.0f;
+inline float silu_us(int M, int F) { return 4.0f + (float)M * (float)F * 6.0f / 4.5e6f; }
+
 inline int splitk_slices(int tiles, int K) { return std::min(std::min(16, 256 / std::max(tiles, 1)), K / 32 / 8); }
-// The best cut, whether or not it beats whole tiles (the scratch it would take is what callers provide).
-inline SplitKPlan splitk_candidate(int M, int N, int K) {
-    SplitKPlan p;
-    if (M <= 256 || M > 1024 || N % 16 != 0 || K % 32 != 0) return p;
-    // 128-column tiles first: for the same number of workgroups they need half the slices of the 256-column
-    // tiles, i.e. half the fp32 partials to write and to add up, and at these sizes that traffic, not the
-    // matrix cores, sets the time (317 x 4096 x 4096: 28 us with 2 x 32 tiles x 4 slices against 36 us with
-    // 2 x 16 tiles x 8).  Rows per tile: 160, 192 or 256, whichever leaves the shorter slice per workgroup at
-    // its measured rate (640 x 4096 x 4096: 24.7 us as 4 x 32 tiles of 160 rows, 27.6 us of 192 rows).
-    auto consider = [&](const TileShape& t, int least, float& best) {
-        const int s = splitk_slices((M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn), K);
-        const float c = (float)(t.bm * t.bn) / (t.rate * (float)s);
-        if (s < least || c >= best) return;
-        best = c;
-        p = {t.bm, t.bn, s};
+// The most slices a cut may take, which sets the scratch that callers provide (0: no cut): those that fill one round
+// on the tiles that then have the shortest slices, 128 columns first, which need half the slices of 256.
+inline int splitk_most(int M, int N, int K) {
+    if (M <= 256 || M > 1024 || N % 16 != 0 || K % 32 != 0) return 0;
+    auto shortest = [&](std::initializer_list<TileId> ids, int least) {
+        int most = 0;
+        float best = 1e30f;
+        for (TileId id : ids) {
+            const TileShape& t = kTiles[id];
+            const int s = splitk_slices(tile_count(t, M, N), K);
+            const float c = (float)(t.bm * t.bn) / (t.rate * (float)s);
+            if (s < least || c >= best) continue;
+            best = c;
+            most = s;
+        }
+        return most;
     };
-    float cost = 1e30f;
-    for (TileId id : {T160x128, T192x128, T256x128}) consider(kTiles[id], 2, cost);
-    // (not with slices longer than 4096 of k: inside a layer the 640-row down projection, K = 11008, takes
-    // 110 us as 4 x 32 tiles x 2 slices against 91 us as 3 x 16 tiles x 5)
-    if (p.splits < 2 || K / p.splits > 4096) {
-        p = {};
-        cost = 1e30f;
-        for (TileId id : {T160x256, T192x256, T256x256}) consider(kTiles[id], 3, cost);
-    }
-    if (p.splits != 0) p.us = splitk_us(cost, M, N, K, p.splits);
-    return p;
+    const int most = shortest({T160x128, T192x128, T256x128}, 2);
+    return most < 2 || K / most > 4096 ? shortest({T160x256, T192x256, T256x256}, 3) : most;
 }
-// The cut to take: none if one launch of whole tiles, which needs no second pass, takes no longer: the partials are
-// written and read once at about 4.5 TB/s, and the reduction costs a launch (920 x 4096 x 4096: 33 us on 8 x 32
-// tiles of 128 x 128 against 33 + 13 us in two slices).
-inline SplitKPlan splitk_plan(int M, int N, int K) {
-    SplitKPlan p = splitk_candidate(M, N, K);
-    float whole = 1e30f;
-    for (int i = 0; i < T128x128R; ++i) whole = std::min(whole, tile_cost(kTiles[i], M, N));
-    whole = whole * (float)K * GM_TILE_US + GM_LAUNCH_US;
-    if (p.splits == 0 || whole < p.us) {
-        p = {};
-        p.us = whole;
+// The cheapest cut over the tiles `ids` of at most `most` slices, if it beats p.us.
+inline void splitk_best(SplitKPlan& p, std::initializer_list<TileId> ids, int M, int N, int K, int most) {
+    const float add = slice_us(M, N);
+    for (TileId id : ids) {
+        const TileShape& t = kTiles[id];
+        const int fit = std::min(most, splitk_slices(tile_count(t, M, N), K));
+        if (fit < 2) continue;
+        // within one round the time is a / s + s add + a constant: least at sqrt(a / add), up to whole slices
+        const int s0 = std::min((int)std::sqrt(0.81f * t.us * (float)K / (4096.0f * add)), fit - 1);
+        for (int s = std::max(2, s0); s <= std::min(s0 + 1, fit); ++s) {
+            const float us = launch_us(t, M, N, K, s) + GM_REDUCTION_US + (float)s * add;
+            if (us < p.us) p = {t.bm, t.bn, s, us};
+        }
     }
+}
+// The cut to take, if it beats one launch of the whole tiles that the launcher would pick, which needs no second pass.
+// sumsq: with the norm side output; whole_extra_us: what the caller has to launch after whole tiles but not after
+// slices (negative: the other way round).
+inline SplitKPlan splitk_plan(int M, int N, int K, bool sumsq = false, float whole_extra_us = 0.f) {
+    SplitKPlan p;
+    p.us = launch_us(kTiles[choose_tile(M, N, K, sumsq, 768)], M, N, K) + whole_extra_us;
+    splitk_best(p, {T160x128, T192x128, T256x128, T160x256, T192x256, T256x256}, M, N, K, splitk_most(M, N, K));
     return p;
 }
 // K, Q and V of a layer as ONE launch of k-slices (tiles of 192 columns may hold the end of one matrix and the start
-// of the next; 317 x 12288 x 4096: 2 x 64 tiles of 160 x 192 in two slices), where that beats a launch of K and one
-// of the Q/V pair.
+// of the next), where that beats a launch of K and one of the Q/V pair.
 inline SplitKPlan qkv_plan(int M, int qd, int kd, int K) {
     SplitKPlan p;
-    const int N = qd + 2 * kd;
     if (M <= 256 || M > 1024 || K % 32 != 0 || qd % 128 != 0 || kd % 128 != 0 || qd < 256 || kd < 256) return p;
-    p.us = splitk_plan(M, kd, K).us + splitk_plan(M, qd + kd, K).us;
-    for (TileId id : {T160x128, T192x128, T256x128, T160x192G, T192x192G}) {
-        const TileShape& t = kTiles[id];
-        const int s = splitk_slices((M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn), K);
-        if (s < 2) continue;
-        const float us = splitk_us((float)(t.bm * t.bn) / (t.rate * (float)s), M, N, K, s);
-        if (us < p.us) p = {t.bm, t.bn, s, us};
-    }
+    const SplitKPlan k = splitk_plan(M, kd, K), qv = splitk_plan(M, qd + kd, K);
+    p.us = k.us + qv.us + (k.splits && qv.splits ? 0.f : GM_ROPE_US);
+    splitk_best(p, {T160x128, T192x128, T256x128, T160x192G, T192x192G}, M, qd + 2 * kd, K, 16);
     return p;
 }
 // Which way launch_gemm_qkv_rope_ws goes at M rows: 1 the three matrices in one few-row launch, 3 in one launch of
@@ -268,9 +284,7 @@ inline int qkv_path(int M, int qd, int kd, int d, int K) {
     if (d != 64 && d != 128) return 0;
     if (gemm_skinny_applies(M, kd + qd + kd, K) && kd % 128 == 0 && qd % 128 == 0) return 1;
     if (qkv_plan(M, qd, kd, K).splits) return 3;
-    if (splitk_plan(M, kd, K).splits && splitk_plan(M, qd + kd, K).splits && qd % 256 == 0 && kd % 256 == 0)
-        return 2;
-    return 0;
+    return qd % 256 == 0 && kd % 256 == 0 && splitk_plan(M, kd, K).splits && splitk_plan(M, qd + kd, K).splits ? 2 : 0;
 }
 
 }  // namespace vitcop

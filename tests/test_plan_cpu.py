@@ -1,0 +1,67 @@
+"""The rules that pick a projection's launches (csrc/gemm_plan.h), compiled for the CPU."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HEADER = os.path.join(ROOT, "paper_2601_17818_amd", "csrc", "gemm_plan.h")
+
+WRAPPER = """
+#include "%s"
+using namespace vitcop;
+extern "C" {
+int splitk(int M, int N, int K, int* o) {
+    const SplitKPlan p = splitk_plan(M, N, K);
+    o[0] = p.bm; o[1] = p.bn;
+    return p.splits;
+}
+int most_slices(int M, int N, int K) { return splitk_most(M, N, K); }
+int whole_tile(int M, int N, int K, int* o) {
+    const TileShape& t = kTiles[choose_tile(M, N, K, false, 768)];
+    o[0] = t.bm; o[1] = t.bn;
+    return 0;
+}
+int few_rows(int M, int N, int K, int* o) {
+    const SkinnyPlan p = skinny_plan(M, N, K);
+    o[0] = skinny_rows(M); o[1] = p.cols;
+    return p.slices;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(WRAPPER % HEADER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-o", str(d / "plan.so"), str(d / "plan.cpp")], check=True)
+    return C.CDLL(str(d / "plan.so"))
+
+
+def picked(plan, M, N, K):
+    """(rows, columns, slices) of the tiles of a launch of 257 rows or more; whole tiles have 1 slice."""
+    o = (C.c_int * 2)()
+    slices = plan.splitk(M, N, K, o)
+    if slices == 0:
+        plan.whole_tile(M, N, K, o)
+    return o[0], o[1], max(slices, 1)
+
+
+@pytest.mark.parametrize("M,N,K,least,most", [
+    # narrow outputs: each further slice costs the reduction more than it saves (21 us in 14 slices, 18 in 4 to 8)
+    (576, 512, 3584, 1, 8), (1000, 512, 3584, 1, 8), (480, 768, 3072, 1, 8), (700, 1024, 2816, 1, 8),
+    # one round of whole tiles over a long k takes a fifth to two fifths longer than slices of large tiles
+    (640, 3584, 3584, 2, 3), (1000, 4096, 11008, 2, 4), (1024, 3584, 14336, 3, 4), (800, 5120, 13824, 3, 3),
+    # few columns, short k: the narrow whole tiles need no reduction (12.5 us against 19 in the best number of slices)
+    (320, 2048, 2048, 1, 1), (257, 1024, 1024, 1, 1)])
+def test_slices_are_priced(plan, M, N, K, least, most):
+    assert least <= picked(plan, M, N, K)[2] <= most
+
+
+def test_slices_fit_the_scratch_that_callers_provide(plan):
+    for M in range(1, 1100):
+        for N, K in ((512, 3584), (1024, 1024), (4096, 4096), (5120, 5120), (9216, 8192), (3584, 14336), (272, 4128)):
+            slices = picked(plan, M, N, K)[2]
+            assert slices == 1 or (256 < M <= 1024 and slices <= plan.most_slices(M, N, K))

@@ -167,15 +167,19 @@ struct SkinnyPlan {
     int cols, slices;
     float us;                            // of the launch and the traffic of its partial sums
 };
+// (A slice costs its traffic and a wait: the reduction reads the slices in order, and with few rows has too few
+// wavefronts to hide that.  With the traffic alone the smallest outputs took 16 slices: 8 x 1024 x 1024 9.2 us, in four
+// 7.6; 16 x 512 x 1024 9.2 and 7.7; 8 x 9216 x 8192 34.8 us in seven slices, 33.3 in three.)
 inline SkinnyPlan skinny_plan(int M, int N, int K) {
     const int steps = K / SK_UNIT;
+    const float add = 0.03f + 1.2f / (float)M;
     SkinnyPlan best{0, 0, 1e30f};
     for (int cols : {64, 96, 128}) {
         const int tiles = (N + cols - 1) / cols;
         const int most = std::min(std::min(16, steps), skinny_scratch_columns(N, K) / N);
         for (int s = 1; s <= most; ++s) {
             const float us = skinny_us(skinny_rows(M), cols, tiles * s, (steps + s - 1) / s * SK_UNIT) +
-                             (float)s * (float)M * (float)N * 12.0f / 4.5e6f;
+                             (float)s * ((float)M * (float)N * 12.0f / 4.5e6f + add);
             if (us < best.us) best = {cols, s, us};
         }
     }

@@ -28,12 +28,12 @@ struct TileShape {
 enum TileId { T256x256, T224x256, T192x256, T160x256, T256x128, T192x128, T160x128, T128x128, T128x128R, T128x32,
               T192x192G, T160x192G, T_COUNT };
 inline constexpr TileShape kTiles[T_COUNT] = {
-    {256, 256, 1.00f, true, 75.5f},  {224, 256, 1.00f, true, 72.7f},  {192, 256, 0.96f, true, 63.5f},
-    {160, 256, 0.94f, true, 59.8f},  {256, 128, 0.89f, false, 47.4f}, {192, 128, 0.83f, false, 41.7f},
-    {160, 128, 0.79f, false, 38.8f}, {128, 128, 0.75f, false, 32.8f}, {128, 128, 0.73f, true, 33.6f},
-    {128, 32, 0.0f, false, 15.3f},
+    {256, 256, 1.00f, true, 80.0f},  {224, 256, 1.00f, true, 76.5f},  {192, 256, 0.96f, true, 65.9f},
+    {160, 256, 0.94f, true, 61.2f},  {256, 128, 0.89f, false, 50.4f}, {192, 128, 0.83f, false, 43.3f},
+    {160, 128, 0.79f, false, 39.7f}, {128, 128, 0.75f, false, 33.8f}, {128, 128, 0.73f, true, 34.6f},
+    {128, 32, 0.0f, false, 16.1f},
     // gate/up launches and k-slices only (a gate/up tile holds 96 + 96 columns)
-    {192, 192, 0.91f, false, 55.0f}, {160, 192, 0.88f, false, 48.0f},
+    {192, 192, 0.91f, false, 57.5f}, {160, 192, 0.88f, false, 50.0f},
 };
 
 // Estimated time of the launch in units of (one 256x256 tile at full rate): rounds over the
@@ -206,22 +206,24 @@ struct SplitKPlan {
 };
 inline int tile_count(const TileShape& t, int M, int N) { return (M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn); }
 // Microseconds of one launch, alone or in `slices` over k: a start and an end that grow with the tile (pipeline fill,
-// epilogue), and rounds over its k, slower by a fifth with all CUs at work than with few.  This, the cost of
-// partial sums and the table's `us` are one fit to 435 sizes of 257 to 1024 rows (256 to 12288 columns, K 768 to
-// 28672, weights from HBM) on each tile shape and up to 16 slices: 6 % rms; what it picks takes 1 % longer on average
-// than the best measured.  The rates of full rounds alone, used before, priced a single round of whole tiles up to
-// a sixth too low and slices at their traffic, and left the 128 x 32 tiles out (800 x 5120 x 13824: whole tiles
-// 144 us, three slices 111; 576 x 512 x 3584: 14 slices 21.0 us, six to eight 17.7; 320 x 2048 x 2048: eight slices
-// 22.1 us, 128 x 32 tiles 12.5).
+// epilogue), and rounds over its k, slower by a fifth with all CUs at work than with few and by a quarter with tiles
+// full of rows than with rows past the end, which are not loaded (640 x 5120 x 5120: 128-row tiles 56 us, 576 rows
+// 48).  This, the cost of partial sums and the table's `us` are one fit to 435 sizes of 257 to 1024 rows (256 to 12288
+// columns, K 768 to 28672, weights from HBM) on each tile shape and up to 16 slices: 6 % rms; what it picks takes 1 %
+// longer on average than the best measured.  The rates of full rounds alone, used before, priced a single round of
+// whole tiles up to a sixth too low and slices at their traffic, and left the 128 x 32 tiles out (800 x 5120 x 13824:
+// whole tiles 144 us, three slices 111; 576 x 512 x 3584: 14 slices 21.0 us, six to eight 17.7; 320 x 2048 x 2048:
+// eight slices 22.1 us, 128 x 32 tiles 12.5).
 inline float launch_us(const TileShape& t, int M, int N, int K, int slices = 1) {
     const int wgs = tile_count(t, M, N) * slices, rounds = (wgs + 255) / 256;
     const float fill = std::min(1.0f, (float)wgs / 256.0f);
-    return 5.3f + 8.2f / 65536.0f * (float)(t.bm * t.bn) +
-           (float)rounds * (float)K / (4096.0f * (float)slices) * t.us * (0.81f + 0.19f * fill);
+    const float full = (float)M / (float)((M + t.bm - 1) / t.bm * t.bm);
+    return 5.2f + 8.4f / 65536.0f * (float)(t.bm * t.bn) +
+           (float)rounds * (float)K / (4096.0f * (float)slices) * t.us * (0.57f + 0.17f * fill + 0.26f * full);
 }
 // What a slice adds: its share of the reduction (partials written and read once, in slice order).
-inline float slice_us(int M, int N) { return 0.25f + 1.05e-6f * (float)M * (float)N; }
-constexpr float GM_REDUCTION_US = 1.3f;        // the reduction's launch
+inline float slice_us(int M, int N) { return 0.27f + 1.02e-6f * (float)M * (float)N; }
+constexpr float GM_REDUCTION_US = 1.4f;        // the reduction's launch
 // Launches that only slices spare or only whole tiles spare: the RMSNorm after a projection and the rotary embedding
 // (in the slices' reduction), the activation after gate and up (in the whole tiles' epilogue).
 constexpr float GM_NORM_US = 4.0f, GM_ROPE_US = 5.0f;
@@ -256,7 +258,7 @@ inline void splitk_best(SplitKPlan& p, std::initializer_list<TileId> ids, int M,
         const int fit = std::min(most, splitk_slices(tile_count(t, M, N), K));
         if (fit < 2) continue;
         // within one round the time is a / s + s add + a constant: least at sqrt(a / add), up to whole slices
-        const int s0 = std::min((int)std::sqrt(0.81f * t.us * (float)K / (4096.0f * add)), fit - 1);
+        const int s0 = std::min((int)std::sqrt(0.8f * t.us * (float)K / (4096.0f * add)), fit - 1);
         for (int s = std::max(2, s0); s <= std::min(s0 + 1, fit); ++s) {
             const float us = launch_us(t, M, N, K, s) + GM_REDUCTION_US + (float)s * add;
             if (us < p.us) p = {t.bm, t.bn, s, us};

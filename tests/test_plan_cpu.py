@@ -54,6 +54,8 @@ def picked(plan, M, N, K):
     (576, 512, 3584, 1, 8), (1000, 512, 3584, 1, 8), (480, 768, 3072, 1, 8), (700, 1024, 2816, 1, 8),
     # one round of whole tiles over a long k takes a fifth to two fifths longer than slices of large tiles
     (640, 3584, 3584, 2, 3), (1000, 4096, 11008, 2, 4), (1024, 3584, 14336, 3, 4), (800, 5120, 13824, 3, 3),
+    # tiles full of rows take longer than ones that end in padding, which is not loaded (whole tiles 56 and 21 us)
+    (640, 5120, 5120, 2, 3), (640, 512, 3584, 4, 8),
     # few columns, short k: the narrow whole tiles need no reduction (12.5 us against 19 in the best number of slices)
     (320, 2048, 2048, 1, 1), (257, 1024, 1024, 1, 1)])
 def test_slices_are_priced(plan, M, N, K, least, most):

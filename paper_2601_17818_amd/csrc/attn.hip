@@ -795,7 +795,6 @@ static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t
     constexpr int BM = 128 * U;
     const int n_qb = (N + BM - 1) / BM;
     const long n_heads = (long)Hq * B;
-    if (n_heads * n_qb > 0x7fffffffL) return fail(VITCOP_EUNSUPPORTED, "attention: grid too large");
     // (sample, head) pairs in flight together: few, so that their query blocks share K/V
     // in L2, but enough to fill the 256 CUs twice over (measured: 32 from N = 2048 up)
     const int group = std::max(32, (512 / n_qb + 7) / 8 * 8);
@@ -810,8 +809,10 @@ int launch_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_
     if (B == 0 || N == 0) return VITCOP_OK;
     if (N > (1 << 22)) return fail(VITCOP_EUNSUPPORTED, "attention: N=%d above 2^22", N);   // grid.z limit
     const float sl2 = scale * 1.4426950408889634f;
-    // the wide kernel addresses K and V of one (sample, KV head) with 32-bit byte offsets
-    const bool wide_ok = ((int64_t)N + AW_BN) * Hkv * d * 2 < ((int64_t)1 << 32);
+    // the wide kernel addresses K and V of one (sample, KV head) with 32-bit byte offsets, and its workgroups by one grid
+    // dimension, which holds fewer than 2^32 threads
+    const bool wide_ok = ((int64_t)N + AW_BN) * Hkv * d * 2 < ((int64_t)1 << 32) &&
+                         (int64_t)Hq * B * ((N + 127) / 128) * 256 < ((int64_t)1 << 32);
     if (!wide_ok) {
         dim3 grid(Hq, B, (N + AT_BM - 1) / AT_BM);
         hipLaunchKernelGGL(d == 64 ? attn_kernel<64> : attn_kernel<128>, grid, dim3(AT_THREADS), 0, s, q, k, v, out, lse,

@@ -175,3 +175,12 @@ def test_deterministic(vc):
     for _ in range(5):
         b, _ = vc.vitcop_prefill_attn(q, k, v)
         assert torch.equal(a, b)
+
+
+# what the pipelined kernel cannot address goes to the kernel with a three-dimensional grid and 64-bit offsets
+def test_more_workgroups_than_one_grid_dimension_holds(vc):
+    B, Hq = 65535, 260                                   # 17 million (sample, head) pairs of one token each
+    q = torch.ones((B, 1, Hq, 64), dtype=torch.bfloat16, device="cuda")
+    k, v = (torch.empty((B, 1, 1, 64), dtype=torch.bfloat16, device="cuda").normal_() for _ in range(2))
+    out, _ = vc.vitcop_prefill_attn(q, k, v)
+    assert bool((out == v).all())                        # a softmax over one key

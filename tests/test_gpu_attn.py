@@ -5,7 +5,7 @@ import torch
 
 import vitcop_inputs as I
 from oracle import vitcop_oracle as O
-from gpu_util import assert_attention_close, dev, host_f64
+from gpu_util import assert_attention_close, dev, host_bits, host_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -184,3 +184,16 @@ def test_more_workgroups_than_one_grid_dimension_holds(vc):
     k, v = (torch.empty((B, 1, 1, 64), dtype=torch.bfloat16, device="cuda").normal_() for _ in range(2))
     out, _ = vc.vitcop_prefill_attn(q, k, v)
     assert bool((out == v).all())                        # a softmax over one key
+
+
+@pytest.mark.parametrize("d,H,N,causal", [(64, 31552, 1000, True), (64, 33600, 960, False), (128, 15776, 1000, True)])
+def test_keys_beyond_32_bit_offsets(vc, d, H, N, causal):
+    assert (N + 64) * H * d * 2 >= 1 << 32
+    g = torch.Generator(device="cuda").manual_seed(d + N)
+    q, k, v = (torch.empty((1, N, H, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(3))
+    out, lse = vc.vitcop_prefill_attn(q, k, v, causal=causal, want_lse=True)
+    heads = [0, 1, H // 2, H - 1]
+    t = [host_bits(x[:, :, heads]) for x in (q, k, v)]
+    ref, ref_lse = O.attention(*t, None, causal)
+    assert_attention_close(host_f64(out[:, :, heads]), ref, f"d={d} N={N}")
+    assert np.abs(lse[:, heads].cpu().numpy() - ref_lse).max() < 1e-3

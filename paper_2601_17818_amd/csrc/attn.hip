@@ -3,17 +3,19 @@
 // FlashAttention kernel computes (Sec. 1 and Sec. 2.2 rely on that
 // compatibility; this is the 4 N^2 d term of Eq. 7).  Head dimensions 128 and 64.
 //
-// Layout of the computation (wave64, v_mfma_f32_32x32x16_bf16):
-//  * a workgroup of 4 wavefronts owns 128 consecutive queries of one
-//    (sample, head); each wavefront owns 32 of them;
+// Two kernels: attn_wide_kernel (below), which every ordinary call takes, and attn_kernel for K/V spans beyond
+// 32-bit byte offsets and for more workgroups than one grid dimension holds.  Layout of the computation of both
+// (wave64, v_mfma_f32_32x32x16_bf16):
+//  * a workgroup of 4 wavefronts owns consecutive queries of one (sample, head), each wavefront one or two
+//    blocks of 32 of them;
 //  * keys/values stream through LDS in tiles of 64 keys;
 //  * scores are computed TRANSPOSED, S^T = K Q^T, so that every lane holds
 //    scores of a single query (its column): the running max / sum are
 //    per-lane scalars plus one exchange with lane^32, and the probabilities
 //    are already laid out as the B operand of the second product
-//    O^T += V^T P^T — they never leave registers;
-//  * V is written to LDS transposed (channel-major) with the keys of each
-//    group of 32 permuted so that the 8 keys a lane needs are contiguous.
+//    O^T += V^T P^T — they never leave registers.
+// attn_kernel stages both through registers and writes V to LDS transposed (channel-major), the keys of each
+// group of 32 permuted so that the 8 keys a lane needs are contiguous.
 #include <atomic>
 #include <type_traits>
 
@@ -22,7 +24,6 @@
 #include <algorithm>
 
 namespace vitcop {
-
 
 constexpr int AT_BM = 128;
 constexpr int AT_BN = 64;
@@ -212,11 +213,11 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// The kernel for head dimensions 128 and 64 (the one above remains for K/V spans beyond 32-bit byte offsets).  A workgroup of 4 wavefronts owns 128 U queries, each wavefront U blocks of 32: with U = 2 (long
-// sequences) every K and V^T fragment read from LDS feeds two MFMAs; with U = 1 (the few hundred tokens that
-// survive pruning) a wavefront's chain per key tile is half as long and there are twice the workgroups.
-// K and V tiles (64 keys) arrive by direct
-// global -> LDS loads into a ring of four stages; both stay row-major in LDS,
+// The kernel of every ordinary call.  A workgroup of 4 wavefronts owns 128 U queries, each wavefront U blocks of 32:
+// with U = 2 (long sequences, head dimension 128) every K and V^T fragment read from LDS feeds two MFMAs; with U = 1
+// (the few hundred tokens that survive pruning, and head dimension 64) a wavefront's chain per key tile is half as
+// long and there are twice the workgroups.  K and V tiles (64 keys) arrive by direct global -> LDS loads into a ring
+// of four stages (three with head dimension 64); both stay row-major in LDS,
 // padded per KiB; V^T fragments come from the transposing LDS read
 // (ds_read_b64_tr_b16), so nothing is staged in or shuffled through registers.
 // The reference of the exponentials is only raised when a score exceeds it by
@@ -236,10 +237,10 @@ template <int D>
 constexpr int AW_KTILE = D / 8 * AW_KGRP;                    // 16640 or 8320 B
 template <int D>
 constexpr int AW_STAGE = AW_KTILE<D> + D / 8 * AW_VGRP;      // K then V
-// tiles in the ring: four, or three with head dimension 64 and one query block, where three workgroups share a CU and
-// cover the shorter prefetch for each other
-template <int D, int U>
-constexpr int AW_STAGES = D == 64 && U == 1 ? 3 : 4;
+// tiles in the ring: four, or three with head dimension 64, where three workgroups share a CU and cover the shorter
+// prefetch for each other
+template <int D>
+constexpr int AW_STAGES = D == 64 ? 3 : 4;
 constexpr float AW_RESCALE_GAP = 8.0f;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -353,19 +354,19 @@ template <int D, int U, bool MASKED>
 constexpr SmTable SM_TABLE_OF = make_sm_table(MASKED, U, D / 8 * U);
 
 template <int D, bool CAUSAL, int U>
-__global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kernel(
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, uint16_t* __restrict__ out, float* __restrict__ lse,
     int N, int Hq, int Hkv, float scale_log2e, int n_qb, int n_heads, int group) {
     extern __shared__ __attribute__((aligned(1024))) char aw_lds[];
-    static_assert(U == 1 || U == 2, "query blocks per wavefront");
+    static_assert(U == 1 || (U == 2 && D == 128), "query blocks per wavefront");
     constexpr int BM = 128 * U, QW = 32 * U;       // queries per workgroup and per wavefront
     constexpr int DC = D / 16, DB = D / 32;        // 16-channel steps of the scores, 32-channel blocks of the output
     constexpr int ROWB = 2 * D;                    // bytes of a K or V row
     constexpr int GROUPS = D / 8, GPW = GROUPS / 4;        // row groups of a tile, and per wavefront
     constexpr int LPR = D / 8;                     // lanes that carry one row of a tile load
     constexpr int LPT = 2 * GPW;                   // loads per wavefront and tile
-    constexpr int ST = AW_STAGES<D, U>;
+    constexpr int ST = AW_STAGES<D>;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -413,7 +414,7 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
     for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int dc = 0; dc < DC; ++dc)
-            if constexpr (D == 128 || U == 2) asm volatile("" : "+a"(qf[u][dc]));
+            if constexpr (D == 128) asm volatile("" : "+a"(qf[u][dc]));
 
     f32x16 o[U][DB];
 #pragma unroll
@@ -773,10 +774,10 @@ __global__ __launch_bounds__(256, D == 64 && U == 1 ? 2 : 1) void attn_wide_kern
 }
 
 // Head dimension 64: half the MFMAs and the same softmax per stage, so the vector work sets the time and a second
-// query block per wavefront saves nothing; one block leaves registers and LDS for two workgroups per CU, whose
-// vector and matrix work overlap.  20 x 577 x 16 heads, bidirectional: 73 us with the kernel above,
-// 67 with two blocks, 56 with one; 1 x 6400, 16 / 4 heads, causal: 168, 118, 111 us; 4 x 384: 13.7, 12.4, 11.1.
-constexpr int AW_U64 = 1;
+// query block per wavefront saves nothing; with one block and a ring of three tiles a CU holds three workgroups, whose
+// vector and matrix work overlap.  20 x 577 x 16 heads, bidirectional: 73 us with attn_kernel, 67 with two blocks, 56
+// with one and four tiles, 49 with three; 1 x 6400, 16 / 4 heads, causal: 168, 118, 111, 108; 4 x 384: 13.7, 12.4,
+// 11.1, 10.
 constexpr int AW_U2_MIN_N = 512;   // a wavefront takes two query blocks from this length on,
 constexpr int AW_U2_MIN_WGS = 256;  // if that still leaves more workgroups than this
 
@@ -784,7 +785,7 @@ template <int D, bool CAUSAL, int U>
 static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                             int B, int N, int Hq, int Hkv, float sl2, hipStream_t s) {
     static std::atomic<bool> attr_set{false};   // set once; a second thread repeating the call is harmless
-    constexpr int lds = AW_STAGES<D, U> * AW_STAGE<D>;
+    constexpr int lds = AW_STAGES<D> * AW_STAGE<D>;
     if (!attr_set.load(std::memory_order_acquire)) {
         const int rc = hip_status(hipFuncSetAttribute((const void*)attn_wide_kernel<D, CAUSAL, U>,
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds),
@@ -820,8 +821,8 @@ int launch_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_
         return launch_status("attn");
     }
     if (d == 64)
-        return causal ? launch_attn_wide<64, true, AW_U64>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
-                      : launch_attn_wide<64, false, AW_U64>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
+        return causal ? launch_attn_wide<64, true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
+                      : launch_attn_wide<64, false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
     // Two query blocks per wavefront halve the LDS reads per MFMA, which is what long sequences need; one
     // block halves the chain of MFMAs a wavefront runs per key tile and doubles the workgroups, which is
     // what the lengths that survive pruning need (a few hundred tokens: one to six key tiles per workgroup,

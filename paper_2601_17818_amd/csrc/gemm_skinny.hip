@@ -26,29 +26,28 @@ namespace vitcop {
 __device__ __forceinline__ void sk_sum_tiles(const SkParts& P, int m, int n, float (&v)[8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = 0.f;
-    auto sum_range = [&](int i, int i_hi, auto tile) {
-        for (; i + 3 <= i_hi; i += 4) {
-            float4 a[4], b[4];
+    auto tile = [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.N + n; };
+    int i = 0;
+    for (; i + 3 < P.slices; i += 4) {
+        float4 a[4], b[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float* p = tile(i + t);
-                a[t] = *reinterpret_cast<const float4*>(p);
-                b[t] = *reinterpret_cast<const float4*>(p + 4);
-            }
+        for (int t = 0; t < 4; ++t) {
+            const float* p = tile(i + t);
+            a[t] = *reinterpret_cast<const float4*>(p);
+            b[t] = *reinterpret_cast<const float4*>(p + 4);
+        }
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                v[0] += a[t].x; v[1] += a[t].y; v[2] += a[t].z; v[3] += a[t].w;
-                v[4] += b[t].x; v[5] += b[t].y; v[6] += b[t].z; v[7] += b[t].w;
-            }
+        for (int t = 0; t < 4; ++t) {
+            v[0] += a[t].x; v[1] += a[t].y; v[2] += a[t].z; v[3] += a[t].w;
+            v[4] += b[t].x; v[5] += b[t].y; v[6] += b[t].z; v[7] += b[t].w;
         }
-        for (; i <= i_hi; ++i) {
-            const float* p = tile(i);
-            const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-            v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
-            v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
-        }
-    };
-    sum_range(0, P.slices - 1, [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.N + n; });
+    }
+    for (; i < P.slices; ++i) {
+        const float* p = tile(i);
+        const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
+        v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
+    }
 }
 
 // The same for two column chunks of one 128-column group at once, n .. n+8 and n+delta .. n+delta+8: both
@@ -56,36 +55,35 @@ __device__ __forceinline__ void sk_sum_tiles(const SkParts& P, int m, int n, flo
 __device__ __forceinline__ void sk_sum_tiles2(const SkParts& P, int m, int n, int delta, float (&v)[8], float (&w)[8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = w[e] = 0.f;
-    auto sum_range = [&](int i, int i_hi, auto tile) {
-        for (; i + 3 <= i_hi; i += 4) {
-            float4 a[4], b[4], c[4], d[4];
+    auto tile = [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.N + n; };
+    int i = 0;
+    for (; i + 3 < P.slices; i += 4) {
+        float4 a[4], b[4], c[4], d[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float* p = tile(i + t);
-                a[t] = *reinterpret_cast<const float4*>(p);
-                b[t] = *reinterpret_cast<const float4*>(p + 4);
-                c[t] = *reinterpret_cast<const float4*>(p + delta);
-                d[t] = *reinterpret_cast<const float4*>(p + delta + 4);
-            }
+        for (int t = 0; t < 4; ++t) {
+            const float* p = tile(i + t);
+            a[t] = *reinterpret_cast<const float4*>(p);
+            b[t] = *reinterpret_cast<const float4*>(p + 4);
+            c[t] = *reinterpret_cast<const float4*>(p + delta);
+            d[t] = *reinterpret_cast<const float4*>(p + delta + 4);
+        }
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                v[0] += a[t].x; v[1] += a[t].y; v[2] += a[t].z; v[3] += a[t].w;
-                v[4] += b[t].x; v[5] += b[t].y; v[6] += b[t].z; v[7] += b[t].w;
-                w[0] += c[t].x; w[1] += c[t].y; w[2] += c[t].z; w[3] += c[t].w;
-                w[4] += d[t].x; w[5] += d[t].y; w[6] += d[t].z; w[7] += d[t].w;
-            }
+        for (int t = 0; t < 4; ++t) {
+            v[0] += a[t].x; v[1] += a[t].y; v[2] += a[t].z; v[3] += a[t].w;
+            v[4] += b[t].x; v[5] += b[t].y; v[6] += b[t].z; v[7] += b[t].w;
+            w[0] += c[t].x; w[1] += c[t].y; w[2] += c[t].z; w[3] += c[t].w;
+            w[4] += d[t].x; w[5] += d[t].y; w[6] += d[t].z; w[7] += d[t].w;
         }
-        for (; i <= i_hi; ++i) {
-            const float* p = tile(i);
-            const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-            const float4 c = *reinterpret_cast<const float4*>(p + delta), d = *reinterpret_cast<const float4*>(p + delta + 4);
-            v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
-            v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
-            w[0] += c.x; w[1] += c.y; w[2] += c.z; w[3] += c.w;
-            w[4] += d.x; w[5] += d.y; w[6] += d.z; w[7] += d.w;
-        }
-    };
-    sum_range(0, P.slices - 1, [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.N + n; });
+    }
+    for (; i < P.slices; ++i) {
+        const float* p = tile(i);
+        const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+        const float4 c = *reinterpret_cast<const float4*>(p + delta), d = *reinterpret_cast<const float4*>(p + delta + 4);
+        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
+        v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
+        w[0] += c.x; w[1] += c.y; w[2] += c.z; w[3] += c.w;
+        w[4] += d.x; w[5] += d.y; w[6] += d.z; w[7] += d.w;
+    }
 }
 
 // y[m, n..n+8) = bf16(sum of the slices' partials, in slice order, + residual);

@@ -282,8 +282,8 @@ static int check_layer(const vitcop_layer_t* L) {
 // before and after pruning; F = 0: no MLP).
 // The need is not monotone in the row count (different paths below 257 and below 1025 rows, slice
 // counts that drop as tiles are added), and a schedule sizes its workspace for its longest sequence:
-// so a launch of M rows reserves the largest need of any row count up to M.  The need grows with M
-// between tile boundaries, which are multiples of 64.
+// so a launch of M rows reserves the largest need of the multiples of 64 up to M and of M itself.  (Tiles end
+// elsewhere too; what a layer asks for in all grows with its rows, which the tests walk row by row.)
 static size_t gemm_scratch_upto(int M, int N, int K) {
     size_t n = gemm_workspace_bytes(M, N, K);
     for (int m = 64; m < M && m <= 1024; m += 64) n = std::max(n, gemm_workspace_bytes(m, N, K));

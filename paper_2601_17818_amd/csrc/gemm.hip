@@ -60,7 +60,6 @@ int launch_gemm_pair(const uint16_t* x, int64_t x_stride, const uint16_t* w1, ui
     return launch_tile(id, x, x_stride, w1, y1, N1, nullptr, 0, M, N1 + N2, K, nullptr, w2, y2, N1, s, N2);
 }
 
-static size_t qkv_plan_bytes(const SplitKPlan& p, int M, int N) { return up256((size_t)p.splits * M * N * 4); }
 static size_t splitk_workspace_bytes(int M, int N, int K) { return up256((size_t)splitk_most(M, N, K) * M * N * 4); }
 
 // scratch of the trailing columns when main_columns cuts the launch (as one matrix, or as the pair N/2 + N/2)
@@ -331,9 +330,11 @@ size_t gemm_qkv_workspace_bytes(int M, int Hq, int Hkv, int d, int K) {
     const int qd = Hq * d, kd = Hkv * d;
     size_t need = std::max(gemm_workspace_bytes(M, kd, K), gemm_workspace_bytes(M, qd + kd, K));
     need = std::max(need, gemm_workspace_bytes(M, kd + qd + kd, K));
-    const int path = qkv_path(M, qd, kd, d, K);
-    if (path == 2) need = std::max(need, splitk_workspace_bytes(M, kd, K) + splitk_workspace_bytes(M, qd + kd, K));
-    if (path == 3) need = std::max(need, qkv_plan_bytes(qkv_plan(M, qd, kd, K), M, qd + 2 * kd));
+    // slices of the three together: what the next multiple of 64 rows takes, so that what a caller reserves up to some
+    // number of rows grows with it (gemm_scratch_upto in api.hip); a launch takes as many slices as that holds
+    const int R = (M + 63) / 64 * 64, path = qkv_path(R, qd, kd, d, K);
+    if (path == 2) need = std::max(need, splitk_workspace_bytes(R, kd, K) + splitk_workspace_bytes(R, qd + kd, K));
+    if (path == 3) need = std::max(need, up256((size_t)qkv_plan(R, qd, kd, K).splits * R * (qd + 2 * kd) * 4));
     return need;
 }
 
@@ -356,9 +357,9 @@ int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t*
         return launch_qkv_finish(P, k, q, v, Hq, Hkv, d, positions, theta, s);
     }
     if (path == 3) {
-        const SplitKPlan p = qkv_plan(M, qd, kd, K);
         const int N = qd + 2 * kd;
-        if (ws_bytes >= qkv_plan_bytes(p, M, N)) {
+        const SplitKPlan p = qkv_plan(M, qd, kd, K, (int)std::min(ws_bytes / ((size_t)M * N * 4), (size_t)16));
+        if (p.splits) {
             const SkParts parts{static_cast<float*>(ws), p.splits, N, M};
             const SkMats mats{{wk, wq, wv}, {k, q, v}, {kd, qd, kd}, {kd, kd + qd, N}};
             const int rc = launch_slices(p, x, x_stride, mats, M, N, K, static_cast<float*>(ws), s);

@@ -275,13 +275,13 @@ inline SplitKPlan splitk_plan(int M, int N, int K, bool sumsq = false, float who
     return p;
 }
 // K, Q and V of a layer as ONE launch of k-slices (tiles of 192 columns may hold the end of one matrix and the start
-// of the next), where that beats a launch of K and one of the Q/V pair.
-inline SplitKPlan qkv_plan(int M, int qd, int kd, int K) {
+// of the next), where that beats a launch of K and one of the Q/V pair.  `most`: slices that the scratch holds.
+inline SplitKPlan qkv_plan(int M, int qd, int kd, int K, int most = 16) {
     SplitKPlan p;
     if (M <= 256 || M > 1024 || K % 32 != 0 || qd % 128 != 0 || kd % 128 != 0 || qd < 256 || kd < 256) return p;
     const SplitKPlan k = splitk_plan(M, kd, K), qv = splitk_plan(M, qd + kd, K);
     p.us = k.us + qv.us + (k.splits && qv.splits ? 0.f : GM_ROPE_US);
-    splitk_best(p, {T160x128, T192x128, T256x128, T160x192G, T192x192G}, M, qd + 2 * kd, K, 16);
+    splitk_best(p, {T160x128, T192x128, T256x128, T160x192G, T192x192G}, M, qd + 2 * kd, K, most);
     return p;
 }
 // Which way launch_gemm_qkv_rope_ws goes at M rows: 1 the three matrices in one few-row launch, 3 in one launch of

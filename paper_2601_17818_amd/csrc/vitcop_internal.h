@@ -71,12 +71,13 @@ int launch_gemm_norm_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w, 
                         const uint16_t* res, int64_t res_stride, int M, int N, int K, const uint16_t* ln_w,
                         float eps, uint16_t* norm_out, int64_t norm_stride, void* ws, size_t ws_bytes,
                         hipStream_t s);
-// Three projections of the same input (dense outputs [M, n[i]]): one launch on the few-row path when
-// it applies and n[0], n[1] are multiples of 128; otherwise the first alone and the other two as a pair.
+// Three projections of the same input (dense outputs [M, n[i]]), n[0] and n[1] multiples of 128: one launch on the
+// few-row path, and of whole tiles above 1024 rows where that is no slower; otherwise the first alone and the other two
+// as a pair.
 int launch_gemm_triple_ws(const uint16_t* x, int64_t x_stride, const uint16_t* const w[3], uint16_t* const y[3],
                           const int n[3], int M, int K, void* ws, size_t ws_bytes, hipStream_t s);
-// out = silu(x wg^T) * (x wu^T) [M, F]: on the few-row path one launch with the activation in its
-// reduction; otherwise the pair of projections into gate and up [M, F] and launch_silu_mul.
+// out = silu(x wg^T) * (x wu^T) [M, F]: one launch with the activation in the tiles' epilogue, on few rows also in the
+// reduction of k-slices; otherwise the pair of projections into gate and up [M, F] and launch_silu_mul.
 int launch_gemm_gated_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wg, const uint16_t* wu, int F,
                          uint16_t* gate, uint16_t* up, uint16_t* out, int M, int K, void* ws, size_t ws_bytes,
                          hipStream_t s);

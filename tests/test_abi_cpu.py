@@ -290,6 +290,21 @@ def test_decoder_validation():
     assert ws(C.byref(desc(d=96))) == 0
 
 
+@pytest.mark.parametrize("D,Hq,Hkv,d,F", [(1024, 16, 4, 64, 2816), (4096, 32, 32, 128, 11008), (3584, 28, 4, 128, 14336),
+                                          (6144, 48, 8, 128, 16384), (8192, 64, 8, 128, 28672)])
+def test_layer_workspace_grows_with_the_rows(D, Hq, Hkv, d, F):
+    """A schedule sizes its workspace for its longest sequence: no shorter one may ask for more."""
+    for part in (1.0, 0.4):
+        largest = 0
+        for T in range(1, 1300):
+            keep = max(1, int(T * part))
+            layer = binding.DecoderLayerT(1, T, D, Hq, Hkv, d, F, 0, T, keep, 1e-5, 10000.0)
+            attn = layer_desc(T=T, D=D, Hq=Hq, Hkv=Hkv, d=d, vis_start=0, n_vis=T, keep=keep)
+            need = (lib.vitcop_decoder_layer_workspace_bytes(C.byref(layer)), lib.vitcop_layer_workspace_bytes(C.byref(attn)))
+            assert T == 1 or (need[0] >= largest[0] and need[1] >= largest[1]), T
+            largest = need
+
+
 def test_decoder_schedule_validation():
     # padding before the pointers and at the end
     assert C.sizeof(binding.DecoderScheduleT) == 11 * 4 + 2 * 4 + 4 + 15 * 8 + 2 * 8 + 8 + 2 * 8    # + stage records

@@ -48,8 +48,8 @@ def test_project_matches_oracle(vc, M, N, K):
                                    (64, 4096, 2752), (33, 256, 8192),
                                    (64, 16512, 256), (200, 8192, 192)])
 def test_project_few_rows_matches_oracle(vc, M, N, K):
-    # M <= 256: the split-K kernel that streams W through registers (1..16 splits, ragged k-ranges,
-    # partial column groups, every row-block count), with residual and the norm side output
+    # M <= 256: tiles that hold all rows, the k-range in slices where the columns are few (ragged slices, partial
+    # column groups, tiles of several heights), with residual and the norm side output
     assert vc.lib.vitcop_project_workspace_bytes(M, N, K) > 0
     x = I.normal_bf16(M + N + K, 0, (M, K))
     w = I.normal_bf16(M + N + K, 1, (N, K), 0.05)
@@ -107,8 +107,8 @@ def test_project_one_to_four_rows_shape_sweep(vc):
 @pytest.mark.parametrize("M,N,K", [(317, 4096, 4096), (640, 4096, 2048), (1000, 1024, 2048), (352, 2048, 11008),
                                    (257, 256, 768), (1024, 4096, 1024)])
 def test_project_split_k_matches_oracle(vc, M, N, K):
-    # 256 < M <= 1024 and few column tiles: 256- or 192-row tiles with the k-range cut into slices
-    # (3..16, ragged), fp32 partials added by the reduction kernel, with residual and norm side output
+    # 256 < M <= 1024 and few column tiles: the k-range cut into slices (ragged), fp32 partials added by the reduction
+    # kernel, or whole tiles where they take no longer, with residual and norm side output
     assert vc.lib.vitcop_project_workspace_bytes(M, N, K) > 0
     x = I.normal_bf16(M + N + K, 0, (M, K))
     w = I.normal_bf16(M + N + K, 1, (N, K), 0.05)

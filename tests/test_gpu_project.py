@@ -42,7 +42,12 @@ def test_tiles_and_k_steps(M, N, K):
     assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
 
 
-@pytest.mark.parametrize("M,N,K", [(257, 512, 4096), (317, 4096, 4064), (640, 4096, 4096), (1024, 1040, 4128), (500, 2064, 3008)])
+# (test_plan_cpu.py checks that these shapes are cut, and that the lists of this file reach every sliced tile)
+SPLIT_K = [(257, 512, 4096), (317, 4096, 4064), (640, 4096, 4096), (1024, 1040, 4128), (500, 2064, 3008),
+           (327, 3840, 2304), (390, 3840, 3584), (257, 8448, 4608), (327, 5632, 8448), (390, 5632, 8448)]
+
+
+@pytest.mark.parametrize("M,N,K", SPLIT_K)
 def test_split_k(M, N, K):
     assert vc.lib.vitcop_project_workspace_bytes(M, N, K) > 0
     x, w, r = draw(M, N, K, M)
@@ -59,8 +64,12 @@ def test_rows_past_the_end_do_not_leak_in():
     check(x, w, y, r)
 
 
-@pytest.mark.parametrize("M", [5, 32, 33, 64, 65, 100, 128, 129, 161, 193, 225, 256])
-@pytest.mark.parametrize("N,K", [(528, 128), (4096, 192), (1552, 2048), (16400, 256)])
+FEW_ROWS = [5, 32, 33, 64, 65, 100, 128, 129, 161, 193, 225, 256]
+FEW_ROWS_NK = [(528, 128), (4096, 192), (1552, 2048), (16400, 256), (8256, 1152), (12352, 2048), (8320, 3456)]
+
+
+@pytest.mark.parametrize("M", FEW_ROWS)
+@pytest.mark.parametrize("N,K", FEW_ROWS_NK)
 def test_few_rows(M, N, K):
     assert vc.lib.vitcop_project_workspace_bytes(M, N, K) > 0
     x, w, r = draw(M, N, K, M + N)
@@ -74,8 +83,15 @@ def test_few_rows(M, N, K):
 
 SIDE_BY_SIDE = ([(M, *layer) for layer in ((512, 4, 2, 64, 1408), (640, 5, 1, 128, 896), (1024, 16, 4, 64, 2816))
                  for M in (7, 40, 115, 200, 300, 700, 1100, 2900)] +
-                # k-slices of 256 columns, K in a launch of its own and Q and V as a pair
-                [(257, 5888, 36, 36, 128, 512)])
+                # K, Q and V as one launch of k-slices on each of its tiles
+                [(257, 512, 2, 2, 128, 256), (257, 512, 44, 11, 128, 256), (327, 512, 22, 11, 128, 256),
+                 (327, 512, 44, 11, 128, 256), (481, 512, 40, 5, 128, 256)] +
+                # K in k-slices of its own, Q and V as a pair in slices of 256 columns
+                [(257, 5888, 36, 36, 128, 512)] +
+                # gate and up of few rows in tiles of 32 + 32 and 64 + 64 columns, and in k-slices
+                [(M, *layer) for M, D in ((20, 7168), (50, 2048), (80, 1536), (120, 1280), (150, 1024), (180, 1024),
+                                          (210, 1024), (250, 1024))
+                 for layer in ((512, 1, 1, 128, 256), (256, 1, 1, 128, 8320), (D, 1, 1, 128, 128))])
 
 
 @pytest.mark.parametrize("M,D,Hq,Hkv,d,F", SIDE_BY_SIDE)
@@ -132,10 +148,15 @@ def test_query_and_value_of_unequal_width(B, n_vis, keep):
         assert float((got - want).norm() / want.norm()) <= 2.0 ** -7
 
 
-@pytest.mark.parametrize("D,Hq,Hkv,keep", [(8192, 64, 8, 300), (8192, 64, 2, 257), (12288, 48, 8, 350), (12288, 48, 8, 640)])
-def test_query_and_value_pair_in_wide_slices(D, Hq, Hkv, keep):
-    """Q and V of wide pruned layers (k-slices of 256 columns over both matrices): the layer's output and the V cache are
-    those of Q and V projected one by one in whole tiles."""
+# slices of 256 columns of 160, 192 and 256 rows, then of 128 columns
+PAIRS = [(8192, 64, 8, 300), (8192, 64, 2, 257), (12288, 48, 8, 350), (12288, 48, 8, 640),
+         (3328, 2, 2, 257), (2304, 28, 4, 327), (3584, 28, 4, 390)]
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,keep", PAIRS)
+def test_query_and_value_pair_in_slices(D, Hq, Hkv, keep):
+    """Q and V of pruned layers as k-slices over both matrices: the layer's output and its caches are those of Q and V
+    projected one by one in whole tiles."""
     d, T = 128, keep + 100
     g = torch.Generator(device="cuda").manual_seed(keep)
 

@@ -5,6 +5,8 @@ import subprocess
 
 import pytest
 
+import test_gpu_project as gpu
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "paper_2601_17818_amd", "csrc", "gemm_plan.h")
 
@@ -23,6 +25,13 @@ int whole_tile(int M, int N, int K, int* o) {
     o[0] = t.bm; o[1] = t.bn;
     return 0;
 }
+int qkv(int M, int qd, int kd, int d, int K, int* o) {
+    const SplitKPlan p = qkv_plan(M, qd, kd, K);
+    o[0] = p.bm; o[1] = p.bn;
+    return qkv_path(M, qd, kd, d, K);
+}
+int gated_columns(int M, int F, int K) { return skinny_gated_columns(skinny_plan(M, 2 * F, K), M, F, K); }
+int direct(int N) { return skinny_direct(N, false); }
 int few_rows(int M, int N, int K, int* o) {
     const SkinnyPlan p = skinny_plan(M, N, K);
     o[0] = skinny_rows(M); o[1] = p.cols;
@@ -73,3 +82,50 @@ def test_slices_fit_the_scratch_that_callers_provide(plan):
 def test_slices_of_few_rows_are_priced(plan, M, N, K):
     """Small outputs over a short k: 9 us in 16 slices, 7.5 in 4 to 8."""
     assert plan.few_rows(M, N, K, (C.c_int * 2)()) <= 8
+
+
+def sliced(plan, M, N, K):
+    """The tile of a launch of one matrix or a pair that is cut over k, or nothing."""
+    if M <= 256:
+        o = (C.c_int * 2)()
+        plan.few_rows(M, N, K, o)
+        return {(o[0], o[1])}
+    t = picked(plan, M, N, K)
+    return {t[:2]} if t[2] > 1 else set()
+
+
+def sliced_three(plan, M, qd, kd, d, K):
+    o = (C.c_int * 2)()
+    return {(o[0], o[1])} if plan.qkv(M, qd, kd, d, K, o) == 3 else set()
+
+
+def gated(plan, M, F, K):
+    return {((M + 31) // 32 * 32, plan.gated_columns(M, F, K))}
+
+
+def test_gpu_tests_reach_every_sliced_tile(plan):
+    """Whatever tile a cut can take, alone, over a pair or over K, Q and V, and whatever form gate and up of few rows
+    can take, a GPU test launches."""
+    one = set().union(*(sliced(plan, *s) for s in gpu.SPLIT_K))
+    assert all(sliced(plan, *s) for s in gpu.SPLIT_K)
+    few = set().union(*(sliced(plan, M, *nk) for M in gpu.FEW_ROWS for nk in gpu.FEW_ROWS_NK if not plan.direct(nk[0])))
+    pair = set().union(*(sliced(plan, keep, (Hq + Hkv) * 128, D) for D, Hq, Hkv, keep in gpu.PAIRS))
+    three, gate_up = set(), set()
+    for M, D, Hq, Hkv, d, F in gpu.SIDE_BY_SIDE:
+        three |= sliced_three(plan, M, Hq * d, Hkv * d, d, D)
+        gate_up |= gated(plan, M, F, D) if M <= 256 else set()
+    for M in range(257, 1025, 9):
+        for K in (256, 512, 768, 1024, 2048, 2304, 3584, 4096, 5120, 5888, 8192, 11008, 14336, 28672):
+            for N in range(256, 12800, 256):
+                assert sliced(plan, M, N, K) <= one, (M, N, K)
+                if N % 512 == 0:
+                    assert sliced(plan, M, N, K) <= pair, (M, N, K)
+            for kd in (256, 384, 512, 640, 1024, 1408, 2048, 4096):
+                for group in (1, 2, 4, 7, 8):
+                    assert sliced_three(plan, M, kd * group, kd, 128, K) <= three, (M, kd * group, kd, K)
+    for M in range(1, 257, 15):
+        for K in (128, 256, 512, 768, 1024, 2048, 3584, 4096, 5120, 8192, 11008, 28672):
+            for N in range(64, 16384, 320):
+                assert plan.direct(N) or sliced(plan, M, N, K) <= few, (M, N, K)
+            for F in range(128, 30000, 1280):
+                assert gated(plan, M, F, K) <= gate_up, (M, F, K)

@@ -157,11 +157,11 @@ int vitcop_prefill_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v,
  *   fixed group of columns; the P parts added in index order give
  *   sum_n y[m,n]^2, i.e. the squared K-norm of Eq. 4 without re-reading K.
  *   ws: NULL, or device scratch of ws_bytes >= vitcop_project_workspace_bytes(M,N,K)
- *   (16-byte aligned, contents undefined afterwards).  With few rows (M <= 256: the
- *   sequence after pruning) the weights are nearly all of the traffic; given the
- *   scratch, such a call streams W once through a split-K kernel whose fp32 partials
- *   live there and are added in a fixed order.  workspace_bytes is 0 where that path
- *   does not apply; without scratch, or with too little, the call uses the big tiles.
+ *   (16-byte aligned, contents undefined afterwards).  With few rows (M <= 1024: the
+ *   sequence after pruning) whole tiles leave most of the chip idle; given the
+ *   scratch, such a call may cut k into slices whose fp32 partials live there and
+ *   are added in a fixed order.  workspace_bytes is 0 where that is not considered;
+ *   without scratch, or with too little, the call uses whole tiles.
  * K % 32 == 0, N % 16 == 0, strides multiples of 8; each operand below 2^31 elements.
  */
 int vitcop_project_sumsq_parts(int N);

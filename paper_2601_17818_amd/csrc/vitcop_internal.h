@@ -57,10 +57,10 @@ int launch_gemm(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t
 int launch_gemm_pair(const uint16_t* x, int64_t x_stride, const uint16_t* w1, uint16_t* y1, int N1,
                      const uint16_t* w2, uint16_t* y2, int N2, int M, int K, hipStream_t s);
 
-// The same two calls with a scratch buffer: launches with few rows (M <= 256) then stream the weights
-// through a split-K kernel (gemm_skinny.hip) whose fp32 partials live in `ws`; with ws == nullptr, too
-// small a buffer or any other shape they are the calls above.  gemm_workspace_bytes is what the
-// split-K path of one launch (N = N1 + N2 for a pair) needs, 0 if it does not apply.
+// The same two calls with a scratch buffer: launches of at most 256 rows (gemm_skinny.hip) and, where that is
+// estimated faster, of at most 1024 then go out as k-slices whose fp32 partials live in `ws`; with ws == nullptr, too
+// small a buffer or any other shape they are the calls above.  gemm_workspace_bytes is what a cut of one launch
+// (N = N1 + N2 for a pair) may need, also where whole tiles are taken in the end; 0 where none is considered.
 size_t gemm_workspace_bytes(int M, int N, int K);
 int launch_gemm_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint16_t* y, int64_t y_stride,
                    const uint16_t* res, int64_t res_stride, int M, int N, int K, float* sumsq_parts, void* ws,

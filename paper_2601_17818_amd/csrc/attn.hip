@@ -34,7 +34,7 @@ template <int D>
 __global__ __launch_bounds__(AT_THREADS) void attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, uint16_t* __restrict__ out, float* __restrict__ lse,
-    int N, int Hq, int Hkv, float scale_log2e, int causal) {
+    int N, int Hq, int Hkv, float scale_log2e, int causal, int64_t kv_batch) {
     static_assert(D == 64 || D == 128, "head dimension");
     constexpr int KLD = D + 8;            // bf16 per K row in LDS (odd multiple of 16 B: conflict-free reads)
     constexpr int DC = D / 16;            // 16-channel MFMA steps of Q K^T
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(AT_THREADS) void attn_kernel(
     const int kend = causal ? min(N, q0 + AT_BM) : N;
     const int ntiles = (kend + AT_BN - 1) / AT_BN;
     const int wave_kend = causal ? min(N, wq0 + 32) : N;
-    const uint16_t* kbase = k + (int64_t)b * N * kv_rs + hk * D;
-    const uint16_t* vbase = v + (int64_t)b * N * kv_rs + hk * D;
+    const uint16_t* kbase = k + b * kv_batch + hk * D;
+    const uint16_t* vbase = v + b * kv_batch + hk * D;
 
     const int vkq = tid & 15, vc = tid >> 4;      // V: key quad, channel chunk (threads with vc >= KCH idle)
     const bool v_active = vc < KCH;
@@ -357,7 +357,7 @@ template <int D, bool CAUSAL, int U>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, uint16_t* __restrict__ out, float* __restrict__ lse,
-    int N, int Hq, int Hkv, float scale_log2e, int n_qb, int n_heads, int group) {
+    int N, int Hq, int Hkv, float scale_log2e, int n_qb, int n_heads, int group, int64_t kv_batch) {
     extern __shared__ __attribute__((aligned(1024))) char aw_lds[];
     static_assert(U == 1 || (U == 2 && D == 128), "query blocks per wavefront");
     constexpr int BM = 128 * U, QW = 32 * U;       // queries per workgroup and per wavefront
@@ -440,8 +440,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
     const int my_tiles = wq0 + QW > 0 ? (wave_kend + AW_BN - 1) / AW_BN : 0;
     // tiles whose 64 keys are visible to all 64 queries and lie inside the sequence: no masking
     const int full_tiles = min(CAUSAL ? max(wq0, 0) / AW_BN : N / AW_BN, min(N / AW_BN, my_tiles));
-    const char* kbase = reinterpret_cast<const char*>(k + (int64_t)b * N * kv_rs + hk * D);
-    const char* vbase = reinterpret_cast<const char*>(v + (int64_t)b * N * kv_rs + hk * D);
+    const char* kbase = reinterpret_cast<const char*>(k + b * kv_batch + hk * D);
+    const char* vbase = reinterpret_cast<const char*>(v + b * kv_batch + hk * D);
 
     // Direct-to-LDS loads.  A tile (64 keys) is GROUPS groups of 1 KiB for K and as many for V: group g holds rows
     // {g, g+GROUPS, ..}; a wavefront fetches GPW groups of both, one buffer load of 16 bytes
@@ -783,7 +783,7 @@ constexpr int AW_U2_MIN_WGS = 256;  // if that still leaves more workgroups than
 
 template <int D, bool CAUSAL, int U>
 static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
-                            int B, int N, int Hq, int Hkv, float sl2, hipStream_t s) {
+                            int B, int N, int Hq, int Hkv, float sl2, int64_t kv_batch, hipStream_t s) {
     static std::atomic<bool> attr_set{false};   // set once; a second thread repeating the call is harmless
     constexpr int lds = AW_STAGES<D> * AW_STAGE<D>;
     if (!attr_set.load(std::memory_order_acquire)) {
@@ -800,14 +800,15 @@ static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t
     // in L2, but enough to fill the 256 CUs twice over (measured: 32 from N = 2048 up)
     const int group = std::max(32, (512 / n_qb + 7) / 8 * 8);
     hipLaunchKernelGGL((attn_wide_kernel<D, CAUSAL, U>), dim3((unsigned)(n_heads * n_qb)), dim3(256), lds, s, q, k, v,
-                       out, lse, N, Hq, Hkv, sl2, n_qb, (int)n_heads, group);
+                       out, lse, N, Hq, Hkv, sl2, n_qb, (int)n_heads, group, kv_batch);
     return launch_status("attn_wide");
 }
 
 int launch_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out,
                 float* lse, int B, int N, int Hq, int Hkv, int d, float scale, int causal,
-                hipStream_t s) {
+                hipStream_t s, int64_t kv_batch) {
     if (B == 0 || N == 0) return VITCOP_OK;
+    if (kv_batch == 0) kv_batch = (int64_t)N * Hkv * d;
     if (N > (1 << 22)) return fail(VITCOP_EUNSUPPORTED, "attention: N=%d above 2^22", N);   // grid.z limit
     const float sl2 = scale * 1.4426950408889634f;
     // the wide kernel addresses K and V of one (sample, KV head) with 32-bit byte offsets, and its workgroups by one grid
@@ -817,22 +818,22 @@ int launch_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_
     if (!wide_ok) {
         dim3 grid(Hq, B, (N + AT_BM - 1) / AT_BM);
         hipLaunchKernelGGL(d == 64 ? attn_kernel<64> : attn_kernel<128>, grid, dim3(AT_THREADS), 0, s, q, k, v, out, lse,
-                           N, Hq, Hkv, sl2, causal);
+                           N, Hq, Hkv, sl2, causal, kv_batch);
         return launch_status("attn");
     }
     if (d == 64)
-        return causal ? launch_attn_wide<64, true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
-                      : launch_attn_wide<64, false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
+        return causal ? launch_attn_wide<64, true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s)
+                      : launch_attn_wide<64, false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s);
     // Two query blocks per wavefront halve the LDS reads per MFMA, which is what long sequences need; one
     // block halves the chain of MFMAs a wavefront runs per key tile and doubles the workgroups, which is
     // what the lengths that survive pruning need (a few hundred tokens: one to six key tiles per workgroup,
     // latency and not throughput): below 512 tokens, or while 256-query workgroups would not fill the CUs.
     const long wgs2 = (long)Hq * B * ((N + AW_BM - 1) / AW_BM);
     if (N >= AW_U2_MIN_N && wgs2 > AW_U2_MIN_WGS)
-        return causal ? launch_attn_wide<128, true, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
-                      : launch_attn_wide<128, false, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
-    return causal ? launch_attn_wide<128, true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s)
-                  : launch_attn_wide<128, false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, s);
+        return causal ? launch_attn_wide<128, true, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s)
+                      : launch_attn_wide<128, false, 2>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s);
+    return causal ? launch_attn_wide<128, true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s)
+                  : launch_attn_wide<128, false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s);
 }
 
 }  // namespace vitcop

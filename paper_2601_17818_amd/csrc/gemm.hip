@@ -339,72 +339,54 @@ size_t gemm_qkv_workspace_bytes(int M, int Hq, int Hkv, int d, int K) {
 }
 
 int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wk, const uint16_t* wq,
-                            const uint16_t* wv, uint16_t* k, uint16_t* q, uint16_t* v, int Hq, int Hkv, int d,
+                            const uint16_t* wv, uint16_t* k_tmp, uint16_t* q, uint16_t* v_tmp, int Hq, int Hkv, int d,
                             const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
-                            hipStream_t s) {
+                            uint16_t* k_dst, uint16_t* v_dst, int T, int64_t kv_batch, hipStream_t s,
+                            const int32_t* rows) {
     if (M == 0) return VITCOP_OK;
     const int qd = Hq * d, kd = Hkv * d;
     const uint16_t* const w3[3] = {wk, wq, wv};
-    uint16_t* const y3[3] = {k, q, v};
+    // (rows that lie side by side: the projections write them where they belong, and k is turned in place)
+    const bool dense = !rows && (M <= T || kv_batch == (int64_t)T * kd);
+    uint16_t* const y3[3] = {dense ? k_dst : k_tmp, q, dense ? v_dst : v_tmp};
     const int n3[3] = {kd, qd, kd};
     const int path = ws ? qkv_path(M, qd, kd, d, K) : 0;
+    QkvParts P{};
     if (path == 1 && ws_bytes >= gemm_skinny_workspace_bytes(M, kd + qd + kd, K)) {
         SkParts parts{};
-        int rc = launch_gemm_skinny3(x, x_stride, w3, y3, n3, M, K, ws, s, &parts);
+        const int rc = launch_gemm_skinny3(x, x_stride, w3, y3, n3, M, K, ws, s, &parts);
         if (rc) return rc;
-        if (parts.part == nullptr) return launch_rope(q, k, positions, M, Hq, Hkv, d, theta, s);   // written directly
-        const QkvParts P{{parts, parts, parts}, {0, kd, kd + qd}};
-        return launch_qkv_finish(P, k, q, v, Hq, Hkv, d, positions, theta, s);
-    }
-    if (path == 3) {
+        // (no partial sums: the outputs are written already)
+        P = {{parts, parts, parts}, {0, kd, kd + qd}};
+    } else {
         const int N = qd + 2 * kd;
-        const SplitKPlan p = qkv_plan(M, qd, kd, K, (int)std::min(ws_bytes / ((size_t)M * N * 4), (size_t)16));
+        SplitKPlan p;
+        if (path == 3) p = qkv_plan(M, qd, kd, K, (int)std::min(ws_bytes / ((size_t)M * N * 4), (size_t)16));
+        const size_t need_k = splitk_workspace_bytes(M, kd, K), need_qv = splitk_workspace_bytes(M, qd + kd, K);
         if (p.splits) {
             const SkParts parts{static_cast<float*>(ws), p.splits, N, M};
-            const SkMats mats{{wk, wq, wv}, {k, q, v}, {kd, qd, kd}, {kd, kd + qd, N}};
+            const SkMats mats{{wk, wq, wv}, {y3[0], q, y3[2]}, {kd, qd, kd}, {kd, kd + qd, N}};
             const int rc = launch_slices(p, x, x_stride, mats, M, N, K, static_cast<float*>(ws), s);
             if (rc) return rc;
-            const QkvParts P{{parts, parts, parts}, {0, kd, kd + qd}};
-            return launch_qkv_finish(P, k, q, v, Hq, Hkv, d, positions, theta, s);
+            P = {{parts, parts, parts}, {0, kd, kd + qd}};
+        } else if (path == 2 && ws_bytes >= need_k + need_qv) {
+            SkParts pk{}, pqv{};
+            int rc = launch_gemm_splitk(splitk_plan(M, kd, K), x, x_stride, wk, y3[0], kd, nullptr, 0, M, kd, K, nullptr,
+                                        ws, s, nullptr, 0.f, nullptr, 0, nullptr, nullptr, 0, &pk);
+            if (rc) return rc;
+            rc = launch_gemm_splitk(splitk_plan(M, qd + kd, K), x, x_stride, wq, q, qd, nullptr, 0, M, qd + kd, K, nullptr,
+                                    static_cast<char*>(ws) + need_k, s, nullptr, 0.f, nullptr, 0, wv, y3[2], qd, &pqv);
+            if (rc) return rc;
+            P = {{pk, pqv, pqv}, {0, 0, qd}};
+        } else {
+            const int rc = launch_gemm_triple_ws(x, x_stride, w3, y3, n3, M, K, ws, ws_bytes, s);
+            if (rc) return rc;
         }
     }
-    const size_t need_k = splitk_workspace_bytes(M, kd, K), need_qv = splitk_workspace_bytes(M, qd + kd, K);
-    if (path == 2 && ws_bytes >= need_k + need_qv) {
-        SkParts pk{}, pqv{};
-        int rc = launch_gemm_splitk(splitk_plan(M, kd, K), x, x_stride, wk, k, kd, nullptr, 0, M, kd, K, nullptr, ws, s,
-                                    nullptr, 0.f, nullptr, 0, nullptr, nullptr, 0, &pk);
-        if (rc) return rc;
-        rc = launch_gemm_splitk(splitk_plan(M, qd + kd, K), x, x_stride, wq, q, qd, nullptr, 0, M, qd + kd, K, nullptr,
-                                static_cast<char*>(ws) + need_k, s, nullptr, 0.f, nullptr, 0, wv, v, qd, &pqv);
-        if (rc) return rc;
-        const QkvParts P{{pk, pqv, pqv}, {0, 0, qd}};
-        return launch_qkv_finish(P, k, q, v, Hq, Hkv, d, positions, theta, s);
-    }
-    const int rc = launch_gemm_triple_ws(x, x_stride, w3, y3, n3, M, K, ws, ws_bytes, s);
-    if (rc) return rc;
-    return launch_rope(q, k, positions, M, Hq, Hkv, d, theta, s);
-}
-
-int launch_gemm_qkv_append_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wk, const uint16_t* wq,
-                              const uint16_t* wv, uint16_t* k_new, uint16_t* q, uint16_t* v_new, int Hq, int Hkv, int d,
-                              const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
-                              uint16_t* k_dst, uint16_t* v_dst, int64_t kv_batch, const int32_t* rows, hipStream_t s) {
-    if (M == 0) return VITCOP_OK;
-    const int qd = Hq * d, kd = Hkv * d;
-    const uint16_t* const w3[3] = {wk, wq, wv};
-    uint16_t* const y3[3] = {k_new, q, v_new};
-    const int n3[3] = {kd, qd, kd};
-    SkParts parts{};
-    int rc;
-    if (ws && qkv_path(M, qd, kd, d, K) == 1 && ws_bytes >= gemm_skinny_workspace_bytes(M, kd + qd + kd, K))
-        rc = launch_gemm_skinny3(x, x_stride, w3, y3, n3, M, K, ws, s, &parts);
-    else
-        rc = launch_gemm_triple_ws(x, x_stride, w3, y3, n3, M, K, ws, ws_bytes, s);
-    if (rc) return rc;
-    if (parts.part != nullptr)
-        return launch_qkv_finish(QkvParts{{parts, parts, parts}, {0, kd, kd + qd}}, k_dst, q, v_dst, Hq, Hkv, d, positions,
-                                 theta, s, kv_batch, rows);
-    return launch_rope_append(q, k_new, v_new, positions, M, Hq, Hkv, d, theta, k_dst, v_dst, kv_batch, s, rows);
+    if (P.parts[0].part != nullptr)
+        return launch_qkv_finish(P, k_dst, q, v_dst, Hq, Hkv, d, positions, theta, T, kv_batch, s, rows);
+    if (dense) return launch_rope(q, k_dst, positions, M, Hq, Hkv, d, theta, s);
+    return launch_rope_append(q, k_tmp, v_tmp, positions, M, Hq, Hkv, d, theta, k_dst, v_dst, T, kv_batch, s, rows);
 }
 
 // dist[b][i,j] = ||f_i - f_j||_2 in fp32 between the rows of each of `batch` bf16 matrices

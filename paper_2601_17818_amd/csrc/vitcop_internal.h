@@ -44,9 +44,10 @@ constexpr size_t FILTER_STATIC_SCRATCH_BYTES = VITCOP_FILTER_STATIC_MAX_BYTES;
 int filter_static_scratch(float** out);
 
 // ---- attention (attn.hip) -------------------------------------------------
+// kv_batch: elements between two samples' K and V (0: dense, N * Hkv * d)
 int launch_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out,
                 float* lse, int B, int N, int Hq, int Hkv, int d, float scale, int causal,
-                hipStream_t s);
+                hipStream_t s, int64_t kv_batch = 0);
 
 // ---- projection GEMM (gemm.hip) -------------------------------------------
 int gemm_sumsq_parts(int N);
@@ -84,21 +85,18 @@ int launch_gemm_gated_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wg
 int launch_gemm_pair_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w1, uint16_t* y1, int N1,
                         const uint16_t* w2, uint16_t* y2, int N2, int M, int K, void* ws, size_t ws_bytes,
                         hipStream_t s);
-// k, q, v = x Wk^T, x Wq^T, x Wv^T (dense [M, Hkv d], [M, Hq d], [M, Hkv d]) with the rotary embedding of q
-// and k at positions[m]: where the projections leave partial sums (few rows, or split-K of K and of the Q/V
-// pair) one launch adds them up and turns q and k; otherwise launch_gemm_triple_ws and rope_kernel.
-// launch_gemm_qkv_append_ws: the same for the M new tokens of a decoding step, whose k and v go to rows of caches
-// (k_dst + m * kv_batch, plus rows[m] cache rows if rows is given); k_new and v_new are scratch [M, Hkv d].
+// q = x Wq^T (dense [M, Hq d]), k = x Wk^T and v = x Wv^T with the rotary embedding of q and k at positions[m]: where
+// the projections leave partial sums (few rows, or split-K of K and of the Q/V pair) one launch adds them up and
+// turns q and k; otherwise launch_gemm_triple_ws and rope_kernel.  Row m of k and v is row m % T of sample m / T, whose
+// rows start at k_dst and v_dst + (m / T) * kv_batch (plus rows[m] rows, if given: the new tokens of a decoding step,
+// T = 1, go to their caches' next rows).  k_tmp and v_tmp: scratch [M, Hkv d].
 // gemm_qkv_workspace_bytes: what ws must hold for every path this may take at M rows.
 size_t gemm_qkv_workspace_bytes(int M, int Hq, int Hkv, int d, int K);
 int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wk, const uint16_t* wq,
-                            const uint16_t* wv, uint16_t* k, uint16_t* q, uint16_t* v, int Hq, int Hkv, int d,
+                            const uint16_t* wv, uint16_t* k_tmp, uint16_t* q, uint16_t* v_tmp, int Hq, int Hkv, int d,
                             const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
-                            hipStream_t s);
-int launch_gemm_qkv_append_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wk, const uint16_t* wq,
-                              const uint16_t* wv, uint16_t* k_new, uint16_t* q, uint16_t* v_new, int Hq, int Hkv, int d,
-                              const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
-                              uint16_t* k_dst, uint16_t* v_dst, int64_t kv_batch, const int32_t* rows, hipStream_t s);
+                            uint16_t* k_dst, uint16_t* v_dst, int T, int64_t kv_batch, hipStream_t s,
+                            const int32_t* rows = nullptr);
 // Up to three weight matrices side by side (projections of the same input in one launch): matrix i
 // covers the columns [n_end[i-1], n_end[i]) of the launch (boundaries multiples of 128; unused
 // entries repeat N) and writes its own output with its own row stride.
@@ -132,10 +130,10 @@ struct QkvParts {
     SkParts parts[3];
     int col0[3];
 };
-// k, q, v [M, Hkv d], [M, Hq d], [M, Hkv d] (dense) = the partial sums added in slice order and rounded to
+// q [M, Hq d], k and v (rows as for launch_gemm_qkv_rope_ws) = the partial sums added in slice order and rounded to
 // bf16, q and k then turned by the rotary embedding at positions[m] (rope_kernel's arithmetic).
 int launch_qkv_finish(const QkvParts& P, uint16_t* k, uint16_t* q, uint16_t* v, int Hq, int Hkv, int d,
-                      const int32_t* positions, float theta, hipStream_t s, int64_t kv_stride = 0 /* dense */,
+                      const int32_t* positions, float theta, int T, int64_t kv_stride, hipStream_t s,
                       const int32_t* kv_rows = nullptr);
 
 int launch_partial_reduce(const SkParts& parts, int N, const SkMats& mats, const uint16_t* res, int64_t res_stride,
@@ -209,11 +207,11 @@ int launch_rmsnorm(const uint16_t* x, int64_t x_stride, const uint16_t* w, float
 // in place; q [n_tokens,Hq,d] and k [n_tokens,Hkv,d] (either may be null), positions [n_tokens]
 int launch_rope(uint16_t* q, uint16_t* k, const int32_t* positions, int64_t n_tokens, int Hq, int Hkv, int d,
                 float theta, hipStream_t s);
-// one new token per sample: q embedded in place, k embedded into k_dst + b * kv_batch, v copied to v_dst + b * kv_batch
-// (rows, nullable: sample b's row lies rows[b] cache rows further on)
-int launch_rope_append(uint16_t* q, const uint16_t* k, const uint16_t* v, const int32_t* positions, int n_tokens,
-                       int Hq, int Hkv, int d, float theta, uint16_t* k_dst, uint16_t* v_dst, int64_t kv_batch,
-                       hipStream_t s, const int32_t* rows = nullptr);
+// q embedded in place, k embedded on its way from k [n_tokens,Hkv,d] to k_dst, v (nullable) copied to v_dst: token m is
+// row m % T of sample m / T, whose rows start kv_batch elements after the sample before (rows, nullable: rows[m] further on)
+int launch_rope_append(uint16_t* q, const uint16_t* k, const uint16_t* v, const int32_t* positions, int64_t n_tokens,
+                       int Hq, int Hkv, int d, float theta, uint16_t* k_dst, uint16_t* v_dst, int64_t T,
+                       int64_t kv_batch, hipStream_t s, const int32_t* rows = nullptr);
 int launch_silu_mul(const uint16_t* gate, const uint16_t* up, uint16_t* out, int64_t n_elems, hipStream_t s);
 
 // ---- decoding step over the KV cache (decode.hip) ---------------------------

@@ -34,7 +34,9 @@ def test_rmsnorm(vc, M, D):
     within_bf16(host_bits(y), Dc.rmsnorm(x, w, 1e-5), "rmsnorm")
 
 
-@pytest.mark.parametrize("Hq,Hkv,d", [(4, 2, 128), (3, 3, 64), (28, 4, 128)])
+# (one, several and many workgroups of units a token; several tokens to a workgroup, the last one short; a head too long
+# for angles in LDS)
+@pytest.mark.parametrize("Hq,Hkv,d", [(4, 2, 128), (3, 3, 64), (28, 4, 128), (1, 1, 16), (5, 2, 48), (1, 1, 2080)])
 def test_rope(vc, Hq, Hkv, d):
     t = I.qkv_tensors(9100 + Hq, 2, 37, Hq, Hkv, d)
     pos = np.stack([np.sort(np.random.default_rng(b).choice(3000, 37, replace=False)) for b in range(2)]).astype(np.int32)
@@ -202,6 +204,42 @@ def test_layers_that_keep_all_tokens_finish_qkv_in_one_launch(vc, B, T, D, Hq, H
         got, want = O.bf16_to_f64(host_bits(caches[0][which])), O.bf16_to_f64(ref["caches"][0][which])
         assert np.all(np.abs(got - want) <= np.maximum(np.abs(want).max(axis=-1, keepdims=True), 1e-6) * 2.0 ** -7), what
     assert_stream_close(host_f64(plan.y), ref["y"], "two layers that keep all tokens")
+
+
+@pytest.mark.parametrize("B,T,D,Hq,Hkv,d", [
+    (1, 300, 1024, 2, 2, 128),     # one sample: every cache row lies where a dense tensor would have it
+    (3, 61, 512, 4, 4, 64),        # few rows: finished from partial sums, 48 units a row (five rows to a workgroup)
+    (3, 131, 1024, 4, 2, 128),     # k-slices or the plain sequence, then the rotary kernel on its way to the cache
+    (2, 600, 256, 3, 1, 64)])      # whole tiles; 16 rotary units and 8 chunks of V a token
+def test_caches_of_any_capacity_and_alignment_hold_the_same_rows(vc, B, T, D, Hq, Hkv, d):
+    # K and V of a layer go straight to rows [0, T') of every sample's cache, where the attention reads them: with a
+    # capacity of exactly T, with room to spare, and with caches that 16-byte stores do not reach (2-byte offset), the
+    # rows and the output are the same bits (the dense ones are checked against the oracle above), the rest untouched
+    F, vs, nv, keep = 256, 5, T - 20, (T - 20) // 3
+    h, layers = schedule_case(9800 + T, B, T, D, Hq, Hkv, d, F, vs, nv, 3)
+    pos = torch.from_numpy(np.stack([np.sort(np.random.default_rng(60 + b).choice(4 * T, T, replace=False))
+                                     for b in range(B)]).astype(np.int32)).cuda()
+    wd = [{k: dev(v) for k, v in w.items()} for w in layers]
+    lens = [T, T - nv + keep, T - nv + keep]
+
+    def run(cap, offset):
+        def cache():
+            flat = torch.full((B * cap * Hkv * d + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+            return flat[offset:offset + B * cap * Hkv * d].view(B, cap, Hkv, d)
+        caches = [(cache(), cache()) for _ in layers]
+        plan = vc.DecoderSchedulePlan(dev(h), pos, wd, Hq, Hkv, d, vs, nv, [(1, keep)], caches=caches)
+        plan.run()
+        torch.cuda.synchronize()
+        return plan.y.clone(), caches
+
+    y, dense = run(T, 0)
+    for cap, offset in ((T + 3, 0), (T + 3, 1)):
+        y2, caches = run(cap, offset)
+        assert torch.equal(y2, y)
+        for l, n in enumerate(lens):
+            for a, b in zip(caches[l], dense[l]):
+                assert torch.equal(a[:, :n], b[:, :n]), (cap, offset, l)
+                assert bool((a[:, n:] == 7.0).all()), (cap, offset, l)
 
 
 def full_case(seed, vs, n, tail, D, Hq, Hkv, d, F, n_layers, grid, regions):

@@ -87,8 +87,8 @@ size_t gemm_workspace_bytes(int M, int N, int K) {
 static int launch_slices(const SplitKPlan& p, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M, int N, int K,
                          float* part, hipStream_t s) {
 #define VITCOP_SPLITK(BM, BN)                                                                                          \
-    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART>(x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s, K, nullptr, \
-                                                      nullptr, part, N, p.splits, 0, 0, (int64_t)M * N)
+    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART>(x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s, K, part, N, \
+                                                      p.splits, 0, 0, (int64_t)M * N)
     switch (p.bm * 1024 + p.bn) {
         case 256 * 1024 + 256: VITCOP_SPLITK(256, 256);
         case 192 * 1024 + 256: VITCOP_SPLITK(192, 256);
@@ -389,25 +389,27 @@ int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t*
     return launch_rope_append(q, k_tmp, v_tmp, positions, M, Hq, Hkv, d, theta, k_dst, v_dst, T, kv_batch, s, rows);
 }
 
-// dist[b][i,j] = ||f_i - f_j||_2 in fp32 between the rows of each of `batch` bf16 matrices
-// f [n,K] (row stride and batch stride in elements), with their squared row norms sq given.
-// sq must be readable, and the rows of dist writable, up to the next multiple of 4 entries
-// (dist_stride % 4 == 0; the pad holds garbage).
-int launch_pairwise_dist(const uint16_t* f, int64_t row_stride, int64_t batch_stride, const float* sq,
-                         int64_t sq_batch, float* dist, int64_t dist_stride, int64_t dist_batch, int n, int K,
-                         int batch, hipStream_t s) {
+// Inner products between the rows of each of `batch` bf16 matrices f [n,K] (row stride and batch stride in elements), in
+// fp32: gram[b][i][j] + gram[b][j][i] = <f_i, f_j> for i != j, sq[b][i] + (sq + sq_half)[b][i] = <f_i, f_i>.  The rows of
+// gram must be writable up to the next multiple of 4 entries (gram_stride % 4 == 0).
+int launch_gram(const uint16_t* f, int64_t row_stride, int64_t batch_stride, float* sq, int64_t sq_batch, int64_t sq_half, float* gram,
+                int64_t gram_stride, int64_t gram_batch, int n, int K, int batch, hipStream_t s) {
     if (n == 0 || batch == 0) return VITCOP_OK;
-    // few tokens: smaller tiles, so that more CUs load, while all of them run at once, two to a CU (clustering
-    // and merging of 8 x 288 tokens x 4096 134 -> 117 us with 200 tiles of 64 x 64 for 72 of 128 x 128, of 4 x 600 122 -> 115
-    // with 400 for 100; but of 1 x 1856 137 -> 148 with 841 for 225)
-#define VITCOP_DIST(BT)                                                                                              \
-    return launch_gemm_cfg<BT, BT, 2, 2, GM_EPI_DIST>(f, row_stride, sk_mats(f, nullptr, 0, n), nullptr, 0, n, n, K, \
-                                                      nullptr, s, row_stride, sq, sq, dist, dist_stride, batch,      \
-                                                      batch_stride, sq_batch, dist_batch)
-    const long t64 = (n + 63) / 64;
-    if (t64 * t64 * batch <= 512) VITCOP_DIST(64);
-    VITCOP_DIST(128);
-#undef VITCOP_DIST
+    // A tile's CU loads its two operands at about 50 KB/us, which is what a launch of one round takes: half of the tiles
+    // are saved by symmetry and the others cut over k in two, onto the smaller tiles unless they need more rounds (8 x 288
+    // tokens x 4096: all 25 tiles of 64 x 64, after a launch for the sums of squares, 6.5 + 19.3 us; in halves 16 for both;
+    // 1 x 1856 x 3584: 225 tiles of 128 x 128 5.2 + 36.7, 240 halves 25.5).
+    auto cost = [&](int t) {
+        const long side = (n + t - 1) / t, wgs = side * (side + 1) * batch;
+        return (wgs + 255) / 256 * t;
+    };
+#define VITCOP_GRAM(BT)                                                                                            \
+    return launch_gemm_cfg<BT, BT, 2, 2, GM_EPI_GRAM>(f, row_stride, sk_mats(f, nullptr, 0, n), nullptr, 0, n, n, K, sq, \
+                                                      s, row_stride, gram, gram_stride, batch, batch_stride, sq_batch, \
+                                                      gram_batch, sq_half)
+    if (cost(64) <= cost(128)) VITCOP_GRAM(64);
+    VITCOP_GRAM(128);
+#undef VITCOP_GRAM
 }
 
 }  // namespace vitcop

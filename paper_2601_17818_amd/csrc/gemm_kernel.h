@@ -60,9 +60,10 @@ __device__ __forceinline__ int gm_swz(int row) { return (row >> 1) & 7; }
 // same input): SkMats says which columns belong to which and where each one's output goes.  A tile belongs to
 // one matrix (their boundaries are multiples of the tile width), except for the k-sliced tiles of at most 192
 // columns, which may hold the end of one and the start of the next (boundaries multiples of 32).
-// EPI selects the epilogue: GM_EPI_BF16 the projection described above; GM_EPI_DIST writes,
-// in fp32, the Euclidean distance between row m of x and row n of w from their inner product
-// and the two squared row norms: dist[m,n] = sqrt(max(0, xsq[m] + wsq[n] - 2 <x_m, w_n>)).
+// EPI selects the epilogue: GM_EPI_BF16 the projection described above; GM_EPI_GRAM the inner products between the
+// rows of one matrix per image (x and w are the same), in two k-slices: the products are symmetric, so the first half
+// of k is summed in the tiles above the diagonal and the second half in those below it, and dist[i][j] + dist[j][i]
+// is <x_i, x_j>; the two halves of the rows' sums of squares go to sumsq_parts[i] and sumsq_parts[sq_half + i].
 // GM_EPI_PART is split-K: a workgroup multiplies its slice's share of the k-steps and writes the
 // raw fp32 accumulators to dist[split][m][n] (row stride dist_stride, slices dist_batch apart) for a
 // reduction kernel to add up.
@@ -70,7 +71,7 @@ __device__ __forceinline__ int gm_swz(int row) { return (row >> 1) & 7; }
 // (gate), its last BN/2 the same rows of the second (up); N counts the columns of each; the epilogue rounds both to bf16 as the
 // two separate projections would, and stores y[m,n] = silu(gate[m,n]) * up[m,n] (WAVES_N == 2: the gate
 // columns of a tile belong to the wavefronts with wn = 0, the up columns to wn = 1).
-constexpr int GM_EPI_BF16 = 0, GM_EPI_DIST = 1, GM_EPI_PART = 2, GM_EPI_GATED = 3;
+constexpr int GM_EPI_BF16 = 0, GM_EPI_GRAM = 1, GM_EPI_PART = 2, GM_EPI_GATED = 3;
 
 // What bounds the big tiles is the issue of MFMAs and, behind it, power: 11776x4096x4096 takes 234 us on all-zero and
 // 278 us on random operands, and over both the matrix cores are busy 69 % of the launch's cycles (62 % before the
@@ -85,9 +86,8 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS>
 __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     const uint16_t* __restrict__ x, int64_t x_stride, SkMats mats, const uint16_t* __restrict__ res,
     int64_t res_stride, int M, int N, int K, float* __restrict__ sumsq_parts, int tiles_m,
-    int tiles_n, int group_m, int64_t w_stride, const float* __restrict__ xsq, const float* __restrict__ wsq,
-    float* __restrict__ dist, int64_t dist_stride, int64_t x_batch, int64_t sq_batch,
-    int64_t dist_batch) {
+    int tiles_n, int group_m, int64_t w_stride, float* __restrict__ dist, int64_t dist_stride, int64_t x_batch,
+    int64_t sq_batch, int64_t sq_half, int64_t dist_batch) {
 #if defined(__HIP_DEVICE_COMPILE__)
     static_assert(WAVES_M * WAVES_N == 4, "four wavefronts");
     constexpr int TM = BM / WAVES_M, TN = BN / WAVES_N;
@@ -104,30 +104,37 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     const int l16 = lane & 15, g4 = lane >> 4;
     const int wm = wv % WAVES_M, wn = wv / WAVES_M;
 
-    // Workgroup -> (z, tile); z is the k-slice (PART) or the image (DIST).  Consecutive workgroup ids go to
+    // Workgroup -> (z, tile); z is the k-slice (PART) or the image (GRAM).  Consecutive workgroup ids go to
     // different XCDs, so id % 8 picks the XCD and id / 8 the slot inside it; each XCD walks a contiguous range
     // of a grouped ordering (group_m tile rows by all tile columns, column-major inside the group), z outermost:
     // the tiles that share rows of W, and the slices that share a k-range of x, meet in one L2.
     int tile_m, tile_n, z;
+    [[maybe_unused]] bool below = false;         // GRAM: a tile of the second half of k
     {
-        const int nt = tiles_m * tiles_n;
+        const int nt = EPI == GM_EPI_GRAM ? tiles_m * (tiles_m + 1) : tiles_m * tiles_n;
         const int xcd = blockIdx.x % GM_XCDS;
         int lin = xcd * (gridDim.x / GM_XCDS) + min(xcd, (int)(gridDim.x % GM_XCDS)) + blockIdx.x / GM_XCDS;
         z = lin / nt;
         lin -= z * nt;
-        const int width = group_m * tiles_n;
-        const int grp = lin / width;
-        const int first = grp * group_m;
-        const int gsz = min(tiles_m - first, group_m);
-        const int in = lin - grp * width;
-        tile_m = first + in % gsz;
-        tile_n = in / gsz;
+        if constexpr (EPI == GM_EPI_GRAM) {      // a list of the tiles on and above the diagonal, then of those mirrored
+            below = lin >= nt / 2;
+            int a = below ? lin - nt / 2 : lin, b = 0;
+            while (a > b) a -= ++b;
+            tile_m = below ? b : a;
+            tile_n = below ? a : b;
+        } else {
+            const int width = group_m * tiles_n;
+            const int grp = lin / width;
+            const int first = grp * group_m;
+            const int gsz = min(tiles_m - first, group_m);
+            const int in = lin - grp * width;
+            tile_m = first + in % gsz;
+            tile_n = in / gsz;
+        }
     }
     if constexpr (EPI == GM_EPI_PART) dist += z * dist_batch;
-    if constexpr (EPI == GM_EPI_DIST) {      // x and w are the same feature matrix
+    if constexpr (EPI == GM_EPI_GRAM) {      // x and w are the same feature matrix
         x += z * x_batch;
-        xsq += z * sq_batch;
-        wsq += z * sq_batch;
         dist += z * dist_batch;
     }
     const int m0 = tile_m * BM;
@@ -139,7 +146,7 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     uint16_t* y = mats.y[0];
     int64_t y_stride = mats.y_stride[0];
     int next_row = BN;               // the first tile row of W that belongs to the next matrix
-    if constexpr (EPI == GM_EPI_DIST) {
+    if constexpr (EPI == GM_EPI_GRAM) {
         w = w_next = mats.w[0] + z * x_batch;
     } else if constexpr (EPI == GM_EPI_GATED) {
         next_row = BN / 2;
@@ -254,6 +261,16 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
         nk = (int)((int64_t)all * (z + 1) / slices) - k_lo;
         if (half_step >= 0) half_step -= k_lo;
     }
+    if constexpr (EPI == GM_EPI_GRAM) {      // the first half (K <= 64: all) or the second (K <= 64: nothing, which reads as zeros)
+        const int first_half = (nk + 1) / 2;
+        if (below) {
+            k_lo = first_half;
+            if (half_step >= 0) half_step -= k_lo;
+            nk -= first_half;
+        } else {
+            nk = first_half;
+        }
+    }
     // Few rows: every workgroup streams its own rows of W, a power of two apart as often as not, and in step they
     // all ask for the same few columns of it, i.e. for a part of the memory channels.  So long slices start one
     // k-step further on from tile to tile and wrap around (64 rows: 12288x4096 25.7 -> 22.6 us, gate/up 22016x4096
@@ -272,7 +289,23 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     auto k_past = [&](int t) __attribute__((always_inline)) {
         return k_at(t) == half_step && chunk >= 64 ? 0xFFFFFF00u : 0u;
     };
+    // GRAM, tiles on the diagonal: the sums of squares of the tile's rows, from the slab while it is there (16 or 32
+    // elements per thread and step, a sum for each pair: as many terms per sum as the half has steps, then pairwise).  The
+    // diagonal of the product itself, one chain of K / 64 MFMAs per element, made the densities a sixth less accurate.
+    constexpr int SQ_TPR = GM_THREADS / BM > 0 ? GM_THREADS / BM : 1, SQ_CHUNKS = EPI == GM_EPI_GRAM ? 8 / SQ_TPR : 1;
+    [[maybe_unused]] float row_sq[SQ_CHUNKS][4];
+    if constexpr (EPI == GM_EPI_GRAM)
+#pragma unroll
+        for (int c = 0; c < SQ_CHUNKS; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) row_sq[c][e] = 0.f;
     auto step = [&](int t, int slab_off, int next_off, int prev_off) __attribute__((always_inline)) {
+        [[maybe_unused]] bf16x8 own_row[SQ_CHUNKS];          // (read ahead of the barrier that releases the slab)
+        if constexpr (EPI == GM_EPI_GRAM)
+#pragma unroll
+            for (int c = 0; c < SQ_CHUNKS; ++c)
+                own_row[c] = *reinterpret_cast<const bf16x8*>(gemm_lds + slab_off + tid / SQ_TPR * ROWB +
+                                                              (((tid % SQ_TPR * SQ_CHUNKS + c) ^ gm_swz(tid / SQ_TPR)) << 4));
         const unsigned px = k_off(t - 1 + NS, rec_x), pw = k_off(t - 1 + NS, rec_w);
         const unsigned cx = k_off(t + NS, rec_x), cw = k_off(t + NS, rec_w);
         const unsigned p_past = k_past(t - 1 + NS), c_past = k_past(t + NS);
@@ -314,6 +347,18 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
             }
             __builtin_amdgcn_sched_barrier(0);
         });
+        if constexpr (EPI == GM_EPI_GRAM)
+            if (tile_m == tile_n)
+#pragma unroll
+                for (int c = 0; c < SQ_CHUNKS; ++c) {
+                    const u32x4 word = __builtin_bit_cast(u32x4, own_row[c]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {        // two squares per instruction
+                        const uint32_t w32 = word[e];    // (a copy: a bit cast of the vector's element takes the first one)
+                        const bf16x2 two = __builtin_bit_cast(bf16x2, w32);
+                        row_sq[c][e] = __builtin_amdgcn_fdot2_f32_bf16(two, two, row_sq[c][e], false);
+                    }
+                }
     };
     static_for<NS>([&](auto i) __attribute__((always_inline)) {
         static_for<decltype(i)::value == NS - 1 ? FIRST : NL>([&](auto q) __attribute__((always_inline)) {
@@ -355,26 +400,39 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
         }
         return;
     }
-    if constexpr (EPI == GM_EPI_DIST) {
+    if constexpr (EPI == GM_EPI_GRAM) {
 #pragma unroll
         for (int j = 0; j < MI; ++j) {
             const int m = m0 + wm * TM + j * 16 + l16;
             if (m >= M) continue;
-            const float sm = xsq[m];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int n = n0 + wn * TN + i * 16 + 4 * g4;
-                if (n >= N) continue;
-                // wsq and the rows of dist are padded to a multiple of 4 entries, so the run
-                // of 4 may be read and written whole even when N cuts it
-                const float4 sn = *reinterpret_cast<const float4*>(wsq + n);
-                float4 o;
-                o.x = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][0], sm + sn.x)));
-                o.y = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][1], sm + sn.y)));
-                o.z = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][2], sm + sn.z)));
-                o.w = __builtin_sqrtf(fmaxf(0.f, fmaf(-2.f, acc[i][j][3], sm + sn.w)));
-                *reinterpret_cast<float4*>(dist + (int64_t)m * dist_stride + n) = o;
+                float* out = dist + (int64_t)m * dist_stride + n;
+                // a run of 4 may end in the row's pad (rows are padded to a multiple of 4)
+                if (tile_m != tile_n) {
+                    if (n < N) *reinterpret_cast<f32x4*>(out) = acc[i][j];
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (n + r < N && (below ? n + r < m : n + r > m)) out[r] = acc[i][j][r];
+                }
             }
+        }
+        if (tile_m == tile_n) {
+            float ss = 0.f;
+#pragma unroll
+            for (int e = 4; e > 1; e >>= 1)              // pairwise
+#pragma unroll
+                for (int c = 0; c < SQ_CHUNKS; ++c)
+#pragma unroll
+                    for (int u = 0; u < e / 2; ++u) row_sq[c][u] += row_sq[c][u + e / 2];
+#pragma unroll
+            for (int c = 0; c < SQ_CHUNKS; ++c) ss += row_sq[c][0];
+#pragma unroll
+            for (int o = 1; o < SQ_TPR; o <<= 1) ss += __shfl_xor(ss, o, 64);
+            const int m = m0 + tid / SQ_TPR;
+            if (tid % SQ_TPR == 0 && m < M) sumsq_parts[(below ? sq_half : 0) + z * sq_batch + m] = ss;
         }
         return;
     }
@@ -480,9 +538,8 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128))>
 static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
                            int64_t res_stride, int M, int N, int K, float* sumsq_parts,
-                           hipStream_t s, int64_t w_stride = 0, const float* xsq = nullptr,
-                           const float* wsq = nullptr, float* dist = nullptr, int64_t dist_stride = 0,
-                           int batch = 1, int64_t x_batch = 0, int64_t sq_batch = 0, int64_t dist_batch = 0) {
+                           hipStream_t s, int64_t w_stride = 0, float* dist = nullptr, int64_t dist_stride = 0,
+                           int batch = 1, int64_t x_batch = 0, int64_t sq_batch = 0, int64_t dist_batch = 0, int64_t sq_half = 0) {
     if (w_stride == 0) w_stride = K;
     auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, NS>;
     constexpr size_t lds = gemm_lds_bytes<BM, BN, WAVES_M, WAVES_N, NS>();
@@ -500,8 +557,9 @@ static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const SkMats& ma
     // tile rows per group: a patch of about 32 tiles (one XCD's worth of workgroups) near square
     int group_m = 1;
     while (group_m * 2 <= tiles_m && group_m * group_m * 2 <= 32) group_m *= 2;
-    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * batch), dim3(GM_THREADS), lds, s, x, x_stride, mats, res,
-                       res_stride, M, N, K, sumsq_parts, tiles_m, tiles_n, group_m, w_stride, xsq, wsq, dist, dist_stride, x_batch, sq_batch, dist_batch);
+    const int tiles = EPI == GM_EPI_GRAM ? tiles_m * (tiles_m + 1) : tiles_m * tiles_n;
+    hipLaunchKernelGGL(kern, dim3(tiles * batch), dim3(GM_THREADS), lds, s, x, x_stride, mats, res,
+                       res_stride, M, N, K, sumsq_parts, tiles_m, tiles_n, group_m, w_stride, dist, dist_stride, x_batch, sq_batch, sq_half, dist_batch);
     return launch_status("gemm");
 }
 

@@ -316,8 +316,8 @@ template <int BM>
 static int launch_skinny_parts(int cols, int slices, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M,
                                int N, int K, float* part, hipStream_t s) {
 #define VITCOP_SKINNY(BN)                                                                                            \
-    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART>(x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s, K, nullptr, \
-                                                      nullptr, part, N, slices, 0, 0, (int64_t)M * N)
+    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART>(x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s, K, part, N, \
+                                                      slices, 0, 0, (int64_t)M * N)
     if (cols == 64) VITCOP_SKINNY(64);
     if (cols == 96) VITCOP_SKINNY(96);
     VITCOP_SKINNY(128);

@@ -180,12 +180,11 @@ int launch_gemm_skinny(const uint16_t* x, int64_t x_stride, const uint16_t* w, u
                        const uint16_t* ln_w = nullptr, float eps = 0.f, uint16_t* norm_out = nullptr,
                        int64_t norm_stride = 0);
 
-// dist[b][i,j] = ||f_i - f_j||_2 (fp32) between the rows of each of `batch` matrices, from MFMA
-// inner products and given squared row norms; sq readable and dist rows writable up to the next
-// multiple of 4 entries, dist_stride % 4 == 0
-int launch_pairwise_dist(const uint16_t* f, int64_t row_stride, int64_t batch_stride, const float* sq,
-                         int64_t sq_batch, float* dist, int64_t dist_stride, int64_t dist_batch, int n, int K,
-                         int batch, hipStream_t s);
+// gram[b][i][j] + gram[b][j][i] = <f_i, f_j> (fp32, i != j) between the rows of each of `batch` matrices, from MFMA, and
+// sq[b][i] + (sq + sq_half)[b][i] = <f_i, f_i>; rows of gram writable up to the next multiple of 4 entries,
+// gram_stride % 4 == 0
+int launch_gram(const uint16_t* f, int64_t row_stride, int64_t batch_stride, float* sq, int64_t sq_batch, int64_t sq_half,
+                float* gram, int64_t gram_stride, int64_t gram_batch, int n, int K, int batch, hipStream_t s);
 
 // ---- Visual Information Clustering (vic.hip) --------------------------------
 size_t vic_workspace_bytes(int B, int n);

@@ -64,7 +64,10 @@ def check_image(c, g, b, n_centers, d_c=D_C, tau=TAU, dist_rows=None):
 
 
 @pytest.mark.parametrize("n,D,n_centers", [(1, 32, 1), (2, 32, 1), (5, 64, 2), (63, 96, 6), (64, 256, 7),
-                                           (65, 256, 7), (172, 1024, 17), (288, 1024, 29), (130, 4096, 13)])
+                                           (65, 256, 7), (172, 1024, 17), (288, 1024, 29), (130, 4096, 13),
+                                           # (k cut in two: one step of 64, one and a half, an odd number of them; the
+                                           # last rows of a workgroup and the columns past a round of 512)
+                                           (9, 96, 2), (128, 160, 12), (511, 32, 40), (513, 192, 40)])
 def test_matches_oracle_steps(vc, n, D, n_centers):
     c = I.vic_inputs(7000 + n, n, D, n_regions=min(12, max(1, n // 8)), noise=0.2)
     g = run(vc, [c], n_centers)

@@ -110,7 +110,8 @@ __global__ __launch_bounds__(256) void collab_emit_kernel(
     const int32_t* __restrict__ elite, const int32_t* __restrict__ assign,
     const int32_t* __restrict__ out_index, const int32_t* __restrict__ n_out, int n, int D,
     uint16_t* __restrict__ out_feats) {
-    const int r = blockIdx.x, b = blockIdx.y;
+    // merged rows, the last ones, take longest: they start first (8 x 288 tokens x 4096 9.6 -> 9.1 us, 1856 x 3584 14.5 -> 12.5)
+    const int r = n - 1 - blockIdx.x, b = blockIdx.y;
     if (r >= n_out[b]) return;
     feats += b * batch_stride;
     elite += (int64_t)b * n;
@@ -140,12 +141,20 @@ __global__ __launch_bounds__(256) void collab_emit_kernel(
     const float inv = 1.0f / (float)count;
     for (int c = tid * 8; c < D; c += 256 * 8) {
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int m = 0; m < count; ++m) {
-            const uint4 u = *reinterpret_cast<const uint4*>(feats + (int64_t)members[m] * row_stride + c);
-            acc[0] += bf16_lo(u.x); acc[1] += bf16_hi(u.x);
-            acc[2] += bf16_lo(u.y); acc[3] += bf16_hi(u.y);
-            acc[4] += bf16_lo(u.z); acc[5] += bf16_hi(u.z);
-            acc[6] += bf16_lo(u.w); acc[7] += bf16_hi(u.w);
+        for (int m0 = 0; m0 < count; m0 += 4) {               // four members' rows in flight
+            u32x4 row[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (m0 + e < count)
+                    row[e] = *reinterpret_cast<const u32x4*>(feats + (int64_t)members[m0 + e] * row_stride + c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (m0 + e < count) {
+                    acc[0] += bf16_lo(row[e].x); acc[1] += bf16_hi(row[e].x);
+                    acc[2] += bf16_lo(row[e].y); acc[3] += bf16_hi(row[e].y);
+                    acc[4] += bf16_lo(row[e].z); acc[5] += bf16_hi(row[e].z);
+                    acc[6] += bf16_lo(row[e].w); acc[7] += bf16_hi(row[e].w);
+                }
         }
         uint4 o;
         o.x = pack_bf16(acc[0] * inv, acc[1] * inv);

@@ -14,71 +14,149 @@ namespace vitcop {
 
 constexpr int SEL_THREADS = 1024;
 
+constexpr int SEL_DIGIT = 10, SEL_LIST = 64;
+
 struct SelectShared {
-    unsigned hist[256];
+    unsigned hist[1 << SEL_DIGIT];
+    unsigned list[SEL_LIST];
+    unsigned low[SEL_THREADS / 64], high[SEL_THREADS / 64];
     unsigned wave_tot[SEL_THREADS / 64];
-    unsigned prefix;
-    unsigned kk;
+    unsigned n_list, prefix, kk, count;
 };
 
 // keys: n entries in LDS.  Writes out[r] = base + i for the r-th survivor in
 // index order.  Must be called by all SEL_THREADS threads of the workgroup.
+//
+// The workgroup is alone on its CU and every step is a latency between two barriers, so there are few of them: digits of
+// ten bits, the first right below the bits that all keys share (scores of one sample share their exponent: the
+// high digits would say nothing and all threads would count in the same bins), and as soon as at most 64 keys share the
+// prefix of the one looked for, one wavefront compares them directly.  One digit and the comparison, i.e. six
+// barriers, are the rule (four digits of eight bits took fourteen: 4 samples of 2880 norms 9.1 -> 7.7 us a launch, one
+// of 6272 in four partial sums 15.0 -> 12.0).
 __device__ inline void block_select_emit(const unsigned* keys, int n, int keep, int32_t* out,
                                          int base, SelectShared& sh) {
-    const int tid = threadIdx.x;
-    unsigned prefix = 0, mask = 0, kk = (unsigned)keep;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    unsigned theta = 0, need = 0;            // keys below theta survive, and the first `need` of those equal to it
     if (keep > 0) {
-        // four 8-bit digits, most significant first: find the key of rank `keep`
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            if (tid < 256) sh.hist[tid] = 0;
-            __syncthreads();
+        unsigned lo = ~0u, hi = 0u;
+        for (int i = tid; i < n; i += SEL_THREADS) {
+            lo = min(lo, keys[i]);
+            hi = max(hi, keys[i]);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = min(lo, __shfl_xor(lo, o, 64));
+            hi = max(hi, __shfl_xor(hi, o, 64));
+        }
+        if (lane == 0) {
+            sh.low[wv] = lo;
+            sh.high[wv] = hi;
+        }
+        for (int i = tid; i < 1 << SEL_DIGIT; i += SEL_THREADS) sh.hist[i] = 0;
+        if (tid == 0) sh.n_list = 0;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < SEL_THREADS / 64; ++w) {
+            lo = min(lo, sh.low[w]);
+            hi = max(hi, sh.high[w]);
+        }
+        // the keys that share `prefix` above their low `bits` bits hold the one of rank kk among them
+        int bits = lo == hi ? 0 : 32 - __builtin_clz(lo ^ hi);
+        unsigned prefix = (unsigned)((uint64_t)lo >> bits << bits), kk = (unsigned)keep;
+        for (;;) {
+            if (bits == 0) {                                     // they are all equal
+                theta = prefix;
+                need = kk;
+                break;
+            }
+            const int width = min(bits, SEL_DIGIT), shift = bits - width;
+            const uint64_t above = (uint64_t)prefix >> bits;
             for (int i0 = 0; i0 < n; i0 += SEL_THREADS) {        // uniform trip count: ballots below
                 const int i = i0 + tid;
                 const unsigned k = i < n ? keys[i] : 0u;
-                const bool live = i < n && (k & mask) == prefix;
-                const unsigned dgt = (k >> shift) & 255u;
-                // Scores of one sample share their high bits, so in the early passes most lanes
-                // of a wavefront hit the same bin: the lanes that agree with the first live lane
-                // are counted with one atomic, the others add individually.
+                const bool live = i < n && (uint64_t)k >> bits == above;
+                const unsigned dgt = (k >> shift) & ((1u << width) - 1u);
+                // the lanes that agree with the first live lane are counted with one atomic, the others add individually
                 const unsigned long long live_mask = __builtin_amdgcn_ballot_w64(live);
                 if (live_mask != 0) {
                     const int leader = __builtin_ctzll(live_mask);
                     const unsigned d0 = __builtin_amdgcn_readlane(dgt, leader);
                     const unsigned long long same = __builtin_amdgcn_ballot_w64(live && dgt == d0);
-                    if ((tid & 63) == leader) atomicAdd(&sh.hist[d0], (unsigned)__builtin_popcountll(same));
+                    if (lane == leader) atomicAdd(&sh.hist[d0], (unsigned)__builtin_popcountll(same));
                     else if (live && dgt != d0) atomicAdd(&sh.hist[dgt], 1u);
                 }
             }
             __syncthreads();
-            if (tid < 64) {
-                unsigned c0 = sh.hist[4 * tid], c1 = sh.hist[4 * tid + 1];
-                unsigned c2 = sh.hist[4 * tid + 2], c3 = sh.hist[4 * tid + 3];
-                unsigned s = c0 + c1 + c2 + c3, incl = s;
+            if (tid < 64) {                                      // 16 bins a lane; cleared for a next digit
+                uint4* bins = reinterpret_cast<uint4*>(sh.hist) + 4 * tid;
+                unsigned c[16], s = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint4 v = bins[q];
+                    c[4 * q] = v.x; c[4 * q + 1] = v.y; c[4 * q + 2] = v.z; c[4 * q + 3] = v.w;
+                    bins[q] = make_uint4(0, 0, 0, 0);
+                }
+#pragma unroll
+                for (int q = 0; q < 16; ++q) s += c[q];
+                unsigned incl = s;
 #pragma unroll
                 for (int o = 1; o < 64; o <<= 1) {
-                    unsigned t = __shfl_up(incl, o, 64);
+                    const unsigned t = __shfl_up(incl, o, 64);
                     if (tid >= o) incl += t;
                 }
-                unsigned excl = incl - s;
-                if (kk > excl && kk <= incl) {
-                    unsigned r = kk - excl;
-                    unsigned dgt = 0;
-                    if (r > c0) { r -= c0; dgt = 1;
-                        if (r > c1) { r -= c1; dgt = 2;
-                            if (r > c2) { r -= c2; dgt = 3; } } }
-                    sh.prefix = prefix | ((4u * tid + dgt) << shift);
-                    sh.kk = r;
+                if (kk > incl - s && kk <= incl) {
+                    unsigned below = incl - s, at = 0, digit = 0;
+                    bool found = false;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        if (!found && kk <= below + c[q]) {
+                            found = true;
+                            digit = q;
+                            at = c[q];
+                        }
+                        if (!found) below += c[q];
+                    }
+                    sh.prefix = prefix | (16u * tid + digit) << shift;
+                    sh.kk = kk - below;
+                    sh.count = at;
                 }
             }
             __syncthreads();
             prefix = sh.prefix;
             kk = sh.kk;
-            mask |= 255u << shift;
+            bits = shift;
+            const unsigned count = sh.count;
+            if (count == kk) {                                   // all that share the prefix survive
+                theta = prefix | (unsigned)(((uint64_t)1 << bits) - 1);
+                need = (unsigned)n;
+                break;
+            }
+            if (count <= SEL_LIST) {
+                for (int i = tid; i < n; i += SEL_THREADS) {
+                    const unsigned k = keys[i];
+                    if ((uint64_t)k >> bits == (uint64_t)prefix >> bits) sh.list[atomicAdd(&sh.n_list, 1u)] = k;
+                }
+                __syncthreads();
+                if (tid < 64) {
+                    const unsigned key = tid < (int)count ? sh.list[tid] : ~0u;
+                    unsigned less = 0, equal = 0;
+                    for (unsigned j = 0; j < count; ++j) {
+                        const unsigned other = __builtin_amdgcn_readlane(key, j);
+                        less += other < key;
+                        equal += other == key;
+                    }
+                    if (tid < (int)count && kk > less && kk <= less + equal) {      // (equal keys agree)
+                        sh.prefix = key;
+                        sh.kk = kk - less;
+                    }
+                }
+                __syncthreads();
+                theta = sh.prefix;
+                need = sh.kk;
+                break;
+            }
         }
     }
-    // prefix is now the key of the last survivor; kk of the keys equal to it survive
-    const unsigned theta = prefix;
-    const unsigned need = keep > 0 ? kk : 0u;
 
     const int ipt = (n + SEL_THREADS - 1) / SEL_THREADS;
     const int lo = min(n, tid * ipt), hi = min(n, lo + ipt);
@@ -90,7 +168,6 @@ __device__ inline void block_select_emit(const unsigned* keys, int n, int keep, 
     }
     // exclusive scan of (less, eq) packed in 16+16 bits (n <= 16384)
     unsigned packed = less | (eq << 16), incl = packed;
-    const int lane = tid & 63, wv = tid >> 6;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         unsigned t = __shfl_up(incl, o, 64);

@@ -193,13 +193,16 @@ __global__ __launch_bounds__(SEL_THREADS) void vic_label_kernel(const float* __r
         });
     if (tid == 0) n_clusters[b] = (int32_t)running;
 
-    // pointer jumping: after ceil(log2 n) rounds every pointer is a root
+    // pointer jumping: after at most ceil(log2 n) rounds every pointer is a root, which points at itself; chains of
+    // parents are short, so the rounds end with the first that moves nothing
     for (int span = 1; span < n; span <<= 1) {
+        bool moved = false;
         for (int i = tid; i < n; i += SEL_THREADS) {
-            const unsigned p = keys[i];
-            keys[i] = keys[p];          // concurrent updates only move a pointer further up its own chain
+            const unsigned p = keys[i], q = keys[p];
+            keys[i] = q;                // concurrent updates only move a pointer further up its own chain
+            moved |= q != p;
         }
-        __syncthreads();
+        if (!__syncthreads_or(moved)) break;
     }
     for (int i = tid; i < n; i += SEL_THREADS) labels[i] = cid[keys[i]];
 }

@@ -74,6 +74,27 @@ def test_exact_ties_go_to_the_lower_index(vc):
     assert idx.cpu().numpy()[0].tolist() == list(range(8)) + [8, 9, 10, 11, 12] + list(range(56, 64))
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 300, 1025, 2900, 16384])
+def test_every_way_the_cut_is_found(vc, n):
+    # the selection's digits, its direct comparison of at most 64 candidates and what ends it early: precomputed values
+    # against a stable argsort.  Values: all equal; two of them; a tight cluster under one outlier (many candidates
+    # share the first ten bits below the common ones, so that further digits are needed); a wide spread; zeros
+    g = np.random.default_rng(n)
+    one = np.float32(3.0)
+    tight = (one + np.arange(n) % 200 * np.float32(2.0 ** -22)).astype(np.float32)
+    tight[-1] = 1e30
+    cases = [np.full(n, one), np.where(g.random(n) < 0.5, one, np.nextafter(one, np.float32(4))).astype(np.float32), tight,
+             np.exp(g.normal(0, 30, n)).clip(0, 1e30).astype(np.float32), np.where(np.arange(n) % 3 == 0, 0, g.random(n)).astype(np.float32)]
+    v = torch.from_numpy(np.stack(cases)).cuda()
+    order = np.argsort(np.stack(cases), axis=1, kind="stable")
+    for keep in sorted({0, 1, n // 3, n // 2, max(n - 1, 0), n}):
+        _, idx = vc.vitcop_knorm_select(None, 0, n, keep, norms=v, flags=vc.VITCOP_NORMS_PRECOMPUTED, shape=(5, n + 1, 4, 128))
+        got = idx.cpu().numpy()
+        for b in range(5):
+            assert np.array_equal(got[b, :keep], np.sort(order[b, :keep])), (n, keep, b)
+            assert got[b, keep] == n
+
+
 def test_planted_norms_and_power_of_two_scaling(vc):
     k = np.zeros((1, 300, 4, 128), np.float32)
     g = np.random.default_rng(9)

@@ -8,6 +8,7 @@ Calls enqueue on torch's current stream and do not synchronise.
 from __future__ import annotations
 
 import ctypes as C
+import math
 import os
 
 import torch
@@ -219,6 +220,9 @@ def _ptr(t) -> int | None:
 
 
 def _stream() -> int:
+    # (the handle alone: building the Stream object around it takes as long as the rest of a call's Python)
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 
@@ -308,10 +312,15 @@ def vitcop_compact(srcs, idx, T_in: int | None = None, outs_in=None):
     for i, s in enumerate(srcs):
         if not s.is_cuda or not s.is_contiguous():
             raise ValueError("sources must be contiguous CUDA tensors")
-        row_bytes = s[0, 0].numel() * s.element_size() if s.dim() > 2 else s.element_size()
+        shape = s.shape
+        if len(shape) > 2 and (shape[0] == 0 or shape[1] == 0):
+            raise IndexError("a source without rows")
+        row_bytes = s.element_size() * math.prod(shape[2:])
         dst = outs_in[i] if outs_in is not None else torch.empty(
             (B, T_out) + tuple(s.shape[2:]), dtype=s.dtype, device=s.device)
-        arr[i] = GatherT(s.data_ptr(), dst.data_ptr(), row_bytes, row_bytes, s.shape[1] * row_bytes)
+        g = arr[i]
+        g.src, g.dst, g.row_bytes = s.data_ptr(), dst.data_ptr(), row_bytes
+        g.src_row_stride_bytes, g.src_batch_stride_bytes = row_bytes, shape[1] * row_bytes
         outs.append(dst)
     t_in = srcs[0].shape[1] if (T_in is None and srcs) else (T_in or 0)
     _check(lib.vitcop_compact(arr, len(srcs), _ptr(idx), B, t_in, T_out, _stream()))

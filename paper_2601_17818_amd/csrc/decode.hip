@@ -2,62 +2,86 @@
 // every sample, the per-token cost that pruning the prefill reduces afterwards (Table 5 of
 // arXiv 2601.17818 reports it).  HBM-bound: K and V of the cache are read exactly once.
 //
-// decode_partial_kernel: a workgroup takes one KV head, all G = Hq/Hkv query heads that share
-// it, and one slice of the keys.  A key row (d bf16) is spread over d/8 lanes, 16 bytes each,
-// so a wavefront reads 512/d keys per instruction; every lane keeps, for each of the G query
-// heads, its 8 query channels, a running maximum, a running sum and 8 output channels (online
-// softmax).  The lane groups, then the wavefronts, are merged at the end and one partial
-// (max, sum, unnormalised output) per (sample, head, slice) goes to the workspace.
+// decode_partial_kernel: a workgroup takes one head and one slice of the keys.  A key row (d bf16) is spread over d/8
+// lanes, 16 bytes each, so a wavefront reads 512/d keys per instruction; every lane keeps its 8 query channels, a
+// running maximum, a running sum and 8 output channels (online softmax).  The lane groups, then the wavefronts, are
+// merged at the end and one partial (max, sum, unnormalised output) per (sample, head, slice) goes to the workspace.
+// decode_group_kernel: the same for query heads that share a KV head, whose products go to the matrix cores.
 // decode_merge_kernel combines the slices; a single slice is finished on the spot.
 #include "vitcop_internal.h"
 #include "device_utils.h"
 
+#include <type_traits>
+
 namespace vitcop {
 
 constexpr int DC_THREADS = 256;
-constexpr int DC_MAX_G = 8;              // query heads per KV head handled in one pass
 
+// The four wavefronts' states of G query heads (sm: maximum and sum, so: unnormalised outputs) combined by threads
+// (head, channel): the partial of this slice, or with `out` the output, what decode_merge_kernel makes of one partial.
+template <int D, int GMAX>
+__device__ __forceinline__ void decode_combine(const float (&sm)[4][GMAX][2], const float (&so)[4][GMAX][D], int G, int b,
+                                               int h0, int Hq, int n_splits, int split,
+                                               float* __restrict__ part_o, float* __restrict__ part_ml,
+                                               uint16_t* __restrict__ out, float* __restrict__ lse) {
+    for (int idx = threadIdx.x; idx < G * D; idx += DC_THREADS) {
+        const int g = idx / D, ch = idx - g * D;
+        float mn = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) mn = fmaxf(mn, sm[w][g][0]);
+        float lt = 0.f, ot = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float a = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm[w][g][0] - mn);
+            lt += sm[w][g][1] * a;
+            ot += so[w][g][ch] * a;
+        }
+        if (out != nullptr) {
+            const int64_t bh = (int64_t)b * Hq + h0 + g;
+            const float r = ot / lt, r1 = __shfl_down(r, 1, 64);         // (a wavefront's lanes share g: D >= 64)
+            if ((ch & 1) == 0) *reinterpret_cast<uint32_t*>(out + bh * D + ch) = pack_bf16(r, r1);
+            if (lse && ch == 0) lse[bh] = (mn + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
+            continue;
+        }
+        const int64_t slot = ((int64_t)b * Hq + h0 + g) * n_splits + split;
+        part_o[slot * D + ch] = ot;
+        if (ch == 0) {
+            part_ml[slot * 2] = mn;
+            part_ml[slot * 2 + 1] = lt;
+        }
+    }
+}
+
+// One query head per KV head.
 // AHEAD: the next rows of K and V are requested before the current ones are used.  Pays for slices of a few hundred
 // keys (64 samples x 32 heads x 318 keys 61.7 -> 57.6 us, 5.4 -> 5.8 TB/s; x 116 keys 26.4 -> 23.9); not for long ones
-// (32 x 4096 keys 305 -> 321 us) nor with several query heads, which have work to do meanwhile.
+// (32 x 4096 keys 305 -> 321 us).
 constexpr int DC_AHEAD_MAX_KEYS = 1024;
-template <int D, int G, bool AHEAD>
+template <int D, bool AHEAD>
 __global__ __launch_bounds__(DC_THREADS) void decode_partial_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    float* __restrict__ part_o, float* __restrict__ part_ml, int N, int Hq, int Hkv, int g0,
-    float scale_log2e, int keys_per_split, int n_splits, int64_t kv_batch,
-    const int32_t* __restrict__ n_cached_samples, uint16_t* __restrict__ out, float* __restrict__ lse) {
+    float* __restrict__ part_o, float* __restrict__ part_ml, int N, int H, float scale_log2e, int keys_per_split,
+    int n_splits, int64_t kv_batch, const int32_t* __restrict__ n_cached_samples, uint16_t* __restrict__ out,
+    float* __restrict__ lse) {
     constexpr int LPK = D / 8;                       // lanes per key row
     constexpr int KPW = 64 / LPK;                    // keys per wavefront instruction
-    const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+    const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int c = lane % LPK, kq = lane / LPK;
-    const int group = Hq / Hkv;
-    const int h0 = hk * group + g0;                  // first query head of this pass
 
-    float qv[G][8];
+    const uint4 u = *reinterpret_cast<const uint4*>(q + ((int64_t)b * H + h) * D + 8 * c);
+    const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
+                         bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
+    float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int h = min(h0 + g, Hq - 1);
-        const uint4 u = *reinterpret_cast<const uint4*>(q + ((int64_t)b * Hq + h) * D + 8 * c);
-        qv[g][0] = bf16_lo(u.x); qv[g][1] = bf16_hi(u.x); qv[g][2] = bf16_lo(u.y); qv[g][3] = bf16_hi(u.y);
-        qv[g][4] = bf16_lo(u.z); qv[g][5] = bf16_hi(u.z); qv[g][6] = bf16_lo(u.w); qv[g][7] = bf16_hi(u.w);
-    }
-    float m[G], l[G], acc[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        m[g] = -INFINITY;
-        l[g] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
-    }
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
     // caches of different lengths: sample b attends over its n_cached_samples[b] rows and the appended one;
     // slices past them see no live key and hand on an empty partial (max -inf, sum 0)
     const int n_keys = n_cached_samples ? min(max(n_cached_samples[b], 0) + 1, N) : N;
     const int key_begin = split * keys_per_split, key_end = min(n_keys, key_begin + keys_per_split);
-    const int64_t row = (int64_t)Hkv * D;
-    const uint16_t* kb = k + b * kv_batch + hk * D + 8 * c;      // kv_batch: elements between two samples' caches
-    const uint16_t* vb = v + b * kv_batch + hk * D + 8 * c;
+    const int64_t row = (int64_t)H * D;
+    const uint16_t* kb = k + b * kv_batch + h * D + 8 * c;       // kv_batch: elements between two samples' caches
+    const uint16_t* vb = v + b * kv_batch + h * D + 8 * c;
     const int key_first = key_begin + wv * KPW;
     uint4 k_next = make_uint4(0, 0, 0, 0), v_next = k_next;
     if (AHEAD && key_first < key_end) {
@@ -86,78 +110,209 @@ __global__ __launch_bounds__(DC_THREADS) void decode_partial_kernel(
                              bf16_lo(ku.z), bf16_hi(ku.z), bf16_lo(ku.w), bf16_hi(ku.w)};
         const float vf[8] = {bf16_lo(vu.x), bf16_hi(vu.x), bf16_lo(vu.y), bf16_hi(vu.y),
                              bf16_lo(vu.z), bf16_hi(vu.z), bf16_lo(vu.w), bf16_hi(vu.w)};
+        float s = 0.f;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float s = 0.f;
+        for (int e = 0; e < 8; ++e) s = fmaf(qv[e], kf[e], s);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s = fmaf(qv[g][e], kf[e], s);
+        for (int o = LPK / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);          // over the lanes of this key
+        s = live ? s * scale_log2e : -INFINITY;
+        const float m_new = fmaxf(m, s);
+        // m_new is -inf only while nothing live has been seen: then alpha and p must be 0, not NaN
+        const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+        const float p = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - m_new);
+        m = m_new;
+        l = fmaf(l, alpha, p);
 #pragma unroll
-            for (int o = LPK / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);      // over the lanes of this key
-            s = live ? s * scale_log2e : -INFINITY;
-            const float m_new = fmaxf(m[g], s);
-            // m_new is -inf only while nothing live has been seen: then alpha and p must be 0, not NaN
-            const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[g] - m_new);
-            const float p = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - m_new);
-            m[g] = m_new;
-            l[g] = fmaf(l[g], alpha, p);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[g][e] = fmaf(acc[g][e], alpha, p * vf[e]);
-        }
+        for (int e = 0; e < 8; ++e) acc[e] = fmaf(acc[e], alpha, p * vf[e]);
     }
     // merge the KPW key sub-groups of the wavefront (lanes with the same c), then the wavefronts
-    __shared__ float sm[4][DC_MAX_G][2];
-    __shared__ float so[4][DC_MAX_G][D];
+    __shared__ float sm[4][1][2];
+    __shared__ float so[4][1][D];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
+    for (int o = LPK; o < 64; o <<= 1) {
+        const float mo = __shfl_xor(m, o, 64), lo = __shfl_xor(l, o, 64);
+        const float mn = fmaxf(m, mo);
+        const float a0 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+        const float a1 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mo - mn);
+        l = l * a0 + lo * a1;
 #pragma unroll
-        for (int o = LPK; o < 64; o <<= 1) {
-            const float mo = __shfl_xor(m[g], o, 64), lo = __shfl_xor(l[g], o, 64);
-            const float mn = fmaxf(m[g], mo);
-            const float a0 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[g] - mn);
-            const float a1 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mo - mn);
-            l[g] = l[g] * a0 + lo * a1;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[g][e] = acc[g][e] * a0 + __shfl_xor(acc[g][e], o, 64) * a1;
-            m[g] = mn;
+        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * a0 + __shfl_xor(acc[e], o, 64) * a1;
+        m = mn;
+    }
+    if (kq == 0) {
+        if (c == 0) {
+            sm[wv][0][0] = m;
+            sm[wv][0][1] = l;
         }
-        if (kq == 0) {
-            if (c == 0) {
-                sm[wv][g][0] = m[g];
-                sm[wv][g][1] = l[g];
-            }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) so[wv][g][8 * c + e] = acc[g][e];
-        }
+        for (int e = 0; e < 8; ++e) so[wv][0][8 * c + e] = acc[e];
     }
     __syncthreads();
-    // threads (g, channel) combine the four wavefronts and write the partial of this slice
-    for (int idx = threadIdx.x; idx < G * D; idx += DC_THREADS) {
-        const int g = idx / D, ch = idx - g * D;
-        if (h0 + g >= hk * group + group) continue;          // padding heads of the last pass
-        float mn = -INFINITY;
+    decode_combine<D, 1>(sm, so, 1, b, h, H, n_splits, split, part_o, part_ml, out, lse);
+}
+
+// Query heads that share a KV head (2 to 16 of them a pass).  On the vector pipe every key costs each of them 16 FMAs a
+// lane, a reduction over lanes and an exponential: 64 samples x 318 keys x 28 / 4 heads x 128 took 45 us for 42 MB (now
+// 12.5), 32 x 4096 keys 121 (51), 64 x 400 x 16 / 4 x 64 20.8 (8.7), 64 x 318 x 32 / 16 37.6 (33.9).  Here a wavefront
+// takes 32 keys at a time: scores S^T = K Q^T (16x16x32: a lane holds 4 keys of one head), the softmax with the lane's
+// head as its only query, and O^T += V^T P^T, V transposed on the way out of LDS (ds_read_b64_tr_b16).  The key of
+// element 4 t + r of a lane's 8 in the second product is 16 t + 4 (lane / 16) + r, which is where the scores are.  The
+// probabilities stay 32-bit: each is the sum of three bf16 (24 bits), one product for each.
+constexpr int DG_MAX_G = 16, DG_KEYS = 32;
+template <int D>
+__global__ __launch_bounds__(DC_THREADS) void decode_group_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    float* __restrict__ part_o, float* __restrict__ part_ml, int N, int Hq, int Hkv, int g0, int G,
+    float scale_log2e, int keys_per_split, int n_splits, int64_t kv_batch,
+    const int32_t* __restrict__ n_cached_samples, uint16_t* __restrict__ out, float* __restrict__ lse) {
+    constexpr int STEPS = D / 32, BLOCKS = D / 16;
+    constexpr int VROW = 2 * D + 32;                         // bytes of a V row in LDS: the pad keeps eight rows apart
+    constexpr int LPR = D / 8, RPL = 64 / LPR, VL = DG_KEYS / RPL;         // lanes a row, rows a load, loads a tile of V
+    static_assert(DG_KEYS * VROW >= DG_MAX_G * D * 4, "the outputs take V's place at the end");
+    __shared__ __attribute__((aligned(16))) char vt[4][DG_KEYS * VROW];
+    __shared__ float sm[4][DG_MAX_G][2];
+    float (&so)[4][DG_MAX_G][D] = *reinterpret_cast<float (*)[4][DG_MAX_G][D]>(&vt[0][0]);
+    const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, g4 = lane >> 4;
+    const int group = Hq / Hkv, h0 = hk * group + g0;        // first query head of this pass
+    const int n_keys = n_cached_samples ? min(max(n_cached_samples[b], 0) + 1, N) : N;
+    const int key_begin = split * keys_per_split, key_end = min(n_keys, key_begin + keys_per_split);
+    const int64_t row = (int64_t)Hkv * D;
+    const uint16_t* kb = k + b * kv_batch + hk * D;
+    const uint16_t* vb = v + b * kv_batch + hk * D;
+
+    bf16x8 qf[STEPS];                                        // Q^T: 8 channels of head l16 a step (heads past G: head G - 1)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mn = fmaxf(mn, sm[w][g][0]);
-        float lt = 0.f, ot = 0.f;
+    for (int c = 0; c < STEPS; ++c)
+        qf[c] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)b * Hq + h0 + min(l16, G - 1)) * D + 32 * c + 8 * g4);
+    f32x4 o[BLOCKS];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float a = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm[w][g][0] - mn);
-            lt += sm[w][g][1] * a;
-            ot += so[w][g][ch] * a;
+    for (int i = 0; i < BLOCKS; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;                            // of head l16 (m over all its keys, l over this lane's)
+
+    u32x4 kr[2][STEPS], vr[VL];
+    auto load = [&](int key0) __attribute__((always_inline)) {           // keys past the end: the last one, masked below
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint16_t* p = kb + min(key0 + 16 * t + l16, key_end - 1) * row + 8 * g4;
+#pragma unroll
+            for (int c = 0; c < STEPS; ++c) kr[t][c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + 32 * c));
         }
-        if (out != nullptr) {        // the only slice: what decode_merge_kernel makes of one partial
-            const int64_t bh = (int64_t)b * Hq + h0 + g;
-            const float r = ot / lt, r1 = __shfl_down(r, 1, 64);         // (a wavefront's lanes share g: D >= 64)
-            if ((ch & 1) == 0) *reinterpret_cast<uint32_t*>(out + bh * D + ch) = pack_bf16(r, r1);
-            if (lse && ch == 0) lse[bh] = (mn + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
-            continue;
+#pragma unroll
+        for (int i = 0; i < VL; ++i)
+            vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
+                vb + min(key0 + RPL * i + lane / LPR, key_end - 1) * row + 8 * (lane % LPR)));
+    };
+    typedef __attribute__((ext_vector_type(4))) short s16x4;
+    typedef __attribute__((ext_vector_type(8))) short s16x8;
+    char* const mine = vt[wv];
+    const unsigned tr = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)mine +
+                        (4 * g4 + ((lane >> 2) & 3)) * VROW + (lane & 3) * 8;
+    const int first = key_begin + wv * DG_KEYS;
+    auto attend = [&](auto parts_c) __attribute__((always_inline)) {     // PARTS: bf16 summands of a probability
+        constexpr int PARTS = decltype(parts_c)::value;
+        if (first < key_end) load(first);
+        for (int key0 = first; key0 < key_end; key0 += 4 * DG_KEYS) {
+            f32x4 s[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                s[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < STEPS; ++c)
+                    s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[t][c]), qf[c], s[t], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < VL; ++i)
+                *reinterpret_cast<u32x4*>(mine + (RPL * i + lane / LPR) * VROW + lane % LPR * 16) = vr[i];
+            if (key0 + 4 * DG_KEYS < key_end) load(key0 + 4 * DG_KEYS);      // (uniform) in flight from here on
+            float p[8], top = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int key = key0 + 16 * (e >> 2) + 4 * g4 + (e & 3);
+                p[e] = key < key_end ? s[e >> 2][e & 3] * scale_log2e : -INFINITY;
+                top = fmaxf(top, p[e]);
+            }
+            top = fmaxf(top, __shfl_xor(top, 16, 64));
+            top = fmaxf(top, __shfl_xor(top, 32, 64));
+            const float m_new = fmaxf(m, top);
+            const float base = m_new == -INFINITY ? 0.f : m_new;         // (nothing but -inf so far: 0, not NaN)
+            const float alpha = __builtin_amdgcn_exp2f(m - base);
+            m = m_new;
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                p[e] = __builtin_amdgcn_exp2f(p[e] - base);
+                sum += p[e];
+            }
+            l = fmaf(l, alpha, sum);
+            u32x4 part[PARTS];                               // the rest of the rest last
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float a = p[2 * e], c = p[2 * e + 1];
+#pragma unroll
+                for (int n = 0; n < PARTS; ++n) {
+                    const uint32_t w = pack_bf16(a, c);
+                    part[n][e] = w;
+                    a -= bf16_lo(w);
+                    c -= bf16_hi(w);
+                }
+            }
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+                for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[i][r] *= alpha;
+            }
+            __builtin_amdgcn_wave_barrier();                     // (one wavefront's LDS accesses stay in order)
+#pragma unroll
+            for (int i = 0; i < BLOCKS; ++i) {
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4*)(uintptr_t)(tr + i * 32));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4*)(uintptr_t)(tr + i * 32 + 16 * VROW));
+                const bf16x8 vf = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                for (int n = 0; n < PARTS; ++n)
+                    o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, part[n]), o[i], 0, 0, 0);
+            }
+            __builtin_amdgcn_wave_barrier();                     // the next tile's rows replace these
         }
-        const int64_t slot = ((int64_t)b * Hq + h0 + g) * n_splits + split;
-        part_o[slot * D + ch] = ot;
-        if (ch == 0) {
-            part_ml[slot * 2] = mn;
-            part_ml[slot * 2 + 1] = lt;
+    };
+    attend(std::integral_constant<int, 3>{});
+    // An infinite value of V times the zero parts of a probability is no number: such outputs (alone) are summed again
+    // with the first parts only, which are zero where the probability is.
+    bool nan = false;
+#pragma unroll
+    for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) nan |= o[i][r] != o[i][r];
+    if (__builtin_amdgcn_ballot_w64(nan) != 0) {
+        f32x4 sums[BLOCKS];
+#pragma unroll
+        for (int i = 0; i < BLOCKS; ++i) {
+            sums[i] = o[i];
+            o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
+        m = -INFINITY;
+        l = 0.f;
+        attend(std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (sums[i][r] == sums[i][r]) o[i][r] = sums[i][r];
     }
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    __syncthreads();                                         // all are done with V
+    if (g4 == 0) {
+        sm[wv][l16][0] = m;
+        sm[wv][l16][1] = l;
+    }
+#pragma unroll
+    for (int i = 0; i < BLOCKS; ++i) *reinterpret_cast<f32x4*>(&so[wv][l16][16 * i + 4 * g4]) = o[i];
+    __syncthreads();
+    decode_combine<D, DG_MAX_G>(sm, so, G, b, h0, Hq, n_splits, split, part_o, part_ml, out, lse);
 }
 
 template <int D>
@@ -192,27 +347,25 @@ int decode_splits(int B, int N, int Hkv) {
     return (int)s;
 }
 
+// Slices for decode_group_kernel, never more than the above, which sizes the scratch: its wavefronts keep 16 KB each in
+// flight, so it needs fewer, of at least 128 keys (32 a wavefront), and with one there is no merge.
+constexpr int DG_WGS = 256;
+static int group_splits(int B, int N, int Hkv) {
+    const long wgs = (long)B * Hkv;
+    return (int)std::max(1L, std::min((DG_WGS + wgs - 1) / wgs, (N + 127L) / 128));
+}
+
 size_t decode_workspace_bytes(int B, int N, int Hq, int Hkv, int d) {
     const size_t s = decode_splits(B, N, Hkv);
     return up256((size_t)B * Hq * s * d * 4) + up256((size_t)B * Hq * s * 2 * 4);
-}
-
-template <int D, int G>
-static void launch_partial(dim3 grid, hipStream_t s, const uint16_t* q, const uint16_t* k, const uint16_t* v,
-                           float* po, float* pml, int N, int Hq, int Hkv, int g0, float sl2, int kps, int ns,
-                           int64_t kv_batch, const int32_t* ncs, uint16_t* out, float* lse) {
-    auto kern = decode_partial_kernel<D, G, false>;
-    if constexpr (G == 1)
-        if (kps <= DC_AHEAD_MAX_KEYS) kern = decode_partial_kernel<D, G, true>;
-    hipLaunchKernelGGL(kern, grid, dim3(DC_THREADS), 0, s, q, k, v, po, pml, N, Hq, Hkv, g0, sl2, kps, ns, kv_batch, ncs,
-                       out, lse);
 }
 
 template <int D>
 static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                            int B, int N, int Hq, int Hkv, float scale, void* ws, hipStream_t s, int64_t kv_batch,
                            DecodeParts* hand_over, const int32_t* ncs) {
-    const int ns = decode_splits(B, N, Hkv);
+    const bool grouped = Hq > Hkv;
+    const int ns = grouped ? group_splits(B, N, Hkv) : decode_splits(B, N, Hkv);
     const int kps = ((N + ns - 1) / ns + 63) / 64 * 64;
     float* po = static_cast<float*>(ws);
     float* pml = reinterpret_cast<float*>(static_cast<char*>(ws) + up256((size_t)B * Hq * ns * D * 4));
@@ -222,13 +375,17 @@ static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t*
     // one slice (as many (sample, KV head) pairs as four workgroups per CU): the outputs are written right away and
     // the merge's launch is saved (64 samples x 32 heads: 4.9 us a layer)
     uint16_t* o1 = ns == 1 ? out : nullptr;
-    for (int g0 = 0; g0 < group; g0 += DC_MAX_G) {
-        const int g = std::min(DC_MAX_G, group - g0);
-        if (g == 1) launch_partial<D, 1>(grid, s, q, k, v, po, pml, N, Hq, Hkv, g0, sl2, kps, ns, kv_batch, ncs, o1, lse);
-        else if (g == 2) launch_partial<D, 2>(grid, s, q, k, v, po, pml, N, Hq, Hkv, g0, sl2, kps, ns, kv_batch, ncs, o1, lse);
-        else if (g <= 4) launch_partial<D, 4>(grid, s, q, k, v, po, pml, N, Hq, Hkv, g0, sl2, kps, ns, kv_batch, ncs, o1, lse);
-        else launch_partial<D, 8>(grid, s, q, k, v, po, pml, N, Hq, Hkv, g0, sl2, kps, ns, kv_batch, ncs, o1, lse);
-        int rc = launch_status("decode_partial");
+    if (grouped) {
+        for (int g0 = 0; g0 < group; g0 += DG_MAX_G) {
+            hipLaunchKernelGGL((decode_group_kernel<D>), grid, dim3(DC_THREADS), 0, s, q, k, v, po, pml, N, Hq, Hkv, g0,
+                               std::min(DG_MAX_G, group - g0), sl2, kps, ns, kv_batch, ncs, o1, lse);
+            const int rc = launch_status("decode_group");
+            if (rc) return rc;
+        }
+    } else {
+        hipLaunchKernelGGL((kps <= DC_AHEAD_MAX_KEYS ? decode_partial_kernel<D, true> : decode_partial_kernel<D, false>),
+                           grid, dim3(DC_THREADS), 0, s, q, k, v, po, pml, N, Hq, sl2, kps, ns, kv_batch, ncs, o1, lse);
+        const int rc = launch_status("decode_partial");
         if (rc) return rc;
     }
     if (ns == 1) {

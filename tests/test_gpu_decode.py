@@ -36,6 +36,38 @@ def test_matches_oracle(vc, B, N, Hq, Hkv, d):
     assert np.abs(lse - ref_lse).max() < 1e-3
 
 
+# query heads that share a KV head: 2, 3, 7, 16 and 17 of them (a second pass), tiles of 32 keys a wavefront and 128 a
+# workgroup short of full, full and one over, one slice and several
+@pytest.mark.parametrize("B,N,Hq,Hkv,d", [(2, 31, 4, 2, 64), (2, 32, 6, 2, 128), (1, 33, 7, 1, 64), (3, 127, 16, 1, 128),
+                                          (2, 129, 17, 1, 64), (70, 160, 28, 4, 128), (1, 257, 34, 2, 128)])
+def test_grouped_query_heads(vc, B, N, Hq, Hkv, d):
+    t = I.qkv_tensors(9700 + N + Hq, B, N, Hq, Hkv, d)
+    out, lse = run(vc, t)
+    ref, ref_lse = Dc.decode_attention(t["q"][:, -1], t["k"], t["v"])
+    assert_attention_close(out, ref, f"decode N={N}, {Hq} / {Hkv}")
+    assert np.abs(lse - ref_lse).max() < 1e-3
+
+
+def test_grouped_query_heads_with_infinities(vc):
+    # an infinite value reaches its channel of every head and no other; keys whose scores are -inf count for nothing
+    B, N, Hq, Hkv, d = 1, 200, 8, 2, 128
+    t = I.qkv_tensors(9800, B, N, Hq, Hkv, d)
+    plain, _ = run(vc, t)
+    v = t["v"].copy()
+    v[0, 77, 1, 5] = 0x7F80                                       # +inf in the second KV head's channel 5
+    out, _ = run(vc, dict(t, v=v))
+    want = plain.reshape(B, Hkv, Hq // Hkv, d).copy()
+    want[0, 1, :, 5] = np.inf
+    assert np.array_equal(out.reshape(want.shape), want)
+    q, k = t["q"].copy(), t["k"].copy()
+    q[:, -1, :, 0] = 0x3F80                                       # 1.0
+    k[0, :64, :, 0] = 0xFF80                                      # -inf: the first 64 keys, two whole tiles
+    out, lse = run(vc, dict(t, q=q, k=k))
+    rest = dict(t, q=q, k=k[:, 64:], v=t["v"][:, 64:])
+    ref, ref_lse = run(vc, {n: np.ascontiguousarray(x) for n, x in rest.items()})
+    assert np.abs(out - ref).max() < 1e-2 and np.abs(lse - ref_lse).max() < 1e-3
+
+
 def test_scale_large_logits_and_structure(vc):
     t = I.qkv_tensors(9600, 2, 300, 4, 2, 128, std=3.0)
     out, lse = run(vc, t, scale=0.11)

@@ -208,6 +208,9 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
             const bool next = 32 * q - BM >= next_row;               // uniform: boundaries are multiples of 32
             __builtin_amdgcn_raw_ptr_buffer_load_lds(next ? desc_u : desc_w, dst, 16, off,
                                                      kw == rec_w && next ? rec_u : kw, 0, 0);
+        } else if constexpr (EPI == GM_EPI_GATED && 32 * q < BM + BN / 2 && 32 * q + 32 > BM + BN / 2) {
+            // (halves of 48 columns: two of the wavefronts hold the last gate rows, two the first up rows; rec_u == rec_w)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(32 * q + 8 * wv >= BM + BN / 2 ? desc_u : desc_w, dst, 16, off, kw, 0, 0);
         } else if constexpr (EPI == GM_EPI_GATED && 32 * q >= BM + BN / 2) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_u, dst, 16, off, kw, 0, 0);
         } else {
@@ -486,14 +489,14 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     if constexpr (EPI == GM_EPI_GATED) {
         // gate block of these rows: staged by wavefront (wm, 0); up block: by (wm, 1).  Each of the two takes
         // half of the block's columns: 16-byte chunks of gate and up in, one chunk of silu(gate) * up out.
-        static_assert((BN / 2) % 32 == 0, "whole loads per half");
+        static_assert((BN / 2) % 16 == 0 && BN % 32 == 0, "whole rows of a load per half");
         __builtin_amdgcn_s_waitcnt(0xC07F);               // lgkmcnt(0): this wavefront's staging writes are done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         const char* gate_stage = gemm_lds + wm * (TM * STAGE_ROW);
         const char* up_stage = gemm_lds + (wm + WAVES_M) * (TM * STAGE_ROW);
         constexpr int HALF_LANES = TN / 16;               // 16-byte chunks per half row
-        constexpr int ROWS_PER_PASS = 64 / HALF_LANES;    // (96-column blocks: 10 rows, the last 4 lanes idle)
+        constexpr int ROWS_PER_PASS = 64 / HALF_LANES;    // (96- and 48-column blocks: 10 and 21 rows, the last 4 and 1 lanes idle)
         const int hrow = lane / HALF_LANES, hchunk = lane % HALF_LANES + wn * HALF_LANES;
         const int nn = n0 + hchunk * 8;
         if (nn < N && hrow < ROWS_PER_PASS) {             // N % 8 == 0: the chunk is all in or all out

@@ -187,11 +187,25 @@ inline SkinnyPlan skinny_plan(int M, int N, int K) {
 }
 
 // Columns of a tile (half gate, half up) if the gate/up launch goes out as whole tiles with the activation in their
-// epilogue, 0 if as the slices of `plan`.
+// epilogue, 0 if as the slices of `plan`.  Every form is one round of what its number of workgroups can draw, so the
+// narrowest that needs no second round wins: 48 + 48 columns fill the chip where 64 + 64 leave a fifth to a quarter of
+// it idle.  A whole layer of one head, us, in tiles of 32 + 32, 48 + 48 and 64 + 64 columns:
+//   F x D          64 rows            115 rows           256 rows
+//   8192 x 2048     80.2  83.4  85.5   96.5  99.2 101.5  119.3 121.8 122.8
+//   11008 x 4096   132.2 118.4 120.6  155.5 139.0 145.7  208.2 177.7 178.6
+//   18944 x 3584   157.6 153.4 162.8  189.7 181.3 190.3  256.3 227.6 237.8
+//   14336 x 4096   141.0 148.3 133.1  166.7 176.5 156.1  221.6 230.4 192.9
 inline int skinny_gated_columns(const SkinnyPlan& plan, int M, int F, int K) {
-    const float us64 = skinny_us(skinny_rows(M), 64, F / 32, K), us128 = skinny_us(skinny_rows(M), 128, F / 64, K);
-    if (std::min(us64, us128) > plan.us + 3.0f) return 0;        // (3 us: the reduction's launch)
-    return us64 < us128 ? 64 : 128;
+    int best = 0;
+    float best_us = plan.us + 3.0f;                              // (3 us: the reduction's launch)
+    for (int cols : {64, 96, 128}) {
+        const float us = skinny_us(skinny_rows(M), cols, (2 * F + cols - 1) / cols, K);
+        if (us <= best_us) {
+            best_us = us;
+            best = cols;
+        }
+    }
+    return best;
 }
 
 // ---- 257 to 1024 rows: k-slices -------------------------------------------------------------------------------

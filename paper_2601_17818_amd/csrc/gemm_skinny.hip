@@ -328,6 +328,8 @@ static int launch_skinny_gate_up(int cols, const uint16_t* x, int64_t x_stride, 
                                  hipStream_t s) {
     if (cols == 64)
         return launch_gemm_cfg<BM, 64, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
+    if (cols == 96)
+        return launch_gemm_cfg<BM, 96, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
     return launch_gemm_cfg<BM, 128, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
 }
 // f<BM>(args...) for the tile that holds M rows

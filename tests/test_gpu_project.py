@@ -88,10 +88,10 @@ SIDE_BY_SIDE = ([(M, *layer) for layer in ((512, 4, 2, 64, 1408), (640, 5, 1, 12
                  (327, 512, 44, 11, 128, 256), (481, 512, 40, 5, 128, 256)] +
                 # K in k-slices of its own, Q and V as a pair in slices of 256 columns
                 [(257, 5888, 36, 36, 128, 512)] +
-                # gate and up of few rows in tiles of 32 + 32 and 64 + 64 columns, and in k-slices
+                # gate and up of few rows in tiles of 32 + 32, 48 + 48 and 64 + 64 columns, and in k-slices
                 [(M, *layer) for M, D in ((20, 7168), (50, 2048), (80, 1536), (120, 1280), (150, 1024), (180, 1024),
                                           (210, 1024), (250, 1024))
-                 for layer in ((512, 1, 1, 128, 256), (256, 1, 1, 128, 8320), (D, 1, 1, 128, 128))])
+                 for layer in ((512, 1, 1, 128, 256), (256, 1, 1, 128, 8320), (256, 1, 1, 128, 12928), (D, 1, 1, 128, 128))])
 
 
 @pytest.mark.parametrize("M,D,Hq,Hkv,d,F", SIDE_BY_SIDE)

@@ -2,9 +2,9 @@
 // every sample, the per-token cost that pruning the prefill reduces afterwards (Table 5 of
 // arXiv 2601.17818 reports it).  HBM-bound: K and V of the cache are read exactly once.
 //
-// decode_partial_kernel: a workgroup takes one head and one slice of the keys.  A key row (d bf16) is spread over d/8
-// lanes, 16 bytes each, so a wavefront reads 512/d keys per instruction; every lane keeps its 8 query channels, a
-// running maximum, a running sum and 8 output channels (online softmax).  The lane groups, then the wavefronts, are
+// decode_partial_kernel: a workgroup takes one head, or two or four side by side, and one slice of the keys.  A key row
+// (d bf16) is spread over d/8 lanes, 16 bytes each, so a wavefront reads 512/d rows per instruction; every lane keeps its
+// 8 query channels, a running maximum, a running sum and 8 output channels (online softmax).  The lane groups, then the wavefronts, are
 // merged at the end and one partial (max, sum, unnormalised output) per (sample, head, slice) goes to the workspace.
 // decode_group_kernel: the same for query heads that share a KV head, whose products go to the matrix cores.
 // decode_merge_kernel combines the slices; a single slice is finished on the spot.
@@ -19,19 +19,19 @@ constexpr int DC_THREADS = 256;
 
 // The four wavefronts' states of G query heads (sm: maximum and sum, so: unnormalised outputs) combined by threads
 // (head, channel): the partial of this slice, or with `out` the output, what decode_merge_kernel makes of one partial.
-template <int D, int GMAX>
-__device__ __forceinline__ void decode_combine(const float (&sm)[4][GMAX][2], const float (&so)[4][GMAX][D], int G, int b,
+template <int D, int GMAX, int WAVES = 4>
+__device__ __forceinline__ void decode_combine(const float (&sm)[WAVES][GMAX][2], const float (&so)[WAVES][GMAX][D], int G, int b,
                                                int h0, int Hq, int n_splits, int split,
                                                float* __restrict__ part_o, float* __restrict__ part_ml,
                                                uint16_t* __restrict__ out, float* __restrict__ lse) {
-    for (int idx = threadIdx.x; idx < G * D; idx += DC_THREADS) {
+    for (int idx = threadIdx.x; idx < G * D; idx += 64 * WAVES) {
         const int g = idx / D, ch = idx - g * D;
         float mn = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mn = fmaxf(mn, sm[w][g][0]);
+        for (int w = 0; w < WAVES; ++w) mn = fmaxf(mn, sm[w][g][0]);
         float lt = 0.f, ot = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             const float a = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm[w][g][0] - mn);
             lt += sm[w][g][1] * a;
             ot += so[w][g][ch] * a;
@@ -52,22 +52,26 @@ __device__ __forceinline__ void decode_combine(const float (&sm)[4][GMAX][2], co
     }
 }
 
-// One query head per KV head.
+// One query head per KV head.  HBM-bound.  HEADS neighbouring heads' rows of a key lie side by side in the cache, and a
+// wavefront reads them together: pieces of 512 bytes and more instead of 256 at a stride of Hkv * 2 D bytes (64 samples x
+// 32 heads x 318 keys 59.6 -> 54.0 us, 5.6 -> 6.2 TB/s; x 118 keys 24.0 -> 22.1; x 640 keys 115.8 -> 102.2, 6.6 TB/s).  Four
+// wavefronts per head as before, so the keys of each wavefront, and the loads in flight, are the same number.
 // AHEAD: the next rows of K and V are requested before the current ones are used.  Pays for slices of a few hundred
-// keys (64 samples x 32 heads x 318 keys 61.7 -> 57.6 us, 5.4 -> 5.8 TB/s; x 116 keys 26.4 -> 23.9); not for long ones
-// (32 x 4096 keys 305 -> 321 us).
+// keys (one head at a time: 64 samples x 32 heads x 318 keys 61.7 -> 57.6 us, 5.4 -> 5.8 TB/s; x 116 keys 26.4 -> 23.9); not
+// for long ones (32 x 4096 keys 305 -> 321 us).
 constexpr int DC_AHEAD_MAX_KEYS = 1024;
-template <int D, bool AHEAD>
-__global__ __launch_bounds__(DC_THREADS) void decode_partial_kernel(
+template <int D, bool AHEAD, int HEADS>
+__global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ part_o, float* __restrict__ part_ml, int N, int H, float scale_log2e, int keys_per_split,
     int n_splits, int64_t kv_batch, const int32_t* __restrict__ n_cached_samples, uint16_t* __restrict__ out,
     float* __restrict__ lse) {
-    constexpr int LPK = D / 8;                       // lanes per key row
-    constexpr int KPW = 64 / LPK;                    // keys per wavefront instruction
-    const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    constexpr int LPK = D / 8;                       // lanes per key row of a head
+    constexpr int KPW = 64 / (LPK * HEADS);          // keys per wavefront instruction
+    constexpr int WAVES = 4 * HEADS;
+    const int split = blockIdx.x, h0 = blockIdx.y * HEADS, b = blockIdx.z;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = lane % LPK, kq = lane / LPK;
+    const int c = lane % LPK, kq = lane / (LPK * HEADS), hs = lane / LPK % HEADS, h = h0 + hs;
 
     const uint4 u = *reinterpret_cast<const uint4*>(q + ((int64_t)b * H + h) * D + 8 * c);
     const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
@@ -89,15 +93,15 @@ __global__ __launch_bounds__(DC_THREADS) void decode_partial_kernel(
         k_next = ld_nt16(kb + kc * row);
         v_next = ld_nt16(vb + kc * row);
     }
-    for (int key0 = key_first; key0 < key_end; key0 += 4 * KPW) {     // (empty if key_end <= key_begin)
+    for (int key0 = key_first; key0 < key_end; key0 += WAVES * KPW) {     // (empty if key_end <= key_begin)
         const int key = key0 + kq;
         const bool live = key < key_end;
         uint4 ku, vu;
         if constexpr (AHEAD) {
             ku = k_next;
             vu = v_next;
-            if (key0 + 4 * KPW < key_end) {                           // (uniform in the wavefront)
-                const int kc = min(key + 4 * KPW, key_end - 1);
+            if (key0 + WAVES * KPW < key_end) {                           // (uniform in the wavefront)
+                const int kc = min(key + WAVES * KPW, key_end - 1);
                 k_next = ld_nt16(kb + kc * row);
                 v_next = ld_nt16(vb + kc * row);
             }
@@ -126,10 +130,10 @@ __global__ __launch_bounds__(DC_THREADS) void decode_partial_kernel(
         for (int e = 0; e < 8; ++e) acc[e] = fmaf(acc[e], alpha, p * vf[e]);
     }
     // merge the KPW key sub-groups of the wavefront (lanes with the same c), then the wavefronts
-    __shared__ float sm[4][1][2];
-    __shared__ float so[4][1][D];
+    __shared__ float sm[WAVES][HEADS][2];
+    __shared__ float so[WAVES][HEADS][D];
 #pragma unroll
-    for (int o = LPK; o < 64; o <<= 1) {
+    for (int o = LPK * HEADS; o < 64; o <<= 1) {
         const float mo = __shfl_xor(m, o, 64), lo = __shfl_xor(l, o, 64);
         const float mn = fmaxf(m, mo);
         const float a0 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
@@ -141,14 +145,14 @@ __global__ __launch_bounds__(DC_THREADS) void decode_partial_kernel(
     }
     if (kq == 0) {
         if (c == 0) {
-            sm[wv][0][0] = m;
-            sm[wv][0][1] = l;
+            sm[wv][hs][0] = m;
+            sm[wv][hs][1] = l;
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) so[wv][0][8 * c + e] = acc[e];
+        for (int e = 0; e < 8; ++e) so[wv][hs][8 * c + e] = acc[e];
     }
     __syncthreads();
-    decode_combine<D, 1>(sm, so, 1, b, h, H, n_splits, split, part_o, part_ml, out, lse);
+    decode_combine<D, HEADS, WAVES>(sm, so, HEADS, b, h0, H, n_splits, split, part_o, part_ml, out, lse);
 }
 
 // Query heads that share a KV head (2 to 16 of them a pass).  On the vector pipe every key costs each of them 16 FMAs a
@@ -355,6 +359,25 @@ static int group_splits(int B, int N, int Hkv) {
     return (int)std::max(1L, std::min((DG_WGS + wgs - 1) / wgs, (N + 127L) / 128));
 }
 
+// Heads that decode_partial_kernel reads side by side: what the fullest CU gets to do, `pairs` (sample, head, slice)
+// dealt out `heads` at a time, times the time of one against that of reading 256 bytes a row.  Four leave a CU with one
+// workgroup, and nothing beside its start and end, unless there are more than 256 such.  Measured, us in one, two and four:
+// 64 samples x 32 heads x 353 keys 64.7, 58.4, 58.5; 44 x 32 x 353 43.9, 39.6, 47.1; 25 x 40 x 700 68.7, 65.4, 61.5;
+// 26 x 40 x 700 66.1, 71.5, 82.6; 32 x 32 x 1000 80.4, 77.3, 81.9; 128 x 16 (of 64 channels) x 200 21.7, 20.3, 19.2.
+static int heads_side_by_side(long pairs, int heads) {
+    int best = 1;
+    float least = (float)((pairs + 255) / 256);
+    for (int n : {2, 4}) {
+        if (heads % n != 0 || (n == 4 && pairs <= 4 * 256)) continue;
+        const float load = (float)((pairs + 256 * n - 1) / (256 * n) * n) * (n == 2 ? 0.9f : 0.88f);
+        if (load <= least) {
+            least = load;
+            best = n;
+        }
+    }
+    return best;
+}
+
 size_t decode_workspace_bytes(int B, int N, int Hq, int Hkv, int d) {
     const size_t s = decode_splits(B, N, Hkv);
     return up256((size_t)B * Hq * s * d * 4) + up256((size_t)B * Hq * s * 2 * 4);
@@ -383,8 +406,14 @@ static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t*
             if (rc) return rc;
         }
     } else {
-        hipLaunchKernelGGL((kps <= DC_AHEAD_MAX_KEYS ? decode_partial_kernel<D, true> : decode_partial_kernel<D, false>),
-                           grid, dim3(DC_THREADS), 0, s, q, k, v, po, pml, N, Hq, sl2, kps, ns, kv_batch, ncs, o1, lse);
+        const bool ahead = kps <= DC_AHEAD_MAX_KEYS;
+        const int heads = heads_side_by_side((long)B * Hkv * ns, Hkv);
+        auto* kernel = ahead ? decode_partial_kernel<D, true, 1> : decode_partial_kernel<D, false, 1>;
+        if (heads == 2) kernel = ahead ? decode_partial_kernel<D, true, 2> : decode_partial_kernel<D, false, 2>;
+        if (heads == 4) kernel = ahead ? decode_partial_kernel<D, true, 4> : decode_partial_kernel<D, false, 4>;
+        grid.y = Hkv / heads;
+        hipLaunchKernelGGL(kernel, grid, dim3(DC_THREADS * heads), 0, s, q, k, v, po, pml, N, Hq, sl2, kps, ns, kv_batch, ncs,
+                           o1, lse);
         const int rc = launch_status("decode_partial");
         if (rc) return rc;
     }

@@ -65,6 +65,45 @@ __global__ __launch_bounds__(KN_THREADS) void knorm_generic_kernel(
     if (lane == 0) norms[(int64_t)b * n_vis + row] = sqrtf(a);
 }
 
+// The candidates' norms of a sample, added up from their parts: keys in LDS and, if asked for, norms_out.  A thread takes RU
+// candidates at a time, PU parts of each: 32 independent loads in flight per round trip (the workgroup is alone on its CU
+// and the reads are all latency); every candidate's parts are added in index order, so the sums do not depend on the grouping.
+template <int RU, int PU>
+__device__ __forceinline__ void collect_norms(const float* __restrict__ src, int n_parts, int64_t part_stride, int do_sqrt,
+                                              float* __restrict__ norms_out, int n_vis, unsigned* sel_keys) {
+    const int tid = threadIdx.x;
+    for (int i0 = tid; i0 < n_vis; i0 += SEL_THREADS * RU) {
+        int row[RU];
+        float v[RU];
+#pragma unroll
+        for (int r = 0; r < RU; ++r) {
+            row[r] = min(i0 + r * SEL_THREADS, n_vis - 1);      // past the end: a valid row, not stored
+            v[r] = 0.f;                                         // (0 + part 0 is part 0 exactly)
+        }
+        for (int p = 0; p < n_parts; p += PU) {                 // the last group may be short: its loads repeat
+            float w[RU][PU];                                     // the last part and are not added
+#pragma unroll
+            for (int r = 0; r < RU; ++r)
+#pragma unroll
+                for (int j = 0; j < PU; ++j)
+                    w[r][j] = src[(int64_t)min(p + j, n_parts - 1) * part_stride + row[r]];
+#pragma unroll
+            for (int r = 0; r < RU; ++r)
+#pragma unroll
+                for (int j = 0; j < PU; ++j)
+                    if (p + j < n_parts) v[r] += w[r][j];
+        }
+#pragma unroll
+        for (int r = 0; r < RU; ++r) {
+            const int i = i0 + r * SEL_THREADS;
+            if (i >= n_vis) continue;
+            const float val = do_sqrt ? sqrtf(v[r]) : v[r];
+            if (norms_out) norms_out[i] = val;
+            sel_keys[i] = __float_as_uint(val);      // val >= 0: bit order = value order
+        }
+    }
+}
+
 __global__ __launch_bounds__(SEL_THREADS) void select_smallest_kernel(
     const float* __restrict__ parts, int n_parts, int64_t part_stride, int64_t sample_stride,
     int64_t offset, int do_sqrt, float* __restrict__ norms_out, int T, int vis_start, int n_vis_max,
@@ -81,42 +120,14 @@ __global__ __launch_bounds__(SEL_THREADS) void select_smallest_kernel(
     const int keep = min(keep_max, n_vis);
     const int T_real = T - (n_vis_max - n_vis);
     const float* src = parts + (int64_t)b * sample_stride + offset;
-    // Four candidates per thread at a time, eight parts each: 32 independent loads in flight per round trip
-    // (the workgroup is alone on its CU and the reads are all latency); every candidate's parts are added in
-    // index order, so the sums do not depend on the grouping.
-    constexpr int RU = 4;
-    for (int i0 = tid; i0 < n_vis; i0 += SEL_THREADS * RU) {
-        int row[RU];
-        float v[RU];
-#pragma unroll
-        for (int r = 0; r < RU; ++r) {
-            row[r] = min(i0 + r * SEL_THREADS, n_vis - 1);      // past the end: a valid row, not stored
-            v[r] = 0.f;                                         // (0 + part 0 is part 0 exactly)
-        }
-        for (int p = 0; p < n_parts; p += 8) {                  // the last group may be short: its loads repeat
-            float w[RU][8];                                     // the last part and are not added
-#pragma unroll
-            for (int r = 0; r < RU; ++r)
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    w[r][j] = src[(int64_t)min(p + j, n_parts - 1) * part_stride + row[r]];
-#pragma unroll
-            for (int r = 0; r < RU; ++r)
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (p + j < n_parts) v[r] += w[r][j];
-        }
-#pragma unroll
-        for (int r = 0; r < RU; ++r) {
-            const int i = i0 + r * SEL_THREADS;
-            if (i >= n_vis) continue;
-            const float val = do_sqrt ? sqrtf(v[r]) : v[r];
-            if (norms_out) norms_out[(int64_t)b * n_vis_max + i] = val;
-            sel_keys[i] = __float_as_uint(val);      // val >= 0: bit order = value order
-        }
-    }
-    if (norms_out)
-        for (int i = n_vis + tid; i < n_vis_max; i += SEL_THREADS) norms_out[(int64_t)b * n_vis_max + i] = 0.f;
+    float* norms = norms_out ? norms_out + (int64_t)b * n_vis_max : nullptr;
+    // (up to a candidate a thread, groups of four would load three times in vain: one sample of 576 in 32 parts 8.2 us a
+    // launch with eight parts at a time, 7.0 with all; 6272 in 4 parts 11.2 us by four candidates, 9.9 by eight)
+    if (n_vis <= SEL_THREADS && n_parts > 8) collect_norms<1, 32>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
+    else if (n_parts <= 4) collect_norms<8, 4>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
+    else collect_norms<4, 8>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
+    if (norms)
+        for (int i = n_vis + tid; i < n_vis_max; i += SEL_THREADS) norms[i] = 0.f;
     // text before and after the visual span is always kept; padding rows of the output name the last row
     for (int i = tid; i < vis_start; i += SEL_THREADS) out[i] = i;
     for (int i = vis_start + n_vis + tid; i < T_real; i += SEL_THREADS) out[i - n_vis + keep] = i;

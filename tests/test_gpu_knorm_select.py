@@ -95,6 +95,23 @@ def test_every_way_the_cut_is_found(vc, n):
             assert got[b, keep] == n
 
 
+# candidates up to a thread each and more, parts up to one round trip's (4, 8, 32) and one over
+@pytest.mark.parametrize("n,P", [(n, P) for n in (1, 700, 1024, 1025, 8193) for P in (1, 4, 5, 8, 9, 32, 33)])
+def test_norms_from_any_number_of_parts(vc, n, P):
+    B, T, vis_start, keep = 2, n + 3, 2, max(1, n // 3)
+    parts = np.random.default_rng(100 * n + P).random((P, B * T), dtype=np.float32)
+    norms, idx = vc.vitcop_select_from_sumsq(torch.from_numpy(parts).cuda(), B, T, vis_start, n, keep)
+    norms, idx = norms.cpu().numpy(), idx.cpu().numpy()
+    total = np.zeros(B * T, np.float32)
+    for p in range(P):
+        total += parts[p]                                             # in index order, in 32 bits: the same sums
+    want = np.sqrt(total.reshape(B, T)[:, vis_start:vis_start + n])
+    assert np.all(np.abs(norms - want) <= np.spacing(want))           # (the root within a unit in the last place)
+    for b in range(B):
+        kept = np.sort(np.argsort(norms[b], kind="stable")[:keep]) + vis_start
+        assert idx[b].tolist() == [0, 1] + kept.tolist() + [T - 1]
+
+
 def test_planted_norms_and_power_of_two_scaling(vc):
     k = np.zeros((1, 300, 4, 128), np.float32)
     g = np.random.default_rng(9)

@@ -1,7 +1,8 @@
 // Compaction of the surviving tokens: dst[b,j,:] = src[b, idx[b,j], :] for up
 // to eight tensors in one launch (the token removal implied by
-// TopK(V_current, ...) in Alg. 1).  Pure HBM copy: 16-byte loads and stores,
-// one workgroup per (output row, tensor).
+// TopK(V_current, ...) in Alg. 1).  A copy: 16-byte loads and stores, one workgroup per (output row, tensor).  The rows
+// are loaded the ordinary way, since what chose them has often just read them and some are still in a cache (three
+// tensors of 4 x 384 rows of 8 KB after the norms of the same K: 20.8 us with non-temporal loads, 17.5 without).
 #include "vitcop_internal.h"
 #include "device_utils.h"
 
@@ -30,7 +31,7 @@ __global__ __launch_bounds__(CP_THREADS) void compact_kernel(GatherArgs a,
         const uint4* s4 = (const uint4*)src;
         uint4* d4 = (uint4*)dst;
         for (int i = threadIdx.x; i < n; i += CP_THREADS)
-            st_nt16(d4 + i, ld_nt16(s4 + i));
+            st_nt16(d4 + i, s4[i]);
     } else {
         const int n = (int)(g.row_bytes >> 2);
         const uint32_t* s1 = (const uint32_t*)src;

@@ -2,7 +2,8 @@
 // to eight tensors in one launch (the token removal implied by
 // TopK(V_current, ...) in Alg. 1).  A copy: 16-byte loads and stores, one workgroup per (output row, tensor).  The rows
 // are loaded the ordinary way, since what chose them has often just read them and some are still in a cache (three
-// tensors of 4 x 384 rows of 8 KB after the norms of the same K: 20.8 us with non-temporal loads, 17.5 without).
+// tensors of 4 x 384 rows of 8 KB after the norms of the same K: the three launches 45.4 us with non-temporal loads, 42.7
+// without; in a trace this one takes 20.8 to 21.9 us and 17.5 to 19.3).
 #include "vitcop_internal.h"
 #include "device_utils.h"
 

@@ -194,8 +194,12 @@ __global__ __launch_bounds__(DC_THREADS) void decode_group_kernel(
     for (int i = 0; i < BLOCKS; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;                            // of head l16 (m over all its keys, l over this lane's)
 
+    // Rows past the end: of K the last one, masked below; of V zeros, for which the descriptor ends with the last row (a
+    // copy would not do: the zero probability of an infinite value is NaN).  A sample's cache is below 4 GiB.
+    const unsigned row_b = (unsigned)row * 2;
+    const auto v_desc = __builtin_amdgcn_make_buffer_rsrc((void*)vb, 0, (key_end - 1) * row_b + 2 * D, 0x00020000);
     u32x4 kr[2][STEPS], vr[VL];
-    auto load = [&](int key0) __attribute__((always_inline)) {           // keys past the end: the last one, masked below
+    auto load = [&](int key0) __attribute__((always_inline)) {
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const uint16_t* p = kb + min(key0 + 16 * t + l16, key_end - 1) * row + 8 * g4;
@@ -204,8 +208,8 @@ __global__ __launch_bounds__(DC_THREADS) void decode_group_kernel(
         }
 #pragma unroll
         for (int i = 0; i < VL; ++i)
-            vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
-                vb + min(key0 + RPL * i + lane / LPR, key_end - 1) * row + 8 * (lane % LPR)));
+            vr[i] = __builtin_amdgcn_raw_buffer_load_b128(
+                v_desc, min(key0 + RPL * i + lane / LPR, key_end) * row_b + 16 * (lane % LPR), 0, 2 /* non-temporal */);
     };
     typedef __attribute__((ext_vector_type(4))) short s16x4;
     typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -283,8 +287,8 @@ __global__ __launch_bounds__(DC_THREADS) void decode_group_kernel(
         }
     };
     attend(std::integral_constant<int, 3>{});
-    // An infinite value of V times the zero parts of a probability is no number: such outputs (alone) are summed again
-    // with the first parts only, which are zero where the probability is.
+    // An infinite value of V times a zero among the later parts of its probability is no number: such outputs (alone)
+    // are summed again with the first parts only, of which one is zero only where the probability itself is.
     bool nan = false;
 #pragma unroll
     for (int i = 0; i < BLOCKS; ++i)

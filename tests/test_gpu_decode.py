@@ -82,6 +82,23 @@ def test_grouped_query_heads_with_infinities(vc):
     assert np.abs(out - ref).max() < 1e-2 and np.abs(lse - ref_lse).max() < 1e-3
 
 
+# the newest row of a cache is the last of its slice's last, partly filled tile (of 32 keys a wavefront)
+@pytest.mark.parametrize("B,N,Hq,Hkv,d", [(1, 1, 8, 2, 128), (1, 31, 8, 2, 64), (2, 129, 8, 2, 128), (1, 200, 8, 2, 128),
+                                          (1, 257, 14, 2, 64), (40, 165, 28, 4, 128), (1, 129, 34, 2, 128)])
+def test_an_infinite_value_in_the_last_row(vc, B, N, Hq, Hkv, d):
+    # it reaches its channel of every head of its KV head, and nothing else: the slots past the last key count for nothing
+    t = I.qkv_tensors(9850 + N + Hq, 1, N, Hq, Hkv, d)
+    t = {n: np.repeat(x, B, axis=0) for n, x in t.items()}
+    plain, plain_lse = run(vc, t)
+    v = t["v"].copy()
+    v[B - 1, N - 1, Hkv - 1, 5] = 0x7F80                          # +inf
+    out, lse = run(vc, dict(t, v=v))
+    want = plain.reshape(B, Hkv, Hq // Hkv, d).copy()
+    want[B - 1, Hkv - 1, :, 5] = np.inf
+    assert np.array_equal(out.reshape(want.shape), want)
+    assert np.array_equal(lse, plain_lse)
+
+
 def test_scale_large_logits_and_structure(vc):
     t = I.qkv_tensors(9600, 2, 300, 4, 2, 128, std=3.0)
     out, lse = run(vc, t, scale=0.11)

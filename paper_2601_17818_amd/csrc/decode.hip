@@ -110,6 +110,8 @@ __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
             ku = ld_nt16(kb + kc * row);
             vu = ld_nt16(vb + kc * row);
         }
+        // a slot past the end holds a copy of the last row: the zero probability of an infinite value would be NaN
+        if (KPW > 1 && !live) vu = make_uint4(0, 0, 0, 0);
         const float kf[8] = {bf16_lo(ku.x), bf16_hi(ku.x), bf16_lo(ku.y), bf16_hi(ku.y),
                              bf16_lo(ku.z), bf16_hi(ku.z), bf16_lo(ku.w), bf16_hi(ku.w)};
         const float vf[8] = {bf16_lo(vu.x), bf16_hi(vu.x), bf16_lo(vu.y), bf16_hi(vu.y),

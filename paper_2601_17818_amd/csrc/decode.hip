@@ -164,9 +164,12 @@ __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
 // head as its only query, and O^T += V^T P^T, V transposed on the way out of LDS (ds_read_b64_tr_b16).  The key of
 // element 4 t + r of a lane's 8 in the second product is 16 t + 4 (lane / 16) + r, which is where the scores are.  The
 // probabilities stay 32-bit: each is the sum of three bf16 (24 bits), one product for each.
+// Registers for three workgroups on a CU (d = 64: four): many pairs of a few keys are a chain of latencies each, which
+// only other workgroups fill (us with two and with three: 250 samples x 40 keys x 32 / 16 x 128 35.2, 30.2; x 100 x 28 / 4
+// 16.2, 14.9; where the keys are many it is the loads that count, 64 x 2000 x 28 / 4 47.6, 47.9).
 constexpr int DG_MAX_G = 16, DG_KEYS = 32;
 template <int D>
-__global__ __launch_bounds__(DC_THREADS) void decode_group_kernel(
+__global__ __launch_bounds__(DC_THREADS, D == 128 ? 3 : 4) void decode_group_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ part_o, float* __restrict__ part_ml, int N, int Hq, int Hkv, int g0, int G,
     float scale_log2e, int keys_per_split, int n_splits, int64_t kv_batch,
@@ -221,8 +224,10 @@ __global__ __launch_bounds__(DC_THREADS) void decode_group_kernel(
     const int first = key_begin + wv * DG_KEYS;
     auto attend = [&](auto parts_c) __attribute__((always_inline)) {     // PARTS: bf16 summands of a probability
         constexpr int PARTS = decltype(parts_c)::value;
-        if (first < key_end) load(first);
+        constexpr bool AHEAD = PARTS > 1;                    // (the registers of the second pass hold the first's outputs)
+        if (AHEAD && first < key_end) load(first);
         for (int key0 = first; key0 < key_end; key0 += 4 * DG_KEYS) {
+            if (!AHEAD) load(key0);
             f32x4 s[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(DC_THREADS) void decode_group_kernel(
 #pragma unroll
             for (int i = 0; i < VL; ++i)
                 *reinterpret_cast<u32x4*>(mine + (RPL * i + lane / LPR) * VROW + lane % LPR * 16) = vr[i];
-            if (key0 + 4 * DG_KEYS < key_end) load(key0 + 4 * DG_KEYS);      // (uniform) in flight from here on
+            if (AHEAD && key0 + 4 * DG_KEYS < key_end) load(key0 + 4 * DG_KEYS);      // (uniform) in flight from here on
             float p[8], top = -INFINITY;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {

@@ -52,15 +52,16 @@ __device__ __forceinline__ void decode_combine(const float (&sm)[WAVES][GMAX][2]
     }
 }
 
-// One query head per KV head.  HBM-bound.  HEADS neighbouring heads' rows of a key lie side by side in the cache, and a
-// wavefront reads them together: pieces of 512 bytes and more instead of 256 at a stride of Hkv * 2 D bytes (64 samples x
-// 32 heads x 318 keys 59.6 -> 54.0 us, 5.6 -> 6.2 TB/s; x 118 keys 24.0 -> 22.1; x 640 keys 115.8 -> 102.2, 6.6 TB/s).  Four
-// wavefronts per head as before, so the keys of each wavefront, and the loads in flight, are the same number.
+// One query head per KV head (G = 1), or two where group_on_vectors says so.  HBM-bound.  HEADS neighbouring heads' rows of
+// a key lie side by side in the cache, and a wavefront reads them together: pieces of 512 bytes and more instead of 256 at a
+// stride of Hkv * 2 D bytes (64 samples x 32 heads x 318 keys 59.6 -> 54.0 us, 5.6 -> 6.2 TB/s; x 118 keys 24.0 -> 22.1; x 640
+// keys 115.8 -> 102.2, 6.6 TB/s).  Four wavefronts per head as before, so the keys of each wavefront, and the loads in flight,
+// are the same number.
 // AHEAD: the next rows of K and V are requested before the current ones are used.  Pays for slices of a few hundred
 // keys (one head at a time: 64 samples x 32 heads x 318 keys 61.7 -> 57.6 us, 5.4 -> 5.8 TB/s; x 116 keys 26.4 -> 23.9); not
-// for long ones (32 x 4096 keys 305 -> 321 us).
+// for long ones (32 x 4096 keys 305 -> 321 us), nor with two query heads, which have work to do meanwhile.
 constexpr int DC_AHEAD_MAX_KEYS = 1024;
-template <int D, bool AHEAD, int HEADS>
+template <int D, bool AHEAD, int HEADS, int G = 1>
 __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     float* __restrict__ part_o, float* __restrict__ part_ml, int N, int H, float scale_log2e, int keys_per_split,
@@ -73,12 +74,17 @@ __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int c = lane % LPK, kq = lane / (LPK * HEADS), hs = lane / LPK % HEADS, h = h0 + hs;
 
-    const uint4 u = *reinterpret_cast<const uint4*>(q + ((int64_t)b * H + h) * D + 8 * c);
-    const float qv[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
-                         bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
-    float m = -INFINITY, l = 0.f, acc[8];
+    float qv[G][8], m[G], l[G], acc[G][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    for (int g = 0; g < G; ++g) {
+        const uint4 u = *reinterpret_cast<const uint4*>(q + (((int64_t)b * H + h) * G + g) * D + 8 * c);
+        qv[g][0] = bf16_lo(u.x); qv[g][1] = bf16_hi(u.x); qv[g][2] = bf16_lo(u.y); qv[g][3] = bf16_hi(u.y);
+        qv[g][4] = bf16_lo(u.z); qv[g][5] = bf16_hi(u.z); qv[g][6] = bf16_lo(u.w); qv[g][7] = bf16_hi(u.w);
+        m[g] = -INFINITY;
+        l[g] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
+    }
     // caches of different lengths: sample b attends over its n_cached_samples[b] rows and the appended one;
     // slices past them see no live key and hand on an empty partial (max -inf, sum 0)
     const int n_keys = n_cached_samples ? min(max(n_cached_samples[b], 0) + 1, N) : N;
@@ -116,50 +122,57 @@ __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
                              bf16_lo(ku.z), bf16_hi(ku.z), bf16_lo(ku.w), bf16_hi(ku.w)};
         const float vf[8] = {bf16_lo(vu.x), bf16_hi(vu.x), bf16_lo(vu.y), bf16_hi(vu.y),
                              bf16_lo(vu.z), bf16_hi(vu.z), bf16_lo(vu.w), bf16_hi(vu.w)};
-        float s = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s = fmaf(qv[e], kf[e], s);
+        for (int g = 0; g < G; ++g) {
+            float s = 0.f;
 #pragma unroll
-        for (int o = LPK / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);          // over the lanes of this key
-        s = live ? s * scale_log2e : -INFINITY;
-        const float m_new = fmaxf(m, s);
-        // m_new is -inf only while nothing live has been seen: then alpha and p must be 0, not NaN
-        const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
-        const float p = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - m_new);
-        m = m_new;
-        l = fmaf(l, alpha, p);
+            for (int e = 0; e < 8; ++e) s = fmaf(qv[g][e], kf[e], s);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = fmaf(acc[e], alpha, p * vf[e]);
+            for (int o = LPK / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);      // over the lanes of this key
+            s = live ? s * scale_log2e : -INFINITY;
+            const float m_new = fmaxf(m[g], s);
+            // m_new is -inf only while nothing live has been seen: then alpha and p must be 0, not NaN
+            const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[g] - m_new);
+            const float p = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s - m_new);
+            m[g] = m_new;
+            l[g] = fmaf(l[g], alpha, p);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[g][e] = fmaf(acc[g][e], alpha, p * vf[e]);
+        }
     }
     // merge the KPW key sub-groups of the wavefront (lanes with the same c), then the wavefronts
-    __shared__ float sm[WAVES][HEADS][2];
-    __shared__ float so[WAVES][HEADS][D];
+    __shared__ float sm[WAVES][HEADS * G][2];
+    __shared__ float so[WAVES][HEADS * G][D];
 #pragma unroll
-    for (int o = LPK * HEADS; o < 64; o <<= 1) {
-        const float mo = __shfl_xor(m, o, 64), lo = __shfl_xor(l, o, 64);
-        const float mn = fmaxf(m, mo);
-        const float a0 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
-        const float a1 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mo - mn);
-        l = l * a0 + lo * a1;
+    for (int g = 0; g < G; ++g) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = acc[e] * a0 + __shfl_xor(acc[e], o, 64) * a1;
-        m = mn;
-    }
-    if (kq == 0) {
-        if (c == 0) {
-            sm[wv][hs][0] = m;
-            sm[wv][hs][1] = l;
+        for (int o = LPK * HEADS; o < 64; o <<= 1) {
+            const float mo = __shfl_xor(m[g], o, 64), lo = __shfl_xor(l[g], o, 64);
+            const float mn = fmaxf(m[g], mo);
+            const float a0 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[g] - mn);
+            const float a1 = mn == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mo - mn);
+            l[g] = l[g] * a0 + lo * a1;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[g][e] = acc[g][e] * a0 + __shfl_xor(acc[g][e], o, 64) * a1;
+            m[g] = mn;
         }
+        if (kq == 0) {
+            if (c == 0) {
+                sm[wv][hs * G + g][0] = m[g];
+                sm[wv][hs * G + g][1] = l[g];
+            }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) so[wv][hs][8 * c + e] = acc[e];
+            for (int e = 0; e < 8; ++e) so[wv][hs * G + g][8 * c + e] = acc[g][e];
+        }
     }
     __syncthreads();
-    decode_combine<D, HEADS, WAVES>(sm, so, HEADS, b, h0, H, n_splits, split, part_o, part_ml, out, lse);
+    decode_combine<D, HEADS * G, WAVES>(sm, so, HEADS * G, b, h0 * G, H * G, n_splits, split, part_o, part_ml, out, lse);
 }
 
 // Query heads that share a KV head (2 to 16 of them a pass).  On the vector pipe every key costs each of them 16 FMAs a
 // lane, a reduction over lanes and an exponential: 64 samples x 318 keys x 28 / 4 heads x 128 took 45 us for 42 MB (now
-// 12.5), 32 x 4096 keys 121 (51), 64 x 400 x 16 / 4 x 64 20.8 (8.7), 64 x 318 x 32 / 16 37.6 (33.9).  Here a wavefront
+// 12.5), 32 x 4096 keys 121 (51), 64 x 400 x 16 / 4 x 64 20.8 (8.7), 64 x 318 x 32 / 16 37.6 (33.9); where that is still the
+// faster way: group_on_vectors.  Here a wavefront
 // takes 32 keys at a time: scores S^T = K Q^T (16x16x32: a lane holds 4 keys of one head), the softmax with the lane's
 // head as its only query, and O^T += V^T P^T, V transposed on the way out of LDS (ds_read_b64_tr_b16).  The key of
 // element 4 t + r of a lane's 8 in the second product is 16 t + 4 (lane / 16) + r, which is where the scores are.  The
@@ -370,6 +383,19 @@ static int group_splits(int B, int N, int Hkv) {
     return (int)std::max(1L, std::min((DG_WGS + wgs - 1) / wgs, (N + 127L) / 128));
 }
 
+// Two query heads to a KV head (`pairs`: of a sample and a KV head) go to decode_partial_kernel where a workgroup's tile of
+// 128 keys is mostly empty, the more so the more pairs wait for their turn, and where the pairs are so many that the bytes
+// alone count, which its small workgroups draw faster.  On the matrix cores and on this kernel, us, of 128 channels: 16 pairs
+// x 16 keys 4.5, 3.9, x 48 4.8, 5.2; 512 x 32 7.0, 6.6, x 48 7.6, 7.9; 2000 x 16 16.3, 9.5, x 64 20.7, 19.2, x 100 24.0, 27.6;
+// 8000 x 16 55, 27, x 317 238, 217; 4000 x 100 42, 44, x 640 236, 230.  Of 64 channels: 4000 x 16 16.3, 15.5, x 64 21.1, 21.8,
+// x 100 25.4, 29.2, x 317 71, 67; 2048 x 317 38.7, 42.4; 8000 x 640 279, 234.  Three and four query heads were faster there
+// up to 16 keys alone (8000 pairs x 8 keys x 4 heads 58, 52; x 32 58, 60), more of them at no size.
+static bool group_on_vectors(long pairs, int N, int group, int d) {
+    if (group != 2) return false;
+    if (pairs > 12 * 256) return d == 128 || N <= 16 || N > 128;
+    return d == 128 && N <= std::max(16L, std::min(64L, pairs / 16));
+}
+
 // Heads that decode_partial_kernel reads side by side: what the fullest CU gets to do, `pairs` (sample, head, slice)
 // dealt out `heads` at a time, times the time of one against that of reading 256 bytes a row.  Four leave a CU with one
 // workgroup, and nothing beside its start and end, unless there are more than 256 such.  Measured, us in one, two and four:
@@ -398,7 +424,7 @@ template <int D>
 static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                            int B, int N, int Hq, int Hkv, float scale, void* ws, hipStream_t s, int64_t kv_batch,
                            DecodeParts* hand_over, const int32_t* ncs) {
-    const bool grouped = Hq > Hkv;
+    const bool on_vectors = Hq > Hkv && group_on_vectors((long)B * Hkv, N, Hq / Hkv, D), grouped = Hq > Hkv && !on_vectors;
     const int ns = grouped ? group_splits(B, N, Hkv) : decode_splits(B, N, Hkv);
     const int kps = ((N + ns - 1) / ns + 63) / 64 * 64;
     float* po = static_cast<float*>(ws);
@@ -418,12 +444,13 @@ static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t*
         }
     } else {
         const bool ahead = kps <= DC_AHEAD_MAX_KEYS;
-        const int heads = heads_side_by_side((long)B * Hkv * ns, Hkv);
+        const int heads = on_vectors ? 1 : heads_side_by_side((long)B * Hkv * ns, Hkv);
         auto* kernel = ahead ? decode_partial_kernel<D, true, 1> : decode_partial_kernel<D, false, 1>;
         if (heads == 2) kernel = ahead ? decode_partial_kernel<D, true, 2> : decode_partial_kernel<D, false, 2>;
         if (heads == 4) kernel = ahead ? decode_partial_kernel<D, true, 4> : decode_partial_kernel<D, false, 4>;
+        if (on_vectors) kernel = decode_partial_kernel<D, false, 1, 2>;
         grid.y = Hkv / heads;
-        hipLaunchKernelGGL(kernel, grid, dim3(DC_THREADS * heads), 0, s, q, k, v, po, pml, N, Hq, sl2, kps, ns, kv_batch, ncs,
+        hipLaunchKernelGGL(kernel, grid, dim3(DC_THREADS * heads), 0, s, q, k, v, po, pml, N, Hkv, sl2, kps, ns, kv_batch, ncs,
                            o1, lse);
         const int rc = launch_status("decode_partial");
         if (rc) return rc;

@@ -82,13 +82,27 @@ def test_grouped_query_heads_with_infinities(vc):
     assert np.abs(out - ref).max() < 1e-2 and np.abs(lse - ref_lse).max() < 1e-3
 
 
+# two query heads to a KV head, on both sides of each line between the vector and the matrix-core kernel: few pairs (16 keys),
+# up to 64 keys by their number, many pairs (of 64 channels: from 129 keys on and up to 16)
+@pytest.mark.parametrize("B,N,Hkv,d", [(2, 1, 2, 128), (2, 16, 2, 128), (2, 17, 2, 128), (34, 34, 16, 128), (33, 34, 16, 128),
+                                       (64, 64, 16, 128), (64, 65, 16, 128), (193, 65, 16, 128), (192, 66, 16, 128),
+                                       (193, 16, 16, 64), (193, 17, 16, 64), (193, 129, 16, 64), (192, 129, 16, 64)])
+def test_two_query_heads_to_a_kv_head(vc, B, N, Hkv, d):
+    t = I.qkv_tensors(9750 + N + B, B, N, 2 * Hkv, Hkv, d)
+    out, lse = run(vc, t)
+    ref, ref_lse = Dc.decode_attention(t["q"][:, -1], t["k"], t["v"])
+    assert_attention_close(out, ref, f"decode N={N}, {2 * Hkv} / {Hkv}")
+    assert np.abs(lse - ref_lse).max() < 1e-3
+
+
 # the newest row of a cache is the last of its slice's last, partly filled tile (of 32 keys a wavefront; with one query head
 # per KV head: of the keys of a load, where heads are read one, two and four at a time, slices long and short)
 @pytest.mark.parametrize("B,N,Hq,Hkv,d", [(1, 1, 8, 2, 128), (1, 31, 8, 2, 64), (2, 129, 8, 2, 128), (1, 200, 8, 2, 128),
                                           (1, 257, 14, 2, 64), (40, 165, 28, 4, 128), (1, 129, 34, 2, 128),
                                           (1, 201, 2, 2, 128), (1, 203, 4, 4, 64), (32, 33, 32, 32, 128),
                                           (64, 33, 32, 32, 128), (32, 37, 32, 32, 64), (128, 67, 16, 16, 64),
-                                          (32, 1029, 32, 32, 64)])
+                                          (32, 1029, 32, 32, 64), (2, 15, 4, 2, 128), (64, 31, 16, 8, 128),
+                                          (193, 131, 32, 16, 64)])
 def test_an_infinite_value_in_the_last_row(vc, B, N, Hq, Hkv, d):
     # it reaches its channel of every head of its KV head, and nothing else: the slots past the last key count for nothing
     t = I.qkv_tensors(9850 + N + Hq, 1, N, Hq, Hkv, d)

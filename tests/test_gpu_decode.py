@@ -42,12 +42,13 @@ def test_matches_oracle(vc, B, N, Hq, Hkv, d):
                                      (64, 1, 32, 128), (64, 17, 32, 128), (128, 65, 16, 128), (64, 33, 32, 64),
                                      (64, 1030, 32, 64), (64, 50, 27, 128), (26, 20, 40, 128), (40, 20, 32, 64)])
 def test_heads_side_by_side(vc, B, N, H, d):
-    t = I.qkv_tensors(9900 + N + H, 2, N, H, H, d)
-    out, lse = run(vc, {n: np.concatenate([x[:1], np.repeat(x[1:], B - 1, axis=0)]) for n, x in t.items()})
+    # three different samples dealt out at random, and every sample's result against its own
+    t = I.qkv_tensors(9900 + N + H, 3, N, H, H, d)
+    of = np.random.default_rng(B + N).integers(0, 3, B)
+    out, lse = run(vc, {n: x[of] for n, x in t.items()})
     ref, ref_lse = Dc.decode_attention(t["q"][:, -1], t["k"], t["v"])
-    for b in (0, 1, B - 1):
-        assert_attention_close(out[b:b + 1], ref[min(b, 1):min(b, 1) + 1], f"decode N={N}, sample {b}")
-        assert np.abs(lse[b] - ref_lse[min(b, 1)]).max() < 1e-3
+    assert_attention_close(out, ref[of], f"decode N={N}")
+    assert np.abs(lse - ref_lse[of]).max() < 1e-3
 
 
 # query heads that share a KV head: 2, 3, 7, 16 and 17 of them (a second pass), tiles of 32 keys a wavefront and 128 a

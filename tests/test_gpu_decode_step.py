@@ -210,3 +210,32 @@ def test_decode_step_per_sample_cache_lengths(vc, B, dims, lengths):
             n = ns[b]
             assert np.array_equal(host_bits(kc)[b, :n], k[b, :n]) and np.array_equal(host_bits(vcache)[b, :n], v[b, :n])
             assert not host_bits(kc)[b, n + 1:].any() and not host_bits(vcache)[b, n + 1:].any()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,lengths", [
+    (3, 4, 4, 128, (200, 0, 17)),              # one query head per KV head: several slices, empty ones among them
+    (64, 8, 8, 128, (0, 90, 3, 33, 16, 64)),   # two heads read side by side: 8 wavefronts, not all of which have a key
+    (256, 8, 8, 128, (0, 90, 3, 33, 16, 64)),  # four heads, 16 wavefronts
+    (256, 8, 8, 64, (0, 90, 3, 33, 16, 64)),
+    (64, 16, 8, 128, (0, 30, 3, 15, 16, 7))])  # two query heads per KV head on the vector kernel
+def test_per_sample_cache_lengths_of_vector_kernels(vc, B, Hq, Hkv, d, lengths):
+    # one layer, the lengths dealt out at random: every sample's output against the oracle over the samples of its length
+    D, F, cap = 512, 640, 256
+    of = np.random.default_rng(B + d).integers(0, len(lengths), B)
+    of[:len(lengths)] = np.arange(len(lengths))
+    ns = [lengths[i] for i in of]
+    h, layers = model(7800 + B + Hq, 1, B, 1, D, Hq, Hkv, d, F)
+    h = h[:, 0]
+    pos = np.array([300 + 11 * b for b in range(B)], dtype=np.int32)
+    k, v = (I.normal_bf16(7900 + d, i, (B, max(lengths), Hkv, d)) for i in (0, 1))
+    kc, vcache = cache_pair(B, cap, Hkv, d)
+    for cache, rows in ((kc, k), (vcache, v)):
+        cache[:, :max(lengths)] = dev(rows)    # (what lies past a sample's rows is not to be seen)
+    plan = vc.DecoderDecodePlan(dev(h), torch.from_numpy(pos).cuda(), [{n: dev(w) for n, w in layers[0].items()}], Hq, Hkv, d,
+                                [(kc, vcache)], [ns])
+    y = host_f64(plan.run())
+    for i, n in enumerate(lengths):
+        at = np.flatnonzero(of == i)
+        ref = Dc.decode_step(h[at], layers, [(k[at, :n], v[at, :n])], pos[at], Hq, Hkv, d)
+        assert_stream_close(y[at], ref["y"], f"decode step output, samples of {n} keys")
+        rope_close(host_bits(kc)[at, n], ref["appended"][0][0], f"appended K, samples of {n} keys")

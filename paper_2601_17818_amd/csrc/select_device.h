@@ -17,7 +17,7 @@ constexpr int SEL_THREADS = 1024;
 constexpr int SEL_DIGIT = 10, SEL_LIST = 64;
 
 struct SelectShared {
-    unsigned hist[1 << SEL_DIGIT];
+    alignas(16) unsigned hist[1 << SEL_DIGIT];       // (read and cleared 16 bytes at a time)
     unsigned list[SEL_LIST];
     unsigned low[SEL_THREADS / 64], high[SEL_THREADS / 64];
     unsigned wave_tot[SEL_THREADS / 64];

@@ -121,10 +121,7 @@ __global__ __launch_bounds__(VIC_THREADS) void vic_parent_kernel(
     float best = INFINITY, best2 = INFINITY;                 // (best2 squared: a root only where it may matter)
     int best_j = 0x7fffffff;
     vic_distances(gram + img * batch, stride, sq + img * sq_batch, sq_half, n, i0,
-                  [&](int j) {
-                      const float2 xy = *reinterpret_cast<const float2*>(pos + 2 * j);
-                      return make_float3(xy.x, xy.y, rho[j]);
-                  },
+                  [&](int j) { return make_float3(pos[2 * j], pos[2 * j + 1], rho[j]); },      // (pos: aligned to 4 bytes)
                   [&](int j, float d2, const float3& col) {
                       const float dx = col.x - px, dy = col.y - py;
                       if (col.z > rho_i && dx * dx + dy * dy <= tau2 && d2 < best2) {

@@ -307,6 +307,28 @@ def test_full_schedule_matches_oracle(vc, stage2_layer, schedule):
     assert_stream_close(host_f64(y), ref["y"], "full schedule output")
 
 
+def test_full_schedule_with_grid_positions_at_any_address(vc):
+    # the positions on the grid are floats of the caller's: at a multiple of 4 bytes they give what they give at 16
+    D, Hq, Hkv, d, F, vs, n, tail = 256, 4, 2, 128, 384, 12, 150, 10
+    h, layers, xy = full_case(9970, vs, n, tail, D, Hq, Hkv, d, F, 2, 16, 6)
+    pos = torch.arange(vs + n + tail, dtype=torch.int32, device="cuda")[None]
+    wd = [{k: dev(v) for k, v in w.items()} for w in layers]
+
+    def run(offset):
+        flat = torch.zeros((2 * n + 4,), dtype=torch.float32, device="cuda")
+        grid = flat[offset:offset + 2 * n].view(1, n, 2)
+        grid.copy_(torch.from_numpy(xy.astype(np.float32)[None]))
+        plan = vc.FullSchedulePlan(dev(h), pos, wd, Hq, Hkv, d, vs, n,
+                                   {"layer": 1, "budget": 60, "n_centers": 6, "d_c": 8.0, "tau": 0.6, "xy": grid}, ())
+        y, p = plan.run()
+        torch.cuda.synchronize()
+        return plan.labels.clone(), y.clone(), p.clone()
+
+    want = run(0)
+    for offset in (1, 2, 3):
+        assert all(torch.equal(a, b) for a, b in zip(run(offset), want)), offset
+
+
 def test_full_schedule_caches_then_decode(vc):
     # the paper's whole procedure, then generation: prefill with Stage II on entry to layer 1 and Stage III on
     # entry to layer 3, every layer leaving its KV cache (three different lengths), then one decoding step over

@@ -219,10 +219,15 @@ def _ptr(t) -> int | None:
     return None if t is None else t.data_ptr()
 
 
+# (private names: a torch without them takes the way round by the Stream object)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     # (the handle alone: building the Stream object around it takes as long as the rest of a call's Python)
-    if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _current_raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+        return _current_raw_stream(_current_device())
     return torch.cuda.current_stream().cuda_stream
 
 

@@ -406,3 +406,19 @@ def test_decoder_decode_validation():
     for bad in (desc(d=96), desc(D=4100), desc(F=11000), desc(B=300)):
         assert run(C.byref(bad), A16, 1 << 40, None) == binding.VITCOP_EUNSUPPORTED
     assert ws(C.byref(desc(n_cached=(640, 1, 1)))) == 0        # a full cache has no row for the new token
+
+
+def test_stream_handle_without_torchs_private_names(monkeypatch):
+    import importlib.util
+    from types import SimpleNamespace
+
+    import torch
+
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("binding_of_another_torch", binding.__file__)
+    other = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(other)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=1234))
+    assert other._stream() == 1234

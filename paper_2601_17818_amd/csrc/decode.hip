@@ -1,11 +1,13 @@
 // One decoding step over a (compacted) KV cache: o = softmax(scale K q) V for the new token of
 // every sample, the per-token cost that pruning the prefill reduces afterwards (Table 5 of
-// arXiv 2601.17818 reports it).  HBM-bound: K and V of the cache are read exactly once.
+// arXiv 2601.17818 reports it).  HBM-bound: K and V of the cache are read once (once for every 16 query heads of a KV head;
+// once more by the wavefronts of decode_group_kernel that meet an infinite value).
 //
-// decode_partial_kernel: a workgroup takes one head, or two or four side by side, and one slice of the keys.  A key row
+// decode_partial_kernel: a workgroup takes one KV head, or two or four side by side, and one slice of the keys.  A key row
 // (d bf16) is spread over d/8 lanes, 16 bytes each, so a wavefront reads 512/d rows per instruction; every lane keeps its
-// 8 query channels, a running maximum, a running sum and 8 output channels (online softmax).  The lane groups, then the wavefronts, are
-// merged at the end and one partial (max, sum, unnormalised output) per (sample, head, slice) goes to the workspace.
+// 8 query channels, a running maximum, a running sum and 8 output channels (online softmax).  The lane groups, then the
+// wavefronts, are merged at the end and one partial (max, sum, unnormalised output) per (sample, head, slice) goes to the
+// workspace.
 // decode_group_kernel: the same for query heads that share a KV head, whose products go to the matrix cores.
 // decode_merge_kernel combines the slices; a single slice is finished on the spot.
 #include "vitcop_internal.h"
@@ -389,7 +391,7 @@ static int group_splits(int B, int N, int Hkv) {
 // x 16 keys 4.5, 3.9, x 48 4.8, 5.2; 512 x 32 7.0, 6.6, x 48 7.6, 7.9; 2000 x 16 16.3, 9.5, x 64 20.7, 19.2, x 100 24.0, 27.6;
 // 8000 x 16 55, 27, x 317 238, 217; 4000 x 100 42, 44, x 640 236, 230.  Of 64 channels: 4000 x 16 16.3, 15.5, x 64 21.1, 21.8,
 // x 100 25.4, 29.2, x 317 71, 67; 2048 x 317 38.7, 42.4; 8000 x 640 279, 234.  Three and four query heads were faster there
-// up to 16 keys alone (8000 pairs x 8 keys x 4 heads 58, 52; x 32 58, 60), more of them at no size.
+// up to 16 keys alone (8000 pairs x 8 keys x 4 heads 58, 52; x 32 58, 69), more of them at no size.
 static bool group_on_vectors(long pairs, int N, int group, int d) {
     if (group != 2) return false;
     if (pairs > 12 * 256) return d == 128 || N <= 16 || N > 128;
@@ -432,8 +434,8 @@ static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t*
     const float sl2 = scale * 1.4426950408889634f;
     const int group = Hq / Hkv;
     dim3 grid(ns, Hkv, B);
-    // one slice (as many (sample, KV head) pairs as four workgroups per CU): the outputs are written right away and
-    // the merge's launch is saved (64 samples x 32 heads: 4.9 us a layer)
+    // one slice (few keys, or as many (sample, KV head) pairs as four workgroups per CU, of grouped heads as one): the
+    // outputs are written right away and the merge's launch is saved (64 samples x 32 heads: 4.9 us a layer)
     uint16_t* o1 = ns == 1 ? out : nullptr;
     if (grouped) {
         for (int g0 = 0; g0 < group; g0 += DG_MAX_G) {

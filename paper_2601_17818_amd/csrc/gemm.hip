@@ -395,8 +395,8 @@ int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t*
 int launch_gram(const uint16_t* f, int64_t row_stride, int64_t batch_stride, float* sq, int64_t sq_batch, int64_t sq_half, float* gram,
                 int64_t gram_stride, int64_t gram_batch, int n, int K, int batch, hipStream_t s) {
     if (n == 0 || batch == 0) return VITCOP_OK;
-    // A tile's CU loads its two operands at about 50 KB/us, which is what a launch of one round takes: half of the tiles
-    // are saved by symmetry and the others cut over k in two, onto the smaller tiles unless they need more rounds (8 x 288
+    // A launch of one round takes its tiles' loads of their two operands, about 50 KB/us a CU in these launches: half of the
+    // tiles are saved by symmetry and the others cut over k in two, onto the smaller tiles unless they need more rounds (8 x 288
     // tokens x 4096: all 25 tiles of 64 x 64, after a launch for the sums of squares, 6.5 + 19.3 us; in halves 16 for both;
     // 1 x 1856 x 3584: 225 tiles of 128 x 128 5.2 + 36.7, 240 halves 25.5).
     auto cost = [&](int t) {

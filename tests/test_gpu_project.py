@@ -55,6 +55,25 @@ def test_split_k(M, N, K):
     check(x, w, y, r)
 
 
+# slices of 32 k-steps and more start at different k and wrap around: one, two and four tile rows, a last step of half a
+# step in the middle of the walk (test_plan_cpu.py checks their length)
+LONG_SLICES = [(20, 4096, 8192), (64, 4096, 12288), (100, 8192, 8192), (250, 8192, 8192), (300, 4096, 8224), (300, 8192, 8224),
+               (700, 4096, 12320), (1000, 4096, 8224), (640, 4096, 4128)]
+
+
+@pytest.mark.parametrize("M,N,K", LONG_SLICES)
+def test_long_slices(M, N, K):
+    x, w, r = draw(M, N, K, M)
+    y, _ = vc.vitcop_project(x, w, residual=r)
+    check(x, w, y, r)
+
+
+@pytest.mark.parametrize("M,D,Hq,Hkv,d,F", [(120, 2048, 2, 2, 128, 8320), (250, 2112, 1, 1, 128, 8320), (300, 2080, 2, 2, 128, 8320)])
+def test_long_gate_up(M, D, Hq, Hkv, d, F):
+    """The same walk in whole tiles of gate and up."""
+    test_matrices_side_by_side(M, D, Hq, Hkv, d, F)
+
+
 def test_rows_past_the_end_do_not_leak_in():
     """What lies behind the last row of x in memory (here infinities) is never multiplied."""
     x, w, r = draw(300, 512, 96, 3)

@@ -84,6 +84,12 @@ def test_slices_of_few_rows_are_priced(plan, M, N, K):
     assert plan.few_rows(M, N, K, (C.c_int * 2)()) <= 8
 
 
+@pytest.mark.parametrize("M,N,K", gpu.LONG_SLICES)
+def test_long_slices_are_long(plan, M, N, K):
+    slices = plan.few_rows(M, N, K, (C.c_int * 2)()) if M <= 256 else picked(plan, M, N, K)[2]
+    assert (K + 63) // 64 // slices >= 32
+
+
 def sliced(plan, M, N, K):
     """The tile of a launch of one matrix or a pair that is cut over k, or nothing."""
     if M <= 256:

@@ -100,6 +100,15 @@ def test_few_rows(M, N, K):
     assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
 
 
+@pytest.mark.parametrize("M", [1, 2, 3, 4])
+@pytest.mark.parametrize("N,K", [(48, 512), (4096, 2048), (1040, 2080), (3008, 4128), (2064, 11008), (512, 12288)])
+def test_one_to_four_rows(M, N, K):
+    """Pieces of a row pair in rotated order: one to six of them, the last one short, pairs cut between wavefronts."""
+    x, w, r = draw(M, N, K, M + K)
+    y, _ = vc.vitcop_project(x, w, residual=r)
+    check(x, w, y, r)
+
+
 SIDE_BY_SIDE = ([(M, *layer) for layer in ((512, 4, 2, 64, 1408), (640, 5, 1, 128, 896), (1024, 16, 4, 64, 2816))
                  for M in (7, 40, 115, 200, 300, 700, 1100, 2900)] +
                 # K, Q and V as one launch of k-slices on each of its tiles

@@ -45,6 +45,32 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// Inclusive scan over the 64 lanes (all of them active) in vector registers: four steps inside the rows of sixteen, then
+// the rows' last lanes to the rows behind them.  (A shuffle is a round trip through LDS.)
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_move(T identity, T v) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, identity), __builtin_bit_cast(int, v),
+                                                             CTRL, ROWS, 0xF, false));
+}
+template <typename T, typename Op>
+__device__ __forceinline__ T row_scan(T v, T identity, Op op) {
+    v = op(v, dpp_move<0x111, 0xF>(identity, v));        // row_shr:1, 2, 4, 8
+    v = op(v, dpp_move<0x112, 0xF>(identity, v));
+    v = op(v, dpp_move<0x114, 0xF>(identity, v));
+    return op(v, dpp_move<0x118, 0xF>(identity, v));
+}
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_scan(T v, T identity, Op op) {
+    v = row_scan(v, identity, op);
+    v = op(v, dpp_move<0x142, 0xA>(identity, v));        // row_bcast:15 to rows 1 and 3
+    return op(v, dpp_move<0x143, 0xC>(identity, v));     // row_bcast:31 to rows 2 and 3
+}
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_reduce(T v, T identity, Op op) {       // the same value in every lane
+    const T all = wave_scan(v, identity, op);
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, all), 63));
+}
+
 // Sum of squares of the 8 bf16 values packed in a uint4.
 __device__ __forceinline__ float sumsq8(const uint4& u, float acc) {
     float a;

@@ -8,7 +8,7 @@
 //                          one logit per (head, token) goes to the workspace.
 // filter_finalize_kernel : one workgroup per image: per-head max and
 //                          normaliser, head-summed softmax weight per patch,
-//                          then the same radix selection as the K-norm path
+//                          then the same selection as the K-norm path
 //                          on complemented keys (largest first).
 #include <mutex>
 
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(SEL_THREADS) void filter_finalize_kernel(
     const float* lg = logits + (int64_t)b * H * N1;
     // (the workgroup is alone on its CU and everything it reads is a round trip to L2: a head's row is read
     // once, all of its loads in flight together, and kept in registers for the second pass)
-    constexpr int FF_HELD = 16;                    // logits per lane held in registers: rows up to 1024 tokens
+    constexpr int FF_HELD = 17;                    // logits per lane held in registers: up to 1024 patches and [CLS]
     for (int h = wv; h < H; h += SEL_THREADS / 64) {
         const float* row = lg + (int64_t)h * N1;
         float m = -INFINITY, z = 0.f;
@@ -135,7 +135,6 @@ __global__ __launch_bounds__(SEL_THREADS) void filter_finalize_kernel(
         if (scores_out) scores_out[(int64_t)b * N + i] = s;
         sel_keys[i] = ~__float_as_uint(s);         // s >= 0: complement reverses the order
     }
-    __syncthreads();
     block_select_emit(sel_keys, N, keep, idx_out + (int64_t)b * keep, 0, sh);
 }
 

@@ -121,10 +121,13 @@ __global__ __launch_bounds__(SEL_THREADS) void select_smallest_kernel(
     const int T_real = T - (n_vis_max - n_vis);
     const float* src = parts + (int64_t)b * sample_stride + offset;
     float* norms = norms_out ? norms_out + (int64_t)b * n_vis_max : nullptr;
-    // (up to a candidate a thread, groups of four would load three times in vain: one sample of 576 in 32 parts 8.2 us a
-    // launch with eight parts at a time, 7.0 with all; 6272 in 4 parts 11.2 us by four candidates, 9.9 by eight)
-    if (n_vis <= SEL_THREADS && n_parts > 8) collect_norms<1, 32>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
+    // Candidates of a thread x parts in one round trip: what does not exist is loaded again in its place, so neither is
+    // much larger than there are (one sample of 2880 in one part: groups of 8 x 4 8.2 us a launch, of 8 x 1 6.7; four
+    // samples of 2880 in 32 parts: 4 x 8 11.8, 3 x 16 9.7; one of 576 in 32: 4 x 8 8.2, 1 x 32 7.0 before the keys' bins).
+    if (n_parts == 1) collect_norms<8, 1>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
     else if (n_parts <= 4) collect_norms<8, 4>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
+    else if (n_vis <= SEL_THREADS && n_parts > 8) collect_norms<1, 32>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
+    else if (n_vis <= 3 * SEL_THREADS && n_parts > 8) collect_norms<3, 16>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
     else collect_norms<4, 8>(src, n_parts, part_stride, do_sqrt, norms, n_vis, sel_keys);
     if (norms)
         for (int i = n_vis + tid; i < n_vis_max; i += SEL_THREADS) norms[i] = 0.f;
@@ -133,7 +136,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_smallest_kernel(
     for (int i = vis_start + n_vis + tid; i < T_real; i += SEL_THREADS) out[i - n_vis + keep] = i;
     for (int j = T_real - n_vis + keep + tid; j < Tp; j += SEL_THREADS) out[j] = T - 1;
     if (n_vis_samples_out && tid == 0) n_vis_samples_out[b] = keep;
-    __syncthreads();
     block_select_emit(sel_keys, n_vis, keep, out + vis_start, vis_start, sh);
 }
 

@@ -172,7 +172,6 @@ __global__ __launch_bounds__(SEL_THREADS) void vic_label_kernel(const float* __r
     // largest gamma = rho delta first (+inf without a parent): complement of the bit pattern (gamma >= 0)
     for (int i = tid; i < n; i += SEL_THREADS)
         keys[i] = ~__float_as_uint(parent[i] < 0 ? INFINITY : rho[i] * delta[i]);
-    __syncthreads();
     block_select_emit(keys, n, n_centers, chosen, 0, sh);
     __syncthreads();
     for (int i = tid; i < n; i += SEL_THREADS) is_root[i] = parent[i] < 0 ? 1u : 0u;

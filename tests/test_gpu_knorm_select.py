@@ -95,6 +95,22 @@ def test_every_way_the_cut_is_found(vc, n):
             assert got[b, keep] == n
 
 
+@pytest.mark.parametrize("n", [1024, 1026, 3072, 3073, 8192, 8193])
+def test_cuts_at_the_edges_of_the_keys_a_thread_holds(vc, n):
+    # precomputed values against a stable argsort: infinities that tie behind finite values, values across a power of two
+    # (bins between the least and the largest), few distinct values far apart, subnormals beside large ones
+    g = np.random.default_rng(n)
+    some = np.exp(g.normal(0, 0.5, n)).astype(np.float32)
+    cases = [np.where(g.random(n) < 0.6, np.float32(np.inf), some), g.uniform(3.99, 4.01, n).astype(np.float32),
+             g.choice(np.array([0, 1e-3, 1, 1e30], np.float32), n), np.where(g.random(n) < 0.5, some * np.float32(1e-42), some)]
+    v = torch.from_numpy(np.stack(cases).astype(np.float32)).cuda()
+    order = np.argsort(np.stack(cases), axis=1, kind="stable")
+    for keep in (1, n // 10, n // 2, n - 1):
+        _, idx = vc.vitcop_knorm_select(None, 0, n, keep, norms=v, flags=vc.VITCOP_NORMS_PRECOMPUTED, shape=(4, n, 4, 128))
+        for b, got in enumerate(idx.cpu().numpy()):
+            assert np.array_equal(got, np.sort(order[b, :keep])), (n, keep, b)
+
+
 # candidates up to a thread each and more, parts up to one round trip's (4, 8, 32) and one over
 @pytest.mark.parametrize("n,P", [(n, P) for n in (1, 700, 1024, 1025, 8193) for P in (1, 4, 5, 8, 9, 32, 33)])
 def test_norms_from_any_number_of_parts(vc, n, P):

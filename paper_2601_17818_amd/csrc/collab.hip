@@ -56,7 +56,7 @@ __global__ __launch_bounds__(CB_ROW_THREADS) void collab_rank_kernel(
 
 // One workgroup per image.  LDS: has_rest[R] / merged_row[R] and first_rest[R], R <= n.
 __global__ __launch_bounds__(CB_PLAN_THREADS) void collab_plan_kernel(
-    const int32_t* __restrict__ labels, const int32_t* __restrict__ elite,
+    const int32_t* __restrict__ labels, int32_t* __restrict__ elite,
     const int32_t* __restrict__ n_clusters, int n, int32_t* __restrict__ assign,
     int32_t* __restrict__ out_index, int32_t* __restrict__ n_out) {
     extern __shared__ __attribute__((aligned(16))) int cb_lds[];
@@ -102,53 +102,80 @@ __global__ __launch_bounds__(CB_PLAN_THREADS) void collab_plan_kernel(
     for (int i = tid; i < n; i += CB_PLAN_THREADS)
         if (!elite[i]) assign[i] = merged_row[label_of(i)];
     if (tid == 0) n_out[b] = n_elite + n_merged;
+    __syncthreads();                     // the flags have been read: their first entry now says how many elites there are
+    if (tid == 0 && n > 0) elite[0] = n_elite;
 }
 
-// One workgroup per (output row, image); a thread owns 8 channels.
-__global__ __launch_bounds__(256) void collab_emit_kernel(
+// One workgroup per (output row, image); a thread owns 8 channels.  Rows [0, n_elite) are elites, the merged ones follow.
+// A chain of round trips to memory: what the row is, and which tokens go to it, are read together, then eight members'
+// rows at a time (8 x 288 tokens x 4096, 36 MB: 8.7 us with the elite flag and the assignment read one after the other and
+// four members at a time by half the threads, 7.6 now).
+constexpr int CB_TOKENS = 1024;          // tokens looked at between two barriers
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void collab_emit_kernel(
     const uint16_t* __restrict__ feats, int64_t row_stride, int64_t batch_stride,
     const int32_t* __restrict__ elite, const int32_t* __restrict__ assign,
     const int32_t* __restrict__ out_index, const int32_t* __restrict__ n_out, int n, int D,
     uint16_t* __restrict__ out_feats) {
+    constexpr int WAVES = THREADS / 64, CHUNKS = CB_TOKENS / THREADS;
     // merged rows, the last ones, take longest: they start first (8 x 288 tokens x 4096 9.6 -> 9.1 us, 1856 x 3584 14.5 -> 12.5)
     const int r = n - 1 - blockIdx.x, b = blockIdx.y;
-    if (r >= n_out[b]) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     feats += b * batch_stride;
-    elite += (int64_t)b * n;
     assign += (int64_t)b * n;
     uint16_t* dst = out_feats + ((int64_t)b * n + r) * D;
-    const int first = out_index[(int64_t)b * n + r];
-    if (elite[first]) {                                   // an elite row: plain copy
+    const int rows = n_out[b], elites = elite[(int64_t)b * n];       // (left there by collab_plan_kernel)
+    const int first = out_index[(int64_t)b * n + r];      // (of a row past the end: unused)
+    int to[CHUNKS];
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) to[c] = assign[min(c * THREADS + tid, n - 1)];
+    if (r >= rows) return;
+    if (r < elites) {                                     // an elite row: plain copy
         const uint16_t* src = feats + (int64_t)first * row_stride;
-        for (int c = threadIdx.x * 8; c < D; c += 256 * 8)
+        for (int c = tid * 8; c < D; c += THREADS * 8)
             *reinterpret_cast<uint4*>(dst + c) = *reinterpret_cast<const uint4*>(src + c);
         return;
     }
-    // a merged row: list the absorbed tokens in ascending order (block-wide ordered compaction of
-    // the tokens assigned to this row), then average them channel by channel
+    // a merged row: list the absorbed tokens in ascending order, then average them channel by channel
     __shared__ int members[VITCOP_VIC_MAX_TOKENS];
-    __shared__ int wave_tot[4];
-    __shared__ int total;
-    const int tid = threadIdx.x;
-    const int running = block_exclusive_scan<256>(
-        first, n, wave_tot, [&](int i) { return assign[i] == r ? 1 : 0; },
-        [&](int i, int f, int pos) {
-            if (f) members[pos] = i;
-        });
-    if (tid == 0) total = running;
-    __syncthreads();
-    const int count = total;
-    const float inv = 1.0f / (float)count;
-    for (int c = tid * 8; c < D; c += 256 * 8) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int m0 = 0; m0 < count; m0 += 4) {               // four members' rows in flight
-            u32x4 row[4];
+    __shared__ unsigned found[2][CHUNKS * WAVES];         // (two: one may be read while the next is written)
+    static_assert(CHUNKS * WAVES <= 64, "a count a lane");
+    int count = 0;
+    for (int i0 = 0; i0 < n; i0 += CB_TOKENS) {
+        unsigned* counts = found[i0 / CB_TOKENS & 1];
+        if (i0 > 0)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int c = 0; c < CHUNKS; ++c) to[c] = assign[min(i0 + c * THREADS + tid, n - 1)];
+        unsigned long long mask[CHUNKS];
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {
+            mask[c] = __builtin_amdgcn_ballot_w64(i0 + c * THREADS + tid < n && to[c] == r);
+            if (lane == 0) counts[c * WAVES + wv] = (unsigned)__builtin_popcountll(mask[c]);
+        }
+        __syncthreads();
+        const unsigned mine = lane < CHUNKS * WAVES ? counts[lane] : 0u;
+        const unsigned incl = wave_scan(mine, 0u, [](unsigned x, unsigned y) { return x + y; }), before = incl - mine;
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c)
+            if (mask[c] >> lane & 1u)
+                members[count + __builtin_amdgcn_readlane(before, c * WAVES + wv) +
+                        __builtin_amdgcn_mbcnt_hi((unsigned)(mask[c] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask[c], 0u))] =
+                    i0 + c * THREADS + tid;
+        count += (int)__builtin_amdgcn_readlane(incl, 63);
+    }
+    __syncthreads();
+    const float inv = 1.0f / (float)count;
+    for (int c = tid * 8; c < D; c += THREADS * 8) {
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int m0 = 0; m0 < count; m0 += 8) {               // eight members' rows in flight
+            u32x4 row[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
                 if (m0 + e < count)
                     row[e] = *reinterpret_cast<const u32x4*>(feats + (int64_t)members[m0 + e] * row_stride + c);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 8; ++e)
                 if (m0 + e < count) {
                     acc[0] += bf16_lo(row[e].x); acc[1] += bf16_hi(row[e].x);
                     acc[2] += bf16_lo(row[e].y); acc[3] += bf16_hi(row[e].y);
@@ -194,8 +221,12 @@ int launch_collab(const uint16_t* feats, int64_t row_stride, int64_t batch_strid
                        n_clusters, n, assign, out_index, n_out);
     int rc = launch_status("collab_plan");
     if (rc || n == 0) return rc;
-    hipLaunchKernelGGL(collab_emit_kernel, dim3(n, B), dim3(256), 0, s, feats, row_stride, batch_stride, elite, assign,
-                       out_index, n_out, n, D, out_feats);
+    if (D > 2048)                        // (one pass over the channels up to 4096)
+        hipLaunchKernelGGL(collab_emit_kernel<512>, dim3(n, B), dim3(512), 0, s, feats, row_stride, batch_stride, elite,
+                           assign, out_index, n_out, n, D, out_feats);
+    else
+        hipLaunchKernelGGL(collab_emit_kernel<256>, dim3(n, B), dim3(256), 0, s, feats, row_stride, batch_stride, elite,
+                           assign, out_index, n_out, n, D, out_feats);
     return launch_status("collab_emit");
 }
 

@@ -133,15 +133,10 @@ __global__ __launch_bounds__(VIC_THREADS) void vic_parent_kernel(
                           }
                       }
                   });
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ob = __shfl_xor(best, o, 64);
-        const int oj = __shfl_xor(best_j, o, 64);
-        if (ob < best || (ob == best && oj < best_j)) {
-            best = ob;
-            best_j = oj;
-        }
-    }
+    // the least distance of the row, then the least index that has it
+    const float least = wave_reduce(best, INFINITY, [](float a, float b) { return b < a ? b : a; });
+    best_j = wave_reduce(best == least ? best_j : 0x7fffffff, 0x7fffffff, [](int a, int b) { return min(a, b); });
+    best = least;
     if ((threadIdx.x & 63) == 0 && i < n) {
         delta[(int64_t)img * n + i] = best;                  // +inf when no candidate
         parent[(int64_t)img * n + i] = best_j == 0x7fffffff ? -1 : best_j;

@@ -66,6 +66,15 @@ def test_matches_oracle(vc, n, D, n_c, budget):
     check(run(vc, [c], budget), 0, c, budget)
 
 
+@pytest.mark.parametrize("n,D,n_c,budget", [(1024, 2048, 3, 40), (1025, 2056, 3, 40), (2100, 2304, 40, 900), (3000, 8, 2, 2)])
+def test_members_beyond_one_look_at_the_tokens(vc, n, D, n_c, budget):
+    """Merged rows listed in one, two and three pieces, by 256 and by 512 threads; hundreds of members to a row."""
+    cases = [case(8200 + n + b, n, D, n_c) for b in range(2)]
+    r = run(vc, cases, budget)
+    for b, c in enumerate(cases):
+        check(r, b, c, budget)
+
+
 def test_batch_and_empty(vc):
     cases = [case(8100 + b, 120, 128, 5 + b) for b in range(3)]
     r = run(vc, cases, 40)

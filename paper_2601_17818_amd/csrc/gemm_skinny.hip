@@ -21,34 +21,43 @@
 
 namespace vitcop {
 
-// v[0..8) = sum, in slice order, of the partials of row m, columns n .. n+8 (n a
-// multiple of 8).  Four loads are in flight at a time; the additions keep the order.
-__device__ __forceinline__ void sk_sum_tiles(const SkParts& P, int m, int n, float (&v)[8]) {
+// The sum, in slice order, of the partials of row m, columns n .. n+8 (n a multiple of 8).  The first four slices'
+// loads go out when it is declared, so that a kernel's other loads can follow before the first wait (a reduction of a few
+// rows is a chain of round trips to memory); further slices follow four at a time.
+struct SkSum {
+    const float* p;
+    int64_t slice;
+    int slices;
+    f32x4 a[4], b[4];
+    __device__ __forceinline__ SkSum() {}
+    __device__ __forceinline__ SkSum(const SkParts& P, int m, int n)
+        : p(P.part + (int64_t)m * P.N + n), slice((int64_t)P.M * P.N), slices(P.slices) {
+        request(0);
+    }
+    __device__ __forceinline__ void request(int s0) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = 0.f;
-    auto tile = [&](int sl) { return P.part + ((int64_t)sl * P.M + m) * P.N + n; };
-    int i = 0;
-    for (; i + 3 < P.slices; i += 4) {
-        float4 a[4], b[4];
+        for (int t = 0; t < 4; ++t)
+            if (s0 + t < slices) {
+                a[t] = *reinterpret_cast<const f32x4*>(p + (s0 + t) * slice);
+                b[t] = *reinterpret_cast<const f32x4*>(p + (s0 + t) * slice + 4);
+            }
+    }
+    __device__ __forceinline__ void add_up(float (&v)[8]) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const float* p = tile(i + t);
-            a[t] = *reinterpret_cast<const float4*>(p);
-            b[t] = *reinterpret_cast<const float4*>(p + 4);
-        }
+        for (int e = 0; e < 8; ++e) v[e] = 0.f;
+        for (int s0 = 0; s0 < slices; s0 += 4) {
+            if (s0 > 0) request(s0);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            v[0] += a[t].x; v[1] += a[t].y; v[2] += a[t].z; v[3] += a[t].w;
-            v[4] += b[t].x; v[5] += b[t].y; v[6] += b[t].z; v[7] += b[t].w;
+            for (int t = 0; t < 4; ++t)
+                if (s0 + t < slices)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[e] += a[t][e];
+                        v[4 + e] += b[t][e];
+                    }
         }
     }
-    for (; i < P.slices; ++i) {
-        const float* p = tile(i);
-        const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w;
-        v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
-    }
-}
+};
 
 // y[m, n..n+8) = bf16(sum of the slices' partials, in slice order, + residual);
 // one thread per 8 columns, 16 consecutive lanes per 128-column group, which also yields that
@@ -63,12 +72,14 @@ __global__ __launch_bounds__(256) void gemm_skinny_reduce_kernel(
     const int n = c * 8, grp = c >> 4;
     float ss = 0.f;
     if (m < M && n < N) {
-        float v[8];
-        sk_sum_tiles(parts, m, n, v);
+        SkSum sum(parts, m, n);
+        uint4 r = make_uint4(0, 0, 0, 0);
+        if (res) r = *reinterpret_cast<const uint4*>(res + (int64_t)m * res_stride + n);
         const SkPick pick = sk_pick(mats, n);
         uint16_t* dst = mats.y[pick.mi] + (int64_t)m * mats.y_stride[pick.mi] + (n - pick.start);
+        float v[8];
+        sum.add_up(v);
         if (res) {
-            const uint4 r = *reinterpret_cast<const uint4*>(res + (int64_t)m * res_stride + n);
             v[0] += bf16_lo(r.x); v[1] += bf16_hi(r.x);
             v[2] += bf16_lo(r.y); v[3] += bf16_hi(r.y);
             v[4] += bf16_lo(r.z); v[5] += bf16_hi(r.z);
@@ -102,59 +113,70 @@ __global__ __launch_bounds__(256) void gemm_skinny_reduce_kernel(
 // The same reduction followed by an RMSNorm of the finished row (the next operation of a decoder
 // layer after its attention and MLP output projections): y as above, and
 // norm_out[m, :] = y[m, :] / sqrt(mean(y[m, :]^2) + eps) * ln_w, computed from the ROUNDED y exactly as
-// rmsnorm_kernel does.  One workgroup per row; a thread owns the chunks tid, tid + 256, ...
-// (N <= 8 * 256 * SK_NORM_CHUNKS).
-constexpr int SK_NORM_CHUNKS = 16;
+// rmsnorm_kernel does.  One workgroup per row; a thread owns the chunks tid, tid + 512, ... (J of them; N <= 8 * 512 * J).
+// Everything a thread reads is requested before the first wait (half the threads, two chunks each one after the other, the
+// residual and the weight when they were needed: 4096 columns in four slices, 317 rows 6.95 -> 6.70 us, 115 rows
+// 5.10 -> 4.79, 64 rows 4.75 either way; the plain reduction of 640 rows 6.5 -> 6.05, of 93 rows x 8192 5.0 -> 4.35).
+constexpr int SK_NORM_THREADS = 512, SK_NORM_CHUNKS = 8;
 
-__global__ __launch_bounds__(256) void gemm_skinny_reduce_norm_kernel(
+template <int J>
+__global__ __launch_bounds__(SK_NORM_THREADS) void gemm_skinny_reduce_norm_kernel(
     SkParts parts, int N, uint16_t* __restrict__ y, int64_t y_stride, const uint16_t* __restrict__ res,
     int64_t res_stride, const uint16_t* __restrict__ ln_w, float eps, uint16_t* __restrict__ norm_out,
     int64_t norm_stride) {
-    __shared__ float wave_part[4];
+    constexpr int AHEAD = J < 2 ? J : 2;             // chunks requested together
+    __shared__ float wave_part[SK_NORM_THREADS / 64];
     const int m = blockIdx.x, tid = threadIdx.x;
     const int chunks = N / 8;
-    u32x4 held[SK_NORM_CHUNKS];          // (a native vector type: arrays of the uint4 struct end up in scratch)
+    u32x4 held[J], weight[J];            // (native vector types: arrays of the uint4 struct end up in scratch)
     float ss = 0.f;
 #pragma unroll
-    for (int j = 0; j < SK_NORM_CHUNKS; ++j) {
-        const int c = tid + 256 * j;
-        if (c >= chunks) break;
-        const int n = c * 8;
-        float v[8];
-        sk_sum_tiles(parts, m, n, v);
-        if (res) {
-            const uint4 r = *reinterpret_cast<const uint4*>(res + (int64_t)m * res_stride + n);
-            v[0] += bf16_lo(r.x); v[1] += bf16_hi(r.x);
-            v[2] += bf16_lo(r.y); v[3] += bf16_hi(r.y);
-            v[4] += bf16_lo(r.z); v[5] += bf16_hi(r.z);
-            v[6] += bf16_lo(r.w); v[7] += bf16_hi(r.w);
+    for (int j0 = 0; j0 < J; j0 += AHEAD) {
+        SkSum sum[AHEAD];
+        u32x4 r[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int c = tid + SK_NORM_THREADS * (j0 + u);
+            if (c >= chunks) continue;
+            sum[u] = SkSum(parts, m, 8 * c);
+            r[u] = res ? *reinterpret_cast<const u32x4*>(res + (int64_t)m * res_stride + 8 * c) : u32x4{0, 0, 0, 0};
+            weight[j0 + u] = *reinterpret_cast<const u32x4*>(ln_w + 8 * c);
         }
-        uint4 o;
-        o.x = pack_bf16(v[0], v[1]);
-        o.y = pack_bf16(v[2], v[3]);
-        o.z = pack_bf16(v[4], v[5]);
-        o.w = pack_bf16(v[6], v[7]);
-        *reinterpret_cast<uint4*>(y + (int64_t)m * y_stride + n) = o;
-        held[j] = u32x4{o.x, o.y, o.z, o.w};
-        ss = sumsq8(o, ss);
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int c = tid + SK_NORM_THREADS * (j0 + u);
+            if (c >= chunks) continue;
+            float v[8];
+            sum[u].add_up(v);
+            if (res)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[2 * e] += bf16_lo(r[u][e]);
+                    v[2 * e + 1] += bf16_hi(r[u][e]);
+                }
+            const u32x4 o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+            *reinterpret_cast<u32x4*>(y + (int64_t)m * y_stride + 8 * c) = o;
+            held[j0 + u] = o;
+            ss = sumsq8(make_uint4(o.x, o.y, o.z, o.w), ss);
+        }
     }
     ss = wave_sum(ss);
     if ((tid & 63) == 0) wave_part[tid >> 6] = ss;
     __syncthreads();
-    ss = (wave_part[0] + wave_part[1]) + (wave_part[2] + wave_part[3]);
+    ss = 0.f;
+#pragma unroll
+    for (int w = 0; w < SK_NORM_THREADS / 64; ++w) ss += wave_part[w];
     const float r = __builtin_amdgcn_rsqf(ss / (float)N + eps);
 #pragma unroll
-    for (int j = 0; j < SK_NORM_CHUNKS; ++j) {
-        const int c = tid + 256 * j;
-        if (c >= chunks) break;
-        const uint4 v = make_uint4(held[j].x, held[j].y, held[j].z, held[j].w);
-        const uint4 g = *reinterpret_cast<const uint4*>(ln_w + 8 * c);
-        uint4 o;
-        o.x = pack_bf16(bf16_lo(v.x) * r * bf16_lo(g.x), bf16_hi(v.x) * r * bf16_hi(g.x));
-        o.y = pack_bf16(bf16_lo(v.y) * r * bf16_lo(g.y), bf16_hi(v.y) * r * bf16_hi(g.y));
-        o.z = pack_bf16(bf16_lo(v.z) * r * bf16_lo(g.z), bf16_hi(v.z) * r * bf16_hi(g.z));
-        o.w = pack_bf16(bf16_lo(v.w) * r * bf16_lo(g.w), bf16_hi(v.w) * r * bf16_hi(g.w));
-        *reinterpret_cast<uint4*>(norm_out + (int64_t)m * norm_stride + 8 * c) = o;
+    for (int j = 0; j < J; ++j) {
+        const int c = tid + SK_NORM_THREADS * j;
+        if (c >= chunks) continue;
+        const u32x4 v = held[j], g = weight[j];
+        u32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            o[e] = pack_bf16(bf16_lo(v[e]) * r * bf16_lo(g[e]), bf16_hi(v[e]) * r * bf16_hi(g[e]));
+        *reinterpret_cast<u32x4*>(norm_out + (int64_t)m * norm_stride + 8 * c) = o;
     }
 }
 
@@ -168,12 +190,13 @@ __global__ __launch_bounds__(256) void gemm_skinny_reduce_silu_kernel(
     const int m = (int)(id / chunks), c = (int)(id % chunks);
     if (m >= M) return;
     // bf16(sum of the partials of the 8 columns from n on, in slice order), packed
-    auto reduced = [&](int n) {
+    auto reduced = [&](SkSum& sum) {
         float v[8];
-        sk_sum_tiles(parts, m, n, v);
+        sum.add_up(v);
         return make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
     };
-    const uint4 g = reduced(8 * c), u = reduced(F + 8 * c);
+    SkSum gate(parts, m, 8 * c), up(parts, m, F + 8 * c);
+    const uint4 g = reduced(gate), u = reduced(up);
     auto gated = [](uint32_t gw, uint32_t uw) {
         const float g0 = bf16_lo(gw), g1 = bf16_hi(gw);
         const float s0 = g0 / (1.0f + __expf(-g0)), s1 = g1 / (1.0f + __expf(-g1));
@@ -380,8 +403,14 @@ int launch_partial_reduce(const SkParts& parts, int N, const SkMats& mats, const
         return launch_status("gemm_skinny_reduce_silu");
     }
     if (ln_w != nullptr) {
-        hipLaunchKernelGGL(gemm_skinny_reduce_norm_kernel, dim3(M), dim3(256), 0, s, parts, N, mats.y[0],
-                           mats.y_stride[0], res, res_stride, ln_w, eps, norm_out, norm_stride);
+#define VITCOP_REDUCE_NORM(J)                                                                                              \
+    hipLaunchKernelGGL(gemm_skinny_reduce_norm_kernel<J>, dim3(M), dim3(SK_NORM_THREADS), 0, s, parts, N, mats.y[0],         \
+                       mats.y_stride[0], res, res_stride, ln_w, eps, norm_out, norm_stride)
+        const int per_thread = (N / 8 + SK_NORM_THREADS - 1) / SK_NORM_THREADS;
+        if (per_thread <= 1) VITCOP_REDUCE_NORM(1);
+        else if (per_thread <= 2) VITCOP_REDUCE_NORM(2);
+        else VITCOP_REDUCE_NORM(SK_NORM_CHUNKS);
+#undef VITCOP_REDUCE_NORM
         return launch_status("gemm_skinny_reduce_norm");
     }
     const int chunks = (N + SK_COLS - 1) / SK_COLS * 16;
@@ -391,7 +420,7 @@ int launch_partial_reduce(const SkParts& parts, int N, const SkMats& mats, const
     return launch_status("gemm_skinny_reduce");
 }
 
-bool partial_reduce_fuses_norm(int N) { return N % 8 == 0 && N <= 8 * 256 * SK_NORM_CHUNKS; }
+bool partial_reduce_fuses_norm(int N) { return N % 8 == 0 && N <= 8 * SK_NORM_THREADS * SK_NORM_CHUNKS; }
 
 // The launch over the matrices of `mats` (N = all their columns) through partial tiles in `ws`
 // (gemm_skinny_workspace_bytes).  res and sumsq_parts only with a single matrix.  With ln_w != nullptr

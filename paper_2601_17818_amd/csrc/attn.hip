@@ -242,6 +242,7 @@ constexpr int AW_STAGE = AW_KTILE<D> + D / 8 * AW_VGRP;      // K then V
 template <int D>
 constexpr int AW_STAGES = D == 64 ? 3 : 4;
 constexpr float AW_RESCALE_GAP = 8.0f;
+constexpr int AW_MAX_REST = 8;        // keys past the last whole tile that are attended to without one
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
@@ -353,7 +354,7 @@ constexpr SmTable make_sm_table(bool masked, int U, int slots) {
 template <int D, int U, bool MASKED>
 constexpr SmTable SM_TABLE_OF = make_sm_table(MASKED, U, D / 8 * U);
 
-template <int D, bool CAUSAL, int U>
+template <int D, bool CAUSAL, int U, bool REST = false>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const uint16_t* __restrict__ v, uint16_t* __restrict__ out, float* __restrict__ lse,
@@ -434,9 +435,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
         l_run[u] = 0.f;
     }
 
-    const int kend = CAUSAL ? min(N, q0 + BM) : N;
+    // REST: the keys past the last whole tile (1 to AW_MAX_REST) are attended to first, straight from memory while the tiles
+    // are on their way, instead of as a tile of their own.
+    static_assert(!REST || (!CAUSAL && U == 1), "without the mask, one query block");
+    const int rest = REST ? N % AW_BN : 0;
+    const int kend = CAUSAL ? min(N, q0 + BM) : N - rest;
     const int ntiles = (kend + AW_BN - 1) / AW_BN;                 // tiles the workgroup streams
-    const int wave_kend = CAUSAL ? wq0 + QW : N;                   // keys this wavefront needs
+    const int wave_kend = CAUSAL ? wq0 + QW : N - rest;            // keys this wavefront needs
     const int my_tiles = wq0 + QW > 0 ? (wave_kend + AW_BN - 1) / AW_BN : 0;
     // tiles whose 64 keys are visible to all 64 queries and lie inside the sequence: no masking
     const int full_tiles = min(CAUSAL ? max(wq0, 0) / AW_BN : N / AW_BN, min(N / AW_BN, my_tiles));
@@ -724,9 +729,56 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
         stage_block(1, t, masked_c, true);
     };
 
+    // the rest: rows of K as in a score MFMA (a lane holds 8 channels of key l32), of V as in a value MFMA (keys 4 g .. + 3
+    // of channel l32 of a block of 32; the other keys of its sixteen are zero)
+    bf16x8 rest_k[REST ? DC : 1];
+    uint32_t rest_v[REST ? DB : 1][2];
+    if constexpr (REST) {
+        const uint16_t* kr = reinterpret_cast<const uint16_t*>(kbase) + (N - rest + min(l32, rest - 1)) * kv_rs + 8 * g;
+        const uint16_t* vr = reinterpret_cast<const uint16_t*>(vbase) + (N - rest) * kv_rs + l32;
+#pragma unroll
+        for (int dc = 0; dc < DC; ++dc) rest_k[dc] = *reinterpret_cast<const bf16x8*>(kr + 16 * dc);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int j = 0; j < 4; j += 2) {
+                const uint32_t a = vr[min(4 * g + j, rest - 1) * kv_rs + 32 * db];
+                const uint32_t c = vr[min(4 * g + j + 1, rest - 1) * kv_rs + 32 * db];
+                rest_v[db][j / 2] = (4 * g + j < rest ? a : 0u) | (4 * g + j + 1 < rest ? c << 16 : 0u);
+            }
+    }
     issue_tile(0);
     if (ntiles > 1) issue_tile(1);
     if (ST == 4 && ntiles > 2) issue_tile(2);
+    if constexpr (REST) {
+        f32x16 sr;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sr[r] = 0.f;
+#pragma unroll
+        for (int dc = 0; dc < DC; ++dc) sr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rest_k[dc], qf[0][dc], sr, 0, 0, 0);
+        float p[4], own = -INFINITY;                     // register r: key 4 g + r
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = 4 * g + r < rest ? sr[r] : -INFINITY;
+            own = fmaxf(own, p[r]);
+        }
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
+        const float top = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
+        if (top > -INFINITY) {                           // (otherwise as if nothing had been seen)
+            m_ref[0] = top;
+            thr[0] = fmaxf((top + AW_RESCALE_GAP) / scale_log2e, -3.0e38f);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[r] = top > -INFINITY ? __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -top)) : 0.f;
+        l_run[0] = (p[0] + p[1]) + (p[2] + p[3]);
+        const u32x4 pw = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), 0u, 0u};
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const u32x4 vw = {rest_v[db][0], rest_v[db][1], 0u, 0u};
+            o[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vw), __builtin_bit_cast(bf16x8, pw),
+                                                               o[0][db], 0, 0, 0);
+        }
+    }
     tile_sync(0);                    // also covers the Q fragments, which were requested first
 
     int t = 1;
@@ -781,13 +833,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
 constexpr int AW_U2_MIN_N = 512;   // a wavefront takes two query blocks from this length on,
 constexpr int AW_U2_MIN_WGS = 256;  // if that still leaves more workgroups than this
 
-template <int D, bool CAUSAL, int U>
+template <int D, bool CAUSAL, int U, bool REST = false>
 static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                             int B, int N, int Hq, int Hkv, float sl2, int64_t kv_batch, hipStream_t s) {
     static std::atomic<bool> attr_set{false};   // set once; a second thread repeating the call is harmless
     constexpr int lds = AW_STAGES<D> * AW_STAGE<D>;
     if (!attr_set.load(std::memory_order_acquire)) {
-        const int rc = hip_status(hipFuncSetAttribute((const void*)attn_wide_kernel<D, CAUSAL, U>,
+        const int rc = hip_status(hipFuncSetAttribute((const void*)attn_wide_kernel<D, CAUSAL, U, REST>,
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds),
                                   "hipFuncSetAttribute(attn_wide)");
         if (rc) return rc;
@@ -799,7 +851,7 @@ static int launch_attn_wide(const uint16_t* q, const uint16_t* k, const uint16_t
     // (sample, head) pairs in flight together: few, so that their query blocks share K/V
     // in L2, but enough to fill the 256 CUs twice over (measured: 32 from N = 2048 up)
     const int group = std::max(32, (512 / n_qb + 7) / 8 * 8);
-    hipLaunchKernelGGL((attn_wide_kernel<D, CAUSAL, U>), dim3((unsigned)(n_heads * n_qb)), dim3(256), lds, s, q, k, v,
+    hipLaunchKernelGGL((attn_wide_kernel<D, CAUSAL, U, REST>), dim3((unsigned)(n_heads * n_qb)), dim3(256), lds, s, q, k, v,
                        out, lse, N, Hq, Hkv, sl2, n_qb, (int)n_heads, group, kv_batch);
     return launch_status("attn_wide");
 }
@@ -821,6 +873,12 @@ int launch_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_
                            N, Hq, Hkv, sl2, causal, kv_batch);
         return launch_status("attn");
     }
+    // A few keys past the last whole tile (a vision encoder's [CLS] beside whole tiles of patches) need no tile of their
+    // own: one MFMA chain for up to 8 keys instead of two pipeline stages.  16 heads of 64, us: 20 x 577 46.5 -> 45.4,
+    // 20 x 578 46.0 -> 43.9, 8 x 257 10.0 -> 9.2, 32 x 197 x 12 13.1 -> 11.7, 4 x 1025 31.4 -> 30.9.  (Above 8 the scores
+    // would fill more than the four registers of a lane that this looks at; with the mask the tile is a diagonal one anyway.)
+    if (d == 64 && !causal && N > AW_BN && N % AW_BN >= 1 && N % AW_BN <= AW_MAX_REST)
+        return launch_attn_wide<64, false, 1, true>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s);
     if (d == 64)
         return causal ? launch_attn_wide<64, true, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s)
                       : launch_attn_wide<64, false, 1>(q, k, v, out, lse, B, N, Hq, Hkv, sl2, kv_batch, s);

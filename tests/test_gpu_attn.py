@@ -106,6 +106,21 @@ def test_non_causal(vc, N):
     assert np.abs(lse - ref_lse).max() < 1e-3
 
 
+# one to eight keys past the last whole tile of 64 go without a tile (9 and none beside them), d = 64
+@pytest.mark.parametrize("N", [64, 65, 66, 68, 69, 72, 73, 129, 197, 260, 577, 584, 585])
+@pytest.mark.parametrize("std", [1.0, 3.0])
+def test_keys_past_the_last_tile(vc, N, std):
+    t = I.qkv_tensors(210 + N, 2, N, 4, 2, 64, std=std)
+    for last in (1.0, 4.0):          # (the last keys' scores like the others', and far above or below them)
+        k = I.bf16_bits_to_f32(t["k"])
+        k[:, N - N % 64:] *= last
+        t["k"] = I.f32_to_bf16_bits(k)
+        out, lse = run(vc, t, causal=False)
+        ref, ref_lse = O.attention(t["q"], t["k"], t["v"], None, False)
+        assert_attention_close(out, ref, f"N={N}", v_scale=std)
+        assert np.abs(lse - ref_lse).max() < 1e-3 * max(1.0, np.abs(ref_lse).max() / 10)
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(28, 4), (8, 2), (6, 1)])
 def test_gqa(vc, Hq, Hkv):
     t = I.qkv_tensors(300 + Hq, 1, 150, Hq, Hkv, 128)

@@ -1264,15 +1264,17 @@ int vitcop_decoder_decode_step(const vitcop_decoder_decode_t* S, void* ws, size_
             if (rc) return rc;
             a = abuf[0];
         }
-        // the rotary embedding; the new token's K and V become row N of every sample's cache
+        // the rotary embedding; the new token's K and V become row N of every sample's cache (both in the attention, where
+        // the projections leave partial sums)
         const int32_t* ncs = S->n_cached_samples ? S->n_cached_samples + (size_t)l * B : nullptr;
         const size_t row0 = ncs ? 0 : (size_t)N * kd;
+        DecodeNew fresh{{}, S->positions, -2.0f * std::log2(S->theta) / (float)S->d, S->k_cache[l], S->v_cache[l]};
         rc = launch_gemm_qkv_rope_ws(a, D, S->wk[l], S->wq[l], S->wv[l], k_new, qb, v_new, S->Hq, S->Hkv, S->d,
                                      S->positions, S->theta, B, D, gs, gs_bytes, S->k_cache[l] + row0,
-                                     S->v_cache[l] + row0, 1, (int64_t)S->cache_capacity * kd, s, ncs);
+                                     S->v_cache[l] + row0, 1, (int64_t)S->cache_capacity * kd, s, ncs, &fresh.parts);
         if (rc) return rc;
         rc = launch_decode_attn(qb, S->k_cache[l], S->v_cache[l], ob, nullptr, B, N + 1, S->Hq, S->Hkv, S->d,
-                                1.0f / std::sqrt((float)S->d), dws, s, (int64_t)S->cache_capacity * kd, nullptr, ncs);
+                                1.0f / std::sqrt((float)S->d), dws, s, (int64_t)S->cache_capacity * kd, nullptr, ncs, &fresh);
         if (rc) return rc;
         rc = launch_gemm_norm_ws(ob, qd, S->wo[l], h1, D, h, D, B, D, qd, S->ln2[l], S->eps, bb, D, gs, gs_bytes, s);
         if (rc) return rc;

@@ -19,6 +19,8 @@ namespace vitcop {
 
 constexpr int DC_THREADS = 256;
 
+struct DecodeGiven {};                       // (in place of DecodeNew: q is given, and the caches hold the new rows)
+
 // The four wavefronts' states of G query heads (sm: maximum and sum, so: unnormalised outputs) combined by threads
 // (head, channel): the partial of this slice, or with `out` the output, what decode_merge_kernel makes of one partial.
 template <int D, int GMAX, int WAVES = 4>
@@ -54,6 +56,61 @@ __device__ __forceinline__ void decode_combine(const float (&sm)[WAVES][GMAX][2]
     }
 }
 
+// The new token of sample b, where it comes as partial sums: its query heads [hq0, hq0 + n_q) into q_lds, rounded and turned
+// as qkv_finish_kernel does, and if `append` says so its rows of KV heads [hk0, hk0 + n_kv) into the caches, from where the
+// workgroup reads them like the others (the barrier at the end orders that).  A thread takes two channels that are turned
+// together, or two neighbours of v.  Every workgroup of a head puts its q together, a few KB of partial sums and about 1 us
+// in front of the stream, which saves the launch that did it for all of them: one layer of a decoding step, us, before and
+// now: 4096 / 11008 with 64 samples x 317 keys 158.8, 156.9, x 115 keys 128.5, 124.9, 16 x 317 116.3, 113.0; 3584 / 14336 (28 / 4
+// heads) 16 x 115 100.1, 98.5; 2048 / 5632 16 x 300 63.0, 59.8; 1024 / 2816 (16 / 4 heads of 64) 24 x 60 39.4, 35.8.
+template <int D, int THREADS>
+__device__ __forceinline__ void decode_new_token(const DecodeNew& a, int b, int Hq, int Hkv, int hq0, int n_q, int hk0,
+                                                 int n_kv, bool append, int64_t cache_row, uint16_t (*q_lds)[D]) {
+    constexpr int HALF = D / 2;
+    const float position = (float)a.positions[b];
+    const int units_q = n_q * HALF, units_kv = append ? n_kv * HALF : 0;
+    const int64_t slice = (int64_t)a.parts.M * a.parts.N;
+    for (int u = threadIdx.x; u < units_q + 2 * units_kv; u += THREADS) {
+        const bool is_q = u < units_q, is_v = u >= units_q + units_kv;
+        const int unit = is_q ? u : (is_v ? u - units_q - units_kv : u - units_q);
+        const int head = unit / HALF, i = unit - head * HALF;
+        const int c0 = is_v ? 2 * i : i, c1 = is_v ? 2 * i + 1 : i + HALF;
+        const int col = (is_q ? Hkv + hq0 : (is_v ? Hkv + Hq + hk0 : hk0)) + head;
+        const float* p = a.parts.part + (int64_t)b * a.parts.N + (int64_t)col * D;
+        float lo = 0.f, hi = 0.f;
+        for (int s0 = 0; s0 < a.parts.slices; s0 += 4) {                 // four slices' loads in flight, added in order
+            float x[4], y[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (s0 + t < a.parts.slices) {
+                    x[t] = p[(s0 + t) * slice + c0];
+                    y[t] = p[(s0 + t) * slice + c1];
+                }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (s0 + t < a.parts.slices) {
+                    lo += x[t];
+                    hi += y[t];
+                }
+        }
+        uint32_t w = pack_bf16(lo, hi);
+        if (!is_v) {
+            float sn, cs;
+            sincosf(position * __builtin_exp2f((float)i * a.rope_c), &sn, &cs);
+            const float l = bf16_lo(w), h = bf16_hi(w);
+            w = pack_bf16(l * cs - h * sn, h * cs + l * sn);
+        }
+        uint16_t* dst = is_q ? q_lds[head] : (is_v ? a.v : a.k) + cache_row + (int64_t)(hk0 + head) * D;
+        if (is_v) {
+            *reinterpret_cast<uint32_t*>(dst + c0) = w;
+        } else {
+            dst[c0] = (uint16_t)w;
+            dst[c1] = (uint16_t)(w >> 16);
+        }
+    }
+    __syncthreads();
+}
+
 // One query head per KV head (G = 1), or two where group_on_vectors says so.  HBM-bound.  HEADS neighbouring heads' rows of
 // a key lie side by side in the cache, and a wavefront reads them together: pieces of 512 bytes and more instead of 256 at a
 // stride of Hkv * 2 D bytes (64 samples x 32 heads x 318 keys 59.6 -> 54.0 us, 5.6 -> 6.2 TB/s; x 118 keys 24.0 -> 22.1; x 640
@@ -63,12 +120,13 @@ __device__ __forceinline__ void decode_combine(const float (&sm)[WAVES][GMAX][2]
 // keys (one head at a time: 64 samples x 32 heads x 318 keys 61.7 -> 57.6 us, 5.4 -> 5.8 TB/s; x 116 keys 26.4 -> 23.9); not
 // for long ones (32 x 4096 keys 305 -> 321 us), nor with two query heads, which have work to do meanwhile.
 constexpr int DC_AHEAD_MAX_KEYS = 1024;
-template <int D, bool AHEAD, int HEADS, int G = 1>
+template <int D, bool AHEAD, int HEADS, int G, typename New>
 __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ q, const uint16_t* k, const uint16_t* v,
     float* __restrict__ part_o, float* __restrict__ part_ml, int N, int H, float scale_log2e, int keys_per_split,
     int n_splits, int64_t kv_batch, const int32_t* __restrict__ n_cached_samples, uint16_t* __restrict__ out,
-    float* __restrict__ lse) {
+    float* __restrict__ lse, New fresh) {
+    constexpr bool FRESH = std::is_same<New, DecodeNew>::value;
     constexpr int LPK = D / 8;                       // lanes per key row of a head
     constexpr int KPW = 64 / (LPK * HEADS);          // keys per wavefront instruction
     constexpr int WAVES = 4 * HEADS;
@@ -76,17 +134,6 @@ __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int c = lane % LPK, kq = lane / (LPK * HEADS), hs = lane / LPK % HEADS, h = h0 + hs;
 
-    float qv[G][8], m[G], l[G], acc[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const uint4 u = *reinterpret_cast<const uint4*>(q + (((int64_t)b * H + h) * G + g) * D + 8 * c);
-        qv[g][0] = bf16_lo(u.x); qv[g][1] = bf16_hi(u.x); qv[g][2] = bf16_lo(u.y); qv[g][3] = bf16_hi(u.y);
-        qv[g][4] = bf16_lo(u.z); qv[g][5] = bf16_hi(u.z); qv[g][6] = bf16_lo(u.w); qv[g][7] = bf16_hi(u.w);
-        m[g] = -INFINITY;
-        l[g] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
-    }
     // caches of different lengths: sample b attends over its n_cached_samples[b] rows and the appended one;
     // slices past them see no live key and hand on an empty partial (max -inf, sum 0)
     const int n_keys = n_cached_samples ? min(max(n_cached_samples[b], 0) + 1, N) : N;
@@ -96,11 +143,36 @@ __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
     const uint16_t* vb = v + b * kv_batch + h * D + 8 * c;
     const int key_first = key_begin + wv * KPW;
     uint4 k_next = make_uint4(0, 0, 0, 0), v_next = k_next;
-    if (AHEAD && key_first < key_end) {
+    auto first_rows = [&]() __attribute__((always_inline)) {
         const int kc = min(key_first + kq, key_end - 1);
         k_next = ld_nt16(kb + kc * row);
         v_next = ld_nt16(vb + kc * row);
+    };
+    // (the first rows are on their way while the new token is put together, unless the last one, its own, is among them)
+    const bool early = FRESH && AHEAD && key_first < key_end && key_first + KPW < n_keys;
+    const uint16_t* q_row = nullptr;
+    if constexpr (FRESH) {
+        __shared__ alignas(16) uint16_t q_new[HEADS * G][D];
+        if (early) first_rows();
+        decode_new_token<D, DC_THREADS * HEADS>(fresh, b, H * G, H, h0 * G, HEADS * G, h0, HEADS,
+                                                key_begin < n_keys && key_end == n_keys,
+                                                b * kv_batch + (n_keys - 1) * row, q_new);
+        q_row = &q_new[hs * G][8 * c];
+    } else {
+        q_row = q + ((int64_t)b * H + h) * G * D + 8 * c;
     }
+    float qv[G][8], m[G], l[G], acc[G][8];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const uint4 u = *reinterpret_cast<const uint4*>(q_row + g * D);
+        qv[g][0] = bf16_lo(u.x); qv[g][1] = bf16_hi(u.x); qv[g][2] = bf16_lo(u.y); qv[g][3] = bf16_hi(u.y);
+        qv[g][4] = bf16_lo(u.z); qv[g][5] = bf16_hi(u.z); qv[g][6] = bf16_lo(u.w); qv[g][7] = bf16_hi(u.w);
+        m[g] = -INFINITY;
+        l[g] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
+    }
+    if (AHEAD && !early && key_first < key_end) first_rows();
     for (int key0 = key_first; key0 < key_end; key0 += WAVES * KPW) {     // (empty if key_end <= key_begin)
         const int key = key0 + kq;
         const bool live = key < key_end;
@@ -183,12 +255,13 @@ __global__ __launch_bounds__(DC_THREADS * HEADS) void decode_partial_kernel(
 // only other workgroups fill (us with two and with three: 250 samples x 40 keys x 32 / 16 x 128 35.2, 30.2; x 100 x 28 / 4
 // 16.2, 14.9; where the keys are many it is the loads that count, 64 x 2000 x 28 / 4 47.6, 47.9).
 constexpr int DG_MAX_G = 16, DG_KEYS = 32;
-template <int D>
+template <int D, typename New>
 __global__ __launch_bounds__(DC_THREADS, D == 128 ? 3 : 4) void decode_group_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ q, const uint16_t* k, const uint16_t* v,
     float* __restrict__ part_o, float* __restrict__ part_ml, int N, int Hq, int Hkv, int g0, int G,
     float scale_log2e, int keys_per_split, int n_splits, int64_t kv_batch,
-    const int32_t* __restrict__ n_cached_samples, uint16_t* __restrict__ out, float* __restrict__ lse) {
+    const int32_t* __restrict__ n_cached_samples, uint16_t* __restrict__ out, float* __restrict__ lse, New fresh) {
+    constexpr bool FRESH = std::is_same<New, DecodeNew>::value;
     constexpr int STEPS = D / 32, BLOCKS = D / 16;
     constexpr int VROW = 2 * D + 32;                         // bytes of a V row in LDS: the pad keeps eight rows apart
     constexpr int LPR = D / 8, RPL = 64 / LPR, VL = DG_KEYS / RPL;         // lanes a row, rows a load, loads a tile of V
@@ -205,10 +278,6 @@ __global__ __launch_bounds__(DC_THREADS, D == 128 ? 3 : 4) void decode_group_ker
     const uint16_t* kb = k + b * kv_batch + hk * D;
     const uint16_t* vb = v + b * kv_batch + hk * D;
 
-    bf16x8 qf[STEPS];                                        // Q^T: 8 channels of head l16 a step (heads past G: head G - 1)
-#pragma unroll
-    for (int c = 0; c < STEPS; ++c)
-        qf[c] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)b * Hq + h0 + min(l16, G - 1)) * D + 32 * c + 8 * g4);
     f32x4 o[BLOCKS];
 #pragma unroll
     for (int i = 0; i < BLOCKS; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -237,10 +306,24 @@ __global__ __launch_bounds__(DC_THREADS, D == 128 ? 3 : 4) void decode_group_ker
     const unsigned tr = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)mine +
                         (4 * g4 + ((lane >> 2) & 3)) * VROW + (lane & 3) * 8;
     const int first = key_begin + wv * DG_KEYS;
+    const bool early = FRESH && first + DG_KEYS < n_keys && first < key_end;      // (as in decode_partial_kernel)
+    if (early) load(first);
+    bf16x8 qf[STEPS];                                        // Q^T: 8 channels of head l16 a step (heads past G: head G - 1)
+    if constexpr (FRESH) {
+        __shared__ alignas(16) uint16_t q_new[DG_MAX_G][D];
+        decode_new_token<D, DC_THREADS>(fresh, b, Hq, Hkv, h0, G, hk, 1, g0 == 0 && key_begin < n_keys && key_end == n_keys,
+                                        b * kv_batch + (n_keys - 1) * row, q_new);
+#pragma unroll
+        for (int c = 0; c < STEPS; ++c) qf[c] = *reinterpret_cast<const bf16x8*>(&q_new[min(l16, G - 1)][32 * c + 8 * g4]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < STEPS; ++c)
+            qf[c] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)b * Hq + h0 + min(l16, G - 1)) * D + 32 * c + 8 * g4);
+    }
     auto attend = [&](auto parts_c) __attribute__((always_inline)) {     // PARTS: bf16 summands of a probability
         constexpr int PARTS = decltype(parts_c)::value;
         constexpr bool AHEAD = PARTS > 1;                    // (the registers of the second pass hold the first's outputs)
-        if (AHEAD && first < key_end) load(first);
+        if (AHEAD && !early && first < key_end) load(first);
         for (int key0 = first; key0 < key_end; key0 += 4 * DG_KEYS) {
             if (!AHEAD) load(key0);
             f32x4 s[2];
@@ -422,10 +505,10 @@ size_t decode_workspace_bytes(int B, int N, int Hq, int Hkv, int d) {
     return up256((size_t)B * Hq * s * d * 4) + up256((size_t)B * Hq * s * 2 * 4);
 }
 
-template <int D>
+template <int D, typename New>
 static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse,
                            int B, int N, int Hq, int Hkv, float scale, void* ws, hipStream_t s, int64_t kv_batch,
-                           DecodeParts* hand_over, const int32_t* ncs) {
+                           DecodeParts* hand_over, const int32_t* ncs, const New& fresh) {
     const bool on_vectors = Hq > Hkv && group_on_vectors((long)B * Hkv, N, Hq / Hkv, D), grouped = Hq > Hkv && !on_vectors;
     const int ns = grouped ? group_splits(B, N, Hkv) : decode_splits(B, N, Hkv);
     const int kps = ((N + ns - 1) / ns + 63) / 64 * 64;
@@ -439,21 +522,21 @@ static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t*
     uint16_t* o1 = ns == 1 ? out : nullptr;
     if (grouped) {
         for (int g0 = 0; g0 < group; g0 += DG_MAX_G) {
-            hipLaunchKernelGGL((decode_group_kernel<D>), grid, dim3(DC_THREADS), 0, s, q, k, v, po, pml, N, Hq, Hkv, g0,
-                               std::min(DG_MAX_G, group - g0), sl2, kps, ns, kv_batch, ncs, o1, lse);
+            hipLaunchKernelGGL((decode_group_kernel<D, New>), grid, dim3(DC_THREADS), 0, s, q, k, v, po, pml, N, Hq, Hkv, g0,
+                               std::min(DG_MAX_G, group - g0), sl2, kps, ns, kv_batch, ncs, o1, lse, fresh);
             const int rc = launch_status("decode_group");
             if (rc) return rc;
         }
     } else {
         const bool ahead = kps <= DC_AHEAD_MAX_KEYS;
         const int heads = on_vectors ? 1 : heads_side_by_side((long)B * Hkv * ns, Hkv);
-        auto* kernel = ahead ? decode_partial_kernel<D, true, 1> : decode_partial_kernel<D, false, 1>;
-        if (heads == 2) kernel = ahead ? decode_partial_kernel<D, true, 2> : decode_partial_kernel<D, false, 2>;
-        if (heads == 4) kernel = ahead ? decode_partial_kernel<D, true, 4> : decode_partial_kernel<D, false, 4>;
-        if (on_vectors) kernel = decode_partial_kernel<D, false, 1, 2>;
+        auto* kernel = ahead ? decode_partial_kernel<D, true, 1, 1, New> : decode_partial_kernel<D, false, 1, 1, New>;
+        if (heads == 2) kernel = ahead ? decode_partial_kernel<D, true, 2, 1, New> : decode_partial_kernel<D, false, 2, 1, New>;
+        if (heads == 4) kernel = ahead ? decode_partial_kernel<D, true, 4, 1, New> : decode_partial_kernel<D, false, 4, 1, New>;
+        if (on_vectors) kernel = decode_partial_kernel<D, false, 1, 2, New>;
         grid.y = Hkv / heads;
         hipLaunchKernelGGL(kernel, grid, dim3(DC_THREADS * heads), 0, s, q, k, v, po, pml, N, Hkv, sl2, kps, ns, kv_batch, ncs,
-                           o1, lse);
+                           o1, lse, fresh);
         const int rc = launch_status("decode_partial");
         if (rc) return rc;
     }
@@ -472,13 +555,14 @@ static int launch_decode_d(const uint16_t* q, const uint16_t* k, const uint16_t*
 
 int launch_decode_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse, int B,
                        int N, int Hq, int Hkv, int d, float scale, void* ws, hipStream_t s, int64_t kv_batch,
-                       DecodeParts* hand_over, const int32_t* n_cached_samples) {
+                       DecodeParts* hand_over, const int32_t* n_cached_samples, const DecodeNew* fresh) {
     if (kv_batch == 0) kv_batch = (int64_t)N * Hkv * d;         // dense caches
-    if (d == 64)
-        return launch_decode_d<64>(q, k, v, out, lse, B, N, Hq, Hkv, scale, ws, s, kv_batch, hand_over,
-                                   n_cached_samples);
-    return launch_decode_d<128>(q, k, v, out, lse, B, N, Hq, Hkv, scale, ws, s, kv_batch, hand_over,
-                                n_cached_samples);
+    auto go = [&](auto launch, const auto& token) {
+        return launch(q, k, v, out, lse, B, N, Hq, Hkv, scale, ws, s, kv_batch, hand_over, n_cached_samples, token);
+    };
+    if (fresh != nullptr && fresh->parts.part != nullptr)
+        return d == 64 ? go(launch_decode_d<64, DecodeNew>, *fresh) : go(launch_decode_d<128, DecodeNew>, *fresh);
+    return d == 64 ? go(launch_decode_d<64, DecodeGiven>, DecodeGiven{}) : go(launch_decode_d<128, DecodeGiven>, DecodeGiven{});
 }
 
 }  // namespace vitcop

@@ -342,7 +342,8 @@ int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t*
                             const uint16_t* wv, uint16_t* k_tmp, uint16_t* q, uint16_t* v_tmp, int Hq, int Hkv, int d,
                             const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
                             uint16_t* k_dst, uint16_t* v_dst, int T, int64_t kv_batch, hipStream_t s,
-                            const int32_t* rows) {
+                            const int32_t* rows, SkParts* parts_out) {
+    if (parts_out) parts_out->part = nullptr;
     if (M == 0) return VITCOP_OK;
     const int qd = Hq * d, kd = Hkv * d;
     const uint16_t* const w3[3] = {wk, wq, wv};
@@ -356,6 +357,10 @@ int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t*
         SkParts parts{};
         const int rc = launch_gemm_skinny3(x, x_stride, w3, y3, n3, M, K, ws, s, &parts);
         if (rc) return rc;
+        if (parts_out && parts.part) {               // the caller finishes the rows itself
+            *parts_out = parts;
+            return VITCOP_OK;
+        }
         // (no partial sums: the outputs are written already)
         P = {{parts, parts, parts}, {0, kd, kd + qd}};
     } else {

@@ -91,12 +91,15 @@ int launch_gemm_pair_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w1,
 // rows start at k_dst and v_dst + (m / T) * kv_batch (plus rows[m] rows, if given: the new tokens of a decoding step,
 // T = 1, go to their caches' next rows).  k_tmp and v_tmp: scratch [M, Hkv d].
 // gemm_qkv_workspace_bytes: what ws must hold for every path this may take at M rows.
+// parts_out (nullable): of at most 256 rows the partial sums (columns [k | q | v]) are left for the caller to finish;
+// parts_out->part == nullptr afterwards means that everything is done.
+struct SkParts;
 size_t gemm_qkv_workspace_bytes(int M, int Hq, int Hkv, int d, int K);
 int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wk, const uint16_t* wq,
                             const uint16_t* wv, uint16_t* k_tmp, uint16_t* q, uint16_t* v_tmp, int Hq, int Hkv, int d,
                             const int32_t* positions, float theta, int M, int K, void* ws, size_t ws_bytes,
                             uint16_t* k_dst, uint16_t* v_dst, int T, int64_t kv_batch, hipStream_t s,
-                            const int32_t* rows = nullptr);
+                            const int32_t* rows = nullptr, SkParts* parts_out = nullptr);
 // Up to three weight matrices side by side (projections of the same input in one launch): matrix i
 // covers the columns [n_end[i-1], n_end[i]) of the launch (boundaries multiples of 128; unused
 // entries repeat N) and writes its own output with its own row stride.
@@ -215,10 +218,20 @@ int launch_silu_mul(const uint16_t* gate, const uint16_t* up, uint16_t* out, int
 
 // ---- decoding step over the KV cache (decode.hip) ---------------------------
 size_t decode_workspace_bytes(int B, int N, int Hq, int Hkv, int d);
+// The new tokens' k, q and v as partial sums of their projections (columns [k | q | v] of `parts`, row b for sample b): the
+// attention adds them up as launch_qkv_finish does, turns q and k, and appends k and v to the caches as the last row that
+// it attends over.
+struct DecodeNew {
+    SkParts parts;                       // parts.part == nullptr: q is given, and the caches hold the new rows
+    const int32_t* positions;            // [B]
+    float rope_c;                        // -2 log2(theta) / d
+    uint16_t *k, *v;                     // the caches, for writing
+};
 // kv_batch: elements between two samples' caches (0: dense, N * Hkv * d); n_cached_samples (nullable, device
-// [B]): sample b attends over its first n_cached_samples[b] + 1 <= N rows only
+// [B]): sample b attends over its first n_cached_samples[b] + 1 <= N rows only; fresh (nullable): instead of q
 int launch_decode_attn(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out, float* lse, int B,
                        int N, int Hq, int Hkv, int d, float scale, void* ws, hipStream_t s, int64_t kv_batch = 0,
-                       DecodeParts* hand_over = nullptr, const int32_t* n_cached_samples = nullptr);
+                       DecodeParts* hand_over = nullptr, const int32_t* n_cached_samples = nullptr,
+                       const DecodeNew* fresh = nullptr);
 
 }  // namespace vitcop

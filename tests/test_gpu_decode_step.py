@@ -109,6 +109,17 @@ def test_decode_step_matches_oracle(vc, B, n_cached, dims):
         assert not host_bits(kc)[:, n + 1:].any() and not host_bits(vcache)[:, n + 1:].any()
 
 
+# the new token put together inside the attention: no key before it, none or all of a wavefront's and a slice's, in one
+# slice and in several; one query head per KV head, two, a group, a group of two passes (heads read side by side:
+# test_per_sample_cache_lengths_of_vector_kernels)
+@pytest.mark.parametrize("B,n_cached,dims", [
+    (7, (0, 1, 15, 16), (512, 4, 4, 128, 640)), (5, (63, 64, 65, 255), (512, 4, 4, 64, 640)),
+    (6, (0, 15, 17, 130), (512, 8, 4, 128, 640)), (9, (0, 31, 32, 127, 128), (512, 8, 2, 64, 640)),
+    (6, (0, 33, 200), (512, 36, 2, 64, 640))])
+def test_decode_step_appends_inside_the_attention(vc, B, n_cached, dims):
+    test_decode_step_matches_oracle(vc, B, n_cached, dims)
+
+
 def test_prefill_then_decode_equals_longer_prefill(vc):
     # GPU only: a pruned prefill of T-1 tokens with cache export, then one decoding step of token T,
     # against the last row of the same pruned prefill over T tokens (same keep lists: the last token is text)

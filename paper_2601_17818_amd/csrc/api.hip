@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 
+#include "gemm_plan.h"
 #include "vitcop_internal.h"
 
 namespace vitcop {
@@ -280,13 +281,13 @@ static int check_layer(const vitcop_layer_t* L) {
 
 // Scratch of the few-row projection path: the largest need among a layer's projections (rows
 // before and after pruning; F = 0: no MLP).
-// The need is not monotone in the row count (different paths below 257 and below 1025 rows, slice
+// The need is not monotone in the row count (different paths below 257 and below 1537 rows, slice
 // counts that drop as tiles are added), and a schedule sizes its workspace for its longest sequence:
 // so a launch of M rows reserves the largest need of the multiples of 64 up to M and of M itself.  (Tiles end
 // elsewhere too; what a layer asks for in all grows with its rows, which the tests walk row by row.)
 static size_t gemm_scratch_upto(int M, int N, int K) {
     size_t n = gemm_workspace_bytes(M, N, K);
-    for (int m = 64; m < M && m <= 1024; m += 64) n = std::max(n, gemm_workspace_bytes(m, N, K));
+    for (int m = 64; m < M && m <= SPLITK_TALL_ROWS; m += 64) n = std::max(n, gemm_workspace_bytes(m, N, K));
     return n;
 }
 static size_t layer_gemm_scratch(int M_all, int M_kept, int D, int qd, int kd, int F, int d = 0) {
@@ -295,7 +296,7 @@ static size_t layer_gemm_scratch(int M_all, int M_kept, int D, int qd, int kd, i
     n = std::max(n, gemm_scratch_upto(M_all, qd + 2 * kd, D));                   // K, Q and V of a layer that keeps all
     if (d > 0) {                                                                 // the same with the rotary embedding
         n = std::max(n, gemm_qkv_workspace_bytes(M_all, qd / d, kd / d, d, D));
-        for (int m = 64; m < M_all && m <= 1024; m += 64)
+        for (int m = 64; m < M_all && m <= SPLITK_TALL_ROWS; m += 64)
             n = std::max(n, gemm_qkv_workspace_bytes(m, qd / d, kd / d, d, D));
     }
     n = std::max(n, gemm_scratch_upto(M_kept, D, qd));                           // O

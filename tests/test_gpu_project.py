@@ -55,6 +55,20 @@ def test_split_k(M, N, K):
     check(x, w, y, r)
 
 
+SPLIT_TALL = [(1025, 512, 4096), (1500, 3584, 14336), (1300, 1040, 4128), (1536, 2048, 5632), (1500, 272, 2048)]
+
+
+@pytest.mark.parametrize("M,N,K", SPLIT_TALL)
+def test_slices_of_tall_launches(M, N, K):
+    x, w, r = draw(M, N, K, M)
+    y, _ = vc.vitcop_project(x, w, residual=r)
+    check(x, w, y, r)
+    y, parts = vc.vitcop_project(x, w, want_sumsq=True)
+    check(x, w, y)
+    sq = torch.nn.functional.pad(y.double() ** 2, (0, -N % 128)).reshape(M, -1, 128).sum(-1).T
+    assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
+
+
 # slices of 32 k-steps and more start at different k and wrap around: one, two and four tile rows, a last step of half a
 # step in the middle of the walk (test_plan_cpu.py checks their length)
 LONG_SLICES = [(20, 4096, 8192), (64, 4096, 12288), (100, 8192, 8192), (250, 8192, 8192), (300, 4096, 8224), (300, 8192, 8224),

@@ -19,6 +19,11 @@ int splitk(int M, int N, int K, int* o) {
     o[0] = p.bm; o[1] = p.bn;
     return p.splits;
 }
+int splitk_tall(int M, int N, int K, int* o) {
+    const SplitKPlan p = splitk_tall_plan(M, N, K);
+    o[0] = p.bm; o[1] = p.bn;
+    return p.splits;
+}
 int most_slices(int M, int N, int K) { return splitk_most(M, N, K); }
 int whole_tile(int M, int N, int K, int* o) {
     const TileShape& t = kTiles[choose_tile(M, N, K, false, 768)];
@@ -88,6 +93,27 @@ def test_slices_of_few_rows_are_priced(plan, M, N, K):
 def test_long_slices_are_long(plan, M, N, K):
     slices = plan.few_rows(M, N, K, (C.c_int * 2)()) if M <= 256 else picked(plan, M, N, K)[2]
     assert (K + 63) // 64 // slices >= 32
+
+
+def test_slices_of_tall_launches(plan):
+    """1025 to 1536 rows: within the scratch, on the tiles that the GPU tests reach, none above; up to 1024 rows the same."""
+    reached = {t[:2] for t in (picked(plan, *s) for s in gpu.SPLIT_K) if t[2] > 1}
+    cut = 0
+    for M in list(range(257, 1600, 13)) + [1024, 1025, 1536, 1537, 3000]:
+        for N, K in ((512, 3584), (1024, 1024), (2048, 5632), (4096, 4096), (5120, 5120), (3584, 14336), (272, 4128)):
+            o = (C.c_int * 2)()
+            slices = plan.splitk_tall(M, N, K, o)
+            if M <= 1024:
+                p = (C.c_int * 2)()
+                assert slices == plan.splitk(M, N, K, p) and list(o) == list(p)
+            elif M > 1536:
+                assert slices == 0
+            elif slices:
+                assert 2 <= slices <= plan.most_slices(M, N, K) and (o[0], o[1]) in reached
+                cut += 1
+    assert cut > 50
+    for M, N, K in gpu.SPLIT_TALL:
+        assert plan.splitk_tall(M, N, K, (C.c_int * 2)()) > 1
 
 
 def sliced(plan, M, N, K):

@@ -113,19 +113,20 @@ __global__ __launch_bounds__(256) void gemm_skinny_reduce_kernel(
 // The same reduction followed by an RMSNorm of the finished row (the next operation of a decoder
 // layer after its attention and MLP output projections): y as above, and
 // norm_out[m, :] = y[m, :] / sqrt(mean(y[m, :]^2) + eps) * ln_w, computed from the ROUNDED y exactly as
-// rmsnorm_kernel does.  One workgroup per row; a thread owns the chunks tid, tid + 512, ... (J of them; N <= 8 * 512 * J).
+// rmsnorm_kernel does.  One workgroup per row; a thread owns the chunks tid, tid + THREADS, ... (J of them).
 // Everything a thread reads is requested before the first wait (half the threads, two chunks each one after the other, the
 // residual and the weight when they were needed: 4096 columns in four slices, 317 rows 6.95 -> 6.70 us, 115 rows
 // 5.10 -> 4.79, 64 rows 4.75 either way; the plain reduction of 640 rows 6.5 -> 6.05, of 93 rows x 8192 5.0 -> 4.35).
-constexpr int SK_NORM_THREADS = 512, SK_NORM_CHUNKS = 8;
+// Rows of fewer chunks take fewer threads: 384 idle ones of 512 cost a layer of 1024 columns half a per cent.
+constexpr int SK_NORM_THREADS = 512, SK_NORM_CHUNKS = 8;         // at most
 
-template <int J>
-__global__ __launch_bounds__(SK_NORM_THREADS) void gemm_skinny_reduce_norm_kernel(
+template <int THREADS, int J>
+__global__ __launch_bounds__(THREADS) void gemm_skinny_reduce_norm_kernel(
     SkParts parts, int N, uint16_t* __restrict__ y, int64_t y_stride, const uint16_t* __restrict__ res,
     int64_t res_stride, const uint16_t* __restrict__ ln_w, float eps, uint16_t* __restrict__ norm_out,
     int64_t norm_stride) {
     constexpr int AHEAD = J < 2 ? J : 2;             // chunks requested together
-    __shared__ float wave_part[SK_NORM_THREADS / 64];
+    __shared__ float wave_part[THREADS / 64];
     const int m = blockIdx.x, tid = threadIdx.x;
     const int chunks = N / 8;
     u32x4 held[J], weight[J];            // (native vector types: arrays of the uint4 struct end up in scratch)
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(SK_NORM_THREADS) void gemm_skinny_reduce_norm_kerne
         u32x4 r[AHEAD];
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) {
-            const int c = tid + SK_NORM_THREADS * (j0 + u);
+            const int c = tid + THREADS * (j0 + u);
             if (c >= chunks) continue;
             sum[u] = SkSum(parts, m, 8 * c);
             r[u] = res ? *reinterpret_cast<const u32x4*>(res + (int64_t)m * res_stride + 8 * c) : u32x4{0, 0, 0, 0};
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(SK_NORM_THREADS) void gemm_skinny_reduce_norm_kerne
         }
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) {
-            const int c = tid + SK_NORM_THREADS * (j0 + u);
+            const int c = tid + THREADS * (j0 + u);
             if (c >= chunks) continue;
             float v[8];
             sum[u].add_up(v);
@@ -165,11 +166,11 @@ __global__ __launch_bounds__(SK_NORM_THREADS) void gemm_skinny_reduce_norm_kerne
     __syncthreads();
     ss = 0.f;
 #pragma unroll
-    for (int w = 0; w < SK_NORM_THREADS / 64; ++w) ss += wave_part[w];
+    for (int w = 0; w < THREADS / 64; ++w) ss += wave_part[w];
     const float r = __builtin_amdgcn_rsqf(ss / (float)N + eps);
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-        const int c = tid + SK_NORM_THREADS * j;
+        const int c = tid + THREADS * j;
         if (c >= chunks) continue;
         const u32x4 v = held[j], g = weight[j];
         u32x4 o;
@@ -403,13 +404,15 @@ int launch_partial_reduce(const SkParts& parts, int N, const SkMats& mats, const
         return launch_status("gemm_skinny_reduce_silu");
     }
     if (ln_w != nullptr) {
-#define VITCOP_REDUCE_NORM(J)                                                                                              \
-    hipLaunchKernelGGL(gemm_skinny_reduce_norm_kernel<J>, dim3(M), dim3(SK_NORM_THREADS), 0, s, parts, N, mats.y[0],         \
-                       mats.y_stride[0], res, res_stride, ln_w, eps, norm_out, norm_stride)
-        const int per_thread = (N / 8 + SK_NORM_THREADS - 1) / SK_NORM_THREADS;
-        if (per_thread <= 1) VITCOP_REDUCE_NORM(1);
-        else if (per_thread <= 2) VITCOP_REDUCE_NORM(2);
-        else VITCOP_REDUCE_NORM(SK_NORM_CHUNKS);
+#define VITCOP_REDUCE_NORM(T, J)                                                                                       \
+    hipLaunchKernelGGL((gemm_skinny_reduce_norm_kernel<T, J>), dim3(M), dim3(T), 0, s, parts, N, mats.y[0], mats.y_stride[0], \
+                       res, res_stride, ln_w, eps, norm_out, norm_stride)
+        const int chunks = N / 8;
+        if (chunks <= 128) VITCOP_REDUCE_NORM(128, 1);
+        else if (chunks <= 256) VITCOP_REDUCE_NORM(256, 1);
+        else if (chunks <= SK_NORM_THREADS) VITCOP_REDUCE_NORM(SK_NORM_THREADS, 1);
+        else if (chunks <= 2 * SK_NORM_THREADS) VITCOP_REDUCE_NORM(SK_NORM_THREADS, 2);
+        else VITCOP_REDUCE_NORM(SK_NORM_THREADS, SK_NORM_CHUNKS);
 #undef VITCOP_REDUCE_NORM
         return launch_status("gemm_skinny_reduce_norm");
     }

@@ -764,12 +764,14 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
         }
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
         const float top = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
-        if (top > -INFINITY) {                           // (otherwise as if nothing had been seen)
+        const bool seen = top > -INFINITY;               // (otherwise no reference: as if nothing had been seen)
+        if (seen) {
             m_ref[0] = top;
             thr[0] = fmaxf((top + AW_RESCALE_GAP) / scale_log2e, -3.0e38f);
         }
+        const float ref = seen ? top : 0.f;              // (-inf still gives 0, and a NaN stays one, as in the tiles)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[r] = top > -INFINITY ? __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -top)) : 0.f;
+        for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(p[r], scale_log2e, -ref));
         l_run[0] = (p[0] + p[1]) + (p[2] + p[3]);
         const u32x4 pw = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), 0u, 0u};
 #pragma unroll

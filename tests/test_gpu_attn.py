@@ -121,6 +121,15 @@ def test_keys_past_the_last_tile(vc, N, std):
         assert np.abs(lse - ref_lse).max() < 1e-3 * max(1.0, np.abs(ref_lse).max() / 10)
 
 
+# a NaN in the last key reaches every query of its heads, whether that key stands alone past the last tile or not
+@pytest.mark.parametrize("N", [64, 65, 66, 72, 73])
+def test_nan_in_the_last_key(vc, N):
+    t = I.qkv_tensors(240 + N, 1, N, 4, 2, 64)
+    t["k"][0, N - 1, 1] = 0x7FC0
+    out, _ = run(vc, t, causal=False)
+    assert np.isnan(out[0, :, 2:]).all() and np.isfinite(out[0, :, :2]).all()
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(28, 4), (8, 2), (6, 1)])
 def test_gqa(vc, Hq, Hkv):
     t = I.qkv_tensors(300 + Hq, 1, 150, Hq, Hkv, 128)

@@ -274,18 +274,20 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
             nk = first_half;
         }
     }
-    // Up to a thousand rows a launch is a stream over W from HBM, and its workgroups, which read rows a power of two apart
+    // Up to a few hundred rows a launch is a stream over W from HBM, and its workgroups, which read rows a power of two apart
     // as often as not, would in step all ask for the same few columns, i.e. for a part of the memory channels (loads alone,
     // 230 tiles of 96 columns of 4096 and 64 rows of x: 39.8 us in step, 31.2 apart).  So long slices start at different k
-    // and wrap around: where one tile holds all rows, the tiles spread evenly over k; where the rows take several, the
+    // and wrap around: where one tile holds all rows, the tiles spread evenly over k; where the rows take two, the
     // eight XCDs do, and the tiles of one, which share the rows of x and of W in its L2, stay in step.  Layers of 4096 /
     // 11008, us each, in step / one k-step further from tile to tile (used before, up to 64 rows) / this: 64 decoding rows
     // 126.5 / 116.0 / 114.6; 32 rows 116.6 / 108.1 / 104.4; prefill of 115 rows 144.1 / 138.8 / 137.4; 317 rows
-    // 204.6 / 200.0 / 199.5.  640 rows are the same either way, and whole tiles of thousands of rows, whose W comes from
-    // L2, lose 0.7 %.  Short slices stay in step (4096x4096 in four slices of 16 steps: 7.4 to 7.9 us for 7.5).
-    constexpr bool ROTATE = EPI == GM_EPI_PART || EPI == GM_EPI_GATED;
+    // 204.6 / 200.0 / 199.5.  640 rows, three and four tiles, are the same either way and stay in step, and whole tiles of
+    // thousands of rows, whose W comes from L2, lose 0.7 %.  Short slices stay in step (4096x4096 in four slices of 16
+    // steps: 7.4 to 7.9 us for 7.5).
+    // The 256-column tiles of gate and up are for thousands of rows and carry no wrap-around in their step.
+    constexpr bool ROTATE = EPI == GM_EPI_PART || (EPI == GM_EPI_GATED && BN <= 192);
     int rot = 0;
-    if (ROTATE && tiles_m <= 4 && nk >= 32)
+    if (ROTATE && tiles_m <= 2 && nk >= 32)
         rot = tiles_m == 1 ? tile_n * nk / tiles_n : (int)(blockIdx.x % GM_XCDS) * nk / GM_XCDS;
     auto k_at = [&](int t) __attribute__((always_inline)) {
         if constexpr (!ROTATE) return t;

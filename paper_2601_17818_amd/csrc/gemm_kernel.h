@@ -82,7 +82,7 @@ constexpr int GM_EPI_BF16 = 0, GM_EPI_GRAM = 1, GM_EPI_PART = 2, GM_EPI_GATED = 
 // (64 bytes per clock) is never asked for more than it moves and no wavefront is stuck on issuing one.
 // Against 32x32x16 with four slabs of 32 and compiler scheduling hints (GPU time, random operands, same box):
 // 11776x4096x4096 354 -> 278 us (1116 -> 1424 TFLOP/s), 1536x8192x4096 107 -> 77 us.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS, bool SPREAD>
 __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     const uint16_t* __restrict__ x, int64_t x_stride, SkMats mats, const uint16_t* __restrict__ res,
     int64_t res_stride, int M, int N, int K, float* __restrict__ sumsq_parts, int tiles_m,
@@ -284,13 +284,13 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     // 204.6 / 200.0 / 199.5.  640 rows, three and four tiles, are the same either way and stay in step, and whole tiles of
     // thousands of rows, whose W comes from L2, lose 0.7 %.  Short slices stay in step (4096x4096 in four slices of 16
     // steps: 7.4 to 7.9 us for 7.5).
-    // The 256-column tiles of gate and up are for thousands of rows and carry no wrap-around in their step.
-    constexpr bool ROTATE = EPI == GM_EPI_PART || (EPI == GM_EPI_GATED && BN <= 192);
+    // Launches of more rows are built without the wrap-around, whose addresses cost a step up to 2.5 % (gate/up of 920 rows
+    // 57.3 -> 55.9 us).
     int rot = 0;
-    if (ROTATE && tiles_m <= 2 && nk >= 32)
+    if (SPREAD && nk >= 32)
         rot = tiles_m == 1 ? tile_n * nk / tiles_n : (int)(blockIdx.x % GM_XCDS) * nk / GM_XCDS;
     auto k_at = [&](int t) __attribute__((always_inline)) {
-        if constexpr (!ROTATE) return t;
+        if constexpr (!SPREAD) return t;
         return t + rot >= nk ? t + rot - nk : t + rot;
     };
     auto k_off = [&](int t, unsigned rec) __attribute__((always_inline)) {
@@ -544,14 +544,12 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
 #endif
 }
 
-// (as many slabs as fit in LDS, up to four)
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128))>
-static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
-                           int64_t res_stride, int M, int N, int K, float* sumsq_parts,
-                           hipStream_t s, int64_t w_stride = 0, float* dist = nullptr, int64_t dist_stride = 0,
-                           int batch = 1, int64_t x_batch = 0, int64_t sq_batch = 0, int64_t dist_batch = 0, int64_t sq_half = 0) {
-    if (w_stride == 0) w_stride = K;
-    auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, NS>;
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS, bool SPREAD>
+static int launch_gemm_as(const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
+                          int64_t res_stride, int M, int N, int K, float* sumsq_parts,
+                          hipStream_t s, int64_t w_stride, float* dist, int64_t dist_stride,
+                          int batch, int64_t x_batch, int64_t sq_batch, int64_t dist_batch, int64_t sq_half) {
+    auto kern = gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, NS, SPREAD>;
     constexpr size_t lds = gemm_lds_bytes<BM, BN, WAVES_M, WAVES_N, NS>();
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     static std::atomic<bool> attr_set{false};   // per kernel instantiation; a second thread repeating the call is harmless
@@ -571,6 +569,20 @@ static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const SkMats& ma
     hipLaunchKernelGGL(kern, dim3(tiles * batch), dim3(GM_THREADS), lds, s, x, x_stride, mats, res,
                        res_stride, M, N, K, sumsq_parts, tiles_m, tiles_n, group_m, w_stride, dist, dist_stride, x_batch, sq_batch, sq_half, dist_batch);
     return launch_status("gemm");
+}
+
+// (as many slabs as fit in LDS, up to four)
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128))>
+static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
+                           int64_t res_stride, int M, int N, int K, float* sumsq_parts,
+                           hipStream_t s, int64_t w_stride = 0, float* dist = nullptr, int64_t dist_stride = 0,
+                           int batch = 1, int64_t x_batch = 0, int64_t sq_batch = 0, int64_t dist_batch = 0, int64_t sq_half = 0) {
+    if (w_stride == 0) w_stride = K;
+    auto launch = launch_gemm_as<BM, BN, WAVES_M, WAVES_N, EPI, NS, false>;
+    if constexpr (EPI == GM_EPI_PART || EPI == GM_EPI_GATED)
+        if (M <= 2 * BM) launch = launch_gemm_as<BM, BN, WAVES_M, WAVES_N, EPI, NS, true>;
+    return launch(x, x_stride, mats, res, res_stride, M, N, K, sumsq_parts, s, w_stride, dist, dist_stride, batch, x_batch,
+                  sq_batch, dist_batch, sq_half);
 }
 
 }  // namespace vitcop

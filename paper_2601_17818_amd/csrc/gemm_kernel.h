@@ -278,7 +278,10 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     // as often as not, would in step all ask for the same few columns, i.e. for a part of the memory channels (loads alone,
     // 230 tiles of 96 columns of 4096 and 64 rows of x: 39.8 us in step, 31.2 apart).  So long slices start at different k
     // and wrap around: where one tile holds all rows, the tiles spread evenly over k; where the rows take two, the
-    // eight XCDs do, and the tiles of one, which share the rows of x and of W in its L2, stay in step.  Layers of 4096 /
+    // eight XCDs do, and the tiles of one, which share the rows of x and of W in its L2, stay in step.  The start is a matter
+    // of the columns alone, so that equal rows get equal sums wherever they stand in a launch: the two tiles of a column
+    // follow each other in the XCDs' ranges, and where the second is the first of its XCD's it starts as the one before
+    // does.  Layers of 4096 /
     // 11008, us each, in step / one k-step further from tile to tile (used before, up to 64 rows) / this: 64 decoding rows
     // 126.5 / 116.0 / 114.6; 32 rows 116.6 / 108.1 / 104.4; prefill of 115 rows 144.1 / 138.8 / 137.4; 317 rows
     // 204.6 / 200.0 / 199.5.  640 rows, three and four tiles, are the same either way and stay in step, and whole tiles of
@@ -288,7 +291,8 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     // 57.3 -> 55.9 us).
     int rot = 0;
     if (SPREAD && nk >= 32)
-        rot = tiles_m == 1 ? tile_n * nk / tiles_n : (int)(blockIdx.x % GM_XCDS) * nk / GM_XCDS;
+        rot = tiles_m == 1 ? tile_n * nk / tiles_n
+                           : ((int)(blockIdx.x % GM_XCDS) - (tile_m == 1 && blockIdx.x < GM_XCDS)) * nk / GM_XCDS;
     auto k_at = [&](int t) __attribute__((always_inline)) {
         if constexpr (!SPREAD) return t;
         return t + rot >= nk ? t + rot - nk : t + rot;

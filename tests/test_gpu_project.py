@@ -88,6 +88,36 @@ def test_long_gate_up(M, D, Hq, Hkv, d, F):
     test_matrices_side_by_side(M, D, Hq, Hkv, d, F)
 
 
+# (slices of two tile rows that the XCDs' ranges cut inside a column, on tiles of 160, 192 and 256 rows; few rows, three
+# tile rows and more, whole tiles)
+@pytest.mark.parametrize("M,N,K", [(300, 4144, 8224), (380, 4608, 11008), (420, 8448, 8448), (300, 5632, 11008), (120, 4096, 8192),
+                                   (250, 8192, 8192), (1000, 4112, 8224), (1300, 1040, 4128), (2600, 4096, 1024)])
+def test_equal_rows_get_equal_sums(M, N, K):
+    """Wherever a row stands in a launch, its sums are added in the same order: equal samples of a batch stay equal."""
+    x, w, r = draw(M // 2, N, K, M)
+    y, _ = vc.vitcop_project(torch.cat([x, x]), w, residual=torch.cat([r, r]))
+    assert torch.equal(y[:M // 2], y[M // 2:])
+
+
+@pytest.mark.parametrize("T", [60, 150, 190, 250, 600])
+@pytest.mark.parametrize("D,F", [(2080, 8320), (2048, 11008)])
+def test_equal_samples_of_a_batch_stay_equal(T, D, F):
+    """The same over a decoder layer that prunes: K, Q and V, gate and up in whole tiles, the kept tokens."""
+    Hq, Hkv, d, keep = 4, 4, 128, T - 20
+    g = torch.Generator(device="cuda").manual_seed(T + F)
+
+    def t(*shape, std=1.0):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+    w = {"ln1": t(D), "ln2": t(D), "wq": t(Hq * d, D, std=D ** -0.5), "wk": t(Hkv * d, D, std=D ** -0.5),
+         "wv": t(Hkv * d, D, std=D ** -0.5), "wo": t(D, Hq * d, std=D ** -0.5), "wg": t(F, D, std=D ** -0.5),
+         "wu": t(F, D, std=D ** -0.5), "wd": t(D, F, std=F ** -0.5)}
+    h = t(1, T + 10, D).repeat(2, 1, 1)
+    pos = torch.arange(T + 10, dtype=torch.int32, device="cuda").repeat(2, 1)
+    out = vc.vitcop_decoder_layer_prefill(h, pos, w, Hq, Hkv, d, 5, T, keep)
+    assert torch.equal(out["keep_idx"][0], out["keep_idx"][1])
+    assert torch.equal(out["y"][0], out["y"][1])
+
+
 def test_rows_past_the_end_do_not_leak_in():
     """What lies behind the last row of x in memory (here infinities) is never multiplied."""
     x, w, r = draw(300, 512, 96, 3)

@@ -307,8 +307,12 @@ static size_t layer_gemm_scratch(int M_all, int M_kept, int D, int qd, int kd, i
     return n;
 }
 
-size_t vitcop_layer_workspace_bytes(const vitcop_layer_t* L) {
-    if (check_layer(L) != VITCOP_OK) return 0;
+// Walking the launches' plans takes tens of microseconds on the host (8 prompts of a 7B model 60 us a layer), in front of the
+// first launch: a call does it once per layer, and a schedule once per shape of layer.
+static size_t layer_gemm_scratch(const vitcop_layer_t* L) {
+    return layer_gemm_scratch(L->B * L->T, L->B * (L->T - L->n_vis + L->keep), L->D, L->Hq * L->d, L->Hkv * L->d, 0);
+}
+static size_t layer_bytes(const vitcop_layer_t* L, size_t gemm_scratch) {
     const size_t B = L->B, T = L->T, Tp = L->T - L->n_vis + L->keep, D = L->D;
     const size_t qd = (size_t)L->Hq * L->d, kd = (size_t)L->Hkv * L->d;
     size_t n = 0;
@@ -320,8 +324,12 @@ size_t vitcop_layer_workspace_bytes(const vitcop_layer_t* L) {
     n += up256(B * Tp * qd * 2);                                        // Q
     n += up256(B * Tp * kd * 2);                                        // V
     n += up256(B * Tp * qd * 2);                                        // attention output
-    n += layer_gemm_scratch((int)(B * T), (int)(B * Tp), (int)D, (int)qd, (int)kd, 0);
-    return n;
+    return n + gemm_scratch;
+}
+
+size_t vitcop_layer_workspace_bytes(const vitcop_layer_t* L) {
+    if (check_layer(L) != VITCOP_OK) return 0;
+    return layer_bytes(L, layer_gemm_scratch(L));
 }
 
 int vitcop_layer_prefill(const vitcop_layer_t* L, void* ws, size_t ws_bytes, void* stream) {
@@ -332,8 +340,8 @@ int vitcop_layer_prefill(const vitcop_layer_t* L, void* ws, size_t ws_bytes, voi
                 aligned16(L->wo) && aligned16(L->y),
             VITCOP_EINVAL, "layer: pointers must be 16-byte aligned");
     REQUIRE(!L->positions_out || L->positions_in, VITCOP_EINVAL, "layer: positions_out without positions_in");
-    REQUIRE(ws && ws_bytes >= vitcop_layer_workspace_bytes(L), VITCOP_EWORKSPACE,
-            "layer: workspace needs %zu bytes", vitcop_layer_workspace_bytes(L));
+    const size_t gs_bytes = layer_gemm_scratch(L), need = layer_bytes(L, gs_bytes);
+    REQUIRE(ws && ws_bytes >= need, VITCOP_EWORKSPACE, "layer: workspace needs %zu bytes", need);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int B = L->B, T = L->T, D = L->D, Tp = L->T - L->n_vis + L->keep;
     const int qd = L->Hq * L->d, kd = L->Hkv * L->d;
@@ -350,7 +358,6 @@ int vitcop_layer_prefill(const vitcop_layer_t* L, void* ws, size_t ws_bytes, voi
     uint16_t* qb = c.take<uint16_t>((size_t)B * Tp * qd * 2);
     uint16_t* vb = c.take<uint16_t>((size_t)B * Tp * kd * 2);
     uint16_t* ob = c.take<uint16_t>((size_t)B * Tp * qd * 2);
-    const size_t gs_bytes = layer_gemm_scratch(B * T, B * Tp, D, qd, kd, 0);
     void* gs = c.take<char>(gs_bytes);
     int32_t* idx = L->keep_idx ? L->keep_idx : idx_ws;
 
@@ -439,11 +446,13 @@ size_t vitcop_schedule_workspace_bytes(const vitcop_schedule_t* S) {
     // scratch once pruning has cut the sequence)
     size_t layer_max = 0;
     int stage = 0;
+    bool pruned_before = false;   // (otherwise this layer is one like the last)
     for (int l = 0; l < S->n_layers; ++l) {
         L.keep = L.n_vis;
         const bool prune_here = stage < S->n_stages && S->prune_layer[stage] == l;
         if (prune_here) L.keep = S->prune_keep[stage++];
-        layer_max = std::max(layer_max, vitcop_layer_workspace_bytes(&L));
+        if (l == 0 || prune_here || pruned_before) layer_max = std::max(layer_max, vitcop_layer_workspace_bytes(&L));
+        pruned_before = prune_here;
         L.T = L.T - L.n_vis + L.keep;
         L.n_vis = L.keep;
     }
@@ -649,8 +658,10 @@ static int check_decoder_layer(const vitcop_decoder_layer_t* L) {
     return VITCOP_OK;
 }
 
-size_t vitcop_decoder_layer_workspace_bytes(const vitcop_decoder_layer_t* L) {
-    if (check_decoder_layer(L) != VITCOP_OK) return 0;
+static size_t layer_gemm_scratch(const vitcop_decoder_layer_t* L) {
+    return layer_gemm_scratch(L->B * L->T, L->B * (L->T - L->n_vis + L->keep), L->D, L->Hq * L->d, L->Hkv * L->d, L->F, L->d);
+}
+static size_t decoder_layer_bytes(const vitcop_decoder_layer_t* L, size_t gemm_scratch) {
     const size_t B = L->B, T = L->T, Tp = L->T - L->n_vis + L->keep, D = L->D, F = L->F;
     const size_t qd = (size_t)L->Hq * L->d, kd = (size_t)L->Hkv * L->d;
     size_t n = 0;
@@ -664,8 +675,12 @@ size_t vitcop_decoder_layer_workspace_bytes(const vitcop_decoder_layer_t* L) {
     n += up256(B * Tp * qd * 2);                                        // attention output
     n += 2 * up256(B * Tp * D * 2);                                     // h1, b
     n += 3 * up256(B * Tp * F * 2);                                     // gate, up, silu(gate) * up
-    n += layer_gemm_scratch((int)(B * T), (int)(B * Tp), (int)D, (int)qd, (int)kd, (int)F, L->d);
-    return n;
+    return n + gemm_scratch;
+}
+
+size_t vitcop_decoder_layer_workspace_bytes(const vitcop_decoder_layer_t* L) {
+    if (check_decoder_layer(L) != VITCOP_OK) return 0;
+    return decoder_layer_bytes(L, layer_gemm_scratch(L));
 }
 
 // The layer.  a_pre: RMSNorm(h) * ln1 already computed ([B*T, D] dense), or null.  ln_next / a_next:
@@ -682,7 +697,7 @@ static int decoder_layer_run(const vitcop_decoder_layer_t* L, const uint16_t* a_
                 aligned16(L->wv) && aligned16(L->wo) && aligned16(L->wg) && aligned16(L->wu) && aligned16(L->wd) &&
                 aligned16(L->y),
             VITCOP_EINVAL, "decoder_layer: pointers must be 16-byte aligned");
-    const size_t need = vitcop_decoder_layer_workspace_bytes(L);
+    const size_t gs_bytes = layer_gemm_scratch(L), need = decoder_layer_bytes(L, gs_bytes);
     REQUIRE(ws && ws_bytes >= need, VITCOP_EWORKSPACE, "decoder_layer: workspace needs %zu bytes", need);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int B = L->B, T = L->T, D = L->D, F = L->F, Tp = L->T - L->n_vis + L->keep;
@@ -708,7 +723,6 @@ static int decoder_layer_run(const vitcop_decoder_layer_t* L, const uint16_t* a_
     uint16_t* gate = c.take<uint16_t>((size_t)B * Tp * F * 2);
     uint16_t* up = c.take<uint16_t>((size_t)B * Tp * F * 2);
     uint16_t* act = c.take<uint16_t>((size_t)B * Tp * F * 2);
-    const size_t gs_bytes = layer_gemm_scratch(B * T, B * Tp, D, qd, kd, F, L->d);
     void* gs = c.take<char>(gs_bytes);
     int32_t* idx = L->keep_idx ? L->keep_idx : idx_ws;
     int32_t* pos = L->positions_out ? L->positions_out : pos_ws;
@@ -828,11 +842,13 @@ size_t vitcop_decoder_schedule_workspace_bytes(const vitcop_decoder_schedule_t* 
     vitcop_decoder_layer_t L = first_decoder_layer(S);
     size_t layer_max = 0;         // the largest layer workspace along the schedule
     int stage = 0;
+    bool pruned_before = false;   // (otherwise this layer is one like the last)
     for (int l = 0; l < S->n_layers; ++l) {
         L.keep = L.n_vis;
         const bool prune_here = stage < S->n_stages && S->prune_layer[stage] == l;
         if (prune_here) L.keep = S->prune_keep[stage++];
-        layer_max = std::max(layer_max, vitcop_decoder_layer_workspace_bytes(&L));
+        if (l == 0 || prune_here || pruned_before) layer_max = std::max(layer_max, vitcop_decoder_layer_workspace_bytes(&L));
+        pruned_before = prune_here;
         L.T = L.T - L.n_vis + L.keep;
         L.n_vis = L.keep;
     }

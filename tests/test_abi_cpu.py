@@ -6,6 +6,7 @@ argument checks that run before any HIP call.
 import ctypes as C
 import os
 import re
+import time
 
 import pytest
 
@@ -303,6 +304,33 @@ def test_layer_workspace_grows_with_the_rows(D, Hq, Hkv, d, F):
             need = (lib.vitcop_decoder_layer_workspace_bytes(C.byref(layer)), lib.vitcop_layer_workspace_bytes(C.byref(attn)))
             assert T == 1 or (need[0] >= largest[0] and need[1] >= largest[1]), T
             largest = need
+
+
+def test_a_schedule_sizes_each_shape_of_layer_once():
+    """Sizing a layer walks the plans of its launches, and a pass does it ahead of its first launch: 32 layers of five shapes
+    take the time of about five, not of 32."""
+    layers, n_vis, T = 32, 288, 352
+    stages = ((2, 253), (22, 51))
+    model = dict(D=4096, Hq=32, Hkv=32, d=128, F=11008)
+    S = binding.DecoderScheduleT(B=8, T=T, vis_start=35, n_vis=n_vis, n_layers=layers, n_stages=len(stages), eps=1e-5,
+                                 theta=10000.0, prune_layer=(C.c_int * 2)(*(l for l, _ in stages)),
+                                 prune_keep=(C.c_int * 2)(*(k for _, k in stages)), **model)
+    shapes = [(352, 288, 288), (352, 288, 253), (317, 253, 253), (317, 253, 51), (115, 51, 51)]
+    one_each = [binding.DecoderLayerT(8, t, *model.values(), 35, n, keep, 1e-5, 10000.0) for t, n, keep in shapes]
+
+    def least(f):
+        f()
+        times = []
+        for _ in range(20):
+            start = time.perf_counter()
+            f()
+            times.append(time.perf_counter() - start)
+        return min(times)
+    each = [lib.vitcop_decoder_layer_workspace_bytes(C.byref(L)) for L in one_each]
+    # (the hidden and normalised states and the position ids, twice each, beside the largest layer's)
+    assert lib.vitcop_decoder_schedule_workspace_bytes(C.byref(S)) == max(each) + 4 * 8 * T * 4096 * 2 + 2 * -(-8 * T * 4 // 256) * 256
+    assert least(lambda: lib.vitcop_decoder_schedule_workspace_bytes(C.byref(S))) < \
+        2 * least(lambda: [lib.vitcop_decoder_layer_workspace_bytes(C.byref(L)) for L in one_each])
 
 
 def test_decoder_schedule_validation():

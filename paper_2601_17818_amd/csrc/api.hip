@@ -1236,11 +1236,7 @@ int vitcop_decoder_decode_step(const vitcop_decoder_decode_t* S, void* ws, size_
     void* gs = c.take<char>(gs_bytes);
 
     const uint16_t* h = S->h;
-    // (With four samples every workgroup of the streams would normalise and keep four rows, and the matrix cores' launches,
-    // though more of them, are faster: one layer, us, 4096 / 11008 103.8, 97.0; 2048 / 5632 52.5, 48.1; 1024 / 2816 39.3, 38.3.
-    // With three they are as fast (97.4, 97.9) or slower (47.7, 48.9; 34.9, 36.5).)
-    constexpr int STREAM_SAMPLES = 3;
-    if (B <= STREAM_SAMPLES && gemv_applies(B, D) && gemv_applies(B, qd) && gemv_applies(B, F) && S->d % 2 == 0) {
+    if (B <= stream_samples(qd, kd, S->d, D) && gemv_applies(B, D) && gemv_applies(B, qd) && gemv_applies(B, F) && S->d % 2 == 0) {
         // a handful of rows: every product is a stream over its weights, with the norms, the rotary embedding,
         // the cache append, the activation and the residual adds inside the streaming kernels
         const int64_t kv_batch = (int64_t)S->cache_capacity * kd;

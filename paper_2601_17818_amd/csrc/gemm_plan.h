@@ -322,4 +322,16 @@ inline int qkv_path(int M, int qd, int kd, int d, int K) {
     return pairs && splitk_tall_plan(M, kd, K).splits && splitk_tall_plan(M, qd + kd, K).splits ? 2 : 0;
 }
 
+// ---- decoding steps -------------------------------------------------------------------------------------------
+
+// Up to how many samples a decoding step goes out as streams over the weights (gemv.hip).  With four, every workgroup of the
+// streams normalises and keeps four rows, and the matrix cores' launches, though more of them, are faster where K, Q and V are one
+// of them, whose sums the attention adds up; where they are three launches, a launch for the rotary embedding follows and
+// the streams win.  Four samples x 317 keys, us a layer, streams and matrix cores: 4096 / 11008 107.1, 98.0; 3584 / 14336 (28 / 4
+// heads) 100.7, 95.3; 4096 / 14336 (32 / 8) 111.6, 104.0; 2048 / 5632 56.0, 52.8; 1024 / 2816 (16 / 4 of 64) 42.3, 36.3; but
+// 1024 / 2816 (16 / 1 of 64) 42.5, 47.0; 2048 / 5632 (32 / 1 of 64) 55.6, 69.4, (24 / 3 of 64) 50.6, 63.9; 4096 / 11008 (64 / 1
+// of 64) 109.1, 121.7.  With three samples the matrix cores are as fast (4096 / 11008 97.4, 97.9) or slower (2048 / 5632 47.7,
+// 48.9; 1024 / 2816 34.9, 36.5).
+inline int stream_samples(int qd, int kd, int d, int D) { return qkv_path(4, qd, kd, d, D) == 1 ? 3 : 4; }
+
 }  // namespace vitcop

@@ -1,4 +1,4 @@
-// Projections of one to four rows (the new token of each of up to three samples in a decoding step, Table 5 of
+// Projections of one to four rows (the new token of each of up to four samples in a decoding step, Table 5 of
 // arXiv 2601.17818: time per generated token after a pruned prefill).  With so few rows the
 // product is a stream over the weights and nothing else: y[b, n] = sum_k x[b, k] W[n, k] reads
 // every weight once from HBM and does two flops per element, so the matrix cores have nothing to
@@ -381,9 +381,7 @@ static int launch_gemv_epi(GvArgs& a, int B, hipStream_t s) {
         case 1: return launch_gemv_nb<1, EPI>(a, s);
         case 2: return launch_gemv_nb<2, EPI>(a, s);
         case 3: return launch_gemv_nb<3, EPI>(a, s);
-        default:                             // (four rows: single projections only)
-            if constexpr (EPI == GV_EPI_PLAIN) return launch_gemv_nb<4, EPI>(a, s);
-            else return fail(VITCOP_EUNSUPPORTED, "gemv: %d rows", B);
+        default: return launch_gemv_nb<4, EPI>(a, s);
     }
 }
 

@@ -421,7 +421,7 @@ def test_full_schedule_batch_with_different_counts(vc, seeds):
                 [T - n + k3b] * B]
     assert plan.cache_len == want_len
     y_host, p_host = host_f64(y), p.cpu().numpy()
-    # then one decoding step over those caches of different lengths (2 to 4 samples: the streaming matrix-vector
+    # then one decoding step over those caches of different lengths (2 or 3 samples: the streaming matrix-vector
     # kernels; more: the few-row projections), every sample against the oracle's one-sample step
     h_new = I.decoder_inputs(9960, B, 1, D, Hq, Hkv, d, F)["h"][:, 0]
     new_pos = (2 * T + 5 * np.arange(B)).astype(np.int32)

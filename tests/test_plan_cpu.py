@@ -36,6 +36,7 @@ int qkv(int M, int qd, int kd, int d, int K, int* o) {
     return qkv_path(M, qd, kd, d, K);
 }
 int gated_columns(int M, int F, int K) { return skinny_gated_columns(skinny_plan(M, 2 * F, K), M, F, K); }
+int streams(int qd, int kd, int d, int D) { return stream_samples(qd, kd, d, D); }
 int direct(int N) { return skinny_direct(N, false); }
 int few_rows(int M, int N, int K, int* o) {
     const SkinnyPlan p = skinny_plan(M, N, K);
@@ -114,6 +115,14 @@ def test_slices_of_tall_launches(plan):
     assert cut > 50
     for M, N, K in gpu.SPLIT_TALL:
         assert plan.splitk_tall(M, N, K, (C.c_int * 2)()) > 1
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,d,samples", [
+    (4096, 32, 32, 128, 3), (3584, 28, 4, 128, 3), (2048, 16, 16, 128, 3), (1024, 16, 4, 64, 3), (4160, 24, 6, 128, 3),
+    # widths of K and V that are no whole groups of 128 columns: the matrix cores would take three launches and the rotary one
+    (1024, 16, 1, 64, 4), (2048, 32, 1, 64, 4), (2048, 24, 3, 64, 4), (4096, 64, 1, 64, 4)])
+def test_four_decoding_samples_take_the_faster_way(plan, D, Hq, Hkv, d, samples):
+    assert plan.streams(Hq * d, Hkv * d, d, D) == samples
 
 
 def sliced(plan, M, N, K):

@@ -37,9 +37,8 @@ def hipcc() -> str:
     return exe
 
 
-# per-file extras: the attention kernels never produce NaNs (masked scores are -inf and the
-# reference maximum is finite from the first key on), so fmax needs no NaN-quieting moves
-EXTRA = {"attn.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# per-file extras (none that lets the compiler assume NaNs away: one among the inputs has to reach the output)
+EXTRA = {"attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

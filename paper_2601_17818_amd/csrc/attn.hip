@@ -246,6 +246,11 @@ constexpr int AW_MAX_REST = 8;        // keys past the last whole tile that are 
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
+// The larger one, or a NaN if either is one: one instruction for two or three scores (v_maximum3_f32).  fmaxf, which looks
+// for signalling NaNs, would first quiet every score that comes out of an MFMA, 16 instructions a block.  A query with a NaN
+// among its scores never moves its reference after that, and its probabilities, their sum and its output become NaN.
+__device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 // Transposing LDS read (ds_read_b64_tr_b16): lane 16*h + 4*e + a passes the address of 4
 // consecutive 16-bit values; it receives, for j = 0..3, element (lane & 3) of the quadruple
 // addressed by lane 16*h + 4*j + ((lane >> 2) & 3).
@@ -591,12 +596,12 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
             } else if constexpr (kind == SM_MAX5) {
                 // (the empty asm pins the instruction to its run: nothing else needs the maxima before
                 // the check, so the compiler would otherwise gather them all right in front of it)
-                m5[u][i] = fmaxf(fmaxf(sv[3 * i], sv[3 * i + 1]), sv[3 * i + 2]);
+                m5[u][i] = max_or_nan(max_or_nan(sv[3 * i], sv[3 * i + 1]), sv[3 * i + 2]);
                 asm volatile("" : "+v"(m5[u][i]));
             } else if constexpr (kind == SM_MAX3) {
-                if constexpr (i == 0) m3[u][0] = fmaxf(fmaxf(m5[u][0], m5[u][1]), m5[u][2]);
-                if constexpr (i == 1) m3[u][1] = fmaxf(fmaxf(m5[u][3], m5[u][4]), sv[15]);
-                if constexpr (i == 2) m3[u][2] = fmaxf(m3[u][0], m3[u][1]) - thr[u];   // excess over the threshold
+                if constexpr (i == 0) m3[u][0] = max_or_nan(max_or_nan(m5[u][0], m5[u][1]), m5[u][2]);
+                if constexpr (i == 1) m3[u][1] = max_or_nan(max_or_nan(m5[u][3], m5[u][4]), sv[15]);
+                if constexpr (i == 2) m3[u][2] = max_or_nan(m3[u][0], m3[u][1]) - thr[u];   // excess over the threshold
                 asm volatile("" : "+v"(m3[u][i]));
             } else if constexpr (kind == SM_FMA) {
                 e[u][i] = fmaf(sv[i], scale_log2e, -m_ref[u]);
@@ -620,18 +625,18 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
         // same query, so both decide alike), new reference, alpha = exp2(old - new) (exp2(-inf) = 0 at
         // the start) for the rescaling at the end of the block, new threshold.
         auto check_reference = [&]() __attribute__((always_inline)) {
-            float excess = m3[0][2];
+            bool over = m3[0][2] > 0.f;                      // (each block by itself: one block's NaN is not the other's)
 #pragma unroll
-            for (int u = 1; u < U; ++u) excess = fmaxf(excess, m3[u][2]);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(excess > 0.f) != 0, 0)) {
+            for (int u = 1; u < U; ++u) over |= m3[u][2] > 0.f;
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(over) != 0, 0)) {
                 moved = true;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const float own = fmaxf(m3[u][0], m3[u][1]);
+                    const float own = max_or_nan(m3[u][0], m3[u][1]);
                     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own),
                                                                      false, false);
-                    const float mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-                    const float top = fmaxf(m_ref[u], mx * scale_log2e);
+                    const float mx = max_or_nan(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+                    const float top = max_or_nan(m_ref[u], mx * scale_log2e);
                     const float ref_new = (top > m_ref[u] + AW_RESCALE_GAP) ? top : m_ref[u];
                     alpha[u] = __builtin_amdgcn_exp2f(m_ref[u] - ref_new);
                     m_ref[u] = ref_new;
@@ -760,11 +765,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_wide_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             p[r] = 4 * g + r < rest ? sr[r] : -INFINITY;
-            own = fmaxf(own, p[r]);
+            own = max_or_nan(own, p[r]);
         }
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
-        const float top = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
-        const bool seen = top > -INFINITY;               // (otherwise no reference: as if nothing had been seen)
+        const float top = max_or_nan(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2e;
+        const bool seen = top > -INFINITY;               // (otherwise, -inf or a NaN, no reference: as if nothing had been seen)
         if (seen) {
             m_ref[0] = top;
             thr[0] = fmaxf((top + AW_RESCALE_GAP) / scale_log2e, -3.0e38f);

@@ -27,6 +27,12 @@ def declared_functions():
     return sorted(set(re.findall(r"\b(vitcop_[a-z_0-9]+)\s*\(", text)))
 
 
+def test_the_compiler_may_not_assume_nans_away():
+    """A NaN among the inputs of the attention has to reach its output."""
+    from paper_2601_17818_amd import build
+    assert not [f for flags in [build.FLAGS, *build.EXTRA.values()] for f in flags if "nans" in f or "fast" in f or "finite" in f]
+
+
 def test_every_declared_symbol_is_exported():
     names = declared_functions()
     assert set(names) == set(binding.EXPORTS)

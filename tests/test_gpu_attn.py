@@ -130,6 +130,24 @@ def test_nan_in_the_last_key(vc, N):
     assert np.isnan(out[0, :, 2:]).all() and np.isfinite(out[0, :, :2]).all()
 
 
+# the same for any key, both head dimensions, one and two query blocks to a wavefront (two: 1100 tokens of 128 channels) and
+# with the mask, where the queries before that key do not see it
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,at", [(64, 0), (65, 64), (300, 0), (300, 31), (300, 32), (577, 576), (577, 575), (700, 130), (1100, 1099)])
+def test_nan_in_a_key_reaches_the_queries_that_see_it(vc, causal, d, N, at):
+    B, Hq = (1, 4) if N < 1000 else (4, 32)
+    g = torch.Generator(device="cuda").manual_seed(N + at)
+    q, k, v = (torch.empty((B, N, h, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for h in (Hq, Hq // 2, Hq // 2))
+    want = vc.vitcop_prefill_attn(q, k, v, causal=causal)[0].clone()
+    k[0, at, 1, 3] = float("nan")
+    out = vc.vitcop_prefill_attn(q, k, v, causal=causal)[0]
+    first = at if causal else 0
+    assert bool(out[0, first:, 2:4].isnan().all())
+    out[0, first:, 2:4] = want[0, first:, 2:4]
+    assert torch.equal(out, want)
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(28, 4), (8, 2), (6, 1)])
 def test_gqa(vc, Hq, Hkv):
     t = I.qkv_tensors(300 + Hq, 1, 150, Hq, Hkv, 128)

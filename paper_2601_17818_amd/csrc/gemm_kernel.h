@@ -287,8 +287,8 @@ __global__ __launch_bounds__(GM_THREADS) void gemm_kernel(
     // 204.6 / 200.0 / 199.5.  640 rows, three and four tiles, are the same either way and stay in step, and whole tiles of
     // thousands of rows, whose W comes from L2, lose 0.7 %.  Short slices stay in step (4096x4096 in four slices of 16
     // steps: 7.4 to 7.9 us for 7.5).
-    // Launches of more rows are built without the wrap-around, whose addresses cost a step up to 2.5 % (gate/up of 920 rows
-    // 57.3 -> 55.9 us).
+    // Launches of more rows are built without the wrap-around, whose addresses cost a step up to 2.5 % (2536 rows, the last
+    // 1280 columns of gate and of up on tiles of 160 x 192: 57.3 -> 55.9 us).
     int rot = 0;
     if (SPREAD && nk >= 32)
         rot = tiles_m == 1 ? tile_n * nk / tiles_n
@@ -575,15 +575,16 @@ static int launch_gemm_as(const uint16_t* x, int64_t x_stride, const SkMats& mat
     return launch_status("gemm");
 }
 
-// (as many slabs as fit in LDS, up to four)
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128))>
+// (as many slabs as fit in LDS, up to four; FEW: the tile always holds all rows)
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, bool FEW = false,
+          int NS = std::min(4, 160 * 1024 / ((BM + BN) * 128))>
 static int launch_gemm_cfg(const uint16_t* x, int64_t x_stride, const SkMats& mats, const uint16_t* res,
                            int64_t res_stride, int M, int N, int K, float* sumsq_parts,
                            hipStream_t s, int64_t w_stride = 0, float* dist = nullptr, int64_t dist_stride = 0,
                            int batch = 1, int64_t x_batch = 0, int64_t sq_batch = 0, int64_t dist_batch = 0, int64_t sq_half = 0) {
     if (w_stride == 0) w_stride = K;
-    auto launch = launch_gemm_as<BM, BN, WAVES_M, WAVES_N, EPI, NS, false>;
-    if constexpr (EPI == GM_EPI_PART || EPI == GM_EPI_GATED)
+    auto launch = launch_gemm_as<BM, BN, WAVES_M, WAVES_N, EPI, NS, FEW>;
+    if constexpr (!FEW && (EPI == GM_EPI_PART || EPI == GM_EPI_GATED))
         if (M <= 2 * BM) launch = launch_gemm_as<BM, BN, WAVES_M, WAVES_N, EPI, NS, true>;
     return launch(x, x_stride, mats, res, res_stride, M, N, K, sumsq_parts, s, w_stride, dist, dist_stride, batch, x_batch,
                   sq_batch, dist_batch, sq_half);

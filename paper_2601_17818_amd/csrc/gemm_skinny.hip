@@ -340,7 +340,7 @@ template <int BM>
 static int launch_skinny_parts(int cols, int slices, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M,
                                int N, int K, float* part, hipStream_t s) {
 #define VITCOP_SKINNY(BN)                                                                                            \
-    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART>(x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s, K, part, N, \
+    return launch_gemm_cfg<BM, BN, 2, 2, GM_EPI_PART, true>(x, x_stride, mats, nullptr, 0, M, N, K, nullptr, s, K, part, N, \
                                                       slices, 0, 0, (int64_t)M * N)
     if (cols == 64) VITCOP_SKINNY(64);
     if (cols == 96) VITCOP_SKINNY(96);
@@ -351,10 +351,10 @@ template <int BM>
 static int launch_skinny_gate_up(int cols, const uint16_t* x, int64_t x_stride, const SkMats& mats, int M, int F, int K,
                                  hipStream_t s) {
     if (cols == 64)
-        return launch_gemm_cfg<BM, 64, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
+        return launch_gemm_cfg<BM, 64, 2, 2, GM_EPI_GATED, true>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
     if (cols == 96)
-        return launch_gemm_cfg<BM, 96, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
-    return launch_gemm_cfg<BM, 128, 2, 2, GM_EPI_GATED>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
+        return launch_gemm_cfg<BM, 96, 2, 2, GM_EPI_GATED, true>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
+    return launch_gemm_cfg<BM, 128, 2, 2, GM_EPI_GATED, true>(x, x_stride, mats, nullptr, 0, M, F, K, nullptr, s);
 }
 // f<BM>(args...) for the tile that holds M rows
 #define VITCOP_BY_ROWS(f, M, ...)                  \

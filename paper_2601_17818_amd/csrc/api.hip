@@ -287,7 +287,7 @@ static int check_layer(const vitcop_layer_t* L) {
 // elsewhere too; what a layer asks for in all grows with its rows, which the tests walk row by row.)
 static size_t gemm_scratch_upto(int M, int N, int K) {
     size_t n = gemm_workspace_bytes(M, N, K);
-    for (int m = 64; m < M && m <= SPLITK_TALL_ROWS; m += 64) n = std::max(n, gemm_workspace_bytes(m, N, K));
+    for (int m = 64; m < M && m <= SPLITK_MAX_ROWS; m += 64) n = std::max(n, gemm_workspace_bytes(m, N, K));
     return n;
 }
 static size_t layer_gemm_scratch(int M_all, int M_kept, int D, int qd, int kd, int F, int d = 0) {
@@ -296,7 +296,7 @@ static size_t layer_gemm_scratch(int M_all, int M_kept, int D, int qd, int kd, i
     n = std::max(n, gemm_scratch_upto(M_all, qd + 2 * kd, D));                   // K, Q and V of a layer that keeps all
     if (d > 0) {                                                                 // the same with the rotary embedding
         n = std::max(n, gemm_qkv_workspace_bytes(M_all, qd / d, kd / d, d, D));
-        for (int m = 64; m < M_all && m <= SPLITK_TALL_ROWS; m += 64)
+        for (int m = 64; m < M_all && m <= SPLITK_MAX_ROWS; m += 64)
             n = std::max(n, gemm_qkv_workspace_bytes(m, qd / d, kd / d, d, D));
     }
     n = std::max(n, gemm_scratch_upto(M_kept, D, qd));                           // O

@@ -135,7 +135,7 @@ int launch_gemm_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w, uint1
         return launch_gemm_skinny(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, sumsq_parts, nullptr,
                                   nullptr, 0, ws, s);
     if (ws && ws_bytes >= splitk_workspace_bytes(M, N, K)) {
-        const SplitKPlan p = splitk_tall_plan(M, N, K, sumsq_parts != nullptr);
+        const SplitKPlan p = splitk_plan(M, N, K, sumsq_parts != nullptr);
         if (p.splits)
             return launch_gemm_splitk(p, x, x_stride, w, y, y_stride, res, res_stride, M, N, K, sumsq_parts, ws, s,
                                       nullptr, 0.f, nullptr, 0);
@@ -168,7 +168,7 @@ int launch_gemm_norm_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w, 
         return launch_gemm_skinny(x, x_stride, w, y, y_stride, res, res_stride, M, N, K, nullptr, nullptr, nullptr, 0,
                                   ws, s, ln_w, eps, norm_out, norm_stride);
     if (ws && ws_bytes >= splitk_workspace_bytes(M, N, K) && partial_reduce_fuses_norm(N)) {
-        const SplitKPlan p = splitk_tall_plan(M, N, K, false, GM_NORM_US);
+        const SplitKPlan p = splitk_plan(M, N, K, false, GM_NORM_US);
         if (p.splits)
             return launch_gemm_splitk(p, x, x_stride, w, y, y_stride, res, res_stride, M, N, K, nullptr, ws, s, ln_w, eps,
                                       norm_out, norm_stride);
@@ -213,7 +213,7 @@ int launch_gemm_gated_ws(const uint16_t* x, int64_t x_stride, const uint16_t* wg
     // hundred rows): those produce gate and up separately.  A large tail (many rows, whole rounds plus a part
     // of one) stays on this path: first the columns that fill the whole rounds, then the rest on the tiles
     // that suit it.
-    if (F % 8 == 0 && splitk_tall_plan(M, 2 * F, K, false, -silu_us(M, F)).splits == 0) {
+    if (F % 8 == 0 && splitk_plan(M, 2 * F, K, false, -silu_us(M, F)).splits == 0) {
         const uint16_t *g_w = wg, *u_w = wu;
         uint16_t* o = out;
         int f_left = F;
@@ -303,7 +303,7 @@ int launch_gemm_pair_ws(const uint16_t* x, int64_t x_stride, const uint16_t* w1,
     if (ws && need && ws_bytes >= need && N1 % 128 == 0 && N2 % 128 == 0)
         return launch_gemm_skinny(x, x_stride, w1, y1, N1, nullptr, 0, M, N1 + N2, K, nullptr, w2, y2, N1, ws, s);
     if (ws && ws_bytes >= splitk_workspace_bytes(M, N1 + N2, K) && N1 % 256 == 0 && N2 % 256 == 0) {
-        const SplitKPlan p = splitk_tall_plan(M, N1 + N2, K);             // (no tile of 256 columns straddles the two outputs)
+        const SplitKPlan p = splitk_plan(M, N1 + N2, K);              // (no tile of 256 columns straddles the two outputs)
         if (p.splits)
             return launch_gemm_splitk(p, x, x_stride, w1, y1, N1, nullptr, 0, M, N1 + N2, K, nullptr, ws, s, nullptr, 0.f,
                                       nullptr, 0, w2, y2, N1);
@@ -376,10 +376,10 @@ int launch_gemm_qkv_rope_ws(const uint16_t* x, int64_t x_stride, const uint16_t*
             P = {{parts, parts, parts}, {0, kd, kd + qd}};
         } else if (path == 2 && ws_bytes >= need_k + need_qv) {
             SkParts pk{}, pqv{};
-            int rc = launch_gemm_splitk(splitk_tall_plan(M, kd, K), x, x_stride, wk, y3[0], kd, nullptr, 0, M, kd, K, nullptr,
+            int rc = launch_gemm_splitk(splitk_plan(M, kd, K), x, x_stride, wk, y3[0], kd, nullptr, 0, M, kd, K, nullptr,
                                         ws, s, nullptr, 0.f, nullptr, 0, nullptr, nullptr, 0, &pk);
             if (rc) return rc;
-            rc = launch_gemm_splitk(splitk_tall_plan(M, qd + kd, K), x, x_stride, wq, q, qd, nullptr, 0, M, qd + kd, K, nullptr,
+            rc = launch_gemm_splitk(splitk_plan(M, qd + kd, K), x, x_stride, wq, q, qd, nullptr, 0, M, qd + kd, K, nullptr,
                                     static_cast<char*>(ws) + need_k, s, nullptr, 0.f, nullptr, 0, wv, y3[2], qd, &pqv);
             if (rc) return rc;
             P = {{pk, pqv, pqv}, {0, 0, qd}};

@@ -210,7 +210,7 @@ inline int skinny_gated_columns(const SkinnyPlan& plan, int M, int F, int K) {
 
 // ---- 257 to 1536 rows: k-slices -------------------------------------------------------------------------------
 
-constexpr int SPLITK_ROWS = 1024, SPLITK_TALL_ROWS = 1536;
+constexpr int SPLITK_MAX_ROWS = 1536;
 
 // Split-K for a few hundred to fifteen hundred rows: there are then too few large tiles to fill the chip, and 128 x 128
 // tiles, which would, load more bytes per FLOP.  So the tiles stay 160 to 256 rows tall and the k-range is cut into
@@ -249,7 +249,7 @@ inline int splitk_slices(int tiles, int K) { return std::min(std::min(16, 256 / 
 // The most slices a cut may take, which sets the scratch that callers provide (0: no cut): those that fill one round
 // on the tiles that then have the shortest slices, 128 columns first, which need half the slices of 256.
 inline int splitk_most(int M, int N, int K) {
-    if (M <= 256 || M > SPLITK_TALL_ROWS || N % 16 != 0 || K % 32 != 0) return 0;
+    if (M <= 256 || M > SPLITK_MAX_ROWS || N % 16 != 0 || K % 32 != 0) return 0;
     auto shortest = [&](std::initializer_list<TileId> ids, int least) {
         int most = 0;
         float best = 1e30f;
@@ -284,30 +284,23 @@ inline void splitk_best(SplitKPlan& p, std::initializer_list<TileId> ids, int M,
 // The cut to take, if it beats one launch of the whole tiles that the launcher would pick, which needs no second pass.
 // sumsq: with the norm side output; whole_extra_us: what the caller has to launch after whole tiles but not after
 // slices (negative: the other way round).
-inline SplitKPlan splitk_any(int M, int N, int K, bool sumsq, float whole_extra_us, int most) {
+// Between 1025 and SPLITK_MAX_ROWS rows whole tiles still leave a part of a round idle more often than not, and the price
+// fitted to fewer rows picks well: layers of 3584 / 14336 (28 / 4 heads) at 1032, 1280 and 1520 rows 457 -> 425, 524 -> 494 and
+// 558 -> 524 us; of 4096 / 11008 at 1080 and 1280 rows 462 -> 442 and 510 -> 494, from 1360 on the same; of 2048 / 5632 at 1120
+// and 1440 193 -> 172 and 228 -> 216; of 1024 / 2816 at 1080 94 -> 88.  Above, cuts gain up to 2 % in some layers and lose up to 4
+// in others (2272 rows of 1024 / 2816 112 -> 117).
+inline SplitKPlan splitk_plan(int M, int N, int K, bool sumsq = false, float whole_extra_us = 0.f) {
     SplitKPlan p;
     p.us = launch_us(kTiles[choose_tile(M, N, K, sumsq, 768)], M, N, K) + whole_extra_us;
-    splitk_best(p, {T160x128, T192x128, T256x128, T160x256, T192x256, T256x256}, M, N, K, most);
+    splitk_best(p, {T160x128, T192x128, T256x128, T160x256, T192x256, T256x256}, M, N, K, splitk_most(M, N, K));
     return p;
-}
-inline SplitKPlan splitk_plan(int M, int N, int K, bool sumsq = false, float whole_extra_us = 0.f) {
-    return splitk_any(M, N, K, sumsq, whole_extra_us, M > SPLITK_ROWS ? 0 : splitk_most(M, N, K));
-}
-// The same for up to SPLITK_TALL_ROWS rows, which the launchers ask.  Between 1025 and 1536 rows whole tiles still leave a
-// part of a round idle more often than not, and the price fitted to fewer rows picks well: layers of 3584 / 14336 (28 / 4
-// heads) at 1032, 1280 and 1520 rows 457 -> 425, 524 -> 494 and 558 -> 524 us; of 4096 / 11008 at 1080 and 1280 rows 462 -> 442
-// and 510 -> 494, from 1360 on the same; of 2048 / 5632 at 1120 and 1440 193 -> 172 and 228 -> 216; of 1024 / 2816 at 1080
-// 94 -> 88.  Above, cuts gain up to 2 % in some layers and lose up to 4 in others (2272 rows of 1024 / 2816 112 -> 117).
-inline SplitKPlan splitk_tall_plan(int M, int N, int K, bool sumsq = false, float whole_extra_us = 0.f) {
-    return M <= SPLITK_ROWS ? splitk_plan(M, N, K, sumsq, whole_extra_us)
-                            : splitk_any(M, N, K, sumsq, whole_extra_us, splitk_most(M, N, K));
 }
 // K, Q and V of a layer as ONE launch of k-slices (tiles of 192 columns may hold the end of one matrix and the start
 // of the next), where that beats a launch of K and one of the Q/V pair.  `most`: slices that the scratch holds.
 inline SplitKPlan qkv_plan(int M, int qd, int kd, int K, int most = 16) {
     SplitKPlan p;
-    if (M <= 256 || M > SPLITK_TALL_ROWS || K % 32 != 0 || qd % 128 != 0 || kd % 128 != 0 || qd < 256 || kd < 256) return p;
-    const SplitKPlan k = splitk_tall_plan(M, kd, K), qv = splitk_tall_plan(M, qd + kd, K);
+    if (M <= 256 || M > SPLITK_MAX_ROWS || K % 32 != 0 || qd % 128 != 0 || kd % 128 != 0 || qd < 256 || kd < 256) return p;
+    const SplitKPlan k = splitk_plan(M, kd, K), qv = splitk_plan(M, qd + kd, K);
     p.us = k.us + qv.us + (k.splits && qv.splits ? 0.f : GM_ROPE_US);
     splitk_best(p, {T160x128, T192x128, T256x128, T160x192G, T192x192G}, M, qd + 2 * kd, K, most);
     return p;
@@ -319,7 +312,7 @@ inline int qkv_path(int M, int qd, int kd, int d, int K) {
     if (gemm_skinny_applies(M, kd + qd + kd, K) && kd % 128 == 0 && qd % 128 == 0) return 1;
     if (qkv_plan(M, qd, kd, K).splits) return 3;
     const bool pairs = qd % 256 == 0 && kd % 256 == 0;
-    return pairs && splitk_tall_plan(M, kd, K).splits && splitk_tall_plan(M, qd + kd, K).splits ? 2 : 0;
+    return pairs && splitk_plan(M, kd, K).splits && splitk_plan(M, qd + kd, K).splits ? 2 : 0;
 }
 
 // ---- decoding steps -------------------------------------------------------------------------------------------

@@ -59,7 +59,7 @@ int launch_gemm_pair(const uint16_t* x, int64_t x_stride, const uint16_t* w1, ui
                      const uint16_t* w2, uint16_t* y2, int N2, int M, int K, hipStream_t s);
 
 // The same two calls with a scratch buffer: launches of at most 256 rows (gemm_skinny.hip) and, where that is
-// estimated faster, of at most 1024 then go out as k-slices whose fp32 partials live in `ws`; with ws == nullptr, too
+// estimated faster, of at most 1536 then go out as k-slices whose fp32 partials live in `ws`; with ws == nullptr, too
 // small a buffer or any other shape they are the calls above.  gemm_workspace_bytes is what a cut of one launch
 // (N = N1 + N2 for a pair) may need, also where whole tiles are taken in the end; 0 where none is considered.
 size_t gemm_workspace_bytes(int M, int N, int K);

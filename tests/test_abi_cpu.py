@@ -303,7 +303,7 @@ def test_layer_workspace_grows_with_the_rows(D, Hq, Hkv, d, F):
     """A schedule sizes its workspace for its longest sequence: no shorter one may ask for more."""
     for part in (1.0, 0.4):
         largest = 0
-        for T in range(1, 1300):
+        for T in range(1, 1700):
             keep = max(1, int(T * part))
             layer = binding.DecoderLayerT(1, T, D, Hq, Hkv, d, F, 0, T, keep, 1e-5, 10000.0)
             attn = layer_desc(T=T, D=D, Hq=Hq, Hkv=Hkv, d=d, vis_start=0, n_vis=T, keep=keep)

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(KN_THREADS) void knorm_generic_kernel(
 }
 
 // The candidates' norms of a sample, added up from their parts: keys in LDS and, if asked for, norms_out.  A thread takes RU
-// candidates at a time, PU parts of each: 32 independent loads in flight per round trip (the workgroup is alone on its CU
+// candidates at a time, PU parts of each: up to 48 independent loads in flight per round trip (the workgroup is alone on its CU
 // and the reads are all latency); every candidate's parts are added in index order, so the sums do not depend on the grouping.
 template <int RU, int PU>
 __device__ __forceinline__ void collect_norms(const float* __restrict__ src, int n_parts, int64_t part_stride, int do_sqrt,

@@ -69,10 +69,11 @@ def test_slices_of_tall_launches(M, N, K):
     assert bool(((parts.double() - sq).abs() <= 128 * 2.0 ** -24 * sq + 1e-30).all())
 
 
-# slices of 32 k-steps and more start at different k and wrap around with one or two tile rows; a last step of half a
-# step in the middle of the walk (test_plan_cpu.py checks their length)
-LONG_SLICES = [(20, 4096, 8192), (64, 4096, 12288), (100, 8192, 8192), (250, 8192, 8192), (300, 4096, 8224), (300, 8192, 8224),
-               (700, 4096, 12320), (1000, 4096, 8224), (640, 4096, 4128)]
+# slices of 32 k-steps and more start at different k and wrap around with one or two tile rows, and stay in step with more;
+# a last step of half a step in the middle of the walk (test_plan_cpu.py checks their length and their tile rows)
+SPREAD_SLICES = [(20, 4096, 8192), (64, 4096, 12288), (100, 8192, 8192), (250, 8192, 8192), (300, 4096, 8224), (300, 8192, 8224),
+                 (380, 4144, 8224), (420, 8448, 8448)]
+LONG_SLICES = SPREAD_SLICES + [(700, 4096, 12320), (1000, 4096, 8224), (640, 4096, 4128)]
 
 
 @pytest.mark.parametrize("M,N,K", LONG_SLICES)

@@ -89,6 +89,8 @@ def test_slices_of_few_rows_are_priced(plan, M, N, K):
 def test_long_slices_are_long(plan, M, N, K):
     slices = plan.few_rows(M, N, K, (C.c_int * 2)()) if M <= 256 else picked(plan, M, N, K)[2]
     assert (K + 63) // 64 // slices >= 32
+    rows = (M + 31) // 32 * 32 if M <= 256 else picked(plan, M, N, K)[0]
+    assert (M <= 2 * rows) == ((M, N, K) in gpu.SPREAD_SLICES)
 
 
 def test_slices_of_tall_launches(plan):

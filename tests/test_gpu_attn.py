@@ -121,6 +121,29 @@ def test_keys_past_the_last_tile(vc, N, std):
         assert np.abs(lse - ref_lse).max() < 1e-3 * max(1.0, np.abs(ref_lse).max() / 10)
 
 
+# One key of the tiles holds nearly all of the weight, a key past them lies five binary orders below.  The large probability
+# is exact if it is the reference (its weight rounded to bf16 is off by up to 2^-9, which moves every second output); what
+# is left are the other keys' roundings, 2^-9 of a twentieth of the weight, which move one output in twenty or so.
+@pytest.mark.parametrize("N", [65, 72, 129, 260])
+def test_the_largest_weight_is_exact_beside_keys_past_the_last_tile(vc, N):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    e = torch.empty(64, device="cuda").normal_(generator=g)
+    e = e / e.norm()
+    unit = 8.0 / 1.4426950408889634                          # a score of one in powers of two
+    k = torch.empty((2, N, 4, 64), device="cuda").normal_(0, 0.1, generator=g)
+    k[:, 20] = 13.0 * unit * e
+    k[:, N - 1] = 8.0 * unit * e
+    q = e * torch.empty((2, N, 4, 1), device="cuda").uniform_(0.9, 1.1, generator=g)
+    v = torch.empty((2, N, 4, 64), device="cuda").normal_(generator=g)
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    out = vc.vitcop_prefill_attn(q, k, v, causal=False)[0]
+    qd, kd, vd = (t.double().cpu().permute(0, 2, 1, 3).contiguous() for t in (q, k, v))
+    p = torch.softmax(qd @ kd.transpose(2, 3).contiguous() / 8.0, dim=-1)
+    assert float(p[..., 20].min()) > 0.85
+    want = (p @ vd).permute(0, 2, 1, 3).float().bfloat16()
+    assert float((out.cpu() == want).float().mean()) > 0.85
+
+
 # a NaN in the last key reaches every query of its heads, whether that key stands alone past the last tile or not
 @pytest.mark.parametrize("N", [64, 65, 66, 72, 73])
 def test_nan_in_the_last_key(vc, N):

@@ -162,7 +162,7 @@ __device__ __forceinline__ void gv_finish(const GvArgs& a, int p, int b, float v
 
 // LDS: x as bf16 [NB][k_pad] (k_pad = K rounded up to whole pieces, the tail zero), then the sums of
 // cut pairs [pairs per workgroup][2 slots][2 rows][NB], then the prologue's per-wavefront sums.
-template <int NB, int EPI>
+template <int NB, int EPI, bool TURN>
 __global__ __launch_bounds__((gv_threads<NB, EPI>())) void gemv_kernel(GvArgs a) {
     constexpr int GV_THREADS = gv_threads<NB, EPI>(), GV_WAVES = GV_THREADS / 64;
     constexpr int GV_HELD = GV_MAX_K / 8 / GV_THREADS;                 // chunks of x per thread and row in the prologue
@@ -188,9 +188,9 @@ __global__ __launch_bounds__((gv_threads<NB, EPI>())) void gemv_kernel(GvArgs a)
 
     // Piece kg of pair pl is its columns' block (kg + first + pl) % KG: from the first block on, wavefronts in step would ask for
     // the same few columns of rows a power of two apart, i.e. for a part of the memory channels (4096x11008, six pieces
-    // a pair: 18.8 -> 17.3 us; with two pieces, K = 4096, no change).
-    auto block_of = [&](int turn, int kg) { return kg + turn >= KG ? kg + turn - KG : kg + turn; };
-    int turn = 0;                                   // (p_first + pl) % KG
+    // a pair: 18.8 -> 17.3 us; a layer of 4096 / 11008 with the rotation also of two pieces, K = 4096, 84.8 -> 84.6).
+    auto block_of = [&](int turn, int kg) { return !TURN ? kg : kg + turn >= KG ? kg + turn - KG : kg + turn; };
+    int turn = 0;                                   // (p_first + pl) % KG; TURN: more than one piece a pair
     u32x4 buf[2][GV_U][2];
     const uint16_t *r0 = nullptr, *r1 = nullptr;
     auto load_piece = [&](u32x4 (&dst)[GV_U][2], int pl, int block) {
@@ -207,7 +207,7 @@ __global__ __launch_bounds__((gv_threads<NB, EPI>())) void gemv_kernel(GvArgs a)
     if (t_begin < t_end) {
         pl = t_begin / KG;
         kg = t_begin - pl * KG;
-        turn = (p_first + pl) % KG;
+        if constexpr (TURN) turn = (p_first + pl) % KG;
         load_piece(buf[0], pl, block_of(turn, kg)); // in flight while x is prepared
     }
 
@@ -308,7 +308,7 @@ __global__ __launch_bounds__((gv_threads<NB, EPI>())) void gemv_kernel(GvArgs a)
         if (nkg == KG) {
             nkg = 0;
             ++npl;
-            next_turn = block_of(turn, 1);
+            if constexpr (TURN) next_turn = block_of(turn, 1);
         }
         const bool more = t + 1 < t_end;
         if (more) load_piece(nxt, npl, block_of(next_turn, nkg));
@@ -354,8 +354,8 @@ bool gemv_applies(int B, int K) {
     return B >= 1 && B <= GV_MAX_ROWS && K % 8 == 0 && K >= GV_KBLK && K <= GV_MAX_K;
 }
 
-template <int NB, int EPI>
-static int launch_gemv_nb(GvArgs& a, hipStream_t s) {
+template <int NB, int EPI, bool TURN>
+static int launch_gemv_as(GvArgs& a, hipStream_t s) {
     constexpr int GV_THREADS = gv_threads<NB, EPI>(), GV_WAVES = GV_THREADS / 64;
     const int wgs = max(1, min(gv_max_wgs<NB, EPI>(), a.n_pairs / GV_WAVES));     // at least one row pair per wavefront
     a.pairs_q = a.n_pairs / wgs;
@@ -364,14 +364,21 @@ static int launch_gemv_nb(GvArgs& a, hipStream_t s) {
     const size_t lds = (size_t)NB * KG * GV_U * 64 * 16 + (size_t)(a.pairs_q + 1) * 4 * NB * 4 + GV_WAVES * NB * 4;
     static std::atomic<size_t> raised_to{65536};     // (per instantiation) dynamic LDS the kernel may use so far
     if (lds > raised_to.load()) {
-        const int rc = hip_status(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemv_kernel<NB, EPI>),
+        const int rc = hip_status(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemv_kernel<NB, EPI, TURN>),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
                                   "hipFuncSetAttribute(gemv)");
         if (rc) return rc;
         raised_to.store(lds);
     }
-    hipLaunchKernelGGL((gemv_kernel<NB, EPI>), dim3(wgs), dim3(GV_THREADS), lds, s, a);
+    hipLaunchKernelGGL((gemv_kernel<NB, EPI, TURN>), dim3(wgs), dim3(GV_THREADS), lds, s, a);
     return launch_status("gemv");
+}
+
+// A row of one piece has no order: a kernel without the rotation, whose arithmetic cost a layer of 1024 / 2816 (16 / 4 heads of 64)
+// 0.1 to 0.3 us (one, two and three samples 27.8, 34.3 and 38.2 -> 27.6, 34.0 and 38.1 us).
+template <int NB, int EPI>
+static int launch_gemv_nb(GvArgs& a, hipStream_t s) {
+    return a.K > GV_KBLK * GV_U ? launch_gemv_as<NB, EPI, true>(a, s) : launch_gemv_as<NB, EPI, false>(a, s);
 }
 
 template <int EPI>
